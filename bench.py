@@ -460,7 +460,7 @@ def measure(cfg, args, flush, want_eager=True):
     torch.cuda.synchronize()
     eager_ms = None
     if want_eager or args.no_graph:
-        # eager launch rate (reported, not the headline): Python + ctypes + hipLaunchKernel per call
+        # eager launch rate (reported, not the headline): Python + binding + hipLaunchKernel per call
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         torch.cuda.synchronize()
         e0.record(stream)

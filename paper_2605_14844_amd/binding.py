@@ -1,8 +1,10 @@
-"""ctypes binding of libxfp.so with the same entry-point names as include/xfp.h.
+"""Binding of libxfp.so with the same entry-point names as include/xfp.h.
 
 Argument marshalling only: tensors are passed as raw device pointers and the
 current torch stream as a hipStream_t.  Every computation runs in the HIP
-kernels behind the C ABI.
+kernels behind the C ABI.  The decode calls, which a step makes by the hundred,
+are marshalled by a small extension (csrc/xfp_torch.cpp: 3.3 us a call instead
+of 8 to 10); everything else goes through ctypes.
 """
 from __future__ import annotations
 
@@ -22,6 +24,7 @@ XFP_CHECK_GROUP_ID, XFP_CHECK_ROW_PTR, XFP_CHECK_COL_RANGE, XFP_CHECK_COL_ORDER,
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libxfp.so")
 _lib = None
+_native = None
 
 
 class XfpError(RuntimeError):
@@ -80,6 +83,24 @@ def load_library():
         getattr(lib, name).restype = i32
     _lib = lib
     return lib
+
+
+def _load_native():
+    """The extension that marshals the decode calls, bound to the entry points of the library in use."""
+    global _native
+    lib = load_library()
+    if not os.path.exists(os.path.join(_HERE, "_xfp_torch.so")):
+        from . import build as _build
+        _build.build_extension()
+    from . import _xfp_torch as native
+    native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        lib.xfp_gemv, lib.xfp_gemv_noalloc, lib.xfp_gemv_moe, lib.xfp_gemv_moe_silu_mul, lib.xfp_gemv_moe_combine)), _raise)
+    _native = native
+    return native
+
+
+def _raise(status: int, text: Optional[str] = None):
+    raise XfpError(status, xfp_strerror(status) if text is None else text)
 
 
 def xfp_strerror(status: int) -> str:
@@ -195,91 +216,37 @@ def upload(W, device="cuda") -> DeviceWeights:
 
 def _y_code(dtype, x: Optional[torch.Tensor] = None) -> int:
     """dtype argument of the C ABI: the output type, plus the flag for bf16 activations."""
-    flag = 0
-    if x is not None:
-        if x.dtype == torch.bfloat16:
-            flag = XFP_X_BF16
-        elif x.dtype != torch.float16:
-            raise XfpError(-3, "x dtype must be torch.float16 or torch.bfloat16")
-    if dtype == torch.float16:
-        return XFP_F16 | flag
-    if dtype == torch.float32:
-        return XFP_F32 | flag
-    if dtype == torch.bfloat16:
-        return XFP_BF16 | flag
-    raise XfpError(-3, "y dtype must be torch.float16, torch.bfloat16 or torch.float32")
+    return (_native or _load_native()).y_code(dtype, x)
 
 
 def xfp_gemv(W: DeviceWeights, x: torch.Tensor, y: Optional[torch.Tensor] = None,
              y_dtype=torch.float16, stream=None) -> torch.Tensor:
-    """y[M, N] = x[M, K] * W_hat^T.  x: fp16 device tensor [M, K] or [K], row stride = ldx."""
-    x2 = x if x.dim() == 2 else x.unsqueeze(0)
-    M = x2.shape[0]
-    if y is None:
-        y = torch.empty((M, W.N), dtype=y_dtype, device=x.device)
-    y2 = y if y.dim() == 2 else y.unsqueeze(0)
-    ldx = x2.stride(0) if M > 1 else max(x2.shape[1], 1)
-    ldy = y2.stride(0) if M > 1 else max(y2.shape[1], 1)
-    _check(load_library().xfp_gemv(ctypes.byref(W.desc), _ptr(x2), M, ldx, _ptr(y2),
-                                   _y_code(y2.dtype, x2), ldy, _stream(stream)))
-    return y
+    """y[M, N] = x[M, K] * W_hat^T.  x: fp16 (or bf16) device tensor [M, K] or [K], row stride = ldx."""
+    return (_native or _load_native()).gemv(W.desc, x, y, y_dtype, stream)
 
 
 def xfp_gemv_noalloc(W: DeviceWeights, x: torch.Tensor, y: torch.Tensor, stream=None) -> torch.Tensor:
     """xfp_gemv with its scratch in the library's one static array; the caller brings y (nothing is allocated)."""
-    x2 = x if x.dim() == 2 else x.unsqueeze(0)
-    M = x2.shape[0]
-    y2 = y if y.dim() == 2 else y.unsqueeze(0)
-    ldx = x2.stride(0) if M > 1 else max(x2.shape[1], 1)
-    ldy = y2.stride(0) if M > 1 else max(y2.shape[1], 1)
-    _check(load_library().xfp_gemv_noalloc(ctypes.byref(W.desc), _ptr(x2), M, ldx, _ptr(y2),
-                                           _y_code(y2.dtype, x2), ldy, _stream(stream)))
-    return y
+    return (_native or _load_native()).noalloc(W.desc, x, y, None, stream)
 
 
 def xfp_gemv_moe(bank: DeviceWeights, expert_ids: torch.Tensor, x: torch.Tensor,
                  y: Optional[torch.Tensor] = None, y_dtype=torch.float16, stream=None) -> torch.Tensor:
     """y[t, :] = matrix expert_ids[t] applied to x[t] (x [T, K]) or to the shared x (x [K] or [1, K])."""
-    T = int(expert_ids.numel())
-    shared = x.dim() == 1 or x.shape[0] == 1 and T != 1
-    x_slot_stride = 0 if shared else x.stride(0)
-    if y is None:
-        y = torch.empty((T, bank.N), dtype=y_dtype, device=x.device)
-    ldy = y.stride(0) if y.dim() == 2 and T > 1 else bank.N
-    _check(load_library().xfp_gemv_moe(ctypes.byref(bank.desc), _ptr(expert_ids), T, _ptr(x),
-                                       x_slot_stride, _ptr(y) if T else y.data_ptr(),
-                                       _y_code(y.dtype, x), ldy, _stream(stream)))
-    return y
+    return (_native or _load_native()).moe(bank.desc, expert_ids, x, y, y_dtype, stream)
 
 
 def xfp_gemv_moe_silu_mul(bank: DeviceWeights, expert_ids: Optional[torch.Tensor], x: torch.Tensor,
                           h: Optional[torch.Tensor] = None, h_dtype=torch.float16, stream=None) -> torch.Tensor:
     """h[t, j] = SiLU(y[t, j]) * y[t, N/2 + j] with y as xfp_gemv_moe gives it (gate rows first, then up rows).
     expert_ids None: one matrix (bank.E == 1), slot t is row t of x."""
-    T = int(expert_ids.numel()) if expert_ids is not None else (1 if x.dim() == 1 else int(x.shape[0]))
-    shared = x.dim() == 1 or x.shape[0] == 1 and T != 1
-    x_slot_stride = 0 if shared else x.stride(0)
-    if h is None:
-        h = torch.empty((T, bank.N // 2), dtype=h_dtype, device=x.device)
-    ldh = h.stride(0) if h.dim() == 2 and T > 1 else bank.N // 2
-    _check(load_library().xfp_gemv_moe_silu_mul(
-        ctypes.byref(bank.desc), _ptr(expert_ids) if expert_ids is not None else None, T, _ptr(x), x_slot_stride,
-        _ptr(h) if T else h.data_ptr(), _y_code(h.dtype, x), ldh, _stream(stream)))
-    return h
+    return (_native or _load_native()).silu(bank.desc, expert_ids, x, h, h_dtype, stream)
 
 
 def xfp_gemv_moe_combine(bank: DeviceWeights, expert_ids: torch.Tensor, x: torch.Tensor, slot_weights: torch.Tensor,
                          y: Optional[torch.Tensor] = None, y_dtype=torch.float16, stream=None) -> torch.Tensor:
     """y[n] = sum_t slot_weights[t] * (matrix expert_ids[t] applied to x[t])[n]; slot_weights fp32 [T]."""
-    T = int(expert_ids.numel())
-    assert slot_weights.dtype == torch.float32 and slot_weights.numel() == T
-    shared = x.dim() == 1 or x.shape[0] == 1 and T != 1
-    x_slot_stride = 0 if shared else x.stride(0)
-    if y is None:
-        y = torch.empty((bank.N,), dtype=y_dtype, device=x.device)
-    _check(load_library().xfp_gemv_moe_combine(ctypes.byref(bank.desc), _ptr(expert_ids), T, _ptr(x), x_slot_stride,
-                                               _ptr(slot_weights), _ptr(y), _y_code(y.dtype, x), _stream(stream)))
-    return y
+    return (_native or _load_native()).combine(bank.desc, expert_ids, x, slot_weights, y, y_dtype, stream)
 
 
 def xfp_check_contents(W: DeviceWeights, expert_ids: Optional[torch.Tensor] = None, stream=None) -> dict:

@@ -1,4 +1,4 @@
-"""Build libxfp.so (hipcc, gfx950 only) in-tree next to this file."""
+"""Build libxfp.so (hipcc, gfx950 only) and the binding's native half (g++) in-tree next to this file."""
 from __future__ import annotations
 
 import glob
@@ -42,6 +42,23 @@ def _resources(text):
     return res
 
 
+EXT = os.path.join(HERE, "_xfp_torch.so")            # native marshalling of the binding's decode calls
+EXT_SRC = os.path.join(CSRC, "xfp_torch.cpp")
+
+
+def _ext_command(out):
+    """g++ line of the extension: host code against this interpreter's and this torch's headers and libraries."""
+    import sysconfig
+
+    import torch
+    inc, lib = os.path.join(os.path.dirname(torch.__file__), "include"), os.path.join(os.path.dirname(torch.__file__), "lib")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", inc,
+            "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+            "-isystem", sysconfig.get_paths()["include"], "-o", out, EXT_SRC,
+            f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
 def _run(cmd, verbose, remarks_to=None):
     if verbose:
         print(" ".join(cmd))
@@ -52,7 +69,7 @@ def _run(cmd, verbose, remarks_to=None):
     out = "\n".join(l for l in res.stdout.splitlines()
                     if "packed-fp32-ops" not in l and "-Rpass-analysis" not in l and not l.startswith(("remark:", "  ")) and "remark:" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + res.stdout)
     if verbose and out.strip():
         print(out)
 
@@ -65,6 +82,14 @@ def _stamp(src: str) -> str:
         with open(d, "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
+
+
+def build_extension(verbose: bool = False) -> str:
+    """Compile the binding's native half (g++, a quarter of a minute)."""
+    tmp = EXT + f".tmp{os.getpid()}"
+    _run(_ext_command(tmp), verbose)
+    os.replace(tmp, EXT)
+    return EXT
 
 
 def build(verbose: bool = False, incremental: bool = False) -> str:
@@ -90,9 +115,14 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
                 obj = os.path.join(tmpdir, name + ".o")
                 jobs.append([hipcc, *HIPCC_FLAGS, "-c", "-o", obj, src])
             objs.append(obj)
-        workers = max(1, min(len(jobs), os.cpu_count() or 1, 8))
+        workers = max(1, min(len(jobs) + 1, os.cpu_count() or 1, 8))
         with ThreadPoolExecutor(max_workers=workers) as pool:
+            ext = None
+            if not incremental or not os.path.exists(EXT) or os.path.getmtime(EXT) < os.path.getmtime(EXT_SRC):
+                ext = pool.submit(build_extension, verbose)
             list(pool.map(lambda c: _run(c, verbose, remarks_to=c[c.index("-o") + 1] + ".json"), jobs))
+            if ext is not None:
+                ext.result()
         merged = {}
         for obj in objs:
             if os.path.exists(obj + ".json"):
