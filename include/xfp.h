@@ -29,7 +29,7 @@
  *    caller's contract; violating it is undefined behaviour.
  *    xfp_check_contents checks that contract on the device.
  *  - Calls from several host threads are safe.  The only state kept between
- *    calls is a static ring of eight workspaces of 10 MB in device memory
+ *    calls is a static ring of eight workspaces of 72 MB in device memory
  *    (every GPU the process uses holds its own copy; a call uses the one of the
  *    current device, which must be the device of its pointers and stream).
  *    A call that needs scratch memory (the batched path's re-laid activations,
@@ -148,8 +148,10 @@ typedef struct xfp_weights {
  *        through a static scratch plane.  The same formats with more than 16
  *        tokens read the weights once per up to 64 tokens (as many chunks
  *        of 16 as 16 * ceil(m / 16) * K <= 2^19 allows: 64 tokens up to
- *        K = 8192, 32 up to 16384); any other shape or width runs the
- *        M = 1 path once per token.  Same results either way, to rounding.
+ *        K = 8192, 32 up to 16384); with more than 64 tokens, 128 rows and
+ *        more and K <= 65536 they run as one tiled product per 2^24 / K
+ *        tokens; any other shape or width runs the M = 1 path once per
+ *        token.  Same results either way, to rounding.
  * XFP_ERR_UNSUPPORTED for a row no kernel takes: longer than 16384 columns, not
  * 4-bit V2 (whose rows of any length the tile kernel takes), with no split into
  * equal slices of at most 8192 (or partial sums beyond the scratch plane) AND
@@ -165,7 +167,7 @@ int xfp_gemv(const xfp_weights *W, const void *x, int M, int64_t ldx,
  * harnesses that forbid hipMalloc.  (No paper counterpart.)  Same arguments and
  * same results, bit for bit, as xfp_gemv.  Whatever scratch the call needs
  * (re-laid activations for M >= 2, partial sums of rows cut into slices of K)
- * lives in ONE static device array of 10 MB, not in the ring the other entry
+ * lives in ONE static device array of 72 MB, not in the ring the other entry
  * points cycle through; each GPU the process uses holds its own copy until the
  * process ends.  The call allocates nothing, frees nothing and calls no
  * allocating routine.
@@ -358,7 +360,8 @@ typedef enum {
     XFP_ROUTE_SPLIT_K = 2,   /* the streaming kernel over slices of K plus the fixed-order sum                      */
     XFP_ROUTE_TILE = 3,      /* M = 1 per slot, 32 rows across the lanes                                             */
     XFP_ROUTE_BATCH = 4,     /* 2 .. 16 tokens on the matrix cores, activations in registers                         */
-    XFP_ROUTE_WIDE = 5       /* 17 .. 64 tokens on the matrix cores in one pass over the weights                     */
+    XFP_ROUTE_WIDE = 5,      /* 17 .. 64 tokens on the matrix cores in one pass over the weights                     */
+    XFP_ROUTE_GEMM = 6       /* prompts: more than 64 tokens as a tiled product on the matrix cores                  */
 } xfp_route_id;
 int xfp_route(const xfp_weights *W, int M, int expert_indexed, int *tokens);
 

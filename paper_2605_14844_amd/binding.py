@@ -119,7 +119,7 @@ def xfp_select_kernel(which: int) -> None:
     _check(load_library().xfp_select_kernel(int(which)))
 
 
-XFP_ROUTE_GENERAL, XFP_ROUTE_STREAM, XFP_ROUTE_SPLIT_K, XFP_ROUTE_TILE, XFP_ROUTE_BATCH, XFP_ROUTE_WIDE = range(6)
+XFP_ROUTE_GENERAL, XFP_ROUTE_STREAM, XFP_ROUTE_SPLIT_K, XFP_ROUTE_TILE, XFP_ROUTE_BATCH, XFP_ROUTE_WIDE, XFP_ROUTE_GEMM = range(7)
 
 
 def xfp_route(W, M: int, expert_indexed: bool = False):

@@ -218,6 +218,8 @@ Plan plan(const xfp_weights *W, bool expert_indexed, int slots)
 {
     const int bits = (int)W->bits, mode = (int)W->mode;
     const bool gen = general_only(W);
+    // prompts: one tiled product for all remaining tokens
+    if (!gen && !expert_indexed && xfp::gemm_supports(bits, mode, W->L, W->N, W->K, slots)) return Plan{XFP_ROUTE_GEMM, slots, 0};
     if (!gen && !expert_indexed && slots >= 2) {
         // batched tokens: the weights are read once per 16 tokens, once per up to 64 where the wide kernel takes
         // the format and its re-laid copies fit the workspace
@@ -269,7 +271,7 @@ int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, 
         c.y = static_cast<char *>(y) + (size_t)m0 * (size_t)ldy * ysz;
         if (eids) c.eids = eids + m0;
         const xfp::Workspace *ws = nullptr;
-        if (p.route == XFP_ROUTE_WIDE || p.route == XFP_ROUTE_BATCH || p.route == XFP_ROUTE_SPLIT_K) {
+        if (p.route == XFP_ROUTE_GEMM || p.route == XFP_ROUTE_WIDE || p.route == XFP_ROUTE_BATCH || p.route == XFP_ROUTE_SPLIT_K) {
             hipError_t werr = sc.get(&ws);
             if (werr != hipSuccess) return finish(werr);
         }
@@ -278,6 +280,7 @@ int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, 
         case XFP_ROUTE_WIDE:
             err = xfp::launch_decode_wide(bits, (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : mode, c, p.take, y_f32, ws->xc, ws->part, s);
             break;
+        case XFP_ROUTE_GEMM: err = xfp::launch_decode_gemm(bits, mode, c, p.take, y_f32, ws->xc, s); break;
         case XFP_ROUTE_BATCH: err = xfp::launch_decode_batch(bits, mode, c, p.take, y_f32, ws->part, ws->xc, s); break;
         case XFP_ROUTE_TILE: err = xfp::launch_decode_tile(bits, y_f32, c, p.take, s); break;
         case XFP_ROUTE_STREAM: err = xfp::launch_decode_stream(bits, stream_affine(W) ? 2 : mode, y_f32, c, p.take, s); break;

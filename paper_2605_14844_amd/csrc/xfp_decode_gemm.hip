@@ -1,0 +1,717 @@
+// Prompt form of the fused decode: any number of tokens against one matrix (V2 codebooks or a V2a library, 2 to 4
+// bits), as a tiled matrix product on the matrix cores whose weight operand is dequantised on the way.
+//
+// Why: with hundreds of tokens the product is bound by the matrix cores (28672 x 8192 with 2048 tokens: 0.96 TFLOP),
+// not by the weights' bytes, and the 64-token kernel, which this takes over from above 64 tokens, reads and
+// dequantises the whole matrix once per 64 tokens and fetches its activations from L2 once per 32 rows.
+//
+// Work unit: a workgroup of 8 waves owns BN output rows x BM tokens and walks K.
+//  - Every lane dequantises the weights it needs itself, straight into the A operand of v_mfma_f32_32x32x16_f16: lane
+//    (i, h) owns row i of a block of 32 rows and one half of every 64 columns, the same rows for the whole kernel, so
+//    a V2 row's codebook stays in registers, split into byte planes (low and high bytes of the fp16 entries):
+//    v_perm_b32 then looks four entries up per instruction, with no LDS table, no bank conflict and no address (1.5,
+//    1.8 and 2.9 VALU operations per weight at 2, 3 and 4 bits).  V2a: the planes of the group's library entry are
+//    read from LDS once per block.  (An A tile in LDS, filled by all waves, was measured slower: ds_write_b128 takes
+//    14 to 16 clocks per KB, against 4.5 for a read, and LDS bandwidth is what runs out next to the matrix cores.)
+//  - The B tile (BM tokens) comes from a token-major copy of the activations straight into LDS
+//    (buffer_load_dwordx4 ... lds: no registers, no VALU), through a ring of parts; its rows are XOR-swizzled in
+//    16-byte chunks so that 16 consecutive lanes of a ds_read_b128 cover the 64 banks.
+//  - 28672 x 8192, 4 bits, 2048 tokens: 1.24 ms against 2.13 ms in passes of 64 tokens; 850 us of it are the product
+//    without outliers (1.13 PFLOP/s: three and a half rounds of tiles on 256 CUs; the library's own dense product of
+//    this shape 0.71 ms), 300 us the outliers.  4096 x 4096, 2 bits, 333 tokens: 41 us against 94.
+//
+// Order of k inside 32 weights: what the byte planes give cheaply is not the natural order (at 4 bits the even
+// nibbles of a dword come before the odd ones).  A product does not care as long as both operands agree, so the copy
+// of the activations is written in that order (slot_k), and by steps inside 64 columns.
+//
+// Outliers (fp32, not folded into the fp16 operand: that would round them): the waves share out the tile's rows; an
+// entry's activations of all the tile's tokens are one contiguous read from a k-major copy of x; a row's sums meet in
+// an LDS plane from which the waves load what their results start from.  No atomics, fixed orders.
+#include "xfp_device.h"
+
+#include <atomic>
+#include <type_traits>
+#include <utility>
+
+namespace xfp {
+namespace {
+
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float16_t __attribute__((ext_vector_type(16)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+// index words of 32 weights
+template <int BITS>
+struct WordsOf { typedef uint32_t type __attribute__((ext_vector_type(BITS))); };
+template <int BITS>
+using words_t = typename WordsOf<BITS>::type;
+typedef __attribute__((address_space(3))) u32x4_t lds_u4_t;
+typedef __attribute__((address_space(3))) const u32x4_t lds_cu4_t;
+typedef __attribute__((address_space(3))) const half8_t lds_ch8_t;
+typedef __attribute__((address_space(3))) uint32_t lds_u32_t;
+typedef __attribute__((address_space(3))) const uint32_t lds_cu32_t;
+typedef __attribute__((address_space(3))) const float lds_cf32_t;
+typedef __attribute__((address_space(3))) float4_t lds_f4_t;
+typedef __attribute__((address_space(4))) const int32_t const_i32_t;   // uniform reads go through the scalar cache
+
+// position (0..31) in natural order of the weight in slot s of a dequantised run of 32
+constexpr int slot_k(int bits, int s)
+{
+    const int c = s >> 3, t = s & 7;                       // 16-byte chunk, slot in it
+    if (bits == 4) return 8 * c + (t < 4 ? 2 * t : 2 * (t - 4) + 1);
+    if (bits == 3) return 2 * c + (t >> 2) + 8 * (t & 3);
+    return 16 * (c >> 1) + 2 * (c & 1) + (t >> 2) + 4 * (t & 3);
+}
+
+// Byte planes of a codebook: lo[d] / hi[d] hold the low / high bytes of entries 4 d .. 4 d + 3.
+template <int BITS>
+struct Planes {
+    static constexpr int ND = (1 << BITS) / 4;
+    uint32_t lo[ND], hi[ND];
+    // from the codebook's 2^BITS fp16 entries as dwords
+    __device__ __forceinline__ void set(const uint32_t *c)
+    {
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+            lo[d] = __builtin_amdgcn_perm(c[2 * d + 1], c[2 * d], 0x06040200u);
+            hi[d] = __builtin_amdgcn_perm(c[2 * d + 1], c[2 * d], 0x07050301u);
+        }
+    }
+};
+
+// Bytes (four at a time) of the entries that the selector bytes name: BITS = 4: low three index bits in s, the fourth
+// as j + 4 * bit in byte j of up; fewer bits: the index itself in s.
+template <int BITS>
+__device__ __forceinline__ uint32_t pick(const uint32_t *p, uint32_t s, uint32_t up)
+{
+    if constexpr (BITS == 4)
+        return __builtin_amdgcn_perm(__builtin_amdgcn_perm(p[3], p[2], s), __builtin_amdgcn_perm(p[1], p[0], s), up);
+    else if constexpr (BITS == 3) return __builtin_amdgcn_perm(p[1], p[0], s);
+    else return __builtin_amdgcn_perm(p[0], p[0], s);
+}
+
+// Four weights (two dwords of fp16 pairs) from four selectors.
+template <int BITS>
+__device__ __forceinline__ void four(const Planes<BITS> &P, uint32_t s, uint32_t up, uint32_t &d0, uint32_t &d1)
+{
+    const uint32_t l = pick<BITS>(P.lo, s, up), h = pick<BITS>(P.hi, s, up);
+    d0 = __builtin_amdgcn_perm(h, l, 0x05010400u);
+    d1 = __builtin_amdgcn_perm(h, l, 0x07030602u);
+}
+
+// Index words of 32 weights in the form chunk() wants them: 3 bits: bytes 0, 3, 6, 9 / 1, 4, 7, 10 / 2, 5, 8, 11 of
+// the 12, so that fields 8 apart sit at one bit position of four bytes.
+template <int BITS>
+__device__ __forceinline__ void arrange(words_t<BITS> &w)
+{
+    if constexpr (BITS == 3) {
+        const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x0c060300u), b = __builtin_amdgcn_perm(w[1], w[0], 0x0c070401u),
+                       c = __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0502u), x = w[2];
+        w[0] = __builtin_amdgcn_perm(x, a, 0x05020100u);
+        w[1] = __builtin_amdgcn_perm(x, b, 0x06020100u);
+        w[2] = __builtin_amdgcn_perm(x, c, 0x07040100u);
+    }
+}
+
+// Chunk c (0..3) of a run of 32: slots 8 c .. 8 c + 7 as fp16 pairs.
+template <int BITS>
+__device__ __forceinline__ u32x4_t chunk(const Planes<BITS> &P, const words_t<BITS> &w, int c)
+{
+    uint32_t d0, d1, d2, d3;
+    if constexpr (BITS == 4) {
+        const uint32_t v = w[c], kTop = 0x03020100u;
+        four<4>(P, v & 0x07070707u, ((v >> 1) & 0x04040404u) | kTop, d0, d1);
+        four<4>(P, (v >> 4) & 0x07070707u, ((v >> 5) & 0x04040404u) | kTop, d2, d3);
+    } else if constexpr (BITS == 3) {
+        auto sel = [&](int k0) -> uint32_t {
+            switch (k0) {
+            case 0: return w[0] & 0x07070707u;
+            case 1: return (w[0] >> 3) & 0x07070707u;
+            case 2: return ((w[0] >> 6) & 0x03030303u) | ((w[1] << 2) & 0x04040404u);
+            case 3: return (w[1] >> 1) & 0x07070707u;
+            case 4: return (w[1] >> 4) & 0x07070707u;
+            case 5: return ((w[1] >> 7) & 0x01010101u) | ((w[2] << 1) & 0x06060606u);
+            case 6: return (w[2] >> 2) & 0x07070707u;
+            default: return (w[2] >> 5) & 0x07070707u;
+            }
+        };
+        four<3>(P, sel(2 * c), 0u, d0, d1);
+        four<3>(P, sel(2 * c + 1), 0u, d2, d3);
+    } else {
+        const uint32_t v = w[c >> 1];
+        const int s = 4 * (c & 1);
+        four<2>(P, (v >> s) & 0x03030303u, 0u, d0, d1);
+        four<2>(P, (v >> (s + 2)) & 0x03030303u, 0u, d2, d3);
+    }
+    return u32x4_t{d0, d1, d2, d3};
+}
+
+// Tile geometry: WN x WK waves; a wave owns 32 RB rows and all 32 TB tokens and takes every WK-th block of 64 columns
+// (the waves that share rows add their sums in LDS at the end).  A part of the B tile is SP of the block's four steps of
+// 16 columns, for each of the WK waves; NBUF of them in LDS, NBUF - 1 requested ahead.  R: blocks of index words a wave
+// has in flight.
+// SPLIT: the accumulators are added to a second set every 1024 columns and start again from zero.  A sum of n products
+// of 16 in one fp32 chain is off by about 2e-8 sqrt(n) of its size (n = 256 at 4096 columns: 3.1e-7 measured), which
+// a 16-bit result does not show and an fp32 result does; in chains of 64 it is off by 1.7e-7 at 8192 columns.
+template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_, int R_, bool SPLIT_>
+struct GemmTile {
+    static constexpr int RB = RB_, TB = TB_, WN = WN_, WK = WK_, SP = SP_, NBUF = NBUF_, R = R_;
+    static constexpr bool SPLIT = SPLIT_;
+    static constexpr int BN = 32 * RB * WN, BM = 32 * TB, NW = WN * WK, T = NW * kWave;
+    static constexpr int KB = 16 * SP * WK, RSB = KB * 2, kB = BM * RSB;   // a part: columns, bytes of a row, bytes
+    static constexpr int U = 4 / SP;                           // parts of a block
+    static_assert(SP == 2 || SP == 4, "");
+    static constexpr int AHEAD = NBUF - 1;
+    static constexpr int ND = kB / (NW * 1024);                // loads of a wave per part
+    static constexpr int PR = BN * BM <= 32768 ? BN : 32768 / BM;          // rows of the outlier plane (in front of the tiles' life)
+    static constexpr int kPlane = PR * BM * 4, kSums = (WK - 1) * BN * BM * 4, kTiles = NBUF * kB;
+    static constexpr int kBase = kTiles > kPlane ? (kTiles > kSums ? kTiles : kSums) : (kPlane > kSums ? kPlane : kSums);
+    static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && R >= 2 && PR % NW == 0 && BN % PR == 0, "");
+    // registers: accumulators, operands (B twice), index words, planes; then waves per SIMD
+    static constexpr int kRegs = 16 * RB * TB * (SPLIT ? 2 : 1) + 16 * RB + 8 * TB + 4 * RB * R + 8 * RB + 60;
+    static constexpr int kWavesPerSimd = kRegs <= 128 ? 4 : kRegs <= 168 ? 3 : kRegs <= 256 ? 2 : 1;
+};
+
+// 16-byte chunk c of row r of a tile with C chunks per row sits at position c ^ swz<C>(r)
+template <int C>
+__device__ __forceinline__ uint32_t swz(uint32_t r)
+{
+    if constexpr (C >= 16) return r & 15u;
+    else return (r / (16 / C)) & (uint32_t)(C - 1);
+}
+
+struct GemmArgs {
+    DecodeArgs a;
+    const uint16_t *xp;    // [M][K] fp16, every block of 64 columns in the order of the kernel's steps
+    const uint16_t *xt;    // [K][MP] fp16
+    uint32_t M, MP;        // tokens of this launch; row length of xt (a multiple of 8)
+    uint32_t row0, tiles_n, tiles_m;                           // first row, tiles of this launch
+    int y_f32;
+};
+
+template <class F, int... Is>
+__device__ __forceinline__ void for_each_of(F &&f, std::integer_sequence<int, Is...>) { (f(std::integral_constant<int, Is>{}), ...); }
+// f(0), .., f(n - 1) with compile-time arguments
+template <int n, class F>
+__device__ __forceinline__ void for_each(F &&f) { for_each_of(f, std::make_integer_sequence<int, n>{}); }
+
+template <int BITS, int MODE, class C>
+__global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(GemmArgs ga)
+{
+    static_assert(MODE == 0 || MODE == 1, "V2, V2a");
+    constexpr int BN = C::BN, BM = C::BM, RB = C::RB, TB = C::TB, WK = C::WK, NW = C::NW, R = C::R;
+    constexpr int CB = C::KB / 8;                              // 16-byte chunks of a row of a part
+    extern __shared__ __align__(256) unsigned char smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const DecodeArgs &a = ga.a;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t i = lane & 31, h = lane >> 5;
+    const uint32_t wn = wave % C::WN, wk = wave / C::WN;
+    const uint32_t N = a.N, K = a.K, M = ga.M;
+    const uint32_t wpr = K / 32 * BITS, G = K / kGroup, NBLK = K / 64, NT = (NBLK + WK - 1) / WK;
+
+    // Workgroups are dealt to the 8 XCDs round-robin, each with an L2 of its own: an XCD takes a contiguous run of
+    // tiles, row tiles fastest, so that its workgroups share the activations of one token tile (2 x 4 MB at 8192
+    // columns), which every one of them reads whole and, for the outliers, at random.
+    const uint32_t nt = ga.tiles_n * ga.tiles_m, per = (nt + 7) / 8;
+    const uint32_t t0 = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (t0 >= nt || blockIdx.x / 8 >= per) return;
+    const uint32_t n0 = ga.row0 + t0 % ga.tiles_n * BN, m0 = t0 / ga.tiles_n * BM;
+
+    // ---------------------------------------------------------------- A operands: this lane's rows
+    // Lane (i, h) holds, of row i of every row block, 32 weights of a block of 64 columns: half h.  Chunk s of the 32
+    // IS the operand of step s, so nothing moves between lanes and no A tile is needed.  (The copy of the activations
+    // has chunk s of half h of a block at its 16 bytes 2 s + h, so that a step's columns are neighbours.)
+    uint32_t row[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) row[rb] = min(n0 + (wn * RB + rb) * 32 + i, N - 1);
+    Planes<BITS> P[RB];
+    if constexpr (MODE == 0) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            uint32_t c[1 << (BITS - 1)];
+            const uint32_t *cb = reinterpret_cast<const uint32_t *>(a.cb) + (size_t)row[rb] * (1 << (BITS - 1));
+#pragma unroll
+            for (int d = 0; d < (1 << (BITS - 1)); ++d) c[d] = cb[d];
+            P[rb].set(c);
+        }
+    } else {
+        // the library as planes behind the tiles: entry l at kBase + l * 2^BITS * 2, low bytes first
+        for (uint32_t j = tid; j < a.L * Planes<BITS>::ND; j += C::T) {
+            const uint32_t l = j / Planes<BITS>::ND, d = j % Planes<BITS>::ND;
+            const uint2 v = *reinterpret_cast<const uint2 *>(a.cb + ((size_t)l << BITS) + 4 * d);
+            const uint32_t o = lds0 + C::kBase + l * (2u << BITS) + d * 4;
+            *(lds_u32_t *)(uintptr_t)o = __builtin_amdgcn_perm(v.y, v.x, 0x06040200u);
+            *(lds_u32_t *)(uintptr_t)(o + Planes<BITS>::ND * 4) = __builtin_amdgcn_perm(v.y, v.x, 0x07050301u);
+        }
+    }
+
+    // ---------------------------------------------------------------- results, and the outlier term they start from
+    // acc: what the matrix cores add to; sum: what the results are (the same registers unless SPLIT)
+    float16_t acc[RB][TB], acc2[RB][TB];
+    float16_t (&sum)[RB][TB] = C::SPLIT ? acc2 : acc;
+    auto clear = [](float16_t (&v)[RB][TB]) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[rb][tb][r] = 0.f;
+    };
+    clear(sum);
+    // Wave w owns rows RW w .. of the plane, whose entries are one run of the CSR arrays, and walks it in units of up
+    // to U EP entries of one row: lane (ep, o) takes entries ep, ep + EP, .. of a unit and the tokens m0 + 8 o .. + 7.
+    // Three units are under way at any time (entries fetched, activations gathered, products summed): an entry's
+    // activations are 16 BM / 8 bytes from L2, and it takes about 64 KB in flight per CU to draw them at full rate.
+    const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
+    if (a.col && rp[min(n0, N)] < rp[min(n0 + BN, N)]) {
+        constexpr int OP = BM / 8, EP = 64 / OP, U = NW <= 4 && EP <= 4 ? 8 : 4, UE = U * EP, RW = C::PR / NW;
+        static_assert(OP >= 4 && OP <= 32 && UE <= 64 && RW < 64, "");
+        const uint32_t ep = lane / OP, o = lane % OP;
+        const uint4 *xt = reinterpret_cast<const uint4 *>(ga.xt) + min((m0 >> 3) + o, ga.MP / 8 - 1);
+        const uint32_t xs = ga.MP / 8, plane = lds0 + wave * (RW * BM * 4);
+        struct Unit { uint32_t row; int32_t e, hi; bool last; };                            // wave-uniform
+        struct Gathered { uint4 x[U]; float v[U]; };
+#pragma unroll
+        for (int pass = 0; pass < BN / C::PR; ++pass) {
+            const int32_t rpv = a.rp[min(n0 + pass * C::PR + wave * RW + min(lane, (uint32_t)RW), N)];   // lane r: first entry of row r
+            auto row_at = [&](uint32_t r) { return __builtin_amdgcn_readlane(rpv, (int)r); };
+            auto unit_at = [&](uint32_t r, int32_t e) {
+                Unit u;
+                u.row = r; u.e = e;
+                u.hi = r < (uint32_t)RW ? row_at(r + 1) : e;
+                u.last = e + UE >= u.hi;
+                return u;
+            };
+            auto after = [&](const Unit &u) {
+                const uint32_t r = u.last ? u.row + 1 : u.row;
+                return unit_at(r, r >= (uint32_t)RW ? u.hi : u.last ? row_at(r) : u.e + UE);
+            };
+            auto fetch = [&](const Unit &u) {                  // lane j: entry j of the unit, column | value << 16
+                const int32_t e = u.e + (int32_t)lane;
+                uint32_t v = 0u;
+                if (lane < (uint32_t)UE && e < u.hi) v = (uint32_t)a.col[e] | ((uint32_t)a.val[e] << 16);
+                return v;
+            };
+            auto gather = [&](const Unit &u, uint32_t ents, Gathered &g) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const uint32_t ent = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((j * EP + ep) * 4), (int)ents);
+                    g.v[j] = half_bits_to_float((uint16_t)(ent >> 16));
+                    g.x[j] = make_uint4(0u, 0u, 0u, 0u);       // no entry: zero times zeros
+                    if (u.e + j * EP + (int32_t)ep < u.hi) g.x[j] = xt[(size_t)(ent & 0xFFFFu) * xs];
+                }
+            };
+            float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            auto consume = [&](const Unit &u, const Gathered &g) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    if (j && u.e + j * EP >= u.hi) break;      // wave-uniform
+                    const uint32_t w[4] = {g.x[j].x, g.x[j].y, g.x[j].z, g.x[j].w};
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) s[t] = fmaf(g.v[j], half_bits_to_float((uint16_t)(t & 1 ? w[t / 2] >> 16 : w[t / 2])), s[t]);
+                }
+                if (!u.last) return;
+                // the EP entry lanes of a token octet are added in a fixed tree
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    if constexpr (EP >= 16) s[t] = dpp_add<0x124>(s[t]);           // row_ror:4 (octets in lane % 4)
+                    if constexpr (EP >= 8) s[t] = dpp_add<0x128>(s[t]);            // row_ror:8
+                    uint32_t x = __builtin_bit_cast(uint32_t, s[t]);
+                    if constexpr (EP >= 4) {
+                        const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+                        s[t] = __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
+                        x = __builtin_bit_cast(uint32_t, s[t]);
+                    }
+                    const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+                    s[t] = __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
+                }
+                if (ep == 0) {
+                    const uint32_t d = plane + u.row * (BM * 4) + o * 32;
+                    *(lds_f4_t *)(uintptr_t)d = float4_t{s[0], s[1], s[2], s[3]};
+                    *(lds_f4_t *)(uintptr_t)(d + 16) = float4_t{s[4], s[5], s[6], s[7]};
+                }
+#pragma unroll
+                for (int t = 0; t < 8; ++t) s[t] = 0.f;
+            };
+            Unit u0 = unit_at(0, row_at(0)), u1 = after(u0);
+            uint32_t ents1;
+            Gathered g0, g1;
+            {
+                const uint32_t ents0 = fetch(u0);
+                ents1 = fetch(u1);
+                gather(u0, ents0, g0);
+            }
+#pragma unroll 1
+            while (u0.row < (uint32_t)RW) {
+                Unit u2 = after(u1), u3 = after(u2);
+                const uint32_t ents2 = fetch(u2);
+                gather(u1, ents1, g1);
+                consume(u0, g0);
+                if (u1.row >= (uint32_t)RW) break;
+                ents1 = fetch(u3);
+                gather(u2, ents2, g0);
+                consume(u1, g1);
+                u0 = u2;
+                u1 = u3;
+            }
+            lds_barrier();
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const uint32_t pr = (wn * RB + rb) * 32 - pass * C::PR;        // first row of the block in the plane
+                if (wk == 0 && pr < (uint32_t)C::PR)
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            sum[rb][tb][r] = *(lds_cf32_t *)(uintptr_t)(lds0 + (pr + 8 * (r / 4) + 4 * h + r % 4) * (BM * 4) + (32 * tb + i) * 4);
+            }
+            lds_barrier();
+        }
+    }
+
+    // ---------------------------------------------------------------- loads of the main loop
+    // They are written as instructions because the compiler does not count loads to LDS: every turn issues the same
+    // number of them in the same order (past the end: again the last block's), and every wait below states how many
+    // may still be under way.  Words: block t WK + wk of turn t, 16 (12, 8) bytes per lane and row block.
+    words_t<BITS> iw[R][RB];
+    uint32_t gid[R][RB];
+    auto load_words = [&](auto slot, uint32_t t) {
+        constexpr int S = decltype(slot)::value;
+        const uint32_t blk = min(t * WK + wk, NBLK - 1);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const uint32_t *p = a.idx + (size_t)row[rb] * wpr + (blk * 2 + h) * BITS;
+            words_t<BITS> &w = iw[S][rb];
+            if constexpr (BITS == 4) asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(w) : "v"(p) : "memory");
+            else if constexpr (BITS == 3) asm volatile("global_load_dwordx3 %0, %1, off" : "=v"(w) : "v"(p) : "memory");
+            else asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(w) : "v"(p) : "memory");
+            if constexpr (MODE == 1) {
+                const uint8_t *g = a.gid + (size_t)row[rb] * G + blk / 2;
+                uint32_t &id = gid[S][rb];
+                asm volatile("global_load_ubyte %0, %1, off" : "=v"(id) : "v"(g) : "memory");
+            }
+        }
+    };
+    constexpr int kWords = RB * (1 + MODE), kTurn = C::U * C::ND + kWords;     // loads of a turn: words; all
+    static_assert((R - 1) * kTurn <= 63 && (C::AHEAD - 1) * C::ND + C::AHEAD * kWords <= 63, "what vmcnt can say");
+    const u32x4_t rx = {(uint32_t)(uintptr_t)ga.xp, (uint32_t)((uintptr_t)ga.xp >> 32) & 0xFFFFu, M * K * 2, 0x00020000u};
+    uint32_t boff[C::ND];
+#pragma unroll
+    for (int e = 0; e < C::ND; ++e) {
+        const uint32_t o = (wave * C::ND + e) * 1024 + lane * 16, r = o / C::RSB, p = (o % C::RSB / 16) ^ swz<CB>(r);
+        boff[e] = min(m0 + r, M - 1) * (K * 2) + p / (2 * C::SP) * 128 + p % (2 * C::SP) * 16;
+    }
+    uint32_t bload = 0;                                        // ring slot of the part being requested
+    // Loads e0 .. e1 - 1 of a part.  They are spread over the steps: a wave that issues a part's loads at once stands in
+    // front of its matrix instructions until the address unit has taken them all.
+    auto load_b = [&](uint32_t q, int e0, int e1) {
+        const uint32_t dst = lds0 + bload * C::kB + wave * (C::ND * 1024), so = min(q / C::U, NT - 1) * (WK * 128) + q % C::U * (C::SP * 32);
+#pragma unroll
+        for (int e = e0; e < e1; ++e)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                         :: "s"(dst + e * 1024), "v"(boff[e]), "s"(rx), "s"(so) : "memory");
+        if (e1 == C::ND) bload = bload + 1 == C::NBUF ? 0 : bload + 1;
+    };
+    auto arrived = [&](auto slot) {                            // the words of a slot may be used from here on
+        constexpr int S = decltype(slot)::value;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            words_t<BITS> &w = iw[S][rb];
+            asm volatile("" : "+v"(w));
+            if constexpr (MODE == 1) {
+                uint32_t &id = gid[S][rb];
+                asm volatile("" : "+v"(id));
+                const uint32_t o = lds0 + C::kBase + id * (2u << BITS);
+#pragma unroll
+                for (int d = 0; d < Planes<BITS>::ND; ++d) {
+                    P[rb].lo[d] = *(lds_cu32_t *)(uintptr_t)(o + d * 4);
+                    P[rb].hi[d] = *(lds_cu32_t *)(uintptr_t)(o + (Planes<BITS>::ND + d) * 4);
+                }
+            }
+            arrange<BITS>(iw[S][rb]);
+        }
+    };
+
+    // ---------------------------------------------------------------- prologue: as if the turns before the first had run
+    half8_t af[4][RB], bf[2][TB];
+    auto dequantise = [&](auto slot, int s) {
+        constexpr int S = decltype(slot)::value;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) af[s][rb] = __builtin_bit_cast(half8_t, chunk<BITS>(P[rb], iw[S][rb], s));
+    };
+    const uint32_t br = lds0 + i * C::RSB + (((wk * (2 * C::SP) + h) ^ swz<CB>(i)) * 16);
+    auto operands = [&](int set, uint32_t buf, int s) {
+        const uint32_t ba = (br + buf * C::kB) ^ (uint32_t)(s % C::SP * 32);
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) bf[set][tb] = *(lds_ch8_t *)(uintptr_t)(ba + tb * (32 * C::RSB));
+    };
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for_each<R>([&](auto s) { load_words(s, decltype(s)::value); });
+#pragma unroll
+    for (int q = 0; q < C::AHEAD; ++q) load_b(q, 0, C::ND);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    arrived(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int s = 0; s < 3; ++s) dequantise(std::integral_constant<int, 0>{}, s);
+    operands(0, 0, 0);
+    if constexpr (C::SPLIT) clear(acc);
+
+    // ---------------------------------------------------------------- main loop
+    // A turn is a block of 64 columns, four steps.  In step s the B operands of step s + 1 are read, the A operands of
+    // the next turn's step s - 1 are made (their registers were read by the step before) and the matrix instructions
+    // run.  The barrier that opens the next part stands in front of the last step, whose matrix instructions then cover
+    // the first reads behind it; a part's ring slot is refilled after the barrier that follows its last reads.
+    uint32_t bcur = 0;
+    auto turn = [&](auto slot, uint32_t t) {
+        constexpr int S = decltype(slot)::value, NX = (S + 1) % R;
+        using Next = std::integral_constant<int, NX>;
+        const bool on = WK == 1 || t * WK + wk < NBLK;         // (the last part of a row may have no block for this wave)
+        for_each<4>([&](auto step) {
+            constexpr int s = decltype(step)::value, u = s / C::SP;
+            constexpr bool last = s % C::SP == C::SP - 1;      // of a part
+            const uint32_t bnext = bcur + 1 == C::NBUF ? 0 : bcur + 1;
+            if constexpr (!last) operands((s + 1) & 1, bcur, s + 1);
+            load_b(t * C::U + u + C::AHEAD, s % C::SP * C::ND / C::SP, (s % C::SP + 1) * C::ND / C::SP);
+            if constexpr (s == 0) dequantise(slot, 3);
+            if constexpr (s == 1) {
+                load_words(slot, t + R);
+                asm volatile("s_waitcnt vmcnt(%0)" :: "n"((R - 1) * kTurn) : "memory");     // the next turn's words
+                arrived(Next{});
+            }
+            if constexpr (last) {
+                // The next part, requested AHEAD parts ago.  Younger: the parts requested since, and the words of every
+                // turn whose second step has been since its last load (that is in the second or in the fourth step).
+                constexpr int kWordsSince = C::U == 1 ? C::AHEAD - 1 : (C::AHEAD + (u == 0 ? 1 : 0)) / 2;
+                constexpr int kYounger = (C::AHEAD - 1) * C::ND + kWordsSince * kWords;
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kYounger) : "memory");
+                operands((s + 1) & 1, bnext, (s + 1) % 4);
+            }
+            if constexpr (s > 0) dequantise(Next{}, s - 1);
+            if (on)
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+                        acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[s][rb], bf[s & 1][tb], acc[rb][tb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (last) bcur = bnext;
+        });
+    };
+#pragma unroll 1
+    for (uint32_t t = 0; t < NT; t += R) {
+        for_each<R>([&](auto s) {
+            if (decltype(s)::value == 0 || t + decltype(s)::value < NT) turn(s, t + decltype(s)::value);
+        });
+        if constexpr (C::SPLIT) {
+            static_assert(16 % R == 0, "");
+            if ((t + R) % (16 / WK > R ? 16 / WK : R) == 0 || t + R >= NT) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb) {
+                        sum[rb][tb] += acc[rb][tb];
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[rb][tb][r] = 0.f;
+                    }
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // (loads to LDS that nobody waits for)
+
+    if constexpr (WK > 1) {
+        // the other waves' sums of a block, added in their order; they may overwrite the tiles, which every wave has read
+        lds_barrier();
+        constexpr uint32_t kWave4 = kWave * 16, kBlock = RB * TB * 4 * kWave4;               // four registers of a wave; a wave's block
+        const uint32_t at = lds0 + wn * kBlock + lane * 16;
+        if (wk > 0) {
+#pragma unroll
+            for (int b = 0; b < RB * TB * 4; ++b) {
+                const float16_t &v = sum[b / 4 % RB][b / 4 / RB];
+                *(lds_f4_t *)(uintptr_t)(at + (wk - 1) * (C::WN * kBlock) + b * kWave4) =
+                    float4_t{v[b % 4 * 4], v[b % 4 * 4 + 1], v[b % 4 * 4 + 2], v[b % 4 * 4 + 3]};
+            }
+        }
+        lds_barrier();
+        if (wk > 0) return;
+#pragma unroll 1
+        for (int w = 0; w < WK - 1; ++w)
+#pragma unroll
+            for (int b = 0; b < RB * TB * 4; ++b) {
+                const float4_t x = *(lds_f4_t *)(uintptr_t)(at + w * (C::WN * kBlock) + b * kWave4);
+                float16_t &v = sum[b / 4 % RB][b / 4 / RB];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[b % 4 * 4 + r] += x[r];
+            }
+    }
+
+    // ---------------------------------------------------------------- store: register r of a block is its row 8 (r / 4) + 4 h + r % 4
+    const bool f32 = ga.y_f32 != 0, b16 = a.y_bf16 != 0;
+    const bool quads = !f32 && a.y_stride % 4 == 0 && ((uintptr_t)a.y & 7) == 0;
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+        const uint32_t m = m0 + 32 * tb + i;
+        if (m >= M) continue;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const uint32_t n = n0 + (wn * RB + rb) * 32 + 8 * r4 + 4 * h;
+                const int64_t o = (int64_t)m * a.y_stride + n;
+                float v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = sum[rb][tb][4 * r4 + r];
+                if (quads && n + 3 < N) {
+                    uint16_t b[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) b[r] = b16 ? float_to_bf16_bits(v[r]) : __builtin_bit_cast(uint16_t, (_Float16)v[r]);
+                    *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(a.y) + o) =
+                        make_uint2((uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16));
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (n + r < N) store_out(a.y, o + r, v[r], f32, b16);
+                }
+            }
+    }
+}
+
+// The two copies of the activations.  Blocks [0, nb): xp, one thread per (token, run of 32 columns).  The rest: xt, a
+// block per tile of 64 columns x 64 tokens, through LDS.  bf16 activations are converted to fp16 on the way.
+template <int BITS>
+__global__ __launch_bounds__(256) void relayout_x_gemm_kernel(const uint16_t *x, int64_t ldx, uint32_t M, uint32_t K, int bf16,
+                                                              uint16_t *xp, uint16_t *xt, uint32_t MP, uint32_t nb)
+{
+    if (blockIdx.x < nb) {
+        const uint32_t id = blockIdx.x * 256 + threadIdx.x, runs = K / 32;
+        if (id >= M * runs) return;
+        const uint32_t m = id / runs, c = id - m * runs;
+        const uint4 *p = reinterpret_cast<const uint4 *>(x + (size_t)m * ldx + (size_t)c * 32);
+        uint32_t w[16];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint4 v = p[j];
+            w[4 * j] = v.x; w[4 * j + 1] = v.y; w[4 * j + 2] = v.z; w[4 * j + 3] = v.w;
+        }
+        if (bf16) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) w[j] = bf16x2_to_f16x2(w[j]);
+        }
+        auto at = [&](int s) { const int k = slot_k(BITS, s); return k & 1 ? w[k / 2] >> 16 : w[k / 2] & 0xFFFFu; };
+        uint4 *o = reinterpret_cast<uint4 *>(xp + (size_t)m * K + (size_t)(c / 2) * 64) + c % 2;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            uint32_t d[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) d[e] = at(8 * j + 2 * e) | (at(8 * j + 2 * e + 1) << 16);
+            o[2 * j] = make_uint4(d[0], d[1], d[2], d[3]);
+        }
+        return;
+    }
+    __shared__ uint16_t tile[64][66];
+    const uint32_t b = blockIdx.x - nb, tk = K / 64, k0 = b % tk * 64, m0 = b / tk * 64;
+    const uint32_t c = threadIdx.x % 8, r = threadIdx.x / 8;   // column octet, token
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const uint32_t m = m0 + r + 32 * g;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (m < M) v = *reinterpret_cast<const uint4 *>(x + (size_t)m * ldx + k0 + 8 * c);
+        if (bf16) v = make_uint4(bf16x2_to_f16x2(v.x), bf16x2_to_f16x2(v.y), bf16x2_to_f16x2(v.z), bf16x2_to_f16x2(v.w));
+        uint32_t *d = reinterpret_cast<uint32_t *>(&tile[r + 32 * g][8 * c]);
+        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const uint32_t k = r + 32 * g;                         // now: token octet c, column k
+        uint32_t d[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = (uint32_t)tile[8 * c + 2 * e][k] | ((uint32_t)tile[8 * c + 2 * e + 1][k] << 16);
+        if (m0 + 8 * c < MP) *reinterpret_cast<uint4 *>(xt + (size_t)(k0 + k) * MP + m0 + 8 * c) = make_uint4(d[0], d[1], d[2], d[3]);
+    }
+}
+
+template <int BITS, int MODE, class C>
+hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
+{
+    auto kern = decode_gemm_kernel<BITS, MODE, C>;
+    const int lds = C::kBase + (MODE == 1 ? (int)(ga.a.L * (2u << BITS)) : 0);
+    static std::atomic<int> configured[kMaxDevices];           // per device; idempotent attribute, benign race
+    const int dev = current_device();
+    if (dev < 0) return hipErrorInvalidDevice;
+    if (!configured[dev].load(std::memory_order_relaxed)) {
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             C::kBase + (MODE == 1 ? 256 * (2 << BITS) : 0));
+        if (err != hipSuccess) return err;
+        configured[dev].store(1, std::memory_order_relaxed);
+    }
+    ga.row0 = 0;
+    ga.tiles_n = (ga.a.N + C::BN - 1) / C::BN;
+    ga.tiles_m = (ga.M + C::BM - 1) / C::BM;
+    const uint32_t per = (ga.tiles_n * ga.tiles_m + 7) / 8;
+    hipLaunchKernelGGL(kern, dim3(8 * per), dim3(C::T), lds, s, ga);
+    return hipGetLastError();
+}
+
+template <int BITS, int MODE>
+hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
+{
+    // 256 x 256 tiles while they give more than half of the CUs one (they run at 1.1 PFLOP/s there), else 64 x 128 tiles,
+    // which lose half of that rate to waits and win it back by the number of CUs at work (4096 x 4096, 333 tokens: 192
+    // tiles instead of 32)
+    using Large = GemmTile<1, 8, 8, 1, 2, 4, 2, false>;
+    using LargeSplit = GemmTile<1, 4, 8, 1, 2, 4, 2, true>;
+    using Small = GemmTile<1, 4, 2, 4, 2, 3, 2, false>;
+    using SmallSplit = GemmTile<1, 4, 2, 4, 2, 3, 2, true>;
+    const uint64_t large = (uint64_t)((ga.a.N + 255) / 256) * ((ga.M + 255) / 256);
+    if (large >= 160) return ga.y_f32 ? launch_gemm_t<BITS, MODE, LargeSplit>(ga, s) : launch_gemm_t<BITS, MODE, Large>(ga, s);
+    return ga.y_f32 ? launch_gemm_t<BITS, MODE, SmallSplit>(ga, s) : launch_gemm_t<BITS, MODE, Small>(ga, s);
+}
+
+template <int BITS>
+hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
+{
+    // as many tokens per launch as the copies hold, in whole tiles where there are several launches
+    const uint32_t cap = (uint32_t)(kGemmHalves / a.K);
+    const uint32_t step = (uint32_t)M <= cap ? (uint32_t)M : cap / 256 ? cap / 256 * 256 : cap / 8 * 8;
+    if (!step) return hipErrorInvalidValue;
+    for (uint32_t m0 = 0; m0 < (uint32_t)M; m0 += step) {
+        GemmArgs ga;
+        ga.a = a;
+        ga.M = (uint32_t)M - m0 < step ? (uint32_t)M - m0 : step;
+        ga.MP = (ga.M + 7) / 8 * 8;
+        ga.a.x = a.x + (int64_t)m0 * a.x_stride;
+        ga.a.y = static_cast<char *>(a.y) + (size_t)m0 * (size_t)a.y_stride * (y_f32 ? 4 : 2);
+        ga.xp = xc->xb;
+        ga.xt = xc->xt;
+        ga.y_f32 = (int)y_f32;
+        const uint32_t nb = (uint32_t)(((uint64_t)ga.M * (a.K / 32) + 255) / 256), nt = a.col ? a.K / 64 * ((ga.M + 63) / 64) : 0u;
+        hipLaunchKernelGGL(relayout_x_gemm_kernel<BITS>, dim3(nb + nt), dim3(256), 0, s, ga.a.x, a.x_stride, ga.M, a.K, (int)a.x_bf16,
+                           xc->xb, xc->xt, ga.MP, nb);
+        hipError_t err = hipGetLastError();
+        if (err == hipSuccess) err = mode == 1 ? launch_gemm_m<BITS, 1>(ga, s) : launch_gemm_m<BITS, 0>(ga, s);
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
+}
+
+}  // namespace
+
+// V2 and V2a at 2 to 4 bits, more than 64 tokens.  Rows up to 65536 columns (an outlier's column is kept in 16 bits;
+// the copies of 8 tokens fit the workspace) and 128 rows and more: smaller matrices leave the chip to a few workgroups
+// either way, and the 64-token kernel's 32-row tiles give them more.
+bool gemm_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M)
+{
+    return bits >= 2 && bits <= 4 && (mode == 0 || (mode == 1 && L >= 1)) && M > 64 && N >= 128 && K % kGroup == 0 && K <= 65536;
+}
+
+// M tokens in as many pairs of launches (copies, product) as the workspace's copies need.
+hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
+{
+    if (!xc) return hipErrorInvalidValue;
+    if (bits == 4) return launch_gemm_b<4>(mode, a, M, y_f32, xc, s);
+    if (bits == 3) return launch_gemm_b<3>(mode, a, M, y_f32, xc, s);
+    return launch_gemm_b<2>(mode, a, M, y_f32, xc, s);
+}
+
+}  // namespace xfp

@@ -55,12 +55,15 @@ constexpr int kXtTokens = 16;                      // tokens per launch of the b
 //                               the 64 lanes of a wave read 1 KB contiguous (from the row-major x the
 //                               same load touches 64 different cache lines).
 // Tokens >= M are zero in both.
+// The prompt kernel keeps copies of its own making there, of as many tokens as fit: [k][tokens] and [token][k].
+constexpr uint64_t kGemmHalves = 1ull << 24;       // 2048 tokens of 8192 columns
 struct XCopies {
-    uint16_t xt[kXtMaxK * kXtTokens];
-    uint16_t xb[kXtMaxK * kXtTokens];
+    uint16_t xt[kGemmHalves];
+    uint16_t xb[kGemmHalves];
 };
+static_assert(kGemmHalves >= (uint64_t)kXtMaxK * kXtTokens, "the batched and wide kernels' copies fit too");
 struct WorkspaceLayout {
-    XCopies xc;                  // batched kernel: re-laid activations (2 MB)
+    XCopies xc;                  // re-laid activations (2 x 32 MB)
     float epi[kPlaneFloats];     // unfused epilogues: per-slot fp32 results
     float part[kPlaneFloats];    // split-K: per-slice fp32 partial sums
 };
@@ -128,6 +131,9 @@ bool wide_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
                    uint64_t copy_cap = (uint64_t)kXtMaxK * kXtTokens);
 hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, float *sx,
                               hipStream_t s);
+// Prompt kernel: more than 64 tokens as one tiled product per 2^23 / K tokens (V2 and V2a at 2..4 bits, any library).
+bool gemm_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M);
+hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s);
 hipError_t launch_silu_mul(const float *y, uint32_t half, int slots, void *h, int64_t h_stride, bool h_f32,
                            bool h_bf16, hipStream_t s);
 // Down projection with the router's weighted sum over the slots in one launch (V2, T <= 8, T * K <= 16384)

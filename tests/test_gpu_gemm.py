@@ -1,0 +1,84 @@
+"""The prompt kernel (more than 64 tokens as one tiled product, V2 and V2a at 2 to 4 bits): parity with the oracle at the
+edges of its tiles, its order of k bit-exactly through one-hot activations, types, strides and repeatability."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_14844_amd as xfp
+import xfp_inputs as xi
+from helpers import gated_rel_err
+
+pytestmark = pytest.mark.gpu
+V2, V2A = xi.MODE_V2, xi.MODE_V2A
+
+
+def dev_x(x_bits):
+    return torch.from_numpy(np.ascontiguousarray(x_bits).view(np.int16)).cuda().view(torch.float16)
+
+
+# N: the fewest rows, a ragged last row tile, one row more than a tile; K: one group (fewer columns than a stage of
+# the small tile), odd group counts, a row of 64 groups; M: one token more than the 64-token kernel takes, ragged last
+# token tiles, more than a tile; outliers: none, the benchmark's density, more than LDS holds of a tile
+@pytest.mark.parametrize("N,K,M,dens", [(128, 128, 65, 0.01), (129, 384, 129, 0.003), (200, 4096, 200, 0.003), (257, 1152, 333, 0.0),
+                                        (128, 8192, 70, 0.04), (8200, 256, 1500, 0.003), (8193, 640, 1537, 0.002)])
+@pytest.mark.parametrize("bits", [4, 3, 2])
+@pytest.mark.parametrize("mode", [V2, V2A])
+def test_prompt_parity(mode, bits, N, K, M, dens):
+    W = xi.random_weights(mode, bits, N, K, L=33, density=dens, seed=N + K + M + bits)
+    xb = xi.activations(np.random.default_rng(M), M, K)
+    dW, xd = xfp.upload(W), dev_x(xb)
+    assert xfp.xfp_route(dW, M) == (xfp.XFP_ROUTE_GEMM, M)
+    y32, y16 = xfp.xfp_gemv(dW, xd, y_dtype=torch.float32), xfp.xfp_gemv(dW, xd)
+    again = xfp.xfp_gemv(dW, xd, y_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = oracle.gemv_weights(W, xb)
+    assert gated_rel_err(y32.cpu().numpy(), ref) <= 1e-4
+    assert gated_rel_err(y16.float().cpu().numpy(), ref) <= 1e-3
+    assert torch.equal(y32, again)
+
+
+@pytest.mark.parametrize("mode,bits,K", [(V2, 4, 640), (V2, 3, 640), (V2, 2, 384), (V2A, 4, 384), (V2A, 3, 640), (V2A, 2, 384)])
+def test_one_hot_tokens_read_single_weights(mode, bits, K):
+    """Token m is one at column (7 m) mod K: y[m][n] is that column of the matrix, one rounding of the sum of its codebook
+    entry and (where there is one) its outlier."""
+    W = xi.random_weights(mode, bits, 150, K, L=5, density=0.02, seed=bits)
+    M = K + 3
+    cols = (7 * np.arange(M)) % K
+    x = np.zeros((M, K), dtype=np.float16)
+    x[np.arange(M), cols] = 1.0
+    dW = xfp.upload(W)
+    y = xfp.xfp_gemv(dW, torch.from_numpy(x).cuda(), y_dtype=torch.float32)
+    bulk = xfp.xfp_dequant_bulk(dW).view(torch.float16).float()
+    torch.cuda.synchronize()
+    dense = bulk.cpu().numpy()
+    for n in range(W.N):
+        s = slice(W.out_row_ptr[n], W.out_row_ptr[n + 1])
+        dense[n, W.out_col[s]] += W.out_val[s].view(np.float16).astype(np.float32)
+    assert np.array_equal(y.cpu().numpy(), dense.T[cols])
+
+
+@pytest.mark.parametrize("N,M", [(300, 100), (8196, 1600)])
+def test_bf16_strides_and_untouched_padding(N, M):
+    K = 512
+    W = xi.random_weights(V2, 4, N, K, density=0.003, seed=77)
+    x = torch.randn((M, K + 24), generator=torch.Generator().manual_seed(3)).bfloat16()
+    x = torch.where(x.abs() < 2.0 ** -10, torch.full_like(x, 0.5), x)                       # exact in fp16
+    ref = oracle.gemv_weights(W, x[:, :K].half().contiguous().view(torch.int16).numpy().view(np.uint16))
+    dW = xfp.upload(W)
+    for ldy in (N + 3, N + 4):                                                             # single and four-value stores
+        buf = torch.full((M, ldy), -3.0, dtype=torch.bfloat16, device="cuda")
+        xfp.xfp_gemv(dW, x.cuda()[:, :K], y=buf[:, :N])
+        torch.cuda.synchronize()
+        assert gated_rel_err(buf[:, :N].float().cpu().numpy(), ref) <= 6e-3
+        assert torch.all(buf[:, N:] == -3.0)
+
+
+def test_more_tokens_than_the_copies_hold():
+    """65536 columns: 128 tokens per pair of launches; 65536 + 128 columns are not this kernel's."""
+    W = xi.random_weights(V2, 2, 130, 65536, density=0.001, seed=5)
+    xb = xi.activations(np.random.default_rng(9), 150, W.K)
+    dW = xfp.upload(W)
+    y = xfp.xfp_gemv(dW, dev_x(xb), y_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert gated_rel_err(y.cpu().numpy(), oracle.gemv_weights(W, xb)) <= 1e-4
