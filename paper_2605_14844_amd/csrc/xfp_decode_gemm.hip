@@ -5,7 +5,7 @@
 // not by the weights' bytes, and the 64-token kernel, which this takes over from above 64 tokens, reads and
 // dequantises the whole matrix once per 64 tokens and fetches its activations from L2 once per 32 rows.
 //
-// Work unit: a workgroup of 8 waves owns BN output rows x BM tokens and walks K.
+// Work unit: a workgroup of 8 or 16 waves owns BN output rows x BM tokens and walks K.
 //  - Every lane dequantises the weights it needs itself, straight into the A operand of v_mfma_f32_32x32x16_f16: lane
 //    (i, h) owns row i of a block of 32 rows and one half of every 64 columns, the same rows for the whole kernel, so
 //    a V2 row's codebook stays in registers, split into byte planes (low and high bytes of the fp16 entries):
@@ -16,9 +16,9 @@
 //  - The B tile (BM tokens) comes from a token-major copy of the activations straight into LDS
 //    (buffer_load_dwordx4 ... lds: no registers, no VALU), through a ring of parts; its rows are XOR-swizzled in
 //    16-byte chunks so that 16 consecutive lanes of a ds_read_b128 cover the 64 banks.
-//  - 28672 x 8192, 4 bits, 2048 tokens: 1.24 ms against 2.13 ms in passes of 64 tokens; 850 us of it are the product
-//    without outliers (1.13 PFLOP/s: three and a half rounds of tiles on 256 CUs; the library's own dense product of
-//    this shape 0.71 ms), 300 us the outliers.  4096 x 4096, 2 bits, 333 tokens: 41 us against 94.
+//  - 28672 x 8192, 4 bits, 2048 tokens: 1.16 ms against 2.13 ms in passes of 64 tokens; 880 us of it are the product
+//    without outliers (1.1 PFLOP/s: three and a half rounds of tiles on 256 CUs; the library's own dense product of
+//    this shape 0.71 ms), 220 us the outliers.  4096 x 4096, 2 bits, 333 tokens: 35 us against 94.
 //
 // Order of k inside 32 weights: what the byte planes give cheaply is not the natural order (at 4 bits the even
 // nibbles of a dword come before the odd ones).  A product does not care as long as both operands agree, so the copy
@@ -146,29 +146,28 @@ __device__ __forceinline__ u32x4_t chunk(const Planes<BITS> &P, const words_t<BI
     return u32x4_t{d0, d1, d2, d3};
 }
 
-// Tile geometry: WN x WK waves; a wave owns 32 RB rows and all 32 TB tokens and takes every WK-th block of 64 columns
-// (the waves that share rows add their sums in LDS at the end).  A part of the B tile is SP of the block's four steps of
-// 16 columns, for each of the WK waves; NBUF of them in LDS, NBUF - 1 requested ahead.  R: blocks of index words a wave
-// has in flight.
-// SPLIT: the accumulators are added to a second set every 1024 columns and start again from zero.  A sum of n products
-// of 16 in one fp32 chain is off by about 2e-8 sqrt(n) of its size (n = 256 at 4096 columns: 3.1e-7 measured), which
-// a 16-bit result does not show and an fp32 result does; in chains of 64 it is off by 1.7e-7 at 8192 columns.
-template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_, int R_, bool SPLIT_>
+// Tile geometry: WN x WK waves; a wave owns 32 RB rows and all 32 TB tokens and takes every WK-th block of 256 columns
+// (the waves that share rows add their sums in LDS at the end), a block in four turns of 64.  A part of the B tile is SP
+// of a turn's four steps of 16 columns, for each of the WK waves; NBUF of them in LDS, NBUF - 1 requested ahead.
+// SPLIT: every block is a chain of its own, whose sums are added to a second set of registers.  A sum of n products of 16
+// in one fp32 chain is off by about 2e-8 sqrt(n) of its size (n = 256 at 4096 columns: 3.1e-7 measured), which a 16-bit
+// result does not show and an fp32 result does.
+template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_, bool SPLIT_>
 struct GemmTile {
-    static constexpr int RB = RB_, TB = TB_, WN = WN_, WK = WK_, SP = SP_, NBUF = NBUF_, R = R_;
+    static constexpr int RB = RB_, TB = TB_, WN = WN_, WK = WK_, SP = SP_, NBUF = NBUF_;
     static constexpr bool SPLIT = SPLIT_;
     static constexpr int BN = 32 * RB * WN, BM = 32 * TB, NW = WN * WK, T = NW * kWave;
     static constexpr int KB = 16 * SP * WK, RSB = KB * 2, kB = BM * RSB;   // a part: columns, bytes of a row, bytes
-    static constexpr int U = 4 / SP;                           // parts of a block
+    static constexpr int U = 4 / SP;                           // parts of a turn
     static_assert(SP == 2 || SP == 4, "");
     static constexpr int AHEAD = NBUF - 1;
     static constexpr int ND = kB / (NW * 1024);                // loads of a wave per part
     static constexpr int PR = BN * BM <= 32768 ? BN : 32768 / BM;          // rows of the outlier plane (in front of the tiles' life)
     static constexpr int kPlane = PR * BM * 4, kSums = (WK - 1) * BN * BM * 4, kTiles = NBUF * kB;
     static constexpr int kBase = kTiles > kPlane ? (kTiles > kSums ? kTiles : kSums) : (kPlane > kSums ? kPlane : kSums);
-    static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && R >= 2 && PR % NW == 0 && BN % PR == 0, "");
+    static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && PR % NW == 0 && BN % PR == 0, "");
     // registers: accumulators, operands (B twice), index words, planes; then waves per SIMD
-    static constexpr int kRegs = 16 * RB * TB * (SPLIT ? 2 : 1) + 16 * RB + 8 * TB + 4 * RB * R + 8 * RB + 60;
+    static constexpr int kRegs = 16 * RB * TB * (SPLIT ? 2 : 1) + 16 * RB + 8 * TB + 36 * RB + 8 * RB + 56;
     static constexpr int kWavesPerSimd = kRegs <= 128 ? 4 : kRegs <= 168 ? 3 : kRegs <= 256 ? 2 : 1;
 };
 
@@ -182,7 +181,7 @@ __device__ __forceinline__ uint32_t swz(uint32_t r)
 
 struct GemmArgs {
     DecodeArgs a;
-    const uint16_t *xp;    // [M][K] fp16, every block of 64 columns in the order of the kernel's steps
+    const uint16_t *xp;    // [M][K rounded up to 256] fp16, every block of 256 columns in the order of the kernel's steps
     const uint16_t *xt;    // [K][MP] fp16
     uint32_t M, MP;        // tokens of this launch; row length of xt (a multiple of 8)
     uint32_t row0, tiles_n, tiles_m;                           // first row, tiles of this launch
@@ -199,7 +198,7 @@ template <int BITS, int MODE, class C>
 __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(GemmArgs ga)
 {
     static_assert(MODE == 0 || MODE == 1, "V2, V2a");
-    constexpr int BN = C::BN, BM = C::BM, RB = C::RB, TB = C::TB, WK = C::WK, NW = C::NW, R = C::R;
+    constexpr int BN = C::BN, BM = C::BM, RB = C::RB, TB = C::TB, WK = C::WK, NW = C::NW;
     constexpr int CB = C::KB / 8;                              // 16-byte chunks of a row of a part
     extern __shared__ __align__(256) unsigned char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
@@ -208,7 +207,8 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     const uint32_t i = lane & 31, h = lane >> 5;
     const uint32_t wn = wave % C::WN, wk = wave / C::WN;
     const uint32_t N = a.N, K = a.K, M = ga.M;
-    const uint32_t wpr = K / 32 * BITS, G = K / kGroup, NBLK = K / 64, NT = (NBLK + WK - 1) / WK;
+    const uint32_t wpr = K / 32 * BITS, G = K / kGroup;
+    const uint32_t NB = (K + 255) / 256, NS = (NB + WK - 1) / WK;          // blocks of a row; of a wave
 
     // Workgroups are dealt to the 8 XCDs round-robin, each with an L2 of its own: an XCD takes a contiguous run of
     // tiles, row tiles fastest, so that its workgroups share the activations of one token tile (2 x 4 MB at 8192
@@ -219,9 +219,12 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     const uint32_t n0 = ga.row0 + t0 % ga.tiles_n * BN, m0 = t0 / ga.tiles_n * BM;
 
     // ---------------------------------------------------------------- A operands: this lane's rows
-    // Lane (i, h) holds, of row i of every row block, 32 weights of a block of 64 columns: half h.  Chunk s of the 32
-    // IS the operand of step s, so nothing moves between lanes and no A tile is needed.  (The copy of the activations
-    // has chunk s of half h of a block at its 16 bytes 2 s + h, so that a step's columns are neighbours.)
+    // Lane (i, h) dequantises, of row i of every row block, one half (a group of 128 weights) of a block: 64, 48 or 32
+    // bytes, fetched at once.  (A row's lines are then drawn once.  In pieces of 64 columns, a turn each, a 128-byte line
+    // was fetched from L2 four to eight times, the activations having displaced it from L1, and the traffic between L2
+    // and the CUs was what bounded the kernel.)  In turn p it makes the A operands of 32 weights, chunk s of them being
+    // step s's: nothing moves between lanes and there is no A tile.  The copy of the activations has chunk s of turn p
+    // of half h at the block's 16 bytes 8 p + 2 s + h.
     uint32_t row[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) row[rb] = min(n0 + (wn * RB + rb) * 32 + i, N - 1);
@@ -236,10 +239,10 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             P[rb].set(c);
         }
     } else {
-        // the library as planes behind the tiles: entry l at kBase + l * 2^BITS * 2, low bytes first
-        for (uint32_t j = tid; j < a.L * Planes<BITS>::ND; j += C::T) {
+        // the library as planes behind the tiles: entry l at kBase + l * 2^BITS * 2, low bytes first; entry L: zeros
+        for (uint32_t j = tid; j < (a.L + 1) * Planes<BITS>::ND; j += C::T) {
             const uint32_t l = j / Planes<BITS>::ND, d = j % Planes<BITS>::ND;
-            const uint2 v = *reinterpret_cast<const uint2 *>(a.cb + ((size_t)l << BITS) + 4 * d);
+            const uint2 v = l < a.L ? *reinterpret_cast<const uint2 *>(a.cb + ((size_t)l << BITS) + 4 * d) : make_uint2(0u, 0u);
             const uint32_t o = lds0 + C::kBase + l * (2u << BITS) + d * 4;
             *(lds_u32_t *)(uintptr_t)o = __builtin_amdgcn_perm(v.y, v.x, 0x06040200u);
             *(lds_u32_t *)(uintptr_t)(o + Planes<BITS>::ND * 4) = __builtin_amdgcn_perm(v.y, v.x, 0x07050301u);
@@ -247,31 +250,28 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     }
 
     // ---------------------------------------------------------------- results, and the outlier term they start from
-    // acc: what the matrix cores add to; sum: what the results are (the same registers unless SPLIT)
+    // acc: what the matrix cores add to; sum: what becomes the results (the same registers unless SPLIT)
     float16_t acc[RB][TB], acc2[RB][TB];
     float16_t (&sum)[RB][TB] = C::SPLIT ? acc2 : acc;
-    auto clear = [](float16_t (&v)[RB][TB]) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) v[rb][tb][r] = 0.f;
-    };
-    clear(sum);
+        for (int tb = 0; tb < TB; ++tb) sum[rb][tb] = float16_t{};
     // Wave w owns rows RW w .. of the plane, whose entries are one run of the CSR arrays, and walks it in units of up
     // to U EP entries of one row: lane (ep, o) takes entries ep, ep + EP, .. of a unit and the tokens m0 + 8 o .. + 7.
-    // Three units are under way at any time (entries fetched, activations gathered, products summed): an entry's
-    // activations are 16 BM / 8 bytes from L2, and it takes about 64 KB in flight per CU to draw them at full rate.
+    // An entry's activations are 2 BM bytes from L2, and it takes about 64 KB in flight per CU to draw them at full rate.
     const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
-    if (a.col && rp[min(n0, N)] < rp[min(n0 + BN, N)]) {
-        constexpr int OP = BM / 8, EP = 64 / OP, U = NW <= 4 && EP <= 4 ? 8 : 4, UE = U * EP, RW = C::PR / NW;
+    const int32_t ob = rp[min(n0, N)], oe = rp[min(n0 + BN, N)];
+    if (a.col && ob < oe) {
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + ob), 0, (oe - ob) * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + ob), 0, (oe - ob) * 2, 0x00020000);
+        constexpr int OP = BM / 8, EP = 64 / OP, U = EP >= 8 ? 2 : 4, D = 4, UE = U * EP, RW = C::PR / NW;
         static_assert(OP >= 4 && OP <= 32 && UE <= 64 && RW < 64, "");
         const uint32_t ep = lane / OP, o = lane % OP;
         const uint4 *xt = reinterpret_cast<const uint4 *>(ga.xt) + min((m0 >> 3) + o, ga.MP / 8 - 1);
         const uint32_t xs = ga.MP / 8, plane = lds0 + wave * (RW * BM * 4);
         struct Unit { uint32_t row; int32_t e, hi; bool last; };                            // wave-uniform
-        struct Gathered { uint4 x[U]; float v[U]; };
+        struct Gathered { uint4 x[U]; uint32_t v[U]; };
 #pragma unroll
         for (int pass = 0; pass < BN / C::PR; ++pass) {
             const int32_t rpv = a.rp[min(n0 + pass * C::PR + wave * RW + min(lane, (uint32_t)RW), N)];   // lane r: first entry of row r
@@ -287,19 +287,19 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
                 const uint32_t r = u.last ? u.row + 1 : u.row;
                 return unit_at(r, r >= (uint32_t)RW ? u.hi : u.last ? row_at(r) : u.e + UE);
             };
+            // No load here hangs on a condition: the compiler counts loads under way only along straight code, and a
+            // branch around one makes it wait for all of them at the next use.
             auto fetch = [&](const Unit &u) {                  // lane j: entry j of the unit, column | value << 16
-                const int32_t e = u.e + (int32_t)lane;
-                uint32_t v = 0u;
-                if (lane < (uint32_t)UE && e < u.hi) v = (uint32_t)a.col[e] | ((uint32_t)a.val[e] << 16);
-                return v;
+                const uint32_t e = (uint32_t)(u.e - ob) + lane;
+                const uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rc, e * 4, 0, 0), v = __builtin_amdgcn_raw_buffer_load_b16(rv, e * 2, 0, 0);
+                return c | (v << 16);                          // (past the tile's entries: zeros; past the row's: another row's)
             };
-            auto gather = [&](const Unit &u, uint32_t ents, Gathered &g) {
+            auto gather = [&](uint32_t ents, Gathered &g) {
 #pragma unroll
                 for (int j = 0; j < U; ++j) {
                     const uint32_t ent = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((j * EP + ep) * 4), (int)ents);
-                    g.v[j] = half_bits_to_float((uint16_t)(ent >> 16));
-                    g.x[j] = make_uint4(0u, 0u, 0u, 0u);       // no entry: zero times zeros
-                    if (u.e + j * EP + (int32_t)ep < u.hi) g.x[j] = xt[(size_t)(ent & 0xFFFFu) * xs];
+                    g.v[j] = ent >> 16;
+                    g.x[j] = xt[(size_t)(ent & 0xFFFFu) * xs];
                 }
             };
             float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -307,9 +307,11 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
 #pragma unroll
                 for (int j = 0; j < U; ++j) {
                     if (j && u.e + j * EP >= u.hi) break;      // wave-uniform
-                    const uint32_t w[4] = {g.x[j].x, g.x[j].y, g.x[j].z, g.x[j].w};
+                    const uint32_t have = u.e + j * EP + (int32_t)ep < u.hi ? ~0u : 0u;     // no entry: zero times zeros
+                    const float v = half_bits_to_float((uint16_t)(g.v[j] & have));
+                    const uint32_t w[4] = {g.x[j].x & have, g.x[j].y & have, g.x[j].z & have, g.x[j].w & have};
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) s[t] = fmaf(g.v[j], half_bits_to_float((uint16_t)(t & 1 ? w[t / 2] >> 16 : w[t / 2])), s[t]);
+                    for (int t = 0; t < 8; ++t) s[t] = fmaf(v, half_bits_to_float((uint16_t)(t & 1 ? w[t / 2] >> 16 : w[t / 2])), s[t]);
                 }
                 if (!u.last) return;
                 // the EP entry lanes of a token octet are added in a fixed tree
@@ -334,26 +336,39 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
 #pragma unroll
                 for (int t = 0; t < 8; ++t) s[t] = 0.f;
             };
-            Unit u0 = unit_at(0, row_at(0)), u1 = after(u0);
-            uint32_t ents1;
-            Gathered g0, g1;
-            {
-                const uint32_t ents0 = fetch(u0);
-                ents1 = fetch(u1);
-                gather(u0, ents0, g0);
+            // D units' activations and, D units further on, D units' entries are under way: a unit's entries were requested
+            // before the activations that have not been used yet, so waiting for them is not waiting for those
+            Unit gu[D], eu[D];
+            uint32_t ents[D];
+            Gathered g[D];
+            Unit next = unit_at(0, row_at(0));
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                gu[d] = next;
+                ents[d] = fetch(next);
+                next = after(next);
             }
-#pragma unroll 1
-            while (u0.row < (uint32_t)RW) {
-                Unit u2 = after(u1), u3 = after(u2);
-                const uint32_t ents2 = fetch(u2);
-                gather(u1, ents1, g1);
-                consume(u0, g0);
-                if (u1.row >= (uint32_t)RW) break;
-                ents1 = fetch(u3);
-                gather(u2, ents2, g0);
-                consume(u1, g1);
-                u0 = u2;
-                u1 = u3;
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                gather(ents[d], g[d]);
+                eu[d] = next;
+                ents[d] = fetch(next);
+                next = after(next);
+            }
+            for (bool more = true; more;) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    if (gu[d].row >= (uint32_t)RW) {
+                        more = false;
+                        break;
+                    }
+                    consume(gu[d], g[d]);
+                    gu[d] = eu[d];
+                    gather(ents[d], g[d]);
+                    eu[d] = next;
+                    ents[d] = fetch(next);
+                    next = after(next);
+                }
             }
             lds_barrier();
 #pragma unroll
@@ -371,151 +386,181 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     }
 
     // ---------------------------------------------------------------- loads of the main loop
-    // They are written as instructions because the compiler does not count loads to LDS: every turn issues the same
+    // They are written as instructions because the compiler does not count loads to LDS: every block issues the same
     // number of them in the same order (past the end: again the last block's), and every wait below states how many
-    // may still be under way.  Words: block t WK + wk of turn t, 16 (12, 8) bytes per lane and row block.
-    words_t<BITS> iw[R][RB];
-    uint32_t gid[R][RB];
-    auto load_words = [&](auto slot, uint32_t t) {
-        constexpr int S = decltype(slot)::value;
-        const uint32_t blk = min(t * WK + wk, NBLK - 1);
+    // may still be under way.
+    u32x4_t iw[2][RB][BITS];                                   // this block's words and the next one's
+    uint32_t gid[2][RB];
+    auto load_words = [&](auto buf, uint32_t t) {              // the wave's t-th block
+        constexpr int B = decltype(buf)::value;
+        const uint32_t grp = min(2 * (t * WK + wk) + h, G - 1);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const uint32_t *p = a.idx + (size_t)row[rb] * wpr + (blk * 2 + h) * BITS;
-            words_t<BITS> &w = iw[S][rb];
-            if constexpr (BITS == 4) asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(w) : "v"(p) : "memory");
-            else if constexpr (BITS == 3) asm volatile("global_load_dwordx3 %0, %1, off" : "=v"(w) : "v"(p) : "memory");
-            else asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(w) : "v"(p) : "memory");
+            const uint32_t *p = a.idx + (size_t)row[rb] * wpr + grp * (4 * BITS);
+#pragma unroll
+            for (int d = 0; d < BITS; ++d) {
+                u32x4_t &w = iw[B][rb][d];
+                asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(w) : "v"(p), "n"(16 * d) : "memory");
+            }
             if constexpr (MODE == 1) {
-                const uint8_t *g = a.gid + (size_t)row[rb] * G + blk / 2;
-                uint32_t &id = gid[S][rb];
+                const uint8_t *g = a.gid + (size_t)row[rb] * G + grp;
+                uint32_t &id = gid[B][rb];
                 asm volatile("global_load_ubyte %0, %1, off" : "=v"(id) : "v"(g) : "memory");
             }
         }
     };
-    constexpr int kWords = RB * (1 + MODE), kTurn = C::U * C::ND + kWords;     // loads of a turn: words; all
-    static_assert((R - 1) * kTurn <= 63 && (C::AHEAD - 1) * C::ND + C::AHEAD * kWords <= 63, "what vmcnt can say");
-    const u32x4_t rx = {(uint32_t)(uintptr_t)ga.xp, (uint32_t)((uintptr_t)ga.xp >> 32) & 0xFFFFu, M * K * 2, 0x00020000u};
+    constexpr int kWords = RB * (BITS + MODE);                 // loads of a block's words
+    static_assert(3 * C::U * C::ND <= 63 && (C::AHEAD - 1) * C::ND + kWords <= 63, "what vmcnt can say");
+    const u32x4_t rx = {(uint32_t)(uintptr_t)ga.xp, (uint32_t)((uintptr_t)ga.xp >> 32) & 0xFFFFu, M * (NB * 512), 0x00020000u};
     uint32_t boff[C::ND];
 #pragma unroll
     for (int e = 0; e < C::ND; ++e) {
         const uint32_t o = (wave * C::ND + e) * 1024 + lane * 16, r = o / C::RSB, p = (o % C::RSB / 16) ^ swz<CB>(r);
-        boff[e] = min(m0 + r, M - 1) * (K * 2) + p / (2 * C::SP) * 128 + p % (2 * C::SP) * 16;
+        boff[e] = min(m0 + r, M - 1) * (NB * 512) + p / (2 * C::SP) * 512 + p % (2 * C::SP) * 16;
     }
     uint32_t bload = 0;                                        // ring slot of the part being requested
     // Loads e0 .. e1 - 1 of a part.  They are spread over the steps: a wave that issues a part's loads at once stands in
     // front of its matrix instructions until the address unit has taken them all.
     auto load_b = [&](uint32_t q, int e0, int e1) {
-        const uint32_t dst = lds0 + bload * C::kB + wave * (C::ND * 1024), so = min(q / C::U, NT - 1) * (WK * 128) + q % C::U * (C::SP * 32);
+        const uint32_t dst = lds0 + bload * C::kB + wave * (C::ND * 1024), x = min(q, 4 * C::U * NS - 1),
+                       so = x / (4 * C::U) * (WK * 512) + x % (4 * C::U) * (C::SP * 32);
 #pragma unroll
         for (int e = e0; e < e1; ++e)
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                          :: "s"(dst + e * 1024), "v"(boff[e]), "s"(rx), "s"(so) : "memory");
         if (e1 == C::ND) bload = bload + 1 == C::NBUF ? 0 : bload + 1;
     };
-    auto arrived = [&](auto slot) {                            // the words of a slot may be used from here on
-        constexpr int S = decltype(slot)::value;
+    words_t<BITS> cw[RB];                                      // the words of the turn whose A operands are being made
+    auto arrived = [&](auto buf, uint32_t t) {                 // the words of a buffer may be used from here on
+        constexpr int B = decltype(buf)::value;
+        const bool dead = 2 * (t * WK + wk) + h >= G;          // second half of the last block of a row with an odd number of groups
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            words_t<BITS> &w = iw[S][rb];
-            asm volatile("" : "+v"(w));
+#pragma unroll
+            for (int d = 0; d < BITS; ++d) {
+                u32x4_t &w = iw[B][rb][d];
+                asm volatile("" : "+v"(w));
+            }
             if constexpr (MODE == 1) {
-                uint32_t &id = gid[S][rb];
+                uint32_t &id = gid[B][rb];
                 asm volatile("" : "+v"(id));
-                const uint32_t o = lds0 + C::kBase + id * (2u << BITS);
+                const uint32_t o = lds0 + C::kBase + (dead ? a.L : id) * (2u << BITS);
 #pragma unroll
                 for (int d = 0; d < Planes<BITS>::ND; ++d) {
                     P[rb].lo[d] = *(lds_cu32_t *)(uintptr_t)(o + d * 4);
                     P[rb].hi[d] = *(lds_cu32_t *)(uintptr_t)(o + (Planes<BITS>::ND + d) * 4);
                 }
+            } else if (dead) {                                 // (such a block is the wave's last)
+#pragma unroll
+                for (int d = 0; d < Planes<BITS>::ND; ++d) P[rb].lo[d] = P[rb].hi[d] = 0u;
             }
-            arrange<BITS>(iw[S][rb]);
+        }
+    };
+    auto take = [&](auto buf, int p) {                         // turn p's words
+        constexpr int B = decltype(buf)::value;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+            for (int d = 0; d < BITS; ++d) cw[rb][d] = iw[B][rb][(p * BITS + d) / 4][(p * BITS + d) % 4];
+            arrange<BITS>(cw[rb]);
         }
     };
 
     // ---------------------------------------------------------------- prologue: as if the turns before the first had run
-    half8_t af[4][RB], bf[2][TB];
-    auto dequantise = [&](auto slot, int s) {
-        constexpr int S = decltype(slot)::value;
+    constexpr int NH = TB >= 8 ? 2 : 1, TBH = TB / NH;         // many tokens: a step's B operands in two halves (registers)
+    half8_t af[4][RB], bf[2][TBH];
+    auto dequantise = [&](int s) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) af[s][rb] = __builtin_bit_cast(half8_t, chunk<BITS>(P[rb], iw[S][rb], s));
+        for (int rb = 0; rb < RB; ++rb) af[s][rb] = __builtin_bit_cast(half8_t, chunk<BITS>(P[rb], cw[rb], s));
     };
     const uint32_t br = lds0 + i * C::RSB + (((wk * (2 * C::SP) + h) ^ swz<CB>(i)) * 16);
-    auto operands = [&](int set, uint32_t buf, int s) {
+    auto operands = [&](int set, uint32_t buf, int s, int half) {
         const uint32_t ba = (br + buf * C::kB) ^ (uint32_t)(s % C::SP * 32);
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) bf[set][tb] = *(lds_ch8_t *)(uintptr_t)(ba + tb * (32 * C::RSB));
+        for (int tb = 0; tb < TBH; ++tb) bf[set][tb] = *(lds_ch8_t *)(uintptr_t)(ba + (half * TBH + tb) * (32 * C::RSB));
     };
+    using Even = std::integral_constant<int, 0>;
+    using Odd = std::integral_constant<int, 1>;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    for_each<R>([&](auto s) { load_words(s, decltype(s)::value); });
+    load_words(Even{}, 0);
 #pragma unroll
     for (int q = 0; q < C::AHEAD; ++q) load_b(q, 0, C::ND);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    arrived(std::integral_constant<int, 0>{});
+    arrived(Even{}, 0);
+    take(Even{}, 0);
 #pragma unroll
-    for (int s = 0; s < 3; ++s) dequantise(std::integral_constant<int, 0>{}, s);
-    operands(0, 0, 0);
-    if constexpr (C::SPLIT) clear(acc);
+    for (int s = 0; s < 3; ++s) dequantise(s);
+    operands(0, 0, 0, 0);
 
     // ---------------------------------------------------------------- main loop
-    // A turn is a block of 64 columns, four steps.  In step s the B operands of step s + 1 are read, the A operands of
-    // the next turn's step s - 1 are made (their registers were read by the step before) and the matrix instructions
-    // run.  The barrier that opens the next part stands in front of the last step, whose matrix instructions then cover
-    // the first reads behind it; a part's ring slot is refilled after the barrier that follows its last reads.
+    // A block is four turns of four steps.  In step s the B operands of step s + 1 are read, the A operands of the next
+    // turn's step s - 1 are made (their registers were read by the step before) and the matrix instructions run.  The
+    // barrier that opens the next part stands in front of a part's last step, whose matrix instructions then cover the
+    // first reads behind it; the loads that refill a ring slot follow the barrier behind its last reads.
     uint32_t bcur = 0;
-    auto turn = [&](auto slot, uint32_t t) {
-        constexpr int S = decltype(slot)::value, NX = (S + 1) % R;
-        using Next = std::integral_constant<int, NX>;
-        const bool on = WK == 1 || t * WK + wk < NBLK;         // (the last part of a row may have no block for this wave)
-        for_each<4>([&](auto step) {
-            constexpr int s = decltype(step)::value, u = s / C::SP;
-            constexpr bool last = s % C::SP == C::SP - 1;      // of a part
+    auto block = [&](auto buf, uint32_t t) {
+        constexpr int B = decltype(buf)::value;
+        using Next = std::integral_constant<int, B ^ 1>;
+        const bool on = WK == 1 || t * WK + wk < NB;           // (the last round of a row may have no block for this wave)
+        for_each<16>([&](auto step) {
+            constexpr int p = decltype(step)::value / 4, s = decltype(step)::value % 4;        // turn, step in it
+            constexpr int x = p * C::U + s / C::SP;            // part of the block
+            constexpr bool last = s % C::SP == C::SP - 1;      // of the part
             const uint32_t bnext = bcur + 1 == C::NBUF ? 0 : bcur + 1;
-            if constexpr (!last) operands((s + 1) & 1, bcur, s + 1);
-            load_b(t * C::U + u + C::AHEAD, s % C::SP * C::ND / C::SP, (s % C::SP + 1) * C::ND / C::SP);
-            if constexpr (s == 0) dequantise(slot, 3);
+            constexpr int set = NH == 2 ? 0 : s & 1;           // where the step's first operands are
+            auto multiply = [&](int from, int half) {
+                if (on)
+#pragma unroll
+                    for (int tb = 0; tb < TBH; ++tb)
+#pragma unroll
+                        for (int rb = 0; rb < RB; ++rb)
+                            acc[rb][half * TBH + tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                                af[s][rb], bf[from][tb], C::SPLIT && p + s == 0 ? float16_t{} : acc[rb][half * TBH + tb], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            load_b(t * (4 * C::U) + x + C::AHEAD, s % C::SP * C::ND / C::SP, (s % C::SP + 1) * C::ND / C::SP);
+            if constexpr (NH == 2) {
+                operands(1, bcur, s, 1);
+                if constexpr (s == 0) dequantise(3);
+                multiply(0, 0);
+            }
+            if constexpr (!last) operands(set ^ (NH & 1), bcur, s + 1, 0);
+            if constexpr (NH == 1 && s == 0) dequantise(3);
             if constexpr (s == 1) {
-                load_words(slot, t + R);
-                asm volatile("s_waitcnt vmcnt(%0)" :: "n"((R - 1) * kTurn) : "memory");     // the next turn's words
-                arrived(Next{});
+                if constexpr (p == 0) load_words(Next{}, t + 1);
+                if constexpr (p == 3) {                        // the next block's words: three turns ago
+                    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * C::U * C::ND) : "memory");
+                    arrived(Next{}, t + 1);
+                    take(Next{}, 0);
+                } else {
+                    take(buf, p + 1);
+                }
             }
             if constexpr (last) {
-                // The next part, requested AHEAD parts ago.  Younger: the parts requested since, and the words of every
-                // turn whose second step has been since its last load (that is in the second or in the fourth step).
-                constexpr int kWordsSince = C::U == 1 ? C::AHEAD - 1 : (C::AHEAD + (u == 0 ? 1 : 0)) / 2;
-                constexpr int kYounger = (C::AHEAD - 1) * C::ND + kWordsSince * kWords;
+                // The next part, requested AHEAD parts ago.  Younger: the parts requested since, and a block's words if
+                // they have been since its last load (they come in the second step of a block).
+                constexpr int from = x + 1 - C::AHEAD + (C::SP == 4 ? 1 : 0);                  // first part whose words are younger
+                constexpr bool words = from <= 0 || (from > x ? false : from % (4 * C::U) == 0);
+                constexpr int kYounger = (C::AHEAD - 1) * C::ND + (words && from <= x ? kWords : 0);
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kYounger) : "memory");
-                operands((s + 1) & 1, bnext, (s + 1) % 4);
+                operands(set ^ (NH & 1), bnext, (s + 1) % 4, 0);
             }
-            if constexpr (s > 0) dequantise(Next{}, s - 1);
-            if (on)
-#pragma unroll
-                for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-                    for (int rb = 0; rb < RB; ++rb)
-                        acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[s][rb], bf[s & 1][tb], acc[rb][tb], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (s > 0) dequantise(s - 1);
+            multiply(NH == 2 ? 1 : set, NH - 1);
             if constexpr (last) bcur = bnext;
         });
-    };
-#pragma unroll 1
-    for (uint32_t t = 0; t < NT; t += R) {
-        for_each<R>([&](auto s) {
-            if (decltype(s)::value == 0 || t + decltype(s)::value < NT) turn(s, t + decltype(s)::value);
-        });
         if constexpr (C::SPLIT) {
-            static_assert(16 % R == 0, "");
-            if ((t + R) % (16 / WK > R ? 16 / WK : R) == 0 || t + R >= NT) {
+            if (on)
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                    for (int tb = 0; tb < TB; ++tb) {
-                        sum[rb][tb] += acc[rb][tb];
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[rb][tb][r] = 0.f;
-                    }
-            }
+                    for (int tb = 0; tb < TB; ++tb) sum[rb][tb] += acc[rb][tb];
         }
+    };
+#pragma unroll 1
+    for (uint32_t t = 0; t < NS; t += 2) {
+        block(Even{}, t);
+        if (t + 1 < NS) block(Odd{}, t + 1);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // (loads to LDS that nobody waits for)
 
@@ -583,22 +628,28 @@ __global__ __launch_bounds__(256) void relayout_x_gemm_kernel(const uint16_t *x,
                                                               uint16_t *xp, uint16_t *xt, uint32_t MP, uint32_t nb)
 {
     if (blockIdx.x < nb) {
-        const uint32_t id = blockIdx.x * 256 + threadIdx.x, runs = K / 32;
+        // run c of token m: half h, turn p of block B in the source's order is run 8 B + 4 h + p; the last block of a row
+        // with an odd number of groups has zeros for its second half
+        const uint32_t id = blockIdx.x * 256 + threadIdx.x, runs = (K + 255) / 256 * 8;
         if (id >= M * runs) return;
-        const uint32_t m = id / runs, c = id - m * runs;
-        const uint4 *p = reinterpret_cast<const uint4 *>(x + (size_t)m * ldx + (size_t)c * 32);
+        const uint32_t m = id / runs, c = id - m * runs, hh = c / 4 % 2, p4 = c % 4;
         uint32_t w[16];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint4 v = p[j];
-            w[4 * j] = v.x; w[4 * j + 1] = v.y; w[4 * j + 2] = v.z; w[4 * j + 3] = v.w;
-        }
-        if (bf16) {
+        for (int j = 0; j < 16; ++j) w[j] = 0u;
+        if (c * 32 < K) {
+            const uint4 *p = reinterpret_cast<const uint4 *>(x + (size_t)m * ldx + (size_t)c * 32);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) w[j] = bf16x2_to_f16x2(w[j]);
+            for (int j = 0; j < 4; ++j) {
+                const uint4 v = p[j];
+                w[4 * j] = v.x; w[4 * j + 1] = v.y; w[4 * j + 2] = v.z; w[4 * j + 3] = v.w;
+            }
+            if (bf16) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) w[j] = bf16x2_to_f16x2(w[j]);
+            }
         }
         auto at = [&](int s) { const int k = slot_k(BITS, s); return k & 1 ? w[k / 2] >> 16 : w[k / 2] & 0xFFFFu; };
-        uint4 *o = reinterpret_cast<uint4 *>(xp + (size_t)m * K + (size_t)(c / 2) * 64) + c % 2;
+        uint4 *o = reinterpret_cast<uint4 *>(xp + ((size_t)m * runs + c / 8 * 8) * 32) + 8 * p4 + hh;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             uint32_t d[4];
@@ -635,13 +686,13 @@ template <int BITS, int MODE, class C>
 hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
 {
     auto kern = decode_gemm_kernel<BITS, MODE, C>;
-    const int lds = C::kBase + (MODE == 1 ? (int)(ga.a.L * (2u << BITS)) : 0);
+    const int lds = C::kBase + (MODE == 1 ? (int)((ga.a.L + 1) * (2u << BITS)) : 0);
     static std::atomic<int> configured[kMaxDevices];           // per device; idempotent attribute, benign race
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
     if (!configured[dev].load(std::memory_order_relaxed)) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             C::kBase + (MODE == 1 ? 256 * (2 << BITS) : 0));
+                                             C::kBase + (MODE == 1 ? 257 * (2 << BITS) : 0));
         if (err != hipSuccess) return err;
         configured[dev].store(1, std::memory_order_relaxed);
     }
@@ -656,13 +707,15 @@ hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
 template <int BITS, int MODE>
 hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
 {
-    // 256 x 256 tiles while they give more than half of the CUs one (they run at 1.1 PFLOP/s there), else 64 x 128 tiles,
-    // which lose half of that rate to waits and win it back by the number of CUs at work (4096 x 4096, 333 tokens: 192
-    // tiles instead of 32)
-    using Large = GemmTile<1, 8, 8, 1, 2, 4, 2, false>;
-    using LargeSplit = GemmTile<1, 4, 8, 1, 2, 4, 2, true>;
-    using Small = GemmTile<1, 4, 2, 4, 2, 3, 2, false>;
-    using SmallSplit = GemmTile<1, 4, 2, 4, 2, 3, 2, true>;
+    // 256 x 256 tiles while they give more than half of the CUs one (they run at 1.1 PFLOP/s there), else 128 x 64 tiles,
+    // which lose more than half of that rate to waits and win it back by the number of CUs at work (4096 x 4096, 333
+    // tokens: 192 tiles instead of 32).  With few workgroups a CU's latency is what counts: 16 waves, four to a SIMD, of
+    // which four share their rows and a quarter of K each.  fp32 results: half the rows, or half the waves, so that the
+    // second set of sums fits the registers.
+    using Large = GemmTile<1, 8, 8, 1, 4, 3, false>;
+    using LargeSplit = GemmTile<1, 4, 8, 1, 4, 3, true>;
+    using Small = GemmTile<1, 2, 4, 4, 4, 3, false>;
+    using SmallSplit = GemmTile<1, 2, 4, 2, 4, 3, true>;
     const uint64_t large = (uint64_t)((ga.a.N + 255) / 256) * ((ga.M + 255) / 256);
     if (large >= 160) return ga.y_f32 ? launch_gemm_t<BITS, MODE, LargeSplit>(ga, s) : launch_gemm_t<BITS, MODE, Large>(ga, s);
     return ga.y_f32 ? launch_gemm_t<BITS, MODE, SmallSplit>(ga, s) : launch_gemm_t<BITS, MODE, Small>(ga, s);
@@ -672,7 +725,7 @@ template <int BITS>
 hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
 {
     // as many tokens per launch as the copies hold, in whole tiles where there are several launches
-    const uint32_t cap = (uint32_t)(kGemmHalves / a.K);
+    const uint32_t runs = (a.K + 255) / 256 * 8, cap = (uint32_t)(kGemmHalves / (runs * 32));
     const uint32_t step = (uint32_t)M <= cap ? (uint32_t)M : cap / 256 ? cap / 256 * 256 : cap / 8 * 8;
     if (!step) return hipErrorInvalidValue;
     for (uint32_t m0 = 0; m0 < (uint32_t)M; m0 += step) {
@@ -685,7 +738,7 @@ hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, XCopi
         ga.xp = xc->xb;
         ga.xt = xc->xt;
         ga.y_f32 = (int)y_f32;
-        const uint32_t nb = (uint32_t)(((uint64_t)ga.M * (a.K / 32) + 255) / 256), nt = a.col ? a.K / 64 * ((ga.M + 63) / 64) : 0u;
+        const uint32_t nb = (uint32_t)(((uint64_t)ga.M * runs + 255) / 256), nt = a.col ? a.K / 64 * ((ga.M + 63) / 64) : 0u;
         hipLaunchKernelGGL(relayout_x_gemm_kernel<BITS>, dim3(nb + nt), dim3(256), 0, s, ga.a.x, a.x_stride, ga.M, a.K, (int)a.x_bf16,
                            xc->xb, xc->xt, ga.MP, nb);
         hipError_t err = hipGetLastError();
