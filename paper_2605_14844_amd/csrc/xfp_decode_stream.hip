@@ -105,27 +105,15 @@ hipError_t launch_silu_mul(const float *y, uint32_t half, int slots, void *h, in
     return hipGetLastError();
 }
 
-// bf16 -> fp16, eight values per thread.  A bf16 value is exact in fp32; the
-// rounding to fp16 is exact inside fp16's normal range, rounds to a multiple of
-// 2^-24 below 2^-14 and saturates at +-65504 (an activation that large would
-// otherwise become an infinity and poison every output).
+// bf16 -> fp16, eight values per thread.
 __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const uint16_t *src, int64_t ld, uint16_t *dst, uint32_t rows,
                                                           uint32_t K)
 {
     const uint32_t c8 = blockIdx.x * 256 + threadIdx.x, row = blockIdx.y;
     if (c8 * 8 >= K) return;
     const uint4 v = *reinterpret_cast<const uint4 *>(src + (size_t)row * ld + (size_t)c8 * 8);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    uint32_t o[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float lo = __builtin_bit_cast(float, w[i] << 16), hi = __builtin_bit_cast(float, w[i] & 0xFFFF0000u);
-        lo = lo != lo ? lo : fminf(fmaxf(lo, -65504.f), 65504.f);      // NaN stays NaN
-        hi = hi != hi ? hi : fminf(fmaxf(hi, -65504.f), 65504.f);
-        const _Float16 l16 = (_Float16)lo, h16 = (_Float16)hi;
-        o[i] = (uint32_t)__builtin_bit_cast(uint16_t, l16) | ((uint32_t)__builtin_bit_cast(uint16_t, h16) << 16);
-    }
-    *reinterpret_cast<uint4 *>(dst + (size_t)row * K + (size_t)c8 * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+    *reinterpret_cast<uint4 *>(dst + (size_t)row * K + (size_t)c8 * 8) =
+        make_uint4(bf16x2_to_f16x2(v.x), bf16x2_to_f16x2(v.y), bf16x2_to_f16x2(v.z), bf16x2_to_f16x2(v.w));
 }
 
 hipError_t launch_bf16_to_f16(const void *src, int64_t ld, void *dst, uint32_t rows, uint32_t K, hipStream_t s)
