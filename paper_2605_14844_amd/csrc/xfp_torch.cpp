@@ -141,12 +141,14 @@ PyObject *py_gemv(PyObject *, PyObject *const *a, Py_ssize_t n)
     try {
         Descriptor W(a[0]);
         const at::Tensor &x = tensor(a[1]);
-        const bool flat = x.dim() == 1;
+        // what is not a matrix is the one row of a matrix: [K] is [1, K] (more dimensions: a row the library refuses as too short)
+        const bool flat = x.dim() != 2;
         const int64_t M = flat ? 1 : x.size(0), cols = flat ? x.size(0) : x.size(1);
         at::Tensor y = output(a[2], a[3], {M, (int64_t)W->N}, x);
+        const bool yflat = y.dim() != 2;
         const int64_t ldx = M > 1 ? x.stride(0) : std::max<int64_t>(cols, 1);
-        const int64_t ycols = y.dim() == 1 ? y.size(0) : y.size(1);
-        const int64_t ldy = M > 1 && y.dim() > 1 ? y.stride(0) : std::max<int64_t>(ycols, 1);
+        const int64_t ycols = yflat ? y.size(0) : y.size(1);
+        const int64_t ldy = M <= 1 ? std::max<int64_t>(ycols, 1) : yflat ? y.size(0) * y.stride(0) : y.stride(0);
         const int code = y_code(y.scalar_type(), x.scalar_type());
         void *s = stream_of(a[4]), *xp = ptr(x), *yp = ptr(y);
         call([&] { return (NOALLOC ? g_gemv_noalloc : g_gemv)(W.get(), xp, (int)M, ldx, yp, code, ldy, s); });

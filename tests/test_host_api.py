@@ -297,3 +297,12 @@ def test_dispatch_invariants_over_random_descriptors():
             left -= n
             launches += 1
             assert launches <= M
+
+
+def test_more_than_two_dimensions_are_not_tokens():
+    """x [2, 1, K] is no matrix of two tokens: one row of two columns, which the library refuses."""
+    import torch
+    W = type("W", (), {"desc": desc(), "N": 64})
+    with pytest.raises(xfp.XfpError) as e:
+        xfp.xfp_gemv(W, torch.zeros((2, 1, 256), dtype=torch.float16), stream=0)
+    assert e.value.status == -2
