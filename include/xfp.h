@@ -148,9 +148,9 @@ typedef struct xfp_weights {
  *        through a static scratch plane.  The same formats with more than 16
  *        tokens read the weights once per up to 64 tokens (as many chunks
  *        of 16 as 16 * ceil(m / 16) * K <= 2^19 allows: 64 tokens up to
- *        K = 8192, 32 up to 16384); with more than 64 tokens, 128 rows and
- *        more and K <= 65536 they run as one tiled product per 2^24 / K
- *        tokens; any other shape or width runs the M = 1 path once per
+ *        K = 8192, 32 up to 16384); prompts (more than about 200 tokens,
+ *        more where the matrix is large, 128 rows and more, K <= 65536) run
+ *        as one tiled product per 2^24 / K tokens; any other shape or width runs the M = 1 path once per
  *        token.  Same results either way, to rounding.
  * XFP_ERR_UNSUPPORTED for a row no kernel takes: longer than 16384 columns, not
  * 4-bit V2 (whose rows of any length the tile kernel takes), with no split into
@@ -361,7 +361,7 @@ typedef enum {
     XFP_ROUTE_TILE = 3,      /* M = 1 per slot, 32 rows across the lanes                                             */
     XFP_ROUTE_BATCH = 4,     /* 2 .. 16 tokens on the matrix cores, activations in registers                         */
     XFP_ROUTE_WIDE = 5,      /* 17 .. 64 tokens on the matrix cores in one pass over the weights                     */
-    XFP_ROUTE_GEMM = 6       /* prompts: more than 64 tokens as a tiled product on the matrix cores                  */
+    XFP_ROUTE_GEMM = 6       /* prompts: many tokens as a tiled product on the matrix cores                          */
 } xfp_route_id;
 int xfp_route(const xfp_weights *W, int M, int expert_indexed, int *tokens);
 

@@ -214,12 +214,34 @@ bool wide_affine(const xfp_weights *W, bool expert_indexed, int tokens)
            xfp::wide_supports((int)W->bits, 2, W->L, W->N, W->K, tokens);
 }
 
+// Prompts: the tiled product against passes of the wide kernel (64 tokens up to 8192 columns, 32 to 16 beyond).  A round
+// of 128 x 64 tiles takes the same time for any number of them up to the 256 CUs, a pass grows with the rows only from
+// 256 tiles of 32 on.  Measured at 2 formats, fp16 and fp32 results, us passes / product:
+//  - one round: 4096 x 4096, fp32: 65 tokens 23 / 47, 128 36 / 47, 193 51 / 44, 512 112 / 45: from 193 tokens on;
+//  - more rounds: 16384 x 8192, fp32: 0.81 of the passes' rate at 257 tokens, 0.92 at 448, 1.02 at 512, 1.5 at 1024;
+//  - more than half a round of 256 x 256 tiles: 28672 x 8192, fp32: 0.99 at 320 tokens, 1.17 at 384;
+//  - rows beyond 16384 columns, which are passed over once per 16 tokens: 2048 x 28672 at 128 tokens 210 / 176 (fp32
+//    212 / 214), 8192 x 28672 326 / 190.
+// Formats that no matrix-core kernel takes otherwise (libraries beyond LDS, rows beyond 32768 columns) run token by token.
+bool prefer_gemm(const xfp_weights *W, int tokens)
+{
+    const int bits = (int)W->bits, mode = (int)W->mode;
+    if (!xfp::gemm_supports(bits, mode, W->L, W->N, W->K, tokens)) return false;
+    if (!xfp::batch_supports(bits, mode, W->L, W->N, W->K, 16) && !xfp::wide_supports(bits, mode, W->L, W->N, W->K, 16) &&
+        (uint64_t)W->N * W->K >= (1ull << 22))
+        return true;
+    if (W->K > 16384 && W->N >= 2048 && tokens >= 128) return true;
+    const uint64_t m = (uint64_t)tokens, small = ((uint64_t)W->N + 127) / 128 * ((m + 63) / 64),
+                   large = ((uint64_t)W->N + 255) / 256 * ((m + 255) / 256);
+    return tokens > 192 && (small <= 256 || tokens >= 512 || (large >= 160 && tokens >= 384));
+}
+
 Plan plan(const xfp_weights *W, bool expert_indexed, int slots)
 {
     const int bits = (int)W->bits, mode = (int)W->mode;
     const bool gen = general_only(W);
     // prompts: one tiled product for all remaining tokens
-    if (!gen && !expert_indexed && xfp::gemm_supports(bits, mode, W->L, W->N, W->K, slots)) return Plan{XFP_ROUTE_GEMM, slots, 0};
+    if (!gen && !expert_indexed && prefer_gemm(W, slots)) return Plan{XFP_ROUTE_GEMM, slots, 0};
     if (!gen && !expert_indexed && slots >= 2) {
         // batched tokens: the weights are read once per 16 tokens, once per up to 64 where the wide kernel takes
         // the format and its re-laid copies fit the workspace

@@ -2,7 +2,7 @@
 // bits), as a tiled matrix product on the matrix cores whose weight operand is dequantised on the way.
 //
 // Why: with hundreds of tokens the product is bound by the matrix cores (28672 x 8192 with 2048 tokens: 0.96 TFLOP),
-// not by the weights' bytes, and the 64-token kernel, which this takes over from above 64 tokens, reads and
+// not by the weights' bytes, and the 64-token kernel reads and
 // dequantises the whole matrix once per 64 tokens and fetches its activations from L2 once per 32 rows.
 //
 // Work unit: a workgroup of 8 or 16 waves owns BN output rows x BM tokens and walks K.
@@ -750,7 +750,7 @@ hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, XCopi
 
 }  // namespace
 
-// V2 and V2a at 2 to 4 bits, more than 64 tokens.  Rows up to 65536 columns (an outlier's column is kept in 16 bits;
+// What the kernel takes: V2 and V2a at 2 to 4 bits, more than 64 tokens (which calls prefer it: prefer_gemm).  Rows up to 65536 columns (an outlier's column is kept in 16 bits;
 // the copies of 8 tokens fit the workspace) and 128 rows and more: smaller matrices leave the chip to a few workgroups
 // either way, and the 64-token kernel's 32-row tiles give them more.
 bool gemm_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M)

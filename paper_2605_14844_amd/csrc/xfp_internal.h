@@ -131,7 +131,7 @@ bool wide_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
                    uint64_t copy_cap = (uint64_t)kXtMaxK * kXtTokens);
 hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, float *sx,
                               hipStream_t s);
-// Prompt kernel: more than 64 tokens as one tiled product per 2^24 / K tokens (V2 and V2a at 2..4 bits, any library).
+// Prompt kernel: many tokens as one tiled product per 2^24 / K tokens (V2 and V2a at 2..4 bits, any library).
 bool gemm_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M);
 hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s);
 hipError_t launch_silu_mul(const float *y, uint32_t half, int slots, void *h, int64_t h_stride, bool h_f32,

@@ -299,6 +299,18 @@ def test_dispatch_invariants_over_random_descriptors():
             assert launches <= M
 
 
+def test_prompts_take_the_product_where_it_is_the_faster_one():
+    v2a = dict(mode=1, group_ids=FAKE)
+    G, Wd = xfp.XFP_ROUTE_GEMM, xfp.XFP_ROUTE_WIDE
+    for kw, M, want in [(dict(N=4096, K=4096), 192, (Wd, 64)), (dict(N=4096, K=4096), 193, (G, 193)), (dict(N=127, K=4096), 193, (Wd, 64)),
+                        (dict(N=8192, K=8192), 256, (G, 256)), (dict(N=8192, K=8192), 257, (Wd, 64)), (dict(N=8192, K=8192), 512, (G, 512)),
+                        (dict(N=28672, K=8192), 383, (Wd, 64)), (dict(N=28672, K=8192), 384, (G, 384)),
+                        (dict(N=2048, K=28672), 127, (xfp.XFP_ROUTE_BATCH, 16)), (dict(N=2048, K=28672), 128, (G, 128)),
+                        (dict(N=4096, K=4096, L=256, **v2a), 65, (G, 65)), (dict(N=512, K=512, L=32, bits=3, **v2a), 65, (Wd, 64)),
+                        (dict(N=4096, K=4096, bits=5), 500, (xfp.XFP_ROUTE_GENERAL, 500))]:
+        assert xfp.xfp_route(desc(**kw), M) == want, (kw, M)
+
+
 def test_more_than_two_dimensions_are_not_tokens():
     """x [2, 1, K] is no matrix of two tokens: one row of two columns, which the library refuses."""
     import torch
