@@ -150,8 +150,9 @@ typedef struct xfp_weights {
  *        of 16 as 16 * ceil(m / 16) * K <= 2^19 allows: 64 tokens up to
  *        K = 8192, 32 up to 16384); prompts (more than about 200 tokens,
  *        more where the matrix is large, 128 rows and more, K <= 65536) run
- *        as one tiled product per 2^24 / K tokens; any other shape or width runs the M = 1 path once per
- *        token.  Same results either way, to rounding.
+ *        as one tiled product per 2^24 / K tokens, tokens left over as above;
+ *        any other shape or width runs the M = 1 path once per token.  Same
+ *        results either way, to rounding.
  * XFP_ERR_UNSUPPORTED for a row no kernel takes: longer than 16384 columns, not
  * 4-bit V2 (whose rows of any length the tile kernel takes), with no split into
  * equal slices of at most 8192 (or partial sums beyond the scratch plane) AND

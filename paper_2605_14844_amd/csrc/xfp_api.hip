@@ -223,13 +223,16 @@ bool wide_affine(const xfp_weights *W, bool expert_indexed, int tokens)
 //  - rows beyond 16384 columns, which are passed over once per 16 tokens: 2048 x 28672 at 128 tokens 210 / 176 (fp32
 //    212 / 214), 8192 x 28672 326 / 190.
 // Formats that no matrix-core kernel takes otherwise (libraries beyond LDS, rows beyond 32768 columns) run token by token.
-bool prefer_gemm(const xfp_weights *W, int tokens)
+bool gemm_only(const xfp_weights *W)
 {
     const int bits = (int)W->bits, mode = (int)W->mode;
-    if (!xfp::gemm_supports(bits, mode, W->L, W->N, W->K, tokens)) return false;
-    if (!xfp::batch_supports(bits, mode, W->L, W->N, W->K, 16) && !xfp::wide_supports(bits, mode, W->L, W->N, W->K, 16) &&
-        (uint64_t)W->N * W->K >= (1ull << 22))
-        return true;
+    return !xfp::batch_supports(bits, mode, W->L, W->N, W->K, 16) && !xfp::wide_supports(bits, mode, W->L, W->N, W->K, 16);
+}
+
+bool prefer_gemm(const xfp_weights *W, int tokens)
+{
+    if (!xfp::gemm_supports((int)W->bits, (int)W->mode, W->L, W->N, W->K, tokens)) return false;
+    if (gemm_only(W) && (uint64_t)W->N * W->K >= (1ull << 22)) return true;
     if (W->K > 16384 && W->N >= 2048 && tokens >= 128) return true;
     const uint64_t m = (uint64_t)tokens, small = ((uint64_t)W->N + 127) / 128 * ((m + 63) / 64),
                    large = ((uint64_t)W->N + 255) / 256 * ((m + 255) / 256);
@@ -240,8 +243,14 @@ Plan plan(const xfp_weights *W, bool expert_indexed, int slots)
 {
     const int bits = (int)W->bits, mode = (int)W->mode;
     const bool gen = general_only(W);
-    // prompts: one tiled product for all remaining tokens
-    if (!gen && !expert_indexed && prefer_gemm(W, slots)) return Plan{XFP_ROUTE_GEMM, slots, 0};
+    // prompts: one tiled product for the tokens that its copies of the activations hold; what is left over is planned
+    // like a call of its own (2049 tokens of 8192 columns: 2048, then one through the M = 1 kernels).  Formats with no other
+    // matrix-core kernel would run up to 64 tokens left over one by one: the last two launches share the tokens.
+    if (!gen && !expert_indexed && prefer_gemm(W, slots)) {
+        int take = xfp::gemm_tokens(W->K, slots);
+        if (slots - take > 0 && slots - take <= 64 && gemm_only(W)) take = (slots + 15) / 16 * 8;
+        return Plan{XFP_ROUTE_GEMM, take, 0};
+    }
     if (!gen && !expert_indexed && slots >= 2) {
         // batched tokens: the weights are read once per 16 tokens, once per up to 64 where the wide kernel takes
         // the format and its re-laid copies fit the workspace

@@ -724,41 +724,40 @@ hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
 template <int BITS>
 hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
 {
-    // as many tokens per launch as the copies hold, in whole tiles where there are several launches
-    const uint32_t runs = (a.K + 255) / 256 * 8, cap = (uint32_t)(kGemmHalves / (runs * 32));
-    const uint32_t step = (uint32_t)M <= cap ? (uint32_t)M : cap / 256 ? cap / 256 * 256 : cap / 8 * 8;
-    if (!step) return hipErrorInvalidValue;
-    for (uint32_t m0 = 0; m0 < (uint32_t)M; m0 += step) {
-        GemmArgs ga;
-        ga.a = a;
-        ga.M = (uint32_t)M - m0 < step ? (uint32_t)M - m0 : step;
-        ga.MP = (ga.M + 7) / 8 * 8;
-        ga.a.x = a.x + (int64_t)m0 * a.x_stride;
-        ga.a.y = static_cast<char *>(a.y) + (size_t)m0 * (size_t)a.y_stride * (y_f32 ? 4 : 2);
-        ga.xp = xc->xb;
-        ga.xt = xc->xt;
-        ga.y_f32 = (int)y_f32;
-        const uint32_t nb = (uint32_t)(((uint64_t)ga.M * runs + 255) / 256), nt = a.col ? a.K / 64 * ((ga.M + 63) / 64) : 0u;
-        hipLaunchKernelGGL(relayout_x_gemm_kernel<BITS>, dim3(nb + nt), dim3(256), 0, s, ga.a.x, a.x_stride, ga.M, a.K, (int)a.x_bf16,
-                           xc->xb, xc->xt, ga.MP, nb);
-        hipError_t err = hipGetLastError();
-        if (err == hipSuccess) err = mode == 1 ? launch_gemm_m<BITS, 1>(ga, s) : launch_gemm_m<BITS, 0>(ga, s);
-        if (err != hipSuccess) return err;
-    }
-    return hipSuccess;
+    const uint32_t runs = (a.K + 255) / 256 * 8;
+    GemmArgs ga;
+    ga.a = a;
+    ga.M = (uint32_t)M;
+    ga.MP = (ga.M + 7) / 8 * 8;
+    if ((uint64_t)a.K * ga.MP > kGemmHalves || (uint64_t)ga.M * runs * 32 > kGemmHalves) return hipErrorInvalidValue;
+    ga.xp = xc->xb;
+    ga.xt = xc->xt;
+    ga.y_f32 = (int)y_f32;
+    const uint32_t nb = (uint32_t)(((uint64_t)ga.M * runs + 255) / 256), nt = a.col ? a.K / 64 * ((ga.M + 63) / 64) : 0u;
+    hipLaunchKernelGGL(relayout_x_gemm_kernel<BITS>, dim3(nb + nt), dim3(256), 0, s, a.x, a.x_stride, ga.M, a.K, (int)a.x_bf16,
+                       xc->xb, xc->xt, ga.MP, nb);
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    return mode == 1 ? launch_gemm_m<BITS, 1>(ga, s) : launch_gemm_m<BITS, 0>(ga, s);
 }
 
 }  // namespace
 
 // What the kernel takes: V2 and V2a at 2 to 4 bits, more than 64 tokens (which calls prefer it: prefer_gemm).  Rows up to 65536 columns (an outlier's column is kept in 16 bits;
-// the copies of 8 tokens fit the workspace) and 128 rows and more: smaller matrices leave the chip to a few workgroups
+// the copies of 256 tokens fit the workspace) and 128 rows and more: smaller matrices leave the chip to a few workgroups
 // either way, and the 64-token kernel's 32-row tiles give them more.
 bool gemm_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M)
 {
     return bits >= 2 && bits <= 4 && (mode == 0 || (mode == 1 && L >= 1)) && M > 64 && N >= 128 && K % kGroup == 0 && K <= 65536;
 }
 
-// M tokens in as many pairs of launches (copies, product) as the workspace's copies need.
+int gemm_tokens(uint32_t K, int M)
+{
+    const uint32_t cap = (uint32_t)(kGemmHalves / ((K + 255) / 256 * 256)) & ~7u;
+    return (uint32_t)M <= cap ? M : (int)(cap >= 256 ? cap & ~255u : cap);
+}
+
+// One pair of launches: the copies of the activations, the product.
 hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
 {
     if (!xc) return hipErrorInvalidValue;

@@ -131,8 +131,11 @@ bool wide_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
                    uint64_t copy_cap = (uint64_t)kXtMaxK * kXtTokens);
 hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, float *sx,
                               hipStream_t s);
-// Prompt kernel: many tokens as one tiled product per 2^24 / K tokens (V2 and V2a at 2..4 bits, any library).
+// Prompt kernel: many tokens as one tiled product (V2 and V2a at 2..4 bits, any library), up to gemm_tokens per launch.
 bool gemm_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M);
+// How many of M tokens one launch takes: what both copies hold, whose rows are M rounded up to 8 and K rounded up to 256
+// halves; where that is not all of them, whole tiles.
+int gemm_tokens(uint32_t K, int M);
 hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s);
 hipError_t launch_silu_mul(const float *y, uint32_t half, int slots, void *h, int64_t h_stride, bool h_f32,
                            bool h_bf16, hipStream_t s);

@@ -74,11 +74,15 @@ def test_bf16_strides_and_untouched_padding(N, M):
         assert torch.all(buf[:, N:] == -3.0)
 
 
-def test_more_tokens_than_the_copies_hold():
-    """65536 columns: 128 tokens per pair of launches; 65536 + 128 columns are not this kernel's."""
-    W = xi.random_weights(V2, 2, 130, 65536, density=0.001, seed=5)
-    xb = xi.activations(np.random.default_rng(9), 150, W.K)
+# 28672 x 585 and 24576 x 682: one token more than a multiple of 8 that both copies hold (2^24 halves each: a row of the
+# k-major one is the tokens rounded up to 8); 65536 columns: 256 tokens a launch, none left for the kernels of few tokens
+@pytest.mark.parametrize("bits,N,K,M,dens,first", [(4, 130, 28672, 585, 0.002, 512), (3, 140, 24576, 682, 0.002, 512), (2, 130, 24576, 680, 0.002, 680),
+                                                   (2, 130, 65536, 256 + 37, 0.001, 152), (4, 140, 5120, 3273, 0.002, 3072)])
+def test_more_tokens_than_the_copies_hold(bits, N, K, M, dens, first):
+    W = xi.random_weights(V2, bits, N, K, density=dens, seed=5)
+    xb = xi.activations(np.random.default_rng(9), M, K)
     dW = xfp.upload(W)
+    assert xfp.xfp_route(dW, M) == (xfp.XFP_ROUTE_GEMM, first)
     y = xfp.xfp_gemv(dW, dev_x(xb), y_dtype=torch.float32)
     torch.cuda.synchronize()
     assert gated_rel_err(y.cpu().numpy(), oracle.gemv_weights(W, xb)) <= 1e-4

@@ -311,6 +311,36 @@ def test_prompts_take_the_product_where_it_is_the_faster_one():
         assert xfp.xfp_route(desc(**kw), M) == want, (kw, M)
 
 
+def test_a_prompt_launch_takes_what_its_copies_hold():
+    """Both copies of the activations hold 2^24 halves: [K][tokens rounded up to 8] and [tokens][K rounded up to 256]."""
+    for K in range(128, 65536 + 1, 128):
+        most = 2**24 // (-(-K // 256) * 256)
+        for M in [m for m in range(most - 9, most + 10) if 512 <= m <= 65535] + [min(65535, 2 * most + 3)]:
+            left = M
+            while left:
+                route, n = xfp.xfp_route(desc(N=16384, K=K, bits=2), left)
+                if left == M:
+                    assert route == xfp.XFP_ROUTE_GEMM or M < 512, (K, M)
+                if route == xfp.XFP_ROUTE_GEMM:
+                    assert K * (-(-n // 8) * 8) <= 2**24 and n * (-(-K // 256) * 256) <= 2**24, (K, M, n)
+                left -= n
+
+
+def test_tokens_left_over_by_prompt_launches():
+    """They are planned like a call of their own; where no other matrix-core kernel takes them, launches share them."""
+    G, Wd, R = xfp.XFP_ROUTE_GEMM, xfp.XFP_ROUTE_WIDE, xfp
+    for kw, M, want in [(dict(N=28672, K=8192), 2049, [(G, 2048), (R.XFP_ROUTE_TILE, 1)]),
+                        (dict(N=28672, K=8192), 2100, [(G, 2048), (Wd, 52)]),
+                        (dict(N=8192, K=8192), 2048 + 300, [(G, 2048), (Wd, 64), (G, 236)]),
+                        (dict(N=2048, K=28672), 585, [(G, 512), (R.XFP_ROUTE_BATCH, 16)]),
+                        (dict(N=130, K=65536, bits=2), 300, [(G, 152), (G, 148)]),
+                        (dict(N=4096, K=4096, L=256, mode=1, group_ids=FAKE), 2 * 4096 + 3, [(G, 4096), (G, 2056), (G, 2043)])]:
+        left = M
+        for step in want:
+            assert xfp.xfp_route(desc(**kw), left) == step, (kw, M, left)
+            left -= step[1]
+
+
 def test_more_than_two_dimensions_are_not_tokens():
     """x [2, 1, K] is no matrix of two tokens: one row of two columns, which the library refuses."""
     import torch
