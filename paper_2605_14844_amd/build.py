@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import glob
 import hashlib
+import importlib.util
 import json
 import os
 import re
@@ -117,12 +118,12 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
             objs.append(obj)
         workers = max(1, min(len(jobs) + 1, os.cpu_count() or 1, 8))
         with ThreadPoolExecutor(max_workers=workers) as pool:
+            # the library is built without torch too, and before a failure of the extension is reported: a C program needs no more
             ext = None
-            if not incremental or not os.path.exists(EXT) or os.path.getmtime(EXT) < os.path.getmtime(EXT_SRC):
+            if importlib.util.find_spec("torch") is not None and (
+                    not incremental or not os.path.exists(EXT) or os.path.getmtime(EXT) < os.path.getmtime(EXT_SRC)):
                 ext = pool.submit(build_extension, verbose)
             list(pool.map(lambda c: _run(c, verbose, remarks_to=c[c.index("-o") + 1] + ".json"), jobs))
-            if ext is not None:
-                ext.result()
         merged = {}
         for obj in objs:
             if os.path.exists(obj + ".json"):
@@ -133,6 +134,8 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
         tmp = LIB + f".tmp{os.getpid()}"
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
         os.replace(tmp, LIB)
+        if ext is not None:
+            ext.result()
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
     return LIB

@@ -348,3 +348,27 @@ def test_more_than_two_dimensions_are_not_tokens():
     with pytest.raises(xfp.XfpError) as e:
         xfp.xfp_gemv(W, torch.zeros((2, 1, 256), dtype=torch.float16), stream=0)
     assert e.value.status == -2
+
+
+@pytest.mark.parametrize("torch_there", [False, True])
+def test_the_library_is_built_without_the_extension(torch_there, monkeypatch, tmp_path):
+    """A C program's build: no torch, or no compiler or headers for the binding's native half."""
+    from paper_2605_14844_amd import build as b
+
+    def run(cmd, verbose, remarks_to=None):
+        if b.EXT_SRC in cmd:
+            raise RuntimeError("no extension here")
+        open(cmd[cmd.index("-o") + 1], "w").close()
+
+    find = b.importlib.util.find_spec
+    monkeypatch.setattr(b.importlib.util, "find_spec", lambda name: find(name) if torch_there else None)
+    monkeypatch.setattr(b, "sources", lambda: [])
+    monkeypatch.setattr(b, "_run", run)
+    for name in ("LIB", "EXT", "RESOURCES"):
+        monkeypatch.setattr(b, name, str(tmp_path / name))
+    if torch_there:
+        with pytest.raises(RuntimeError, match="no extension here"):
+            b.build()
+    else:
+        b.build()
+    assert os.path.exists(b.LIB) and not os.path.exists(b.EXT)
