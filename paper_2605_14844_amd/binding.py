@@ -94,7 +94,7 @@ def _load_native():
         _build.build_extension()
     from . import _xfp_torch as native
     native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
-        lib.xfp_gemv, lib.xfp_gemv_noalloc, lib.xfp_gemv_moe, lib.xfp_gemv_moe_silu_mul, lib.xfp_gemv_moe_combine)), _raise)
+        lib.xfp_gemv, lib.xfp_gemv_noalloc, lib.xfp_gemv_moe, lib.xfp_gemv_moe_silu_mul, lib.xfp_gemv_moe_combine)), xfp_weights, _raise)
     _native = native
     return native
 

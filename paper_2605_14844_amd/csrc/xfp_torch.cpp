@@ -25,6 +25,7 @@ decltype(&xfp_gemv_noalloc) g_gemv_noalloc;
 decltype(&xfp_gemv_moe) g_moe;
 decltype(&xfp_gemv_moe_silu_mul) g_silu;
 decltype(&xfp_gemv_moe_combine) g_combine;
+PyObject *g_descriptor; // the ctypes structure of the descriptor
 PyObject *g_error;      // callable(status[, text]) that raises XfpError
 
 struct Failed {};       // a Python exception is set
@@ -43,12 +44,9 @@ struct Descriptor {
     Py_buffer view{};
     explicit Descriptor(PyObject *o)
     {
-        if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw Failed{};
-        if (view.len < (Py_ssize_t)sizeof(xfp_weights)) {
-            PyBuffer_Release(&view);
-            PyErr_SetString(PyExc_TypeError, "not an xfp_weights descriptor");
-            throw Failed{};
-        }
+        const int is = PyObject_IsInstance(o, g_descriptor);       // any other buffer of this length holds no addresses
+        if (is == 0) PyErr_Format(PyExc_TypeError, "expected an xfp_weights descriptor, got %s", Py_TYPE(o)->tp_name);
+        if (is != 1 || PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw Failed{};
     }
     ~Descriptor() { PyBuffer_Release(&view); }
     Descriptor(const Descriptor &) = delete;
@@ -250,7 +248,7 @@ PyObject *py_y_code(PyObject *, PyObject *const *a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses of gemv, noalloc, moe, silu_mul, combine; callable that raises)
+// bind(addresses of gemv, noalloc, moe, silu_mul, combine; the descriptor's type; callable that raises)
 PyObject *py_bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     if (!arity(n, 6)) return nullptr;
@@ -267,13 +265,14 @@ PyObject *py_bind(PyObject *, PyObject *const *a, Py_ssize_t n)
     g_moe = reinterpret_cast<decltype(g_moe)>(p[2]);
     g_silu = reinterpret_cast<decltype(g_silu)>(p[3]);
     g_combine = reinterpret_cast<decltype(g_combine)>(p[4]);
-    Py_XSETREF(g_error, Py_NewRef(a[5]));
+    Py_XSETREF(g_descriptor, Py_NewRef(a[5]));
+    Py_XSETREF(g_error, Py_NewRef(a[6]));
     Py_RETURN_NONE;
 }
 
 #define XFP_FAST(f) reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL
 PyMethodDef methods[] = {
-    {"bind", XFP_FAST(py_bind), "addresses of the library's entry points and the callable that raises"},
+    {"bind", XFP_FAST(py_bind), "addresses of the library's entry points, the descriptor's type and the callable that raises"},
     {"gemv", XFP_FAST(py_gemv<false>), "(desc, x, y, y_dtype, stream)"},
     {"noalloc", XFP_FAST(py_gemv<true>), "(desc, x, y, y_dtype, stream)"},
     {"moe", XFP_FAST(py_moe), "(desc, expert_ids, x, y, y_dtype, stream)"},

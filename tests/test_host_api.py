@@ -372,3 +372,15 @@ def test_the_library_is_built_without_the_extension(torch_there, monkeypatch, tm
     else:
         b.build()
     assert os.path.exists(b.LIB) and not os.path.exists(b.EXT)
+
+
+@pytest.mark.parametrize("other", [bytes(104), (ctypes.c_char * 104)(), None])
+def test_only_a_descriptor_is_one(other):
+    import torch
+    x, ids = torch.zeros((1, 256), dtype=torch.float16), torch.zeros(1, dtype=torch.int32)
+    W = type("W", (), {"desc": other, "N": 64})
+    for f in (lambda: xfp.xfp_gemv(W, x, stream=0), lambda: xfp.xfp_gemv_moe(W, ids, x, stream=0),
+              lambda: xfp.xfp_gemv_moe_silu_mul(W, ids, x, stream=0),
+              lambda: xfp.xfp_gemv_moe_combine(W, ids, x, torch.ones(1), stream=0)):
+        with pytest.raises(TypeError):
+            f()
