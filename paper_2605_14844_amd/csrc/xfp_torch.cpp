@@ -95,15 +95,19 @@ void *stream_of(PyObject *o)
     return p;
 }
 
-// The output: the caller's tensor, or a new one.
+// The output: the caller's tensor, or a new one (dtype None: torch's default dtype).
 at::Tensor output(PyObject *y, PyObject *dtype, at::IntArrayRef shape, const at::Tensor &x)
 {
     if (y != Py_None) return tensor(y);
-    if (!THPDtype_Check(dtype)) {
-        PyErr_SetString(PyExc_TypeError, "the output dtype must be a torch.dtype");
-        throw Failed{};
+    at::TensorOptions options = at::TensorOptions().device(x.device());
+    if (dtype != Py_None) {
+        if (!THPDtype_Check(dtype)) {
+            PyErr_SetString(PyExc_TypeError, "the output dtype must be a torch.dtype");
+            throw Failed{};
+        }
+        options = options.dtype(reinterpret_cast<THPDtype *>(dtype)->scalar_type);
     }
-    return at::empty(shape, at::TensorOptions().dtype(reinterpret_cast<THPDtype *>(dtype)->scalar_type).device(x.device()));
+    return at::empty(shape, options);
 }
 
 // what goes back: the caller's own object where there was one
@@ -142,7 +146,7 @@ PyObject *py_gemv(PyObject *, PyObject *const *a, Py_ssize_t n)
         // what is not a matrix is the one row of a matrix: [K] is [1, K] (more dimensions: a row the library refuses as too short)
         const bool flat = x.dim() != 2;
         const int64_t M = flat ? 1 : x.size(0), cols = flat ? x.size(0) : x.size(1);
-        at::Tensor y = output(a[2], a[3], {M, (int64_t)W->N}, x);
+        at::Tensor y = NOALLOC ? tensor(a[2]) : output(a[2], a[3], {M, (int64_t)W->N}, x);
         const bool yflat = y.dim() != 2;
         const int64_t ldx = M > 1 ? x.stride(0) : std::max<int64_t>(cols, 1);
         const int64_t ycols = yflat ? y.size(0) : y.size(1);
@@ -251,7 +255,7 @@ PyObject *py_y_code(PyObject *, PyObject *const *a, Py_ssize_t n)
 // bind(addresses of gemv, noalloc, moe, silu_mul, combine; the descriptor's type; callable that raises)
 PyObject *py_bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (!arity(n, 6)) return nullptr;
+    if (!arity(n, 7)) return nullptr;
     void *p[5];
     for (int i = 0; i < 5; ++i) {
         p[i] = PyLong_AsVoidPtr(a[i]);

@@ -384,3 +384,20 @@ def test_only_a_descriptor_is_one(other):
               lambda: xfp.xfp_gemv_moe_combine(W, ids, x, torch.ones(1), stream=0)):
         with pytest.raises(TypeError):
             f()
+
+
+def test_the_output_type_may_be_left_to_torch():
+    """y_dtype=None is torch's default dtype, as in torch.empty: the call gets as far as the library's own refusal."""
+    import torch
+    W = type("W", (), {"desc": desc(), "N": 64})
+    for dtype, status in ((torch.float32, -2), (torch.float64, -3)):      # a row too short; an output of 64 bits
+        before = torch.get_default_dtype()
+        torch.set_default_dtype(dtype)
+        try:
+            with pytest.raises(xfp.XfpError) as e:
+                xfp.xfp_gemv(W, torch.zeros((1, 128), dtype=torch.float16), y_dtype=None, stream=0)
+        finally:
+            torch.set_default_dtype(before)
+        assert e.value.status == status
+    with pytest.raises(TypeError):
+        xfp.xfp_gemv_noalloc(W, torch.zeros((1, 128), dtype=torch.float16), None, stream=0)
