@@ -386,31 +386,31 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     }
 
     // ---------------------------------------------------------------- loads of the main loop
-    // They are written as instructions because the compiler does not count loads to LDS: every block issues the same
-    // number of them in the same order (past the end: again the last block's), and every wait below states how many
-    // may still be under way.
+    // The loads to LDS are written as instructions: as builtins they would make the compiler wait for all of them in front
+    // of every read from LDS.  They have no result registers.  Every block issues the same number of loads in the same
+    // order (past the end: again the last block's), and every wait below states how many may still be under way.
+    // The index words are buffer loads through the builtin, one instruction each, and it is the compiler that waits for
+    // them: in front of their first use, for all loads under way, as it does not count those to LDS.  So a block's last
+    // turn requests nothing before that use; what is then under way is needed two steps later anyway.
     u32x4_t iw[2][RB][BITS];                                   // this block's words and the next one's
     uint32_t gid[2][RB];
+    const uint32_t rows = min(N - n0, (uint32_t)BN);
+    const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc((void *)(a.idx + (size_t)n0 * wpr), 0, rows * wpr * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc((void *)(MODE == 1 ? a.gid + (size_t)n0 * G : nullptr), 0,
+                                                                        MODE == 1 ? rows * G : 0, 0x00020000);
     auto load_words = [&](auto buf, uint32_t t) {              // the wave's t-th block
         constexpr int B = decltype(buf)::value;
         const uint32_t grp = min(2 * (t * WK + wk) + h, G - 1);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const uint32_t *p = a.idx + (size_t)row[rb] * wpr + grp * (4 * BITS);
 #pragma unroll
-            for (int d = 0; d < BITS; ++d) {
-                u32x4_t &w = iw[B][rb][d];
-                asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(w) : "v"(p), "n"(16 * d) : "memory");
-            }
-            if constexpr (MODE == 1) {
-                const uint8_t *g = a.gid + (size_t)row[rb] * G + grp;
-                uint32_t &id = gid[B][rb];
-                asm volatile("global_load_ubyte %0, %1, off" : "=v"(id) : "v"(g) : "memory");
-            }
+            for (int d = 0; d < BITS; ++d)
+                iw[B][rb][d] = __builtin_amdgcn_raw_buffer_load_b128(ri, (row[rb] - n0) * (wpr * 4) + grp * (16 * BITS) + 16 * d, 0, 0);
+            if constexpr (MODE == 1) gid[B][rb] = __builtin_amdgcn_raw_buffer_load_b8(rg, (row[rb] - n0) * G + grp, 0, 0);
         }
     };
     constexpr int kWords = RB * (BITS + MODE);                 // loads of a block's words
-    static_assert(3 * C::U * C::ND <= 63 && (C::AHEAD - 1) * C::ND + kWords <= 63, "what vmcnt can say");
+    static_assert((C::AHEAD - 1) * C::ND + kWords <= 63, "what vmcnt can say");
     const u32x4_t rx = {(uint32_t)(uintptr_t)ga.xp, (uint32_t)((uintptr_t)ga.xp >> 32) & 0xFFFFu, M * (NB * 512), 0x00020000u};
     uint32_t boff[C::ND];
 #pragma unroll
@@ -427,11 +427,11 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
 #pragma unroll
         for (int e = e0; e < e1; ++e)
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                         :: "s"(dst + e * 1024), "v"(boff[e]), "s"(rx), "s"(so) : "memory");
+                         :: "s"(dst + e * 1024), "v"(boff[e]), "s"(rx), "s"(so) : "memory", "m0");
         if (e1 == C::ND) bload = bload + 1 == C::NBUF ? 0 : bload + 1;
     };
     words_t<BITS> cw[RB];                                      // the words of the turn whose A operands are being made
-    auto arrived = [&](auto buf, uint32_t t) {                 // the words of a buffer may be used from here on
+    auto arrived = [&](auto buf, uint32_t t) {                 // the first use of a buffer's words
         constexpr int B = decltype(buf)::value;
         const bool dead = 2 * (t * WK + wk) + h >= G;          // second half of the last block of a row with an odd number of groups
 #pragma unroll
@@ -518,7 +518,9 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
                                 af[s][rb], bf[from][tb], C::SPLIT && p + s == 0 ? float16_t{} : acc[rb][half * TBH + tb], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             };
-            load_b(t * (4 * C::U) + x + C::AHEAD, s % C::SP * C::ND / C::SP, (s % C::SP + 1) * C::ND / C::SP);
+            // (a block's last turn: nothing in the steps up to the first use of the next block's words)
+            constexpr auto e = [](int q) { return p < 3 || C::SP != 4 ? q * C::ND / C::SP : q <= 2 ? 0 : (q - 2) * C::ND / 2; };
+            load_b(t * (4 * C::U) + x + C::AHEAD, e(s % C::SP), e(s % C::SP + 1));
             if constexpr (NH == 2) {
                 operands(1, bcur, s, 1);
                 if constexpr (s == 0) dequantise(3);
@@ -528,8 +530,7 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             if constexpr (NH == 1 && s == 0) dequantise(3);
             if constexpr (s == 1) {
                 if constexpr (p == 0) load_words(Next{}, t + 1);
-                if constexpr (p == 3) {                        // the next block's words: three turns ago
-                    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * C::U * C::ND) : "memory");
+                if constexpr (p == 3) {                        // the next block's words, requested three turns ago
                     arrived(Next{}, t + 1);
                     take(Next{}, 0);
                 } else {

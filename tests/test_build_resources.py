@@ -2,8 +2,10 @@
 in kernel_resources.json.  A change in front of a kernel's loads can silently cost it a wave per SIMD or push it
 into scratch memory (a three-line branch once did: 35 registers, 98 spilled, a 2.4 times slower call), so the
 kernels that the five workloads launch are pinned here."""
+import glob
 import json
 import os
+import re
 
 import pytest
 
@@ -59,13 +61,26 @@ def test_the_workloads_kernels_keep_their_registers(parts, min_waves):
     assert k["waves_per_simd"] >= min_waves, k
 
 
-def test_the_prompt_kernels_move_no_register_that_a_load_may_still_write():
-    """Its index words are loaded by inline asm and waited for three turns later: a spill or a copy to an accumulation
-    register in between would take what has not arrived."""
+def test_the_prompt_kernels_stay_in_registers():
     prompt = {k: v for k, v in resources().items() if "decode_gemm_kernel" in k}
     assert len(prompt) == 24                                          # 2 to 4 bits, V2 and V2a, four tiles
     for k, v in prompt.items():
         assert v["vgpr_spills"] == 0 and v["agprs"] == 0 and v["scratch_bytes_per_lane"] == 0, (k, v)
+
+
+def test_no_load_in_inline_asm_has_a_result_register():
+    """The compiler takes an asm statement's results as there when it ends: it may move, reuse or overwrite their
+    registers while the load is under way.  A load into registers is a builtin's; asm loads go to LDS."""
+    found = 0
+    for path in glob.glob(os.path.join(os.path.dirname(xfp.library_path()), "csrc", "*")):
+        with open(path) as f:
+            text = f.read()
+        for m in re.finditer(r"\basm\b[^(;]*\((.*?)\);", text, re.S):
+            code, _, operands = re.sub(r'"((?:[^"\\]|\\.)*)"\s*(?="|:|$)', r"\1", m.group(1)).partition("::")
+            if re.search(r"(global|buffer|flat|scratch)_load|ds_read|s_load", m.group(1)):
+                found += 1
+                assert operands and re.search(r"\blds\b", code), (path, m.group(0))
+    assert found == 1                                                 # the prompt kernel's loads of the activations
 
 
 def test_kernels_that_address_lds_from_zero_have_no_static_lds():
