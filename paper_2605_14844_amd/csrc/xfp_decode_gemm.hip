@@ -5,7 +5,8 @@
 // not by the weights' bytes, and the 64-token kernel reads and
 // dequantises the whole matrix once per 64 tokens and fetches its activations from L2 once per 32 rows.
 //
-// Work unit: a workgroup of 8 or 16 waves owns BN output rows x BM tokens and walks K.
+// Work unit: a workgroup of 8 or 16 waves owns BN output rows x BM tokens and walks K; a row's sum is taken in two or
+// three steps (GemmTile).
 //  - Every lane dequantises the weights it needs itself, straight into the A operand of v_mfma_f32_32x32x16_f16: lane
 //    (i, h) owns row i of a block of 32 rows and one half of every 64 columns, the same rows for the whole kernel, so
 //    a V2 row's codebook stays in registers, split into byte planes (low and high bytes of the fp16 entries):
@@ -16,9 +17,8 @@
 //  - The B tile (BM tokens) comes from a token-major copy of the activations straight into LDS
 //    (buffer_load_dwordx4 ... lds: no registers, no VALU), through a ring of parts; its rows are XOR-swizzled in
 //    16-byte chunks so that 16 consecutive lanes of a ds_read_b128 cover the 64 banks.
-//  - 28672 x 8192, 4 bits, 2048 tokens: 1.16 ms against 2.13 ms in passes of 64 tokens; 880 us of it are the product
-//    without outliers (1.1 PFLOP/s: three and a half rounds of tiles on 256 CUs; the library's own dense product of
-//    this shape 0.71 ms), 220 us the outliers.  4096 x 4096, 2 bits, 333 tokens: 35 us against 94.
+//  - 28672 x 8192, 4 bits, 2048 tokens: 1.28 ms against 2.08 ms in passes of 64 tokens (the library's own dense product of
+//    this shape 0.71 ms).  4096 x 4096, 2 bits, 333 tokens: 42 us against 98.
 //
 // Order of k inside 32 weights: what the byte planes give cheaply is not the natural order (at 4 bits the even
 // nibbles of a dword come before the odd ones).  A product does not care as long as both operands agree, so the copy
@@ -26,7 +26,7 @@
 //
 // Outliers (fp32, not folded into the fp16 operand: that would round them): the waves share out the tile's rows; an
 // entry's activations of all the tile's tokens are one contiguous read from a k-major copy of x; a row's sums meet in
-// an LDS plane from which the waves load what their results start from.  No atomics, fixed orders.
+// an LDS plane, which is added to the finished sums of the product.  No atomics, fixed orders.
 #include "xfp_device.h"
 
 #include <atomic>
@@ -149,27 +149,35 @@ __device__ __forceinline__ u32x4_t chunk(const Planes<BITS> &P, const words_t<BI
 // Tile geometry: WN x WK waves; a wave owns 32 RB rows and all 32 TB tokens and takes every WK-th block of 256 columns
 // (the waves that share rows add their sums in LDS at the end), a block in four turns of 64.  A part of the B tile is SP
 // of a turn's four steps of 16 columns, for each of the WK waves; NBUF of them in LDS, NBUF - 1 requested ahead.
-// SPLIT: every block is a chain of its own, whose sums are added to a second set of registers.  A sum of n products of 16
-// in one fp32 chain is off by about 2e-8 sqrt(n) of its size (n = 256 at 4096 columns: 3.1e-7 measured), which a 16-bit
-// result does not show and an fp32 result does.
-template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_, bool SPLIT_>
+// Every block is a chain of its own, whose sums are added to a second set of registers: what one fp32 chain through all
+// of a row's products of 16 loses grows with the root of its length (4096 columns: 3.1e-7 of the result, 1.2e-7 in two
+// steps).  The second set halves the tokens that a dequantised weight meets in a wave (28672 x 8192, 2048 tokens, fp16:
+// 1.12 ms in one chain with 256 x 256 tiles, 1.28 in two steps with 256 x 128).
+template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_>
 struct GemmTile {
     static constexpr int RB = RB_, TB = TB_, WN = WN_, WK = WK_, SP = SP_, NBUF = NBUF_;
-    static constexpr bool SPLIT = SPLIT_;
     static constexpr int BN = 32 * RB * WN, BM = 32 * TB, NW = WN * WK, T = NW * kWave;
     static constexpr int KB = 16 * SP * WK, RSB = KB * 2, kB = BM * RSB;   // a part: columns, bytes of a row, bytes
     static constexpr int U = 4 / SP;                           // parts of a turn
     static_assert(SP == 2 || SP == 4, "");
     static constexpr int AHEAD = NBUF - 1;
     static constexpr int ND = kB / (NW * 1024);                // loads of a wave per part
-    static constexpr int PR = BN * BM <= 32768 ? BN : 32768 / BM;          // rows of the outlier plane (in front of the tiles' life)
-    static constexpr int kPlane = PR * BM * 4, kSums = (WK - 1) * BN * BM * 4, kTiles = NBUF * kB;
+    static constexpr int kPlane = BN * BM * 4, kSums = (WK - 1) * BN * BM * 4, kTiles = NBUF * kB;
     static constexpr int kBase = kTiles > kPlane ? (kTiles > kSums ? kTiles : kSums) : (kPlane > kSums ? kPlane : kSums);
-    static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && PR % NW == 0 && BN % PR == 0, "");
-    // registers: accumulators, operands (B twice), index words, planes; then waves per SIMD
-    static constexpr int kRegs = 16 * RB * TB * (SPLIT ? 2 : 1) + 16 * RB + 8 * TB + 36 * RB + 8 * RB + 56;
+    static constexpr bool FINE = NW <= 8;                      // takes short rows (half blocks as chains)
+    static constexpr bool DEEP = WK == 2;                      // a third set of sums in LDS for long rows
+    static constexpr int kDeep = DEEP ? RB * TB * 16 * T * 4 : 0;
+    static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && BN % NW == 0, "");
+    // registers: accumulators and sums, operands (B twice), index words, planes; then waves per SIMD
+    static constexpr int kRegs = 32 * RB * TB + 16 * RB + 8 * TB + 36 * RB + 8 * RB + 56;
     static constexpr int kWavesPerSimd = kRegs <= 128 ? 4 : kRegs <= 168 ? 3 : kRegs <= 256 ? 2 : 1;
 };
+
+// Up to kFineK columns half a block is a chain; above kDeepK two waves that share their rows take their sums in three
+// steps (the third: every eighth block, in LDS).  Error against 64 bits, 1e-8 of the result's norm, without / with that,
+// and of passes of 64 tokens: 512 columns 10.8 / 8.6, 8.6; 1536 11.7 / 10.3, 11.4; 3072 12.5 / 12.0, 13.9; 16384 15.2 / 12.9,
+// 15.8; 28672 17.6 / 13.4, 15.3 (matrices of 8192 rows and more, whose passes are not cut into slices: 38).
+constexpr uint32_t kFineK = 2048, kDeepK = 16384;
 
 // 16-byte chunk c of row r of a tile with C chunks per row sits at position c ^ swz<C>(r)
 template <int C>
@@ -186,6 +194,8 @@ struct GemmArgs {
     uint32_t M, MP;        // tokens of this launch; row length of xt (a multiple of 8)
     uint32_t row0, tiles_n, tiles_m;                           // first row, tiles of this launch
     int y_f32;
+    int fine;              // half blocks are chains of their own
+    uint32_t deep;         // LDS offset of a third set of sums, or 0: none
 };
 
 template <class F, int... Is>
@@ -249,141 +259,11 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
         }
     }
 
-    // ---------------------------------------------------------------- results, and the outlier term they start from
-    // acc: what the matrix cores add to; sum: what becomes the results (the same registers unless SPLIT)
-    float16_t acc[RB][TB], acc2[RB][TB];
-    float16_t (&sum)[RB][TB] = C::SPLIT ? acc2 : acc;
+    float16_t acc[RB][TB], sum[RB][TB];                        // a block's chains; what becomes the results
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) sum[rb][tb] = float16_t{};
-    // Wave w owns rows RW w .. of the plane, whose entries are one run of the CSR arrays, and walks it in units of up
-    // to U EP entries of one row: lane (ep, o) takes entries ep, ep + EP, .. of a unit and the tokens m0 + 8 o .. + 7.
-    // An entry's activations are 2 BM bytes from L2, and it takes about 64 KB in flight per CU to draw them at full rate.
-    const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
-    const int32_t ob = rp[min(n0, N)], oe = rp[min(n0 + BN, N)];
-    if (a.col && ob < oe) {
-        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + ob), 0, (oe - ob) * 4, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + ob), 0, (oe - ob) * 2, 0x00020000);
-        constexpr int OP = BM / 8, EP = 64 / OP, U = EP >= 8 ? 2 : 4, D = 4, UE = U * EP, RW = C::PR / NW;
-        static_assert(OP >= 4 && OP <= 32 && UE <= 64 && RW < 64, "");
-        const uint32_t ep = lane / OP, o = lane % OP;
-        const uint4 *xt = reinterpret_cast<const uint4 *>(ga.xt) + min((m0 >> 3) + o, ga.MP / 8 - 1);
-        const uint32_t xs = ga.MP / 8, plane = lds0 + wave * (RW * BM * 4);
-        struct Unit { uint32_t row; int32_t e, hi; bool last; };                            // wave-uniform
-        struct Gathered { uint4 x[U]; uint32_t v[U]; };
-#pragma unroll
-        for (int pass = 0; pass < BN / C::PR; ++pass) {
-            const int32_t rpv = a.rp[min(n0 + pass * C::PR + wave * RW + min(lane, (uint32_t)RW), N)];   // lane r: first entry of row r
-            auto row_at = [&](uint32_t r) { return __builtin_amdgcn_readlane(rpv, (int)r); };
-            auto unit_at = [&](uint32_t r, int32_t e) {
-                Unit u;
-                u.row = r; u.e = e;
-                u.hi = r < (uint32_t)RW ? row_at(r + 1) : e;
-                u.last = e + UE >= u.hi;
-                return u;
-            };
-            auto after = [&](const Unit &u) {
-                const uint32_t r = u.last ? u.row + 1 : u.row;
-                return unit_at(r, r >= (uint32_t)RW ? u.hi : u.last ? row_at(r) : u.e + UE);
-            };
-            // No load here hangs on a condition: the compiler counts loads under way only along straight code, and a
-            // branch around one makes it wait for all of them at the next use.
-            auto fetch = [&](const Unit &u) {                  // lane j: entry j of the unit, column | value << 16
-                const uint32_t e = (uint32_t)(u.e - ob) + lane;
-                const uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rc, e * 4, 0, 0), v = __builtin_amdgcn_raw_buffer_load_b16(rv, e * 2, 0, 0);
-                return c | (v << 16);                          // (past the tile's entries: zeros; past the row's: another row's)
-            };
-            auto gather = [&](uint32_t ents, Gathered &g) {
-#pragma unroll
-                for (int j = 0; j < U; ++j) {
-                    const uint32_t ent = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((j * EP + ep) * 4), (int)ents);
-                    g.v[j] = ent >> 16;
-                    g.x[j] = xt[(size_t)(ent & 0xFFFFu) * xs];
-                }
-            };
-            float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            auto consume = [&](const Unit &u, const Gathered &g) {
-#pragma unroll
-                for (int j = 0; j < U; ++j) {
-                    if (j && u.e + j * EP >= u.hi) break;      // wave-uniform
-                    const uint32_t have = u.e + j * EP + (int32_t)ep < u.hi ? ~0u : 0u;     // no entry: zero times zeros
-                    const float v = half_bits_to_float((uint16_t)(g.v[j] & have));
-                    const uint32_t w[4] = {g.x[j].x & have, g.x[j].y & have, g.x[j].z & have, g.x[j].w & have};
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) s[t] = fmaf(v, half_bits_to_float((uint16_t)(t & 1 ? w[t / 2] >> 16 : w[t / 2])), s[t]);
-                }
-                if (!u.last) return;
-                // the EP entry lanes of a token octet are added in a fixed tree
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    if constexpr (EP >= 16) s[t] = dpp_add<0x124>(s[t]);           // row_ror:4 (octets in lane % 4)
-                    if constexpr (EP >= 8) s[t] = dpp_add<0x128>(s[t]);            // row_ror:8
-                    uint32_t x = __builtin_bit_cast(uint32_t, s[t]);
-                    if constexpr (EP >= 4) {
-                        const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-                        s[t] = __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
-                        x = __builtin_bit_cast(uint32_t, s[t]);
-                    }
-                    const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-                    s[t] = __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
-                }
-                if (ep == 0) {
-                    const uint32_t d = plane + u.row * (BM * 4) + o * 32;
-                    *(lds_f4_t *)(uintptr_t)d = float4_t{s[0], s[1], s[2], s[3]};
-                    *(lds_f4_t *)(uintptr_t)(d + 16) = float4_t{s[4], s[5], s[6], s[7]};
-                }
-#pragma unroll
-                for (int t = 0; t < 8; ++t) s[t] = 0.f;
-            };
-            // D units' activations and, D units further on, D units' entries are under way: a unit's entries were requested
-            // before the activations that have not been used yet, so waiting for them is not waiting for those
-            Unit gu[D], eu[D];
-            uint32_t ents[D];
-            Gathered g[D];
-            Unit next = unit_at(0, row_at(0));
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                gu[d] = next;
-                ents[d] = fetch(next);
-                next = after(next);
-            }
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                gather(ents[d], g[d]);
-                eu[d] = next;
-                ents[d] = fetch(next);
-                next = after(next);
-            }
-            for (bool more = true; more;) {
-#pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    if (gu[d].row >= (uint32_t)RW) {
-                        more = false;
-                        break;
-                    }
-                    consume(gu[d], g[d]);
-                    gu[d] = eu[d];
-                    gather(ents[d], g[d]);
-                    eu[d] = next;
-                    ents[d] = fetch(next);
-                    next = after(next);
-                }
-            }
-            lds_barrier();
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                const uint32_t pr = (wn * RB + rb) * 32 - pass * C::PR;        // first row of the block in the plane
-                if (wk == 0 && pr < (uint32_t)C::PR)
-#pragma unroll
-                    for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            sum[rb][tb][r] = *(lds_cf32_t *)(uintptr_t)(lds0 + (pr + 8 * (r / 4) + 4 * h + r % 4) * (BM * 4) + (32 * tb + i) * 4);
-            }
-            lds_barrier();
-        }
-    }
 
     // ---------------------------------------------------------------- loads of the main loop
     // The loads to LDS are written as instructions: as builtins they would make the compiler wait for all of them in front
@@ -467,17 +347,16 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     };
 
     // ---------------------------------------------------------------- prologue: as if the turns before the first had run
-    constexpr int NH = TB >= 8 ? 2 : 1, TBH = TB / NH;         // many tokens: a step's B operands in two halves (registers)
-    half8_t af[4][RB], bf[2][TBH];
+    half8_t af[4][RB], bf[2][TB];
     auto dequantise = [&](int s) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) af[s][rb] = __builtin_bit_cast(half8_t, chunk<BITS>(P[rb], cw[rb], s));
     };
     const uint32_t br = lds0 + i * C::RSB + (((wk * (2 * C::SP) + h) ^ swz<CB>(i)) * 16);
-    auto operands = [&](int set, uint32_t buf, int s, int half) {
+    auto operands = [&](int set, uint32_t buf, int s) {
         const uint32_t ba = (br + buf * C::kB) ^ (uint32_t)(s % C::SP * 32);
 #pragma unroll
-        for (int tb = 0; tb < TBH; ++tb) bf[set][tb] = *(lds_ch8_t *)(uintptr_t)(ba + (half * TBH + tb) * (32 * C::RSB));
+        for (int tb = 0; tb < TB; ++tb) bf[set][tb] = *(lds_ch8_t *)(uintptr_t)(ba + tb * (32 * C::RSB));
     };
     using Even = std::integral_constant<int, 0>;
     using Odd = std::integral_constant<int, 1>;
@@ -490,7 +369,7 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     take(Even{}, 0);
 #pragma unroll
     for (int s = 0; s < 3; ++s) dequantise(s);
-    operands(0, 0, 0, 0);
+    operands(0, 0, 0);
 
     // ---------------------------------------------------------------- main loop
     // A block is four turns of four steps.  In step s the B operands of step s + 1 are read, the A operands of the next
@@ -498,6 +377,24 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     // barrier that opens the next part stands in front of a part's last step, whose matrix instructions then cover the
     // first reads behind it; the loads that refill a ring slot follow the barrier behind its last reads.
     uint32_t bcur = 0;
+    auto add = [&] {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) sum[rb][tb] += acc[rb][tb];
+    };
+    auto keep = [&](bool first, bool more) {                   // the sums so far into the third set; at the end back
+        const uint32_t at = lds0 + ga.deep + tid * 16;
+#pragma unroll
+        for (int b = 0; b < RB * TB * 4; ++b) {
+            float16_t &v = sum[b / 4 % RB][b / 4 / RB];
+            float4_t x = {v[b % 4 * 4], v[b % 4 * 4 + 1], v[b % 4 * 4 + 2], v[b % 4 * 4 + 3]};
+            if (!first) x += *(lds_f4_t *)(uintptr_t)(at + b * (C::T * 16));
+            if (more) *(lds_f4_t *)(uintptr_t)(at + b * (C::T * 16)) = x;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[b % 4 * 4 + r] = more ? 0.f : x[r];
+        }
+    };
     auto block = [&](auto buf, uint32_t t) {
         constexpr int B = decltype(buf)::value;
         using Next = std::integral_constant<int, B ^ 1>;
@@ -507,27 +404,20 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             constexpr int x = p * C::U + s / C::SP;            // part of the block
             constexpr bool last = s % C::SP == C::SP - 1;      // of the part
             const uint32_t bnext = bcur + 1 == C::NBUF ? 0 : bcur + 1;
-            constexpr int set = NH == 2 ? 0 : s & 1;           // where the step's first operands are
-            auto multiply = [&](int from, int half) {
-                if (on)
+            constexpr int set = s & 1;                         // where the step's operands are
+            if constexpr (C::FINE && p == 2 && s == 0)
+                if (ga.fine && on) {
+                    add();
 #pragma unroll
-                    for (int tb = 0; tb < TBH; ++tb)
+                    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                        for (int rb = 0; rb < RB; ++rb)
-                            acc[rb][half * TBH + tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                                af[s][rb], bf[from][tb], C::SPLIT && p + s == 0 ? float16_t{} : acc[rb][half * TBH + tb], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            };
+                        for (int tb = 0; tb < TB; ++tb) acc[rb][tb] = float16_t{};
+                }
             // (a block's last turn: nothing in the steps up to the first use of the next block's words)
             constexpr auto e = [](int q) { return p < 3 || C::SP != 4 ? q * C::ND / C::SP : q <= 2 ? 0 : (q - 2) * C::ND / 2; };
             load_b(t * (4 * C::U) + x + C::AHEAD, e(s % C::SP), e(s % C::SP + 1));
-            if constexpr (NH == 2) {
-                operands(1, bcur, s, 1);
-                if constexpr (s == 0) dequantise(3);
-                multiply(0, 0);
-            }
-            if constexpr (!last) operands(set ^ (NH & 1), bcur, s + 1, 0);
-            if constexpr (NH == 1 && s == 0) dequantise(3);
+            if constexpr (!last) operands(set ^ 1, bcur, s + 1);
+            if constexpr (s == 0) dequantise(3);
             if constexpr (s == 1) {
                 if constexpr (p == 0) load_words(Next{}, t + 1);
                 if constexpr (p == 3) {                        // the next block's words, requested three turns ago
@@ -544,19 +434,22 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
                 constexpr bool words = from <= 0 || (from > x ? false : from % (4 * C::U) == 0);
                 constexpr int kYounger = (C::AHEAD - 1) * C::ND + (words && from <= x ? kWords : 0);
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kYounger) : "memory");
-                operands(set ^ (NH & 1), bnext, (s + 1) % 4, 0);
+                operands(set ^ 1, bnext, (s + 1) % 4);
             }
             if constexpr (s > 0) dequantise(s - 1);
-            multiply(NH == 2 ? 1 : set, NH - 1);
-            if constexpr (last) bcur = bnext;
-        });
-        if constexpr (C::SPLIT) {
             if (on)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
+                for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-                    for (int tb = 0; tb < TB; ++tb) sum[rb][tb] += acc[rb][tb];
-        }
+                    for (int rb = 0; rb < RB; ++rb)
+                        acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[s][rb], bf[set][tb], p + s == 0 ? float16_t{} : acc[rb][tb], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (last) bcur = bnext;
+        });
+        if (on) add();
+        // the third set: this thread's own places in LDS, 16 bytes per lane and read or write
+        if constexpr (B == 1 && C::DEEP)
+            if (ga.deep && t % 8 == 7) keep(t == 7, true);
     };
 #pragma unroll 1
     for (uint32_t t = 0; t < NS; t += 2) {
@@ -564,6 +457,8 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
         if (t + 1 < NS) block(Odd{}, t + 1);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // (loads to LDS that nobody waits for)
+    if constexpr (C::DEEP)
+        if (ga.deep && NS >= 8) keep(false, false);
 
     if constexpr (WK > 1) {
         // the other waves' sums of a block, added in their order; they may overwrite the tiles, which every wave has read
@@ -579,7 +474,7 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             }
         }
         lds_barrier();
-        if (wk > 0) return;
+        if (wk == 0)
 #pragma unroll 1
         for (int w = 0; w < WK - 1; ++w)
 #pragma unroll
@@ -590,6 +485,133 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
                 for (int r = 0; r < 4; ++r) v[b % 4 * 4 + r] += x[r];
             }
     }
+
+    // ---------------------------------------------------------------- the outlier term
+    // Behind the product and not in front of it: the sums would otherwise be added to a term that is often larger than all
+    // of theirs, and be rounded at its size (28672 columns, 0.3 % outliers: 2.0e-7 of the result instead of 1.0e-7).
+    // Wave w owns rows RW w .. of the plane, whose entries are one run of the CSR arrays, and walks it in units of up
+    // to U EP entries of one row: lane (ep, o) takes entries ep, ep + EP, .. of a unit and the tokens m0 + 8 o .. + 7.
+    // An entry's activations are 2 BM bytes from L2, and it takes about 64 KB in flight per CU to draw them at full rate.
+    const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
+    const int32_t ob = rp[min(n0, N)], oe = rp[min(n0 + BN, N)];
+    if (a.col && ob < oe) {
+        lds_barrier();                                         // every wave is past its tiles (and sums)
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + ob), 0, (oe - ob) * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + ob), 0, (oe - ob) * 2, 0x00020000);
+        constexpr int OP = BM / 8, EP = 64 / OP, U = EP >= 8 ? 2 : 4, D = 4, UE = U * EP, RW = BN / NW;
+        static_assert(OP >= 4 && OP <= 32 && UE <= 64 && RW < 64, "");
+        const uint32_t ep = lane / OP, o = lane % OP;
+        const uint4 *xt = reinterpret_cast<const uint4 *>(ga.xt) + min((m0 >> 3) + o, ga.MP / 8 - 1);
+        const uint32_t xs = ga.MP / 8, plane = lds0 + wave * (RW * BM * 4);
+        struct Unit { uint32_t row; int32_t e, hi; bool last; };                            // wave-uniform
+        struct Gathered { uint4 x[U]; uint32_t v[U]; };
+        const int32_t rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];     // lane r: first entry of row r
+        auto row_at = [&](uint32_t r) { return __builtin_amdgcn_readlane(rpv, (int)r); };
+        auto unit_at = [&](uint32_t r, int32_t e) {
+            Unit u;
+            u.row = r; u.e = e;
+            u.hi = r < (uint32_t)RW ? row_at(r + 1) : e;
+            u.last = e + UE >= u.hi;
+            return u;
+        };
+        auto after = [&](const Unit &u) {
+            const uint32_t r = u.last ? u.row + 1 : u.row;
+            return unit_at(r, r >= (uint32_t)RW ? u.hi : u.last ? row_at(r) : u.e + UE);
+        };
+        // No load here hangs on a condition: the compiler counts loads under way only along straight code, and a
+        // branch around one makes it wait for all of them at the next use.
+        auto fetch = [&](const Unit &u) {                  // lane j: entry j of the unit, column | value << 16
+            const uint32_t e = (uint32_t)(u.e - ob) + lane;
+            const uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rc, e * 4, 0, 0), v = __builtin_amdgcn_raw_buffer_load_b16(rv, e * 2, 0, 0);
+            return c | (v << 16);                          // (past the tile's entries: zeros; past the row's: another row's)
+        };
+        auto gather = [&](uint32_t ents, Gathered &g) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const uint32_t ent = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((j * EP + ep) * 4), (int)ents);
+                g.v[j] = ent >> 16;
+                g.x[j] = xt[(size_t)(ent & 0xFFFFu) * xs];
+            }
+        };
+        float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        auto consume = [&](const Unit &u, const Gathered &g) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                if (j && u.e + j * EP >= u.hi) break;      // wave-uniform
+                const uint32_t have = u.e + j * EP + (int32_t)ep < u.hi ? ~0u : 0u;     // no entry: zero times zeros
+                const float v = half_bits_to_float((uint16_t)(g.v[j] & have));
+                const uint32_t w[4] = {g.x[j].x & have, g.x[j].y & have, g.x[j].z & have, g.x[j].w & have};
+#pragma unroll
+                for (int t = 0; t < 8; ++t) s[t] = fmaf(v, half_bits_to_float((uint16_t)(t & 1 ? w[t / 2] >> 16 : w[t / 2])), s[t]);
+            }
+            if (!u.last) return;
+            // the EP entry lanes of a token octet are added in a fixed tree
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                if constexpr (EP >= 16) s[t] = dpp_add<0x124>(s[t]);           // row_ror:4 (octets in lane % 4)
+                if constexpr (EP >= 8) s[t] = dpp_add<0x128>(s[t]);            // row_ror:8
+                uint32_t x = __builtin_bit_cast(uint32_t, s[t]);
+                if constexpr (EP >= 4) {
+                    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+                    s[t] = __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
+                    x = __builtin_bit_cast(uint32_t, s[t]);
+                }
+                const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+                s[t] = __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
+            }
+            if (ep == 0) {
+                const uint32_t d = plane + u.row * (BM * 4) + o * 32;
+                *(lds_f4_t *)(uintptr_t)d = float4_t{s[0], s[1], s[2], s[3]};
+                *(lds_f4_t *)(uintptr_t)(d + 16) = float4_t{s[4], s[5], s[6], s[7]};
+            }
+#pragma unroll
+            for (int t = 0; t < 8; ++t) s[t] = 0.f;
+        };
+        // D units' activations and, D units further on, D units' entries are under way: a unit's entries were requested
+        // before the activations that have not been used yet, so waiting for them is not waiting for those
+        Unit gu[D], eu[D];
+        uint32_t ents[D];
+        Gathered g[D];
+        Unit next = unit_at(0, row_at(0));
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            gu[d] = next;
+            ents[d] = fetch(next);
+            next = after(next);
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            gather(ents[d], g[d]);
+            eu[d] = next;
+            ents[d] = fetch(next);
+            next = after(next);
+        }
+        for (bool more = true; more;) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                if (gu[d].row >= (uint32_t)RW) {
+                    more = false;
+                    break;
+                }
+                consume(gu[d], g[d]);
+                gu[d] = eu[d];
+                gather(ents[d], g[d]);
+                eu[d] = next;
+                ents[d] = fetch(next);
+                next = after(next);
+            }
+        }
+        lds_barrier();
+        if (wk == 0)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        sum[rb][tb][r] += *(lds_cf32_t *)(uintptr_t)(lds0 + ((wn * RB + rb) * 32 + 8 * (r / 4) + 4 * h + r % 4) * (BM * 4) + (32 * tb + i) * 4);
+    }
+    if (wk > 0) return;
 
     // ---------------------------------------------------------------- store: register r of a block is its row 8 (r / 4) + 4 h + r % 4
     const bool f32 = ga.y_f32 != 0, b16 = a.y_bf16 != 0;
@@ -687,13 +709,19 @@ template <int BITS, int MODE, class C>
 hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
 {
     auto kern = decode_gemm_kernel<BITS, MODE, C>;
-    const int lds = C::kBase + (MODE == 1 ? (int)((ga.a.L + 1) * (2u << BITS)) : 0);
+    int lds = C::kBase + (MODE == 1 ? (int)((ga.a.L + 1) * (2u << BITS)) : 0);
+    ga.fine = ga.a.K <= kFineK;
+    ga.deep = 0;
+    if (C::DEEP && ga.a.K > kDeepK) {
+        ga.deep = (uint32_t)(lds + 15) / 16 * 16;
+        lds = (int)ga.deep + C::kDeep;
+    }
     static std::atomic<int> configured[kMaxDevices];           // per device; idempotent attribute, benign race
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
     if (!configured[dev].load(std::memory_order_relaxed)) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             C::kBase + (MODE == 1 ? 257 * (2 << BITS) : 0));
+                                             C::kBase + (MODE == 1 ? 257 * (2 << BITS) : 0) + C::kDeep);
         if (err != hipSuccess) return err;
         configured[dev].store(1, std::memory_order_relaxed);
     }
@@ -708,18 +736,25 @@ hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
 template <int BITS, int MODE>
 hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
 {
-    // 256 x 256 tiles while they give more than half of the CUs one (they run at 1.1 PFLOP/s there), else 128 x 64 tiles,
-    // which lose more than half of that rate to waits and win it back by the number of CUs at work (4096 x 4096, 333
-    // tokens: 192 tiles instead of 32).  With few workgroups a CU's latency is what counts: 16 waves, four to a SIMD, of
-    // which four share their rows and a quarter of K each.  fp32 results: half the rows, or half the waves, so that the
-    // second set of sums fits the registers.
-    using Large = GemmTile<1, 8, 8, 1, 4, 3, false>;
-    using LargeSplit = GemmTile<1, 4, 8, 1, 4, 3, true>;
-    using Small = GemmTile<1, 2, 4, 4, 4, 3, false>;
-    using SmallSplit = GemmTile<1, 2, 4, 2, 4, 3, true>;
-    const uint64_t large = (uint64_t)((ga.a.N + 255) / 256) * ((ga.M + 255) / 256);
-    if (large >= 160) return ga.y_f32 ? launch_gemm_t<BITS, MODE, LargeSplit>(ga, s) : launch_gemm_t<BITS, MODE, Large>(ga, s);
-    return ga.y_f32 ? launch_gemm_t<BITS, MODE, SmallSplit>(ga, s) : launch_gemm_t<BITS, MODE, Small>(ga, s);
+    // A round of tiles takes the same time for any number of them up to the 256 CUs, so the tile is as large as it can be
+    // with few rounds.  Measured, 4 bits (2048 x 28672: 3 bits), us in tiles of 64 x 64 / 128 x 64 / 256 x 128 and their number:
+    //   4096 x 4096, 256 tokens: 36 (256) / 51 (128) / 94 (32); 333: 60 (384) / 53 (192) / 94; 1024: 111 / 94 (512) / 97 (128);
+    //   2048: 212 / 181 (1024) / 119 (256)
+    //   8192 x 8192, 256 tokens: 95 (512) / 84 (256) / 155 (64); 512: 177 / 151 (512) / 157 (128); 700: 256 / 216 (704) / 169 (192)
+    //   2048 x 28672, 512 tokens: 143 (256) / 237 (128) / 463 (32); 28672 x 8192, 512 tokens: 610 / 511 (1792) / 346 (448)
+    using Large = GemmTile<1, 4, 8, 1, 4, 3>;
+    using Small = GemmTile<1, 2, 4, 2, 4, 3>;
+    using Small16 = GemmTile<1, 2, 4, 4, 4, 3>;
+    using Tiny = GemmTile<1, 2, 2, 4, 4, 3>;
+    const uint64_t m = (ga.M + 63) / 64, small = (uint64_t)((ga.a.N + 127) / 128) * m;
+    if ((uint64_t)((ga.a.N + 63) / 64) * m <= 256) return launch_gemm_t<BITS, MODE, Tiny>(ga, s);
+    // (rows that ask for a third set of sums, in matrices that the 16-token kernel would cut into slices: see kDeepK)
+    if (small > 512 && (ga.a.K <= kDeepK || ga.a.N >= 8192)) return launch_gemm_t<BITS, MODE, Large>(ga, s);
+    // 2-bit weights leave registers for four waves to a SIMD, of which four share their rows and a quarter of K each
+    // (4096 x 4096, 333 tokens: 42 us against 46 with two waves to a SIMD)
+    if constexpr (BITS == 2)
+        if (ga.a.K > kFineK) return launch_gemm_t<BITS, MODE, Small16>(ga, s);
+    return launch_gemm_t<BITS, MODE, Small>(ga, s);
 }
 
 template <int BITS>

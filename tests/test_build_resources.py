@@ -52,8 +52,8 @@ def test_no_kernel_spills_more_than_a_few_registers():
     (("decode_wide_kernelILi4ELi4ELi1E",), 4),
     (("decode_wide_kernelILi4ELi1ELi2E",), 4),                        # V2a with a scale and a mid-point per group, 16 tokens
     (("decode_wide_kernelILi3ELi1ELi2E",), 4),
-    (("decode_gemm_kernelILi4ELi0ENS0_8GemmTileILi1ELi8E",), 2),      # prompts, large matrices: 8 waves, a workgroup per CU
-    (("decode_gemm_kernelILi2ELi1ENS0_8GemmTileILi1ELi2ELi4ELi4E",), 4),   # prompts, few tiles: 16 waves
+    (("decode_gemm_kernelILi4ELi0ENS0_8GemmTileILi1ELi4E",), 2),      # prompts, many tiles: 8 waves, a workgroup per CU
+    (("decode_gemm_kernelILi2ELi1ENS0_8GemmTileILi1ELi2ELi4ELi4E",), 4),   # prompts, few tiles, 2 bits: 16 waves
 ])
 def test_the_workloads_kernels_keep_their_registers(parts, min_waves):
     k = find(resources(), *parts)
@@ -63,7 +63,7 @@ def test_the_workloads_kernels_keep_their_registers(parts, min_waves):
 
 def test_the_prompt_kernels_stay_in_registers():
     prompt = {k: v for k, v in resources().items() if "decode_gemm_kernel" in k}
-    assert len(prompt) == 24                                          # 2 to 4 bits, V2 and V2a, four tiles
+    assert len(prompt) == 20                                          # 2 to 4 bits, V2 and V2a, three tiles; one of 16 waves at 2 bits
     for k, v in prompt.items():
         assert v["vgpr_spills"] == 0 and v["agprs"] == 0 and v["scratch_bytes_per_lane"] == 0, (k, v)
 
