@@ -29,9 +29,12 @@
  *    caller's contract; violating it is undefined behaviour.
  *    xfp_check_contents checks that contract on the device.
  *  - Calls from several host threads are safe.  The only state kept between
- *    calls is a static ring of eight workspaces of 72 MB in device memory
+ *    calls is a static ring of eight workspaces of 10 MB in device memory
  *    (every GPU the process uses holds its own copy; a call uses the one of the
- *    current device, which must be the device of its pointers and stream).
+ *    current device, which must be the device of its pointers and stream), and,
+ *    from the process's first prompt on that GPU (XFP_ROUTE_GEMM), 64 MB more
+ *    for each of them.  The runtime makes them there when they are first needed,
+ *    and they stay until the process ends.
  *    A call that needs scratch memory (the batched path's re-laid activations,
  *    split-K partial sums, the unfused forms of the epilogues) takes ONE slot
  *    for everything it needs.  Eager calls cycle through four slots, so calls
@@ -168,9 +171,9 @@ int xfp_gemv(const xfp_weights *W, const void *x, int M, int64_t ldx,
  * harnesses that forbid hipMalloc.  (No paper counterpart.)  Same arguments and
  * same results, bit for bit, as xfp_gemv.  Whatever scratch the call needs
  * (re-laid activations for M >= 2, partial sums of rows cut into slices of K)
- * lives in ONE static device array of 72 MB, not in the ring the other entry
- * points cycle through; each GPU the process uses holds its own copy until the
- * process ends.  The call allocates nothing, frees nothing and calls no
+ * lives in ONE static device array of 10 MB (and one of 64 MB for prompts, from
+ * the first one on), not in the ring the other entry points cycle through; each
+ * GPU the process uses holds its own copy until the process ends.  The call allocates nothing, frees nothing and calls no
  * allocating routine.
  * Limits (the array's size): where xfp_gemv would reroute a call because a
  * scratch plane is too small, this one returns XFP_ERR_SCRATCH and launches
@@ -329,9 +332,11 @@ int xfp_probe_copy(const void *src, void *dst, uint64_t bytes, void *hip_stream)
 
 /*
  * Resolves, for the current device, the addresses of the library's static
- * device memory (the ring of workspaces and xfp_gemv_noalloc's array).  Optional: the first call that needs them does the same; call
- * it once per device before recording calls into a HIP graph, so that nothing
- * but launches happens under capture.
+ * device memory (the ring of workspaces and xfp_gemv_noalloc's array; not the
+ * memory of prompts, which the first prompt loads, also under capture).
+ * Optional: the first call that needs them does the same; call it once per
+ * device before recording calls into a HIP graph, so that nothing but launches
+ * happens under capture.
  */
 int xfp_init(void);
 

@@ -311,7 +311,12 @@ int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, 
         case XFP_ROUTE_WIDE:
             err = xfp::launch_decode_wide(bits, (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : mode, c, p.take, y_f32, ws->xc, ws->part, s);
             break;
-        case XFP_ROUTE_GEMM: err = xfp::launch_decode_gemm(bits, mode, c, p.take, y_f32, ws->xc, s); break;
+        case XFP_ROUTE_GEMM: {
+            xfp::PromptCopies *copies = nullptr;
+            err = xfp::prompt_copies(*ws, &copies);
+            if (err == hipSuccess) err = xfp::launch_decode_gemm(bits, mode, c, p.take, y_f32, copies, s);
+            break;
+        }
         case XFP_ROUTE_BATCH: err = xfp::launch_decode_batch(bits, mode, c, p.take, y_f32, ws->part, ws->xc, s); break;
         case XFP_ROUTE_TILE: err = xfp::launch_decode_tile(bits, y_f32, c, p.take, s); break;
         case XFP_ROUTE_STREAM: err = xfp::launch_decode_stream(bits, stream_affine(W) ? 2 : mode, y_f32, c, p.take, s); break;
@@ -403,7 +408,7 @@ int xfp_gemv_noalloc(const xfp_weights *W, const void *x, int M, int64_t ldx, vo
     hipError_t err = scratch_resolve(&ptr);
     if (err != hipSuccess) return finish(err);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    Scratch sc(s, xfp::workspace_at(ptr));
+    Scratch sc(s, xfp::workspace_at(ptr, -1));
     return decode(W, nullptr, M, x, ldx, y, y_dtype, ldy, sc, s);
 }
 

@@ -758,7 +758,7 @@ hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
 }
 
 template <int BITS>
-hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
+hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, PromptCopies *xc, hipStream_t s)
 {
     const uint32_t runs = (a.K + 255) / 256 * 8;
     GemmArgs ga;
@@ -794,7 +794,7 @@ int gemm_tokens(uint32_t K, int M)
 }
 
 // One pair of launches: the copies of the activations, the product.
-hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
+hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, PromptCopies *xc, hipStream_t s)
 {
     if (!xc) return hipErrorInvalidValue;
     if (bits == 4) return launch_gemm_b<4>(mode, a, M, y_f32, xc, s);

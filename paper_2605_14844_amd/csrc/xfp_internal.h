@@ -55,15 +55,22 @@ constexpr int kXtTokens = 16;                      // tokens per launch of the b
 //                               the 64 lanes of a wave read 1 KB contiguous (from the row-major x the
 //                               same load touches 64 different cache lines).
 // Tokens >= M are zero in both.
-// The prompt kernel keeps copies of its own making there, of as many tokens as fit: [k][tokens] and [token][k].
-constexpr uint64_t kGemmHalves = 1ull << 24;       // 2048 tokens of 8192 columns
 struct XCopies {
+    uint16_t xt[kXtMaxK * kXtTokens];
+    uint16_t xb[kXtMaxK * kXtTokens];
+};
+// The prompt kernel's copies, [k][tokens] and [token][k], of as many tokens as fit.  They are 64 MB and apart from the
+// workspaces, in code objects of their own (xfp_workspace_prompt.hip, xfp_workspace_prompt_static.hip): the runtime loads
+// a code object, and with it its static arrays, when something in it is first asked for, so a process that sends no
+// prompts does not hold them.  (Half of it would do at 1024 tokens of 8192 columns a launch: 28672 x 8192, 2048 tokens
+// 1.31 -> 1.50 ms, a launch being three and a half rounds of tiles that take the time of four.)
+constexpr uint64_t kGemmHalves = 1ull << 24;       // 2048 tokens of 8192 columns
+struct PromptCopies {
     uint16_t xt[kGemmHalves];
     uint16_t xb[kGemmHalves];
 };
-static_assert(kGemmHalves >= (uint64_t)kXtMaxK * kXtTokens, "the batched and wide kernels' copies fit too");
 struct WorkspaceLayout {
-    XCopies xc;                  // re-laid activations (2 x 32 MB)
+    XCopies xc;                  // re-laid activations (2 x 1 MB)
     float epi[kPlaneFloats];     // unfused epilogues: per-slot fp32 results
     float part[kPlaneFloats];    // split-K: per-slice fp32 partial sums
 };
@@ -71,11 +78,21 @@ struct Workspace {
     XCopies *xc;
     float *epi;
     float *part;
+    int slot;                    // of the ring, or -1: the static array
 };
-inline Workspace workspace_at(void *base)
+static_assert(sizeof(WorkspaceLayout) == 10u << 20, "what xfp.h states");
+inline Workspace workspace_at(void *base, int slot)
 {
     WorkspaceLayout *l = static_cast<WorkspaceLayout *>(base);
-    return Workspace{&l->xc, l->epi, l->part};
+    return Workspace{&l->xc, l->epi, l->part, slot};
+}
+// The prompt copies that belong to a workspace, on the current device.
+constexpr int kRingSlots = 8;
+hipError_t prompt_copies_ring(int slot, PromptCopies **out);
+hipError_t prompt_copies_static(PromptCopies **out);
+inline hipError_t prompt_copies(const Workspace &ws, PromptCopies **out)
+{
+    return ws.slot < 0 ? prompt_copies_static(out) : prompt_copies_ring(ws.slot, out);
 }
 // One slot of the static ring of workspaces on the current device.  Calls on a
 // stream that is being captured into a graph cycle through slots of their own,
@@ -136,7 +153,7 @@ bool gemm_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
 // How many of M tokens one launch takes: what both copies hold, whose rows are M rounded up to 8 and K rounded up to 256
 // halves; where that is not all of them, whole tiles.
 int gemm_tokens(uint32_t K, int M);
-hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s);
+hipError_t launch_decode_gemm(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, PromptCopies *xc, hipStream_t s);
 hipError_t launch_silu_mul(const float *y, uint32_t half, int slots, void *h, int64_t h_stride, bool h_f32,
                            bool h_bf16, hipStream_t s);
 // Down projection with the router's weighted sum over the slots in one launch (V2, T <= 8, T * K <= 16384)

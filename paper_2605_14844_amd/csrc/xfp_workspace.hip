@@ -18,7 +18,8 @@ namespace {
 constexpr int kEagerSlots = 4;
 constexpr int kCaptureSlots = 4;
 static_assert(sizeof(WorkspaceLayout) % 256 == 0, "slots stay 256-byte aligned");
-__device__ __align__(256) unsigned char g_ring[kEagerSlots + kCaptureSlots][sizeof(WorkspaceLayout)];
+static_assert(kEagerSlots + kCaptureSlots == kRingSlots, "");
+__device__ __align__(256) unsigned char g_ring[kRingSlots][sizeof(WorkspaceLayout)];
 
 std::atomic<void *> g_ring_base[kMaxDevices];      // device address of g_ring, per device
 std::atomic<unsigned> g_ticket_eager{0}, g_ticket_capture{0};
@@ -54,7 +55,8 @@ hipError_t ring_workspace(hipStream_t s, Workspace *out)
     const bool capturing = st != hipStreamCaptureStatusNone;
     const unsigned ticket = (capturing ? g_ticket_capture : g_ticket_eager).fetch_add(1, std::memory_order_relaxed);
     unsigned char *base = static_cast<unsigned char *>(g_ring_base[current_device()].load(std::memory_order_acquire));
-    *out = workspace_at(base + (size_t)ring_slot_index(ticket, capturing) * sizeof(WorkspaceLayout));
+    const int slot = ring_slot_index(ticket, capturing);
+    *out = workspace_at(base + (size_t)slot * sizeof(WorkspaceLayout), slot);
     return hipSuccess;
 }
 

@@ -1,5 +1,10 @@
 """The prompt kernel (many tokens as one tiled product, V2 and V2a at 2 to 4 bits): parity with the oracle at the
 edges of its tiles, its order of k bit-exactly through one-hot activations, types, strides and repeatability."""
+import os
+import re
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -112,3 +117,51 @@ def test_sums_are_as_exact_as_in_passes_of_64_tokens(bits, N, K, M, mode, dens):
     assert err[0] <= 1.05 * err[1], err
     for t in (torch.float16, torch.bfloat16):
         assert torch.equal(xfp.xfp_gemv(dW, x, y_dtype=t), y.to(t))
+
+
+FIRST_PROMPT = """
+import sys
+import numpy as np, torch
+import paper_2605_14844_amd as xfp, xfp_inputs as xi
+
+def used():
+    torch.cuda.synchronize()
+    free, total = torch.cuda.mem_get_info()
+    return (total - free) >> 20
+
+W = xfp.upload(xi.random_weights(xi.MODE_V2, 4, 256, 512, density=0.003, seed=3))
+x = torch.from_numpy(xi.activations(np.random.default_rng(4), 600, 512).view(np.int16)).cuda().view(torch.float16)
+y, y4 = torch.empty((600, 256), dtype=torch.float16, device="cuda"), torch.empty((4, 256), dtype=torch.float16, device="cuda")
+xfp.xfp_gemv(W, x[:1], y=y4[:1])
+before = used()
+xfp.xfp_init()
+xfp.xfp_gemv(W, x[:4], y=y4)
+xfp.xfp_gemv_noalloc(W, x[:4], y4)
+few = used() - before
+side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph, stream=side):
+    xfp.xfp_gemv(W, x, y=y)
+prompt = used() - before
+seen = []
+for _ in range(3):
+    y.zero_()
+    graph.replay()
+    torch.cuda.synchronize()
+    seen.append(y.clone())
+    xfp.xfp_gemv(W, x[:4], y=y4)
+eager, fixed = xfp.xfp_gemv(W, x), torch.empty_like(y)
+xfp.xfp_gemv_noalloc(W, x, fixed)
+torch.cuda.synchronize()
+assert all(torch.equal(s, eager) for s in seen) and torch.equal(fixed, eager)
+print("MB", few, prompt, used() - before)
+"""
+
+
+def test_only_prompts_load_the_memory_of_prompts():
+    """Eight workspaces and the static array are 90 MB; the first prompt loads 512 more (and 64 for xfp_gemv_noalloc), also
+    where it is a call that is being captured."""
+    r = subprocess.run([sys.executable, "-c", FIRST_PROMPT], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                       capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    few, prompt, both = map(int, re.search(r"MB (\d+) (\d+) (\d+)", r.stdout).groups())
+    assert few <= 130 and 512 <= prompt - few and 64 <= both - prompt and both <= 760, (few, prompt, both)
