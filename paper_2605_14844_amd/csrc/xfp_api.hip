@@ -215,13 +215,17 @@ bool wide_affine(const xfp_weights *W, bool expert_indexed, int tokens)
 }
 
 // Prompts: the tiled product against passes of the wide kernel (64 tokens up to 8192 columns, 32 to 16 beyond).  A round
-// of 128 x 64 tiles takes the same time for any number of them up to the 256 CUs, a pass grows with the rows only from
-// 256 tiles of 32 on.  Measured at 2 formats, fp16 and fp32 results, us passes / product:
-//  - one round: 4096 x 4096, fp32: 65 tokens 23 / 47, 128 36 / 47, 193 51 / 44, 512 112 / 45: from 193 tokens on;
-//  - more rounds: 16384 x 8192, fp32: 0.81 of the passes' rate at 257 tokens, 0.92 at 448, 1.02 at 512, 1.5 at 1024;
-//  - more than half a round of 256 x 256 tiles: 28672 x 8192, fp32: 0.99 at 320 tokens, 1.17 at 384;
-//  - rows beyond 16384 columns, which are passed over once per 16 tokens: 2048 x 28672 at 128 tokens 210 / 176 (fp32
-//    212 / 214), 8192 x 28672 326 / 190.
+// of tiles takes the same time for any number of them up to the 256 CUs, a pass grows with the rows only from 256 tiles
+// of 32 on.  Measured, us as this rule has it / in passes alone / as one product (fp16 results; fp32 within a tenth):
+//  - one round of 128 x 64 tiles or less, from 193 tokens on: 4096 x 4096 193 tokens 36 / 59 / 36, 384 50 / 105 / 50;
+//    8192 x 8192 193 81 / 89 / 81; 65 tokens: 25 / 25 / 32 and 37 / 37 / 49;
+//  - a little more than that: passes until one round is left (each launch's leftover is planned anew): 8192 x 8192 257 tokens
+//    106 / 114 / 146, 384 130 / 154 / 145, 448 155 / 179 / 146; 6144 x 4096 333 66 / 105 / 84;
+//  - 28672 x 8192: 320 tokens 332 / 325 / 353, 384 353 / 431 / 353;
+//  - rows beyond 16384 columns, which are passed over once per 16 tokens: 4096 x 28672 128 tokens 123 / 280 / 122.
+// It is nowhere slower than passes (128 .. 28672 rows, 512 .. 28672 columns, 65 .. 511 tokens).  It asks for more tokens than it
+// would have to: the product would win from 100 to 160 tokens on in many shapes (4096 x 4096, 160 tokens 50 / 50 / 34),
+// from 193 on in tall ones (16384 x 2048, 300 tokens 88 / 87 / 61) and from 65 on in long rows (2048 x 16384 91 / 90 / 72).
 // Formats that no matrix-core kernel takes otherwise (libraries beyond LDS, rows beyond 32768 columns) run token by token.
 bool gemm_only(const xfp_weights *W)
 {

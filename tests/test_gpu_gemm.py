@@ -119,6 +119,44 @@ def test_sums_are_as_exact_as_in_passes_of_64_tokens(bits, N, K, M, mode, dens):
         assert torch.equal(xfp.xfp_gemv(dW, x, y_dtype=t), y.to(t))
 
 
+@pytest.mark.parametrize("bits,L", [(4, 256), (3, 255), (2, 256)])
+def test_the_largest_libraries(bits, L):
+    """No other matrix-core kernel takes them; every entry is used, the last one too."""
+    W = xi.random_weights(V2A, bits, 300, 896, L=L, density=0.003, seed=L + bits)
+    W.group_ids.reshape(-1)[:L] = np.arange(L, dtype=np.uint8)
+    xb = xi.activations(np.random.default_rng(L), 230, 896)
+    dW = xfp.upload(W)
+    assert xfp.xfp_route(dW, 230) == (xfp.XFP_ROUTE_GEMM, 230)
+    y = xfp.xfp_gemv(dW, dev_x(xb), y_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert gated_rel_err(y.cpu().numpy(), oracle.gemv_weights(W, xb)) <= 1e-4
+
+
+# odd group counts (half a block is zero times zero), one and several tiles of rows, 64 x 64 and 256 x 128 tiles
+@pytest.mark.parametrize("bits,N,K,M,mode", [(4, 200, 384, 200, V2), (3, 130, 640, 200, V2A), (2, 130, 896, 200, V2), (2, 8200, 640, 600, V2)])
+def test_infinities_and_nan_stay_with_their_tokens(bits, N, K, M, mode):
+    W = xi.random_weights(mode, bits, N, K, L=9, density=0.01, seed=N + bits)
+    x = dev_x(xi.activations(np.random.default_rng(M), M, K)).clone()
+    dW = xfp.upload(W)
+    assert xfp.xfp_route(dW, M) == (xfp.XFP_ROUTE_GEMM, M)
+    plain = xfp.xfp_gemv(dW, x, y_dtype=torch.float32)
+    special = {3: (K - 1, np.inf), 64: (0, -np.inf), M - 1: (K // 2, np.nan)}
+    for m, (k, v) in special.items():
+        x[m, k] = v
+    y = xfp.xfp_gemv(dW, x, y_dtype=torch.float32).cpu().numpy()
+    weight = xfp.xfp_dequant_bulk(dW).view(torch.float16).float().cpu().numpy()
+    for m, (k, v) in special.items():
+        with np.errstate(invalid="ignore"):
+            want = weight[:, k] * np.float32(v)
+            for n in range(N):
+                at = np.flatnonzero(W.out_col[W.out_row_ptr[n]:W.out_row_ptr[n + 1]] == k)
+                for j in at:
+                    want[n] += np.float32(W.out_val[W.out_row_ptr[n] + j].view(np.float16)) * np.float32(v)
+        assert np.array_equal(y[m], want, equal_nan=True), m
+    rest = [m for m in range(M) if m not in special]
+    assert np.array_equal(y[rest], plain.cpu().numpy()[rest])
+
+
 FIRST_PROMPT = """
 import sys
 import numpy as np, torch

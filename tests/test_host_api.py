@@ -327,11 +327,14 @@ def test_a_prompt_launch_takes_what_its_copies_hold():
 
 
 def test_tokens_left_over_by_prompt_launches():
-    """They are planned like a call of their own; where no other matrix-core kernel takes them, launches share them."""
+    """What a launch leaves over is planned like a call of its own (also behind passes: a prompt that is one round of tiles and
+    a little more is passes, then one round); where no other matrix-core kernel takes it, launches share the tokens."""
     G, Wd, R = xfp.XFP_ROUTE_GEMM, xfp.XFP_ROUTE_WIDE, xfp
     for kw, M, want in [(dict(N=28672, K=8192), 2049, [(G, 2048), (R.XFP_ROUTE_TILE, 1)]),
                         (dict(N=28672, K=8192), 2100, [(G, 2048), (Wd, 52)]),
                         (dict(N=8192, K=8192), 2048 + 300, [(G, 2048), (Wd, 64), (G, 236)]),
+                        (dict(N=8192, K=8192), 257, [(Wd, 64), (G, 193)]), (dict(N=8192, K=8192), 320, [(Wd, 64), (G, 256)]),
+                        (dict(N=8192, K=8192), 448, [(Wd, 64)] * 3 + [(G, 256)]), (dict(N=28672, K=8192), 257, [(Wd, 64)] * 4 + [(R.XFP_ROUTE_TILE, 1)]),
                         (dict(N=2048, K=28672), 585, [(G, 512), (R.XFP_ROUTE_BATCH, 16)]),
                         (dict(N=130, K=65536, bits=2), 300, [(G, 152), (G, 148)]),
                         (dict(N=4096, K=4096, L=256, mode=1, group_ids=FAKE), 2 * 4096 + 3, [(G, 4096), (G, 2056), (G, 2043)])]:
