@@ -63,7 +63,7 @@ struct XCopies {
 // workspaces, in code objects of their own (xfp_workspace_prompt.hip, xfp_workspace_prompt_static.hip): the runtime loads
 // a code object, and with it its static arrays, when something in it is first asked for, so a process that sends no
 // prompts does not hold them.  (Half of it would do at 1024 tokens of 8192 columns a launch: 28672 x 8192, 2048 tokens
-// 1.31 -> 1.50 ms, a launch being three and a half rounds of tiles that take the time of four.)
+// 1.31 ms, twice 1024 1.50: three and a half rounds of tiles, which take the time of four.)
 constexpr uint64_t kGemmHalves = 1ull << 24;       // 2048 tokens of 8192 columns
 struct PromptCopies {
     uint16_t xt[kGemmHalves];

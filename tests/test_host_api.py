@@ -309,6 +309,8 @@ def test_prompts_take_the_product_where_it_is_the_faster_one():
                         (dict(N=4096, K=4096, L=256, **v2a), 65, (G, 65)), (dict(N=512, K=512, L=32, bits=3, **v2a), 65, (Wd, 64)),
                         (dict(N=4096, K=4096, bits=5), 500, (xfp.XFP_ROUTE_GENERAL, 500))]:
         assert xfp.xfp_route(desc(**kw), M) == want, (kw, M)
+    assert xfp.xfp_route(desc(N=130, K=65536, bits=2), 256)[0] == G       # an outlier's column is kept in 16 bits
+    assert xfp.xfp_route(desc(N=130, K=65536 + 128, bits=2), 256)[0] != G
 
 
 def test_a_prompt_launch_takes_what_its_copies_hold():
