@@ -1,9 +1,9 @@
 // Prompt form of the fused decode: any number of tokens against one matrix (V2 codebooks or a V2a library, 2 to 4
 // bits), as a tiled matrix product on the matrix cores whose weight operand is dequantised on the way.
 //
-// Why: with hundreds of tokens the product is bound by the matrix cores (28672 x 8192 with 2048 tokens: 0.96 TFLOP),
-// not by the weights' bytes, and the 64-token kernel reads and
-// dequantises the whole matrix once per 64 tokens and fetches its activations from L2 once per 32 rows.
+// Why: with hundreds of tokens the product is bound by arithmetic (28672 x 8192 with 2048 tokens: 0.96 TFLOP; the matrix
+// cores and the VALU, which dequantises, each busy for half of the clocks), not by the weights' bytes, and the 64-token
+// kernel reads and dequantises the whole matrix once per 64 tokens and fetches its activations from L2 once per 32 rows.
 //
 // Work unit: a workgroup of 8 or 16 waves owns BN output rows x BM tokens and walks K; a row's sum is taken in two or
 // three steps (GemmTile).
