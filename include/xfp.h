@@ -108,8 +108,7 @@ typedef enum { XFP_F16 = 0, XFP_F32 = 1, XFP_BF16 = 2 } xfp_dtype;   /* type of 
  * sum(x), which is the same thing by linearity).  Scale 1 and mid-point 0 give
  * the plain library.  At 2 to 4 bits such matrices run a mode of their own of the
  * streaming kernel (rows up to 16384 columns, token by token) or, for several
- * tokens on a large matrix (2^27 weights x tokens and more), of the wide
- * matrix-core kernel, 16 tokens per launch; else the general kernel. */
+ * tokens, of the matrix-core kernels; else the general kernel. */
 #define XFP_FLAG_GROUP_AFFINE 1u
 
 #define XFP_GROUP 128
@@ -358,7 +357,9 @@ int xfp_select_kernel(int which);
  * covers; a call with tokens left over continues with the rule applied to the rest.  The descriptor is validated
  * as by the decode calls (its pointers are not dereferenced).  Returns an xfp_route_id, or a negative xfp_status
  * (XFP_ERR_UNSUPPORTED for a row no kernel takes).  xfp_select_kernel changes what it reports, as it changes
- * what runs.
+ * what runs.  The families are those of the format's and the sizes' limits: where a launch of STREAM, SPLIT_K,
+ * BATCH, WIDE or GENERAL with up to 64 tokens is faster in the kernel that keeps the activations in LDS, that
+ * kernel runs in its place, for these tokens or more of the call's.
  */
 typedef enum {
     XFP_ROUTE_GENERAL = 0,   /* one wave per row, x and tables in LDS: widths 5 and 6, scale + mid-point, odd shapes */

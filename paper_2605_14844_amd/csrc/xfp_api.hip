@@ -280,6 +280,15 @@ Plan plan(const xfp_weights *W, bool expert_indexed, int slots)
     return Plan{XFP_ROUTE_GENERAL, take, 0};
 }
 
+// The tokens that the resident kernel takes in place of a planned launch (0: none): it stands in for the families of a few
+// tokens wherever it is the faster one (few_tokens), not for prompts, expert-indexed calls or what xfp_select_kernel asks for.
+int resident_tokens(const xfp_weights *W, bool expert_indexed, int left, const Plan &p)
+{
+    if (expert_indexed || p.route == XFP_ROUTE_GEMM || W->bits > 4) return 0;
+    if (left == 1 && g_kernel_choice.load(std::memory_order_relaxed) != XFP_KERNEL_AUTO) return 0;
+    return xfp::few_tokens((int)W->bits, (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : (int)W->mode, W->L, W->N, W->K, left, xfp::kPlaneFloats);
+}
+
 // y_dtype: an xfp_dtype, optionally OR-ed with XFP_X_BF16
 int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, int64_t x_stride,
            void *y, int y_dtype, int64_t ldy, Scratch &sc, hipStream_t s)
@@ -306,6 +315,17 @@ int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, 
         c.y = static_cast<char *>(y) + (size_t)m0 * (size_t)ldy * ysz;
         if (eids) c.eids = eids + m0;
         const xfp::Workspace *ws = nullptr;
+        if (const int few = resident_tokens(W, eids != nullptr, slots - m0, p)) {
+            const int fmode = (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : mode;
+            if (xfp::few_is_sliced(bits, fmode, W->L, W->N, W->K, few)) {
+                hipError_t werr = sc.get(&ws);
+                if (werr != hipSuccess) return finish(werr);
+            }
+            hipError_t err = xfp::launch_decode_few(bits, fmode, c, few, y_f32, ws ? ws->part : nullptr, s);
+            if (err != hipSuccess) return finish(err);
+            m0 += few;
+            continue;
+        }
         if (p.route == XFP_ROUTE_GEMM || p.route == XFP_ROUTE_WIDE || p.route == XFP_ROUTE_BATCH || p.route == XFP_ROUTE_SPLIT_K) {
             hipError_t werr = sc.get(&ws);
             if (werr != hipSuccess) return finish(werr);

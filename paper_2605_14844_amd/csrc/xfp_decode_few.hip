@@ -1,0 +1,108 @@
+// Host side of the kernel of xfp_decode_few.inc.h: which calls it is the faster one for, and how a call's rows and columns
+// are shared out.
+#include "xfp_decode_few.inc.h"
+
+namespace xfp {
+
+// defined in xfp_decode_few2.hip, xfp_decode_few3.hip, xfp_decode_few4.hip
+hipError_t launch_few2(int mode, const FewArgs &fa, dim3 grid, int lds, hipStream_t s);
+hipError_t launch_few3(int mode, const FewArgs &fa, dim3 grid, int lds, hipStream_t s);
+hipError_t launch_few4(int mode, const FewArgs &fa, dim3 grid, int lds, hipStream_t s);
+
+namespace {
+
+constexpr uint32_t kLds = 160 * 1024;
+constexpr uint32_t kCUs = 256;
+
+// Blocks of 16 rows, waves per block, groups per slice of K: as few slices as the activations' place in LDS allows (a second
+// launch adds the slices' sums), the blocks of a slice spread over the 256 CUs, and the 16 waves that a CU holds at this
+// kernel's registers (8 from 33 tokens on, whose sums take 5 KB of LDS per wave) sharing the blocks' columns.
+// 7001 x 5504, 2 bits, 5 tokens, us for blocks x waves: 2 x 8 9.9, 2 x 4 11.3, 1 x 8 10.6, 1 x 16 13.8, 4 x 4 14.1.
+struct FewPlan {
+    uint32_t slices, lds;
+    FewArgs fa;
+};
+
+bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M, FewPlan &p)
+{
+    const uint32_t G = K / kGroup, GU = bits == 2 ? 2 : 1, blocks = (N + 15) / 16, most = M <= 32 ? 16 : 8;
+    const uint32_t x_most = kLds - most * 1024 - (mode ? L * (2u << bits) : 0u);
+    for (uint32_t S = (uint32_t)(((uint64_t)M * G * 256 + x_most - 1) / x_most); S <= G; ++S) {
+        uint32_t GS = (G + S - 1) / S;
+        if (bits == 2) GS = (GS + 1) & ~1u;
+        p.slices = (G + GS - 1) / GS;
+        uint32_t RB = (uint32_t)(((uint64_t)blocks * p.slices + kCUs - 1) / kCUs), KW;
+        if (RB > most) RB = most;
+        KW = most / RB;
+        if (KW > (GS + GU - 1) / GU) KW = (GS + GU - 1) / GU;
+        p.lds = few_layout(bits, mode, L, M, RB, KW, GS, p.fa);
+        if (p.lds <= kLds) return true;
+    }
+    return false;
+}
+
+}  // namespace
+
+// How many of `left` tokens the next launch takes in this kernel, 0: none (another kernel is faster).  plane: floats of the
+// scratch plane for the sums of several slices.
+// One launch without a re-laid copy of the activations and without tables wins wherever the activations fit, and loses its
+// edge with the slices that they are cut into otherwise: every slice stages its activations and reads its rows' outliers
+// anew.  Measured, us in the other kernels / here (graph replay, cold weights):
+//  - 2 to 8 tokens: 4096 x 2048 8.3 / 5.0, 7001 x 5504 16 / 9.9, 8192 x 8192 (2 slices) 24 / 18, 28672 x 4096 57 / 27, but
+//    8192 x 14336 (3 slices) 38 / 51; rows beyond 8192 columns in matrices of up to 8160 rows, which are three launches
+//    elsewhere: 3000 x 22016 32 / 16, 300 x 20480 35 / 13;
+//  - 9 to 16: 4096 x 2048 9.8 / 7.4, 28672 x 1024 22 / 12, 12000 x 5504 (2 slices) 43 / 21, but 4096 x 8192 (3) 19.5 / 22;
+//  - 17 to 32: 600 x 1536 11.2 / 7.7, 28672 x 1024 20.5 / 13.9, 600 x 14336 27 / 16, but 8192 x 4096 17 / 36;
+//  - 33 to 64, where the other kernel's tables serve more tokens: 300 x 4096 15 / 13, 600 x 14336 52 / 21, 1200 x 14336
+//    53 / 22, but 1200 x 4096 23 / 28 and 1200 x 640 10.6 / 13.7;
+//  - a scale and a mid-point per group, which run token by token or 16 at a time elsewhere: 8 tokens 16384 x 3072 17.8 / 12.7,
+//    24 4096 x 4096 30 / 14, 64 2000 x 2048 36 / 16, 64 12000 x 5504 94 / 82 (16 at a time), but 2 to 4 tokens of
+//    1200 x 4096 6.6 / 7.3 and 40 of 8192 x 8192 66 / 88;
+//  - one token: library rows that neither fit the registers of the streaming kernel nor leave it time for slices:
+//    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 300 x 20480 6.7 / 12.
+int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane)
+{
+    if (bits < 2 || bits > 4 || K > 65536 || left < 1) return 0;             // (an outlier's column is kept in 16 bits)
+    FewPlan p;
+    auto fits = [&](uint32_t m) { return few_plan(bits, mode, L, N, K, m, p) && (p.slices == 1 || (uint64_t)p.slices * m * N <= plane); };
+    if (left == 1) return mode != 0 && K > 16384 && N >= 4096 && fits(1) ? 1 : 0;
+    const bool split = K > 8192 && N <= 8160;                  // three launches in the 16-token kernel
+    const uint32_t m = left < 64 ? (uint32_t)left : 64u;
+    if (m <= 16) {
+        if (mode == 2 && m <= 4 && K >= 4096 && (uint64_t)N * m <= 8192) return 0;
+        return fits(m) && (p.slices <= 2 || split) ? (int)m : 0;
+    }
+    if (m <= 32) {
+        if (fits(m) && (p.slices == 1 || N <= 1008 || (mode == 2 && p.slices <= 2))) return (int)m;
+    } else if (mode == 2 ? N <= 2048 : (N <= 1008 && K >= 8192) || (N <= 640 && K >= 4096)) {
+        if (fits(m)) return (int)m;
+    } else if (mode == 2) {
+        if (fits(32) && p.slices <= 2) return 32;
+    }
+    if (mode == 2 && fits(16) && p.slices <= 2) return 16;
+    return 0;
+}
+
+// M tokens (few_tokens), fp32 planes of the slices' sums in part
+hipError_t launch_decode_few(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, float *part, hipStream_t s)
+{
+    FewPlan p;
+    if (!few_plan(bits, mode, a.L, a.N, a.K, (uint32_t)M, p) || (p.slices > 1 && !part)) return hipErrorInvalidValue;
+    p.fa.a = a;
+    p.fa.y_f32 = (int)y_f32;
+    p.fa.part = p.slices > 1 ? part : nullptr;
+    const dim3 grid((a.N + p.fa.RB * 16 - 1) / (p.fa.RB * 16), p.slices);
+    hipError_t err = bits == 4   ? launch_few4(mode, p.fa, grid, (int)p.lds, s)
+                     : bits == 3 ? launch_few3(mode, p.fa, grid, (int)p.lds, s)
+                                 : launch_few2(mode, p.fa, grid, (int)p.lds, s);
+    if (err != hipSuccess || p.slices == 1) return err;
+    return launch_splitk_sum(part, p.slices, a.N, M, a.y, a.y_stride, y_f32, a.y_bf16 != 0, s);
+}
+
+bool few_is_sliced(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M)
+{
+    FewPlan p;
+    return few_plan(bits, mode, L, N, K, (uint32_t)M, p) && p.slices > 1;
+}
+
+}  // namespace xfp

@@ -139,6 +139,17 @@ __device__ __forceinline__ float segment_sum(float v)
     return v;
 }
 
+// 16 bytes per lane from a buffer (byte offset voffset + soffset, both in the resource's range check) straight into LDS:
+// lane l's go to lds + 16 l, past the end zeros.  The one load written as an instruction: as a builtin it would make the
+// compiler wait for all of them in front of every read from LDS.  It has no result register; its callers state how many
+// loads may still be under way where they wait.
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t voffset, u32x4_t rsrc, uint32_t soffset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory", "m0");
+}
+
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits
 // for every outstanding global load, which would drain the index prefetch.
 __device__ __forceinline__ void lds_barrier()
