@@ -193,8 +193,7 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
     if constexpr (BITS == 3) voff = lane < 48 ? lane / 3 * (wpr * 4) + lane % 3 * 16 : 0x7FFFFFF0u;
     else voff = lane / 4 * (wpr * 4) + ((lane ^ (lane >> 4)) & 3) * 16;
     auto request = [&](uint32_t t) {                           // the wave's t-th unit
-        load_to_lds(__builtin_amdgcn_readfirstlane(ring + (t % kFewRing) * kFewUnit), voff, ri,
-                    __builtin_amdgcn_readfirstlane((g0 + (u0 + t) * GU) * (16 * BITS)));
+        load_to_lds(__builtin_amdgcn_readfirstlane(ring + (t % kFewRing) * kFewUnit), voff + (g0 + (u0 + t) * GU) * (16 * BITS), ri, 0);
     };
 #pragma unroll
     for (uint32_t t = 0; t < (uint32_t)kFewRing; ++t)

@@ -17,8 +17,8 @@
 //  - The B tile (BM tokens) comes from a token-major copy of the activations straight into LDS
 //    (buffer_load_dwordx4 ... lds: no registers, no VALU), through a ring of parts; its rows are XOR-swizzled in
 //    16-byte chunks so that 16 consecutive lanes of a ds_read_b128 cover the 64 banks.
-//  - 28672 x 8192, 4 bits, 2048 tokens: 1.28 ms against 2.08 ms in passes of 64 tokens (the library's own dense product of
-//    this shape 0.71 ms).  4096 x 4096, 2 bits, 333 tokens: 42 us against 98.
+//  - 28672 x 8192, 4 bits, 2048 tokens: 1.13 ms against 2.08 ms in passes of 64 tokens (the library's own dense product of
+//    this shape 0.71 ms).  4096 x 4096, 2 bits, 333 tokens: 31 us against 98.
 //
 // Order of k inside 32 weights: what the byte planes give cheaply is not the natural order (at 4 bits the even
 // nibbles of a dword come before the odd ones).  A product does not care as long as both operands agree, so the copy
@@ -43,6 +43,9 @@ typedef __attribute__((address_space(3))) u32x4_t lds_u4_t;
 typedef __attribute__((address_space(3))) const u32x4_t lds_cu4_t;
 typedef __attribute__((address_space(3))) const half8_t lds_ch8_t;
 typedef __attribute__((address_space(3))) const float lds_cf32_t;
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const u32x2_t lds_cu2_t;
+typedef __attribute__((address_space(3))) const uint8_t lds_cu8_t;
 typedef __attribute__((address_space(3))) float4_t lds_f4_t;
 typedef __attribute__((address_space(4))) const int32_t const_i32_t;   // uniform reads go through the scalar cache
 
@@ -52,31 +55,35 @@ typedef __attribute__((address_space(4))) const int32_t const_i32_t;   // unifor
 // Every block is a chain of its own, whose sums are added to a second set of registers: what one fp32 chain through all
 // of a row's products of 16 loses grows with the root of its length (4096 columns: 3.1e-7 of the result, 1.2e-7 in two
 // steps).  The second set halves the tokens that a dequantised weight meets in a wave (28672 x 8192, 2048 tokens, fp16:
-// 1.12 ms in one chain with 256 x 256 tiles, 1.28 in two steps with 256 x 128).
-template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_>
+// 256 x 256 tiles in one chain were 13 % faster than 256 x 128 in two steps).
+template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_, int IBUF_>
 struct GemmTile {
-    static constexpr int RB = RB_, TB = TB_, WN = WN_, WK = WK_, SP = SP_, NBUF = NBUF_;
+    static constexpr int RB = RB_, TB = TB_, WN = WN_, WK = WK_, SP = SP_, NBUF = NBUF_, IBUF = IBUF_;
     static constexpr int BN = 32 * RB * WN, BM = 32 * TB, NW = WN * WK, T = NW * kWave;
     static constexpr int KB = 16 * SP * WK, RSB = KB * 2, kB = BM * RSB;   // a part: columns, bytes of a row, bytes
     static constexpr int U = 4 / SP;                           // parts of a turn
     static_assert(SP == 2 || SP == 4, "");
     static constexpr int AHEAD = NBUF - 1;
     static constexpr int ND = kB / (NW * 1024);                // loads of a wave per part
+    // LDS: the B tiles, then the index words (IBUF blocks of every wave); the outliers' plane or the waves' sums in the
+    // same place later; then a V2a library and its ids
     static constexpr int kPlane = BN * BM * 4, kSums = (WK - 1) * BN * BM * 4, kTiles = NBUF * kB;
-    static constexpr int kBase = kTiles > kPlane ? (kTiles > kSums ? kTiles : kSums) : (kPlane > kSums ? kPlane : kSums);
+    template <int BITS> static constexpr int kWordBlock = RB * 1024 * BITS;            // bytes of a wave's block of index words
+    template <int BITS> static constexpr int kLoop = kTiles + NW * IBUF * kWordBlock<BITS>;
+    template <int BITS> static constexpr int kBase = kPlane > kSums ? (kLoop<BITS> > kPlane ? kLoop<BITS> : kPlane) : (kLoop<BITS> > kSums ? kLoop<BITS> : kSums);
+    static constexpr int kIds = BN * 64;                       // ids of 64 groups
     static constexpr bool FINE = NW <= 8;                      // takes short rows (half blocks as chains)
-    static constexpr bool DEEP = WK == 2;                      // a third set of sums in LDS for long rows
-    static constexpr int kDeep = DEEP ? RB * TB * 16 * T * 4 : 0;
+    static constexpr bool DEEP = WK > 1 && NW <= 8;            // a third set of sums for long rows
     static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && BN % NW == 0, "");
     // registers: accumulators and sums, operands (B twice), index words, planes; then waves per SIMD
-    static constexpr int kRegs = 32 * RB * TB + 16 * RB + 8 * TB + 36 * RB + 8 * RB + 56;
+    static constexpr int kRegs = (DEEP ? 48 : 32) * RB * TB + 16 * RB + 8 * TB + 4 * RB + 8 * RB + 56;
     static constexpr int kWavesPerSimd = kRegs <= 128 ? 4 : kRegs <= 168 ? 3 : kRegs <= 256 ? 2 : 1;
 };
 
-// Up to kFineK columns half a block is a chain; above kDeepK two waves that share their rows take their sums in three
-// steps (the third: every eighth block, in LDS).  Error against 64 bits, 1e-8 of the result's norm, without / with that,
-// and of passes of 64 tokens: 512 columns 10.8 / 8.6, 8.6; 1536 11.7 / 10.3, 11.4; 3072 12.5 / 12.0, 13.9; 16384 15.2 / 12.9,
-// 15.8; 28672 17.6 / 13.4, 15.3 (matrices of 8192 rows and more, whose passes are not cut into slices: 38).
+// Half a block is a chain where waves share their rows (their sums take few registers) and up to kFineK columns; above kDeepK
+// eight waves or fewer take their sums in three steps (the third: every eighth block).  Error against 64 bits, 1e-8 of the
+// result's norm, this kernel / passes of 64 tokens: 1024 rows, 512 columns 8.5 / 8.6; 1536 9.5 / 11.3; 4096 10.4 / 15.6; 8192
+// 11.6 / 21.1; 28672 12.2 / 14.2; 8320 rows, 8192 columns 14.9 / 21.1.
 constexpr uint32_t kFineK = 2048, kDeepK = 16384;
 
 // 16-byte chunk c of row r of a tile with C chunks per row sits at position c ^ swz<C>(r)
@@ -95,7 +102,7 @@ struct GemmArgs {
     uint32_t row0, tiles_n, tiles_m;                           // first row, tiles of this launch
     int y_f32;
     int fine;              // half blocks are chains of their own
-    uint32_t deep;         // LDS offset of a third set of sums, or 0: none
+    int deep;              // a third set of sums
 };
 
 template <class F, int... Is>
@@ -130,11 +137,11 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
 
     // ---------------------------------------------------------------- A operands: this lane's rows
     // Lane (i, h) dequantises, of row i of every row block, one half (a group of 128 weights) of a block: 64, 48 or 32
-    // bytes, fetched at once.  (A row's lines are then drawn once.  In pieces of 64 columns, a turn each, a 128-byte line
-    // was fetched from L2 four to eight times, the activations having displaced it from L1, and the traffic between L2
-    // and the CUs was what bounded the kernel.)  In turn p it makes the A operands of 32 weights, chunk s of them being
-    // step s's: nothing moves between lanes and there is no A tile.  The copy of the activations has chunk s of turn p
-    // of half h at the block's 16 bytes 8 p + 2 s + h.
+    // bytes.  In turn p it makes the A operands of 32 weights, chunk s of them being step s's: nothing moves between lanes
+    // and there is no A tile.  The copy of the activations has chunk s of turn p of half h at the block's 16 bytes 8 p + 2 s + h.
+    // The index words come by loads straight into LDS, whole lines at a time, a block of 32 rows x 256 columns per wave, IBUF - 1
+    // blocks ahead; only this wave reads them.  (As loads into registers their first use waited for every load under way, those
+    // of the B tiles included, once per block: 28672 x 8192, 64 tokens 70 us as a product.)
     uint32_t row[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) row[rb] = min(n0 + (wn * RB + rb) * 32 + i, N - 1);
@@ -149,11 +156,11 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             P[rb].set(c);
         }
     } else {
-        // the library as planes behind the tiles: entry l at kBase + l * 2^BITS * 2, low bytes first; entry L: zeros
+        // the library as planes: entry l at kBase + l * 2^BITS * 2, low bytes first; entry L: zeros
         for (uint32_t j = tid; j < (a.L + 1) * Planes<BITS>::ND; j += C::T) {
             const uint32_t l = j / Planes<BITS>::ND, d = j % Planes<BITS>::ND;
             const uint2 v = l < a.L ? *reinterpret_cast<const uint2 *>(a.cb + ((size_t)l << BITS) + 4 * d) : make_uint2(0u, 0u);
-            const uint32_t o = lds0 + C::kBase + l * (2u << BITS) + d * 4;
+            const uint32_t o = lds0 + C::template kBase<BITS> + l * (2u << BITS) + d * 4;
             *(lds_u32_t *)(uintptr_t)o = __builtin_amdgcn_perm(v.y, v.x, 0x06040200u);
             *(lds_u32_t *)(uintptr_t)(o + Planes<BITS>::ND * 4) = __builtin_amdgcn_perm(v.y, v.x, 0x07050301u);
         }
@@ -164,33 +171,55 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) sum[rb][tb] = float16_t{};
+    float16_t deep[C::DEEP ? RB : 1][C::DEEP ? TB : 1];
+#pragma unroll
+    for (int rb = 0; rb < (C::DEEP ? RB : 1); ++rb)
+#pragma unroll
+        for (int tb = 0; tb < (C::DEEP ? TB : 1); ++tb) deep[rb][tb] = float16_t{};
 
     // ---------------------------------------------------------------- loads of the main loop
-    // The loads to LDS are written as instructions: as builtins they would make the compiler wait for all of them in front
-    // of every read from LDS.  They have no result registers.  Every block issues the same number of loads in the same
-    // order (past the end: again the last block's), and every wait below states how many may still be under way.
-    // The index words are buffer loads through the builtin, one instruction each, and it is the compiler that waits for
-    // them: in front of their first use, for all loads under way, as it does not count those to LDS.  So a block's last
-    // turn requests nothing before that use; what is then under way is needed two steps later anyway.
-    u32x4_t iw[2][RB][BITS];                                   // this block's words and the next one's
-    uint32_t gid[2][RB];
+    // All of them go to LDS (load_to_lds) and nothing but the waits below waits for them.  Every block issues the same number
+    // of loads in the same order (past the end: again the last block's), and every wait states how many may still be under way.
     const uint32_t rows = min(N - n0, (uint32_t)BN);
-    const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc((void *)(a.idx + (size_t)n0 * wpr), 0, rows * wpr * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc((void *)(MODE == 1 ? a.gid + (size_t)n0 * G : nullptr), 0,
-                                                                        MODE == 1 ? rows * G : 0, 0x00020000);
-    auto load_words = [&](auto buf, uint32_t t) {              // the wave's t-th block
-        constexpr int B = decltype(buf)::value;
-        const uint32_t grp = min(2 * (t * WK + wk) + h, G - 1);
+    const uint64_t base = (uint64_t)(uintptr_t)(a.idx + (size_t)n0 * wpr);
+    const u32x4_t ri = {(uint32_t)base, (uint32_t)(base >> 32) & 0xFFFFu, rows * wpr * 4, 0x00020000u};
+    // A row's 32 BITS bytes of a block are CPR chunks of 16.  With 8 or 4 of them a chunk's place is turned by the row, so that
+    // the 16 lanes that read one chunk of 16 rows find them in different banks.
+    constexpr uint32_t CPR = 2 * BITS;
+    auto turned = [](uint32_t c, uint32_t r) -> uint32_t { return BITS == 4 ? c ^ (r >> 1 & 7u) : BITS == 2 ? c ^ (r >> 2 & 3u) : c; };
+    uint32_t woff[BITS];
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
+    for (int e = 0; e < BITS; ++e) {
+        const uint32_t id = e * 64 + lane, r = id / CPR;
+        woff[e] = (wn * RB * 32 + r) * (wpr * 4) + turned(id % CPR, r) * 16;
+    }
+    const uint32_t ring = lds0 + C::kTiles + wave * (C::IBUF * C::template kWordBlock<BITS>);
+    uint32_t wload = 0;                                        // slot of the block being requested
+    auto load_words = [&](uint32_t t) {                        // the wave's t-th block
+        const uint32_t so = min(t * WK + wk, NB - 1) * (32 * BITS);
 #pragma unroll
-            for (int d = 0; d < BITS; ++d)
-                iw[B][rb][d] = __builtin_amdgcn_raw_buffer_load_b128(ri, (row[rb] - n0) * (wpr * 4) + grp * (16 * BITS) + 16 * d, 0, 0);
-            if constexpr (MODE == 1) gid[B][rb] = __builtin_amdgcn_raw_buffer_load_b8(rg, (row[rb] - n0) * G + grp, 0, 0);
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int e = 0; e < BITS; ++e)
+                load_to_lds(ring + wload * C::template kWordBlock<BITS> + (rb * BITS + e) * 1024, woff[e] + so + rb * 32 * (wpr * 4), ri, 0);
+        wload = wload + 1 == C::IBUF ? 0 : wload + 1;
+    };
+    constexpr int kWords = RB * BITS;                          // loads of a block's words
+    static_assert((C::AHEAD - 1) * C::ND + kWords <= 63, "what vmcnt can say");
+    // V2a: the ids of 64 groups of the tile's rows in LDS
+    const uint32_t ids = lds0 + C::template kBase<BITS> + (MODE == 1 ? ((a.L + 1) * (2u << BITS) + 15) / 16 * 16 : 0u);
+    auto load_ids = [&](uint32_t g0) {
+        const uint8_t *src = a.gid + (size_t)n0 * G;
+        for (uint32_t j = tid; j < rows * 16; j += C::T) {
+            const uint32_t r = j / 16, g = g0 + j % 16 * 4;
+            uint32_t v = 0;
+            if (g + 3 < G) __builtin_memcpy(&v, src + (size_t)r * G + g, 4);
+            else
+#pragma unroll
+                for (uint32_t b = 0; b < 4; ++b) v |= (g + b < G ? (uint32_t)src[(size_t)r * G + g + b] : 0u) << (8 * b);
+            *(lds_u32_t *)(uintptr_t)(ids + j * 4) = v;
         }
     };
-    constexpr int kWords = RB * (BITS + MODE);                 // loads of a block's words
-    static_assert((C::AHEAD - 1) * C::ND + kWords <= 63, "what vmcnt can say");
     const u32x4_t rx = {(uint32_t)(uintptr_t)ga.xp, (uint32_t)((uintptr_t)ga.xp >> 32) & 0xFFFFu, M * (NB * 512), 0x00020000u};
     uint32_t boff[C::ND];
 #pragma unroll
@@ -210,20 +239,14 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
         if (e1 == C::ND) bload = bload + 1 == C::NBUF ? 0 : bload + 1;
     };
     words_t<BITS> cw[RB];                                      // the words of the turn whose A operands are being made
-    auto arrived = [&](auto buf, uint32_t t) {                 // the first use of a buffer's words
-        constexpr int B = decltype(buf)::value;
+    uint32_t wcur = 0;                                         // slot of the block they are of
+    auto planes = [&](uint32_t t) {                            // the lane's codebooks for the wave's t-th block
         const bool dead = 2 * (t * WK + wk) + h >= G;          // second half of the last block of a row with an odd number of groups
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-            for (int d = 0; d < BITS; ++d) {
-                u32x4_t &w = iw[B][rb][d];
-                asm volatile("" : "+v"(w));
-            }
             if constexpr (MODE == 1) {
-                uint32_t &id = gid[B][rb];
-                asm volatile("" : "+v"(id));
-                const uint32_t o = lds0 + C::kBase + (dead ? a.L : id) * (2u << BITS);
+                const uint32_t id = *(lds_cu8_t *)(uintptr_t)(ids + (row[rb] - n0) * 64 + ((2 * (t * WK + wk) + h) & 63u));
+                const uint32_t o = lds0 + C::template kBase<BITS> + (dead ? a.L : id) * (2u << BITS);
 #pragma unroll
                 for (int d = 0; d < Planes<BITS>::ND; ++d) {
                     P[rb].lo[d] = *(lds_cu32_t *)(uintptr_t)(o + d * 4);
@@ -235,12 +258,16 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             }
         }
     };
-    auto take = [&](auto buf, int p) {                         // turn p's words
-        constexpr int B = decltype(buf)::value;
+    auto take = [&](int p) {                                   // turn p's words
+        const uint32_t o = ring + wcur * C::template kWordBlock<BITS> + i * (32 * BITS);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
+            const uint32_t w = o + rb * (1024 * BITS);
+            if constexpr (BITS == 4) cw[rb] = *(lds_cu4_t *)(uintptr_t)(w + turned(4 * h + p, i) * 16);
+            else if constexpr (BITS == 3) {
 #pragma unroll
-            for (int d = 0; d < BITS; ++d) cw[rb][d] = iw[B][rb][(p * BITS + d) / 4][(p * BITS + d) % 4];
+                for (int d = 0; d < 3; ++d) cw[rb][d] = *(lds_cu32_t *)(uintptr_t)(w + h * 48 + p * 12 + d * 4);
+            } else cw[rb] = *(lds_cu2_t *)(uintptr_t)(w + turned(2 * h + p / 2, i) * 16 + p % 2 * 8);
             arrange<BITS>(cw[rb]);
         }
     };
@@ -257,15 +284,15 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) bf[set][tb] = *(lds_ch8_t *)(uintptr_t)(ba + tb * (32 * C::RSB));
     };
-    using Even = std::integral_constant<int, 0>;
-    using Odd = std::integral_constant<int, 1>;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    load_words(Even{}, 0);
+    if constexpr (MODE == 1) load_ids(0);
+#pragma unroll
+    for (int b = 0; b < C::IBUF - 1; ++b) load_words(b);
 #pragma unroll
     for (int q = 0; q < C::AHEAD; ++q) load_b(q, 0, C::ND);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    arrived(Even{}, 0);
-    take(Even{}, 0);
+    planes(0);
+    take(0);
 #pragma unroll
     for (int s = 0; s < 3; ++s) dequantise(s);
     operands(0, 0, 0);
@@ -282,21 +309,16 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
 #pragma unroll
             for (int tb = 0; tb < TB; ++tb) sum[rb][tb] += acc[rb][tb];
     };
-    auto keep = [&](bool first, bool more) {                   // the sums so far into the third set; at the end back
-        const uint32_t at = lds0 + ga.deep + tid * 16;
+    auto fold = [&] {                                          // the sums so far into the third set
 #pragma unroll
-        for (int b = 0; b < RB * TB * 4; ++b) {
-            float16_t &v = sum[b / 4 % RB][b / 4 / RB];
-            float4_t x = {v[b % 4 * 4], v[b % 4 * 4 + 1], v[b % 4 * 4 + 2], v[b % 4 * 4 + 3]};
-            if (!first) x += *(lds_f4_t *)(uintptr_t)(at + b * (C::T * 16));
-            if (more) *(lds_f4_t *)(uintptr_t)(at + b * (C::T * 16)) = x;
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[b % 4 * 4 + r] = more ? 0.f : x[r];
-        }
+            for (int tb = 0; tb < TB; ++tb) {
+                deep[rb][tb] += sum[rb][tb];
+                sum[rb][tb] = float16_t{};
+            }
     };
-    auto block = [&](auto buf, uint32_t t) {
-        constexpr int B = decltype(buf)::value;
-        using Next = std::integral_constant<int, B ^ 1>;
+    auto block = [&](uint32_t t) {
         const bool on = WK == 1 || t * WK + wk < NB;           // (the last round of a row may have no block for this wave)
         for_each<16>([&](auto step) {
             constexpr int p = decltype(step)::value / 4, s = decltype(step)::value % 4;        // turn, step in it
@@ -312,20 +334,23 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
 #pragma unroll
                         for (int tb = 0; tb < TB; ++tb) acc[rb][tb] = float16_t{};
                 }
-            // (a block's last turn: nothing in the steps up to the first use of the next block's words)
-            constexpr auto e = [](int q) { return p < 3 || C::SP != 4 ? q * C::ND / C::SP : q <= 2 ? 0 : (q - 2) * C::ND / 2; };
-            load_b(t * (4 * C::U) + x + C::AHEAD, e(s % C::SP), e(s % C::SP + 1));
+            load_b(t * (4 * C::U) + x + C::AHEAD, s % C::SP * C::ND / C::SP, (s % C::SP + 1) * C::ND / C::SP);
             if constexpr (!last) operands(set ^ 1, bcur, s + 1);
             if constexpr (s == 0) dequantise(3);
             if constexpr (s == 1) {
-                if constexpr (p == 0) load_words(Next{}, t + 1);
-                if constexpr (p == 3) {                        // the next block's words, requested three turns ago
-                    arrived(Next{}, t + 1);
-                    take(Next{}, 0);
+                if constexpr (p == 0) load_words(t + C::IBUF - 1);
+                if constexpr (p == 3) {                        // the next block's words, older than the part that the last wait was for
+                    wcur = wcur + 1 == C::IBUF ? 0 : wcur + 1;
+                    planes(t + 1);
+                    take(0);
                 } else {
-                    take(buf, p + 1);
+                    take(p + 1);
                 }
             }
+            // the ids of the next 64 groups, behind the barrier that every wave passes after its last use of the old ones; two
+            // more barriers follow before their first use
+            if constexpr (MODE == 1 && p == 1 && s == 0)
+                if ((t + 1) * (2 * WK) % 64 == 0 && t + 1 < NS) load_ids((t + 1) * (2 * WK));
             if constexpr (last) {
                 // The next part, requested AHEAD parts ago.  Younger: the parts requested since, and a block's words if
                 // they have been since its last load (they come in the second step of a block).
@@ -346,18 +371,20 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             if constexpr (last) bcur = bnext;
         });
         if (on) add();
-        // the third set: this thread's own places in LDS, 16 bytes per lane and read or write
-        if constexpr (B == 1 && C::DEEP)
-            if (ga.deep && t % 8 == 7) keep(t == 7, true);
+        if constexpr (C::DEEP)
+            if (ga.deep && t % 8 == 7) fold();
     };
 #pragma unroll 1
-    for (uint32_t t = 0; t < NS; t += 2) {
-        block(Even{}, t);
-        if (t + 1 < NS) block(Odd{}, t + 1);
-    }
+    for (uint32_t t = 0; t < NS; ++t) block(t);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // (loads to LDS that nobody waits for)
     if constexpr (C::DEEP)
-        if (ga.deep && NS >= 8) keep(false, false);
+        if (ga.deep) {
+            fold();
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) sum[rb][tb] = deep[rb][tb];
+        }
 
     if constexpr (WK > 1) {
         // the other waves' sums of a block, added in their order; they may overwrite the tiles, which every wave has read
@@ -388,117 +415,82 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     // ---------------------------------------------------------------- the outlier term
     // Behind the product and not in front of it: the sums would otherwise be added to a term that is often larger than all
     // of theirs, and be rounded at its size (28672 columns, 0.3 % outliers: 2.0e-7 of the result instead of 1.0e-7).
-    // Wave w owns rows RW w .. of the plane, whose entries are one run of the CSR arrays, and walks it in units of up
-    // to U EP entries of one row: lane (ep, o) takes entries ep, ep + EP, .. of a unit and the tokens m0 + 8 o .. + 7.
-    // An entry's activations are 2 BM bytes from L2, and it takes about 64 KB in flight per CU to draw them at full rate.
+    // Wave w owns rows RW w .. of the plane and takes RP of them at a time, GL = BM / 8 lanes each: lane o of a row sums the
+    // tokens m0 + 8 o .. + 7 over the row's entries, whose activations are one contiguous read of 2 BM bytes.  Nothing is
+    // added across lanes.  (With the lanes of a row's token dealt over its entries, every row paid a reduction and the walk
+    // from row to row: 28672 x 8192, 2048 tokens 309 us of 1366 at 0.3 % outliers, 165 at 0.05 %; 4096 x 1024, 256 tokens 6.)
+    // A row's entries are fetched GL at a time, one per lane, and handed to its lanes one by one (row_newbcast); a sum is
+    // taken per GL entries and those are added up.
     const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
     const int32_t ob = rp[min(n0, N)], oe = rp[min(n0 + BN, N)];
     if (a.col && ob < oe) {
         lds_barrier();                                         // every wave is past its tiles (and sums)
         const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + ob), 0, (oe - ob) * 4, 0x00020000);
         const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + ob), 0, (oe - ob) * 2, 0x00020000);
-        constexpr int OP = BM / 8, EP = 64 / OP, U = EP >= 8 ? 2 : 4, D = 4, UE = U * EP, RW = BN / NW;
-        static_assert(OP >= 4 && OP <= 32 && UE <= 64 && RW < 64, "");
-        const uint32_t ep = lane / OP, o = lane % OP;
-        const uint4 *xt = reinterpret_cast<const uint4 *>(ga.xt) + min((m0 >> 3) + o, ga.MP / 8 - 1);
-        const uint32_t xs = ga.MP / 8, plane = lds0 + wave * (RW * BM * 4);
-        struct Unit { uint32_t row; int32_t e, hi; bool last; };                            // wave-uniform
-        struct Gathered { uint4 x[U]; uint32_t v[U]; };
-        const int32_t rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];     // lane r: first entry of row r
-        auto row_at = [&](uint32_t r) { return __builtin_amdgcn_readlane(rpv, (int)r); };
-        auto unit_at = [&](uint32_t r, int32_t e) {
-            Unit u;
-            u.row = r; u.e = e;
-            u.hi = r < (uint32_t)RW ? row_at(r + 1) : e;
-            u.last = e + UE >= u.hi;
-            return u;
+        constexpr int GL = BM / 8, RP = 64 / GL, RW = BN / NW;
+        static_assert((GL == 8 || GL == 16) && RW % RP == 0 && RW < 64, "");
+        const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc((void *)ga.xt, 0, K * ga.MP * 2, 0x00020000);
+        const uint32_t o = lane % GL, rr = lane / GL, octet = min(m0 + 8 * o, ga.MP - 8) * 2, plane = lds0 + wave * (RW * BM * 4) + rr * (BM * 4) + o * 32;
+        const int32_t rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];         // lane r: first entry of row r
+        auto first_of = [&](uint32_t r) { return __builtin_amdgcn_ds_bpermute((int)(min(r, (uint32_t)RW) * 4), rpv); };
+        // lane k of every row's lanes to all of them
+        auto deal = [&](auto k, uint32_t v) -> uint32_t {
+            constexpr int kk = decltype(k)::value;
+            if constexpr (GL == 16) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + kk, 0xf, 0xf, true);
+            else
+                return (uint32_t)__builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + kk, 0xf, 0x3, false),
+                                                             (int)v, 0x158 + kk, 0xf, 0xc, false);
         };
-        auto after = [&](const Unit &u) {
-            const uint32_t r = u.last ? u.row + 1 : u.row;
-            return unit_at(r, r >= (uint32_t)RW ? u.hi : u.last ? row_at(r) : u.e + UE);
-        };
-        // No load here hangs on a condition: the compiler counts loads under way only along straight code, and a
-        // branch around one makes it wait for all of them at the next use.
-        auto fetch = [&](const Unit &u) {                  // lane j: entry j of the unit, column | value << 16
-            const uint32_t e = (uint32_t)(u.e - ob) + lane;
-            const uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rc, e * 4, 0, 0), v = __builtin_amdgcn_raw_buffer_load_b16(rv, e * 2, 0, 0);
-            return c | (v << 16);                          // (past the tile's entries: zeros; past the row's: another row's)
-        };
-        auto gather = [&](uint32_t ents, Gathered &g) {
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const uint32_t ent = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((j * EP + ep) * 4), (int)ents);
-                g.v[j] = ent >> 16;
-                g.x[j] = xt[(size_t)(ent & 0xFFFFu) * xs];
+        uint32_t r0 = 0;
+        int32_t e = first_of(rr), e1 = first_of(rr + 1);
+        // (past the tile's entries: zeros)
+        uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(e + (int32_t)o - ob) * 4, 0, 0),
+                 v = __builtin_amdgcn_raw_buffer_load_b16(rv, (uint32_t)(e + (int32_t)o - ob) * 2, 0, 0);
+        float total[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (;;) {
+            // an entry that is not there: a place past the copy, which reads as zeros, times zero
+            const bool have = e + (int32_t)o < e1;
+            const uint32_t off = have ? __umul24(c, ga.MP * 2) : 0x80000000u, val = __builtin_bit_cast(uint32_t, half_bits_to_float((uint16_t)(have ? v : 0u)));
+            const int32_t at = e, to = e1;
+            const bool more = __builtin_amdgcn_ballot_w64(e + GL < e1) != 0;
+            const uint32_t row = r0;
+            if (more) e += GL;
+            else {
+                r0 += RP;
+                e = first_of(r0 + rr);
+                e1 = first_of(r0 + rr + 1);
             }
-        };
-        float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        auto consume = [&](const Unit &u, const Gathered &g) {
+            c = __builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(e + (int32_t)o - ob) * 4, 0, 0);
+            v = __builtin_amdgcn_raw_buffer_load_b16(rv, (uint32_t)(e + (int32_t)o - ob) * 2, 0, 0);
+            u32x4_t x[GL];
+            for_each<GL / 4>([&](auto q) {
+                constexpr int k0 = 4 * decltype(q)::value;
+                if (__builtin_amdgcn_ballot_w64(at + k0 < to))
+                    for_each<4>([&](auto k) {
+                        constexpr int kk = k0 + decltype(k)::value;
+                        x[kk] = __builtin_amdgcn_raw_buffer_load_b128(rt, deal(std::integral_constant<int, kk>{}, off) + octet, 0, 0);
+                    });
+            });
+            float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            for_each<GL / 4>([&](auto q) {
+                constexpr int k0 = 4 * decltype(q)::value;
+                if (__builtin_amdgcn_ballot_w64(at + k0 < to))
+                    for_each<4>([&](auto k) {
+                        constexpr int kk = k0 + decltype(k)::value;
+                        const float w = __builtin_bit_cast(float, deal(std::integral_constant<int, kk>{}, val));
 #pragma unroll
-            for (int j = 0; j < U; ++j) {
-                if (j && u.e + j * EP >= u.hi) break;      // wave-uniform
-                const uint32_t have = u.e + j * EP + (int32_t)ep < u.hi ? ~0u : 0u;     // no entry: zero times zeros
-                const float v = half_bits_to_float((uint16_t)(g.v[j] & have));
-                const uint32_t w[4] = {g.x[j].x & have, g.x[j].y & have, g.x[j].z & have, g.x[j].w & have};
+                        for (int t = 0; t < 8; ++t)
+                            s[t] = fmaf(w, half_bits_to_float((uint16_t)(t & 1 ? x[kk][t / 2] >> 16 : x[kk][t / 2])), s[t]);
+                    });
+            });
 #pragma unroll
-                for (int t = 0; t < 8; ++t) s[t] = fmaf(v, half_bits_to_float((uint16_t)(t & 1 ? w[t / 2] >> 16 : w[t / 2])), s[t]);
-            }
-            if (!u.last) return;
-            // the EP entry lanes of a token octet are added in a fixed tree
+            for (int t = 0; t < 8; ++t) total[t] += s[t];
+            if (more) continue;
+            *(lds_f4_t *)(uintptr_t)(plane + row * (BM * 4)) = float4_t{total[0], total[1], total[2], total[3]};
+            *(lds_f4_t *)(uintptr_t)(plane + row * (BM * 4) + 16) = float4_t{total[4], total[5], total[6], total[7]};
+            if (r0 >= (uint32_t)RW) break;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                if constexpr (EP >= 16) s[t] = dpp_add<0x124>(s[t]);           // row_ror:4 (octets in lane % 4)
-                if constexpr (EP >= 8) s[t] = dpp_add<0x128>(s[t]);            // row_ror:8
-                uint32_t x = __builtin_bit_cast(uint32_t, s[t]);
-                if constexpr (EP >= 4) {
-                    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-                    s[t] = __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
-                    x = __builtin_bit_cast(uint32_t, s[t]);
-                }
-                const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-                s[t] = __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
-            }
-            if (ep == 0) {
-                const uint32_t d = plane + u.row * (BM * 4) + o * 32;
-                *(lds_f4_t *)(uintptr_t)d = float4_t{s[0], s[1], s[2], s[3]};
-                *(lds_f4_t *)(uintptr_t)(d + 16) = float4_t{s[4], s[5], s[6], s[7]};
-            }
-#pragma unroll
-            for (int t = 0; t < 8; ++t) s[t] = 0.f;
-        };
-        // D units' activations and, D units further on, D units' entries are under way: a unit's entries were requested
-        // before the activations that have not been used yet, so waiting for them is not waiting for those
-        Unit gu[D], eu[D];
-        uint32_t ents[D];
-        Gathered g[D];
-        Unit next = unit_at(0, row_at(0));
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            gu[d] = next;
-            ents[d] = fetch(next);
-            next = after(next);
-        }
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            gather(ents[d], g[d]);
-            eu[d] = next;
-            ents[d] = fetch(next);
-            next = after(next);
-        }
-        for (bool more = true; more;) {
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                if (gu[d].row >= (uint32_t)RW) {
-                    more = false;
-                    break;
-                }
-                consume(gu[d], g[d]);
-                gu[d] = eu[d];
-                gather(ents[d], g[d]);
-                eu[d] = next;
-                ents[d] = fetch(next);
-                next = after(next);
-            }
+            for (int t = 0; t < 8; ++t) total[t] = 0.f;
         }
         lds_barrier();
         if (wk == 0)
@@ -608,19 +600,15 @@ template <int BITS, int MODE, class C>
 hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
 {
     auto kern = decode_gemm_kernel<BITS, MODE, C>;
-    int lds = C::kBase + (MODE == 1 ? (int)((ga.a.L + 1) * (2u << BITS)) : 0);
-    ga.fine = ga.a.K <= kFineK;
-    ga.deep = 0;
-    if (C::DEEP && ga.a.K > kDeepK) {
-        ga.deep = (uint32_t)(lds + 15) / 16 * 16;
-        lds = (int)ga.deep + C::kDeep;
-    }
+    const int lds = C::template kBase<BITS> + (MODE == 1 ? ((int)((ga.a.L + 1) * (2u << BITS)) + 15) / 16 * 16 + C::kIds : 0);
+    static_assert(C::template kBase<BITS> + (MODE == 1 ? (257 * (2 << BITS) + 15) / 16 * 16 + C::kIds : 0) <= 160 * 1024, "");
+    ga.fine = ga.a.K <= kFineK || C::WK > 1;
+    ga.deep = C::DEEP && ga.a.K > kDeepK;
     static std::atomic<int> configured[kMaxDevices];           // per device; idempotent attribute, benign race
     const int dev = current_device();
     if (dev < 0) return hipErrorInvalidDevice;
     if (!configured[dev].load(std::memory_order_relaxed)) {
-        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             C::kBase + (MODE == 1 ? 257 * (2 << BITS) : 0) + C::kDeep);
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (err != hipSuccess) return err;
         configured[dev].store(1, std::memory_order_relaxed);
     }
@@ -641,10 +629,10 @@ hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
     //   2048: 212 / 181 (1024) / 119 (256)
     //   8192 x 8192, 256 tokens: 95 (512) / 84 (256) / 155 (64); 512: 177 / 151 (512) / 157 (128); 700: 256 / 216 (704) / 169 (192)
     //   2048 x 28672, 512 tokens: 143 (256) / 237 (128) / 463 (32); 28672 x 8192, 512 tokens: 610 / 511 (1792) / 346 (448)
-    using Large = GemmTile<1, 4, 8, 1, 4, 3>;
-    using Small = GemmTile<1, 2, 4, 2, 4, 3>;
-    using Small16 = GemmTile<1, 2, 4, 4, 4, 3>;
-    using Tiny = GemmTile<1, 2, 2, 4, 4, 3>;
+    using Large = GemmTile<1, 4, 8, 1, 4, 3, 2>;
+    using Small = GemmTile<1, 2, 4, 2, 4, 3, BITS == 4 ? 2 : 3>;
+    using Small16 = GemmTile<1, 2, 4, 4, 2, 3, 2>;
+    using Tiny = GemmTile<1, 2, 2, 4, 2, 4, 2>;
     const uint64_t m = (ga.M + 63) / 64, small = (uint64_t)((ga.a.N + 127) / 128) * m;
     if ((uint64_t)((ga.a.N + 63) / 64) * m <= 256) return launch_gemm_t<BITS, MODE, Tiny>(ga, s);
     // (rows that ask for a third set of sums, in matrices that the 16-token kernel would cut into slices: see kDeepK)
