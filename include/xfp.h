@@ -32,8 +32,8 @@
  *    calls is a static ring of eight workspaces of 10 MB in device memory
  *    (every GPU the process uses holds its own copy; a call uses the one of the
  *    current device, which must be the device of its pointers and stream), and,
- *    from the process's first prompt on that GPU (XFP_ROUTE_GEMM), 64 MB more
- *    for each of them.  The runtime makes them there when they are first needed,
+ *    from the process's first prompt on that GPU (a call of more than 64 tokens
+ *    that runs as a tiled product), 64 MB more for each of them.  The runtime makes them there when they are first needed,
  *    and they stay until the process ends.
  *    A call that needs scratch memory (the batched path's re-laid activations,
  *    split-K partial sums, the unfused forms of the epilogues) takes ONE slot
@@ -359,7 +359,8 @@ int xfp_select_kernel(int which);
  * (XFP_ERR_UNSUPPORTED for a row no kernel takes).  xfp_select_kernel changes what it reports, as it changes
  * what runs.  The families are those of the format's and the sizes' limits: where a launch of STREAM, SPLIT_K,
  * BATCH, WIDE or GENERAL with up to 64 tokens is faster in the kernel that keeps the activations in LDS, that
- * kernel runs in its place, for these tokens or more of the call's.
+ * kernel runs in its place, and where one of BATCH or WIDE with more than 64 tokens left is faster as a tiled
+ * product, that does, for these tokens or more of the call's.
  */
 typedef enum {
     XFP_ROUTE_GENERAL = 0,   /* one wave per row, x and tables in LDS: widths 5 and 6, scale + mid-point, odd shapes */

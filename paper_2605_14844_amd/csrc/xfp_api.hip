@@ -289,6 +289,25 @@ int resident_tokens(const xfp_weights *W, bool expert_indexed, int left, const P
     return xfp::few_tokens((int)W->bits, (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : (int)W->mode, W->L, W->N, W->K, left, xfp::kPlaneFloats);
 }
 
+// The tokens that the tiled product takes in place of planned passes of 64 or 16 (0: none).  The plan keeps the product for
+// more than 192 tokens and single rounds of its tiles; in launches that cost what they do now it is the faster one from 80
+// tokens on, us in passes / as a product (graph replay, cold weights): 4096 x 4096 80 tokens 25 / 22, 96 31 / 25, 192 50 / 25;
+// 512 x 1024 96 20 / 14; 28672 x 8192 96 124 / 103, 192 192 / 137, 320 325 / 277; 28672 x 1024 224 94 / 37; from 65 on for rows
+// beyond 8192 columns, whose passes are of 16 to 48 tokens: 4096 x 14336 101 / 71, 8192 x 28672 158 / 95 (65 tokens of
+// 8192 x 8192 34 / 36, 80 51 / 43).  Two exceptions: few long rows, where the resident kernel takes the passes (512 x 8192,
+// 96 tokens 31 / 32, 128 43 / 34), and what is at most two passes more than one round of 128 x 64 tiles (8192 x 8192, 320 tokens:
+// a pass and a round 86, two rounds 105).
+int product_tokens(const xfp_weights *W, bool expert_indexed, int left, const Plan &p)
+{
+    if (expert_indexed || left <= 64 || (p.route != XFP_ROUTE_WIDE && p.route != XFP_ROUTE_BATCH) || general_only(W)) return 0;
+    const uint32_t N = W->N, K = W->K;
+    if (!xfp::gemm_supports((int)W->bits, (int)W->mode, W->L, N, K, left)) return 0;
+    if (left < (K > 8192 && N >= 2048 ? 65 : K >= 8192 && N < 1024 ? 128 : 80)) return 0;
+    const uint32_t tiles = (N + 127) / 128, chunks = ((uint32_t)left + 63) / 64, round = tiles <= 256 ? 256 / tiles : 0;
+    if (left > 192 && round >= 3 && chunks > round && chunks <= round + 2) return 0;
+    return xfp::gemm_tokens(K, left);
+}
+
 // y_dtype: an xfp_dtype, optionally OR-ed with XFP_X_BF16
 int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, int64_t x_stride,
            void *y, int y_dtype, int64_t ldy, Scratch &sc, hipStream_t s)
@@ -308,8 +327,9 @@ int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, 
     const size_t ysz = y_f32 ? 4 : 2;
     // the launches of a call run in stream order, so they share the call's workspace
     for (int m0 = 0; m0 < slots;) {
-        const Plan p = plan(W, eids != nullptr, slots - m0);
+        Plan p = plan(W, eids != nullptr, slots - m0);
         if (p.route < 0) return p.route;
+        if (const int take = product_tokens(W, eids != nullptr, slots - m0, p)) p = Plan{XFP_ROUTE_GEMM, take, 0};
         xfp::DecodeArgs c = a;
         c.x = a.x + (int64_t)m0 * x_stride;
         c.y = static_cast<char *>(y) + (size_t)m0 * (size_t)ldy * ysz;
