@@ -68,22 +68,19 @@ __device__ __forceinline__ float half_bits_to_float(uint16_t h)
 // activation that large would otherwise become an infinity and poison every
 // output); NaN stays NaN.  Every kernel converts with these two functions, so a
 // call with bf16 x gives bit for bit what the same call gives on the converted x.
-// minimum / maximum that keep a NaN (v_minimum3_f32, v_maximum3_f32) and one v_cvt_pk_f16_f32 per pair: 7 operations;
-// with comparisons and a conversion each it was 15, in every wave of the streaming kernel for every pair it holds: more
-// than its rows' lookups took (6144x5120 with a record per group: 10.9 us a layer, 9.7 now).
-__device__ __forceinline__ float saturate_f16(float f)
-{
-    return __builtin_elementwise_minimum(__builtin_elementwise_maximum(f, -65504.f), 65504.f);
-}
-__device__ __forceinline__ _Float16 bf16_bits_to_half(uint32_t b)      // b: bf16 pattern in the low 16 bits
-{
-    return (_Float16)saturate_f16(__builtin_bit_cast(float, b << 16));
-}
+// Converted first, an overflow being an infinity, and then limited, both with the instructions that keep a NaN
+// (v_pk_minimum3_f16, v_pk_maximum3_f16): 5 operations per pair.  Limited in fp32 first it was 7, of which the four limits and
+// the conversion take twice the clocks of the others, in every wave of the streaming kernel for every pair it holds.
 __device__ __forceinline__ uint32_t bf16x2_to_f16x2(uint32_t w)
 {
     typedef float float2_t __attribute__((ext_vector_type(2)));
-    const float2_t v = {saturate_f16(__builtin_bit_cast(float, w << 16)), saturate_f16(__builtin_bit_cast(float, w & 0xFFFF0000u))};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, half2_t));
+    const float2_t v = {__builtin_bit_cast(float, w << 16), __builtin_bit_cast(float, w & 0xFFFF0000u)};
+    const half2_t most = {(_Float16)65504.f, (_Float16)65504.f};
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_minimum(__builtin_elementwise_maximum(__builtin_convertvector(v, half2_t), -most), most));
+}
+__device__ __forceinline__ _Float16 bf16_bits_to_half(uint32_t b)      // b: bf16 pattern in the low 16 bits
+{
+    return __builtin_bit_cast(half2_t, bf16x2_to_f16x2(b & 0xFFFFu)).x;
 }
 // one activation as fp32, from its fp16 or bf16 pattern.  Both readings are
 // computed and one is picked bit-wise: as a branch, this handful of instructions
