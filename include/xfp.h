@@ -118,7 +118,7 @@ typedef enum { XFP_F16 = 0, XFP_F32 = 1, XFP_BF16 = 2 } xfp_dtype;   /* type of 
 typedef struct xfp_weights {
     uint32_t struct_size;       /* sizeof(xfp_weights), checked                              */
     uint32_t mode;              /* xfp_mode                                                  */
-    uint32_t bits;              /* 2 .. 6 (paper section 3.1); 5 and 6 run the general kernel only */
+    uint32_t bits;              /* 2 .. 6 (paper section 3.1); 5 and 6 run the general kernel, several tokens of large V2 matrices the resident one */
     uint32_t group;             /* must be 128                                               */
     uint32_t N, K;              /* output channels, input channels; K % 128 == 0             */
     uint32_t L;                 /* V2a: library size, 1..256 (paper default 32); V2: 0       */

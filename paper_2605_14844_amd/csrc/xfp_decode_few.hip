@@ -4,10 +4,11 @@
 
 namespace xfp {
 
-// defined in xfp_decode_few2.hip, xfp_decode_few3.hip, xfp_decode_few4.hip
+// defined in xfp_decode_few2.hip, xfp_decode_few3.hip, xfp_decode_few4.hip, xfp_decode_few56.hip
 hipError_t launch_few2(int mode, const FewArgs &fa, dim3 grid, int lds, hipStream_t s);
 hipError_t launch_few3(int mode, const FewArgs &fa, dim3 grid, int lds, hipStream_t s);
 hipError_t launch_few4(int mode, const FewArgs &fa, dim3 grid, int lds, hipStream_t s);
+hipError_t launch_few56(int bits, const FewArgs &fa, dim3 grid, int lds, hipStream_t s);
 
 namespace {
 
@@ -25,8 +26,8 @@ struct FewPlan {
 
 bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M, FewPlan &p)
 {
-    const uint32_t G = K / kGroup, GU = bits == 2 ? 2 : 1, blocks = (N + 15) / 16, most = M <= 32 ? 16 : 8;
-    const uint32_t x_most = kLds - most * 1024 - (mode ? L * (2u << bits) : 0u);
+    const uint32_t G = K / kGroup, GU = bits == 2 ? 2 : 1, blocks = (N + 15) / 16, most = M <= 32 && bits <= 4 ? 16 : 8;
+    const uint32_t x_most = kLds - most * 1024 - (mode ? L * (2u << bits) : 0u) - (bits > 4 ? 128u << bits : 0u);
     for (uint32_t S = (uint32_t)(((uint64_t)M * G * 256 + x_most - 1) / x_most); S <= G; ++S) {
         uint32_t GS = (G + S - 1) / S;
         if (bits == 2) GS = (GS + 1) & ~1u;
@@ -58,13 +59,25 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 //  - a scale and a mid-point per group, which run token by token or 16 at a time elsewhere: 8 tokens 16384 x 3072 17.8 / 12.7,
 //    24 4096 x 4096 30 / 14, 64 2000 x 2048 36 / 16, 64 12000 x 5504 94 / 82 (16 at a time), but 2 to 4 tokens of
 //    1200 x 4096 6.6 / 7.3 and 40 of 8192 x 8192 66 / 88;
+//  - 5 and 6 bits, which run token by token elsewhere: 8192 x 4096 2 tokens 17.6 / 12.8, 16 92 / 18; 12933 x 1152 2 14.8 / 13.0;
+//    1838 x 10240 3 14.8 / 13.1; 617 x 14208 9 26 / 13, but 2 12.6 / 16.2; 500 x 8192 9 11.8 / 12.3; 300 x 1024
+//    16 4.7 / 6.2.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
 //  - one token: library rows that neither fit the registers of the streaming kernel nor leave it time for slices:
 //    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 300 x 20480 6.7 / 12.
 int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane)
 {
-    if (bits < 2 || bits > 4 || K > 65536 || left < 1) return 0;             // (an outlier's column is kept in 16 bits)
+    if (bits < 2 || (bits > 4 && mode != 0) || K > 65536 || left < 1) return 0;   // (an outlier's column is kept in 16 bits)
     FewPlan p;
     auto fits = [&](uint32_t m) { return few_plan(bits, mode, L, N, K, m, p) && (p.slices == 1 || (uint64_t)p.slices * m * N <= plane); };
+    if (bits > 4) {
+        const uint32_t all = left < 64 ? (uint32_t)left : 64u;
+        for (uint32_t c = 1; c < all; ++c) {
+            const uint32_t m = (all + c - 1) / c;
+            if (N < 4096 && (uint64_t)m * N * K < 40u << 20) return 0;
+            if (fits(m) && p.slices == 1) return (int)m;
+        }
+        return 0;
+    }
     if (left == 1) return mode != 0 && K > 16384 && N >= 4096 && fits(1) ? 1 : 0;
     const bool split = K > 8192 && N <= 8160;                  // three launches in the 16-token kernel
     const uint32_t m = left < 64 ? (uint32_t)left : 64u;
@@ -92,7 +105,8 @@ hipError_t launch_decode_few(int bits, int mode, const DecodeArgs &a, int M, boo
     p.fa.y_f32 = (int)y_f32;
     p.fa.part = p.slices > 1 ? part : nullptr;
     const dim3 grid((a.N + p.fa.RB * 16 - 1) / (p.fa.RB * 16), p.slices);
-    hipError_t err = bits == 4   ? launch_few4(mode, p.fa, grid, (int)p.lds, s)
+    hipError_t err = bits > 4    ? launch_few56(bits, p.fa, grid, (int)p.lds, s)
+                     : bits == 4 ? launch_few4(mode, p.fa, grid, (int)p.lds, s)
                      : bits == 3 ? launch_few3(mode, p.fa, grid, (int)p.lds, s)
                                  : launch_few2(mode, p.fa, grid, (int)p.lds, s);
     if (err != hipSuccess || p.slices == 1) return err;

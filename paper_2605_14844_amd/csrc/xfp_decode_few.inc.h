@@ -1,5 +1,5 @@
-// Up to 64 tokens against one matrix (V2 codebooks, a V2a library, a library with a scale and a mid-point per group; 2 to 4
-// bits) in ONE launch, on the matrix cores, with the activations resident in LDS.
+// Up to 64 tokens against one matrix (V2 codebooks at 2 to 6 bits, a V2a library, a library with a scale and a mid-point per
+// group at 2 to 4) in ONE launch, on the matrix cores, with the activations resident in LDS.
 //
 // Why: the other kernels for several tokens re-lay the activations in a launch of their own and build pair tables per 16 or 32
 // rows before the first product; with few tokens, or few rows, those two are most of a call (7001 x 5504, 2 bits, 5 tokens:
@@ -13,16 +13,20 @@
 //  - Index words come by loads straight into LDS (load_to_lds), a ring of four units per wave, and are read back in the
 //    operand's layout: no table, no transposition, and no barrier in the main loop.
 //  - A lane dequantises 32 weights of its row in registers (xfp_dequant.h: 5, 5 and 10 VALU clocks per weight and SIMD at 2,
-//    3 and 4 bits; a v_perm_b32 takes 4, a two-operand instruction 2).
+//    3 and 4 bits; a v_perm_b32 takes 4, a two-operand instruction 2).  At 5 and 6 bits 32 and 64 entries are too many for
+//    that: one LDS lookup per weight, from a table in the lane's own bank, and 1.5 instructions to pair them up.
 //  - Outliers: four rows of a wave at a time, an entry per lane, 16 tokens per entry from LDS.
 //
 // What bounds it: small matrices the launch (1.5 us), one round trip to memory and the instructions around the main loop
 // (3000 x 2048, 3 bits, 8 tokens: 5.9 us, of which the main loop takes 0.8); large ones the VALU (28672 x 8192, 4 bits, one
 // token: 36 us, HBM 22).  7001 x 5504 as above 9.9 us; 16384 x 3072, a scale and a mid-point per group, 24 tokens 36 -> 20.
+// 5 and 6 bits the lookups (8192 x 4096, 5 bits, 16 tokens 92 us token by token in the general kernel, 18 here; 16257 x 6400,
+// 9 tokens 226 / 36).
 #pragma once
 #include "xfp_dequant.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace xfp {
 
@@ -58,9 +62,10 @@ template <class T>
 __device__ __forceinline__ T &at_lds(uint32_t o) { return *(T *)(uintptr_t)o; }
 
 constexpr int kFewRing = 4;                                    // units of a wave in LDS
-constexpr int kFewUnit = 1024;                                 // bytes of one there (3 bits: 768 used)
+constexpr int few_loads(int bits) { return bits > 4 ? 2 : 1; } // loads of a unit: 64 lanes of 16 bytes (5 and 6 bits: 80 and 96, 3 bits: 48)
+constexpr int few_unit(int bits) { return bits > 4 ? 256 * bits : 1024; }          // bytes of a unit there
 constexpr int kFewOut = 256;                                   // outlier entries of a wave there
-static_assert(kFewOut * 4 <= kFewUnit, "");
+static_assert(kFewOut * 4 <= 1024, "");
 template <int BITS>
 constexpr int few_groups() { return BITS == 2 ? 2 : 1; }       // groups of a unit
 
@@ -72,6 +77,8 @@ __device__ __forceinline__ void put_x(uint32_t run, uint32_t p, const uint4 &w)
     if constexpr (BITS == 4) {
         at_lds<lds_u4_t>(run + 16 * p) = u32x4_t{__builtin_amdgcn_perm(w.y, w.x, kLow), __builtin_amdgcn_perm(w.w, w.z, kLow),
                                                  __builtin_amdgcn_perm(w.y, w.x, kHigh), __builtin_amdgcn_perm(w.w, w.z, kHigh)};
+    } else if constexpr (BITS > 4) {
+        at_lds<lds_u4_t>(run + 16 * p) = u32x4_t{w.x, w.y, w.z, w.w};
     } else if constexpr (BITS == 2) {
         const uint32_t o = run + 32 * (p >> 1) + 4 * (p & 1);
         at_lds<lds_u32_t>(o) = __builtin_amdgcn_perm(w.z, w.x, kLow);
@@ -88,10 +95,30 @@ __device__ __forceinline__ void put_x(uint32_t run, uint32_t p, const uint4 &w)
     }
 }
 
+// Chunk c (0..3) of a run of 32 at 5 and 6 bits: slots 8 c .. 8 c + 7 as fp16 pairs, looked up in a bank that no other lane of
+// the half wave reads: entry e at table + 128 e.
+template <int BITS, int C>
+__device__ __forceinline__ u32x4_t look_up(const words_t<BITS> &w, uint32_t table)
+{
+    uint32_t v[8];
+    auto one = [&](auto slot) {
+        constexpr int t = decltype(slot)::value, bit = BITS * (8 * C + t), word = bit / 32, sh = bit % 32;
+        uint32_t f;                                            // the field at bit 7
+        if constexpr (sh + BITS > 32) f = __builtin_amdgcn_alignbit(w[word + 1], w[word], sh - 7);
+        else if constexpr (sh >= 7) f = w[word] >> (sh - 7);
+        else f = w[word] << (7 - sh);
+        v[t] = at_lds<lds_cu32_t>((f & (((1u << BITS) - 1) << 7)) + table);
+    };
+    one(std::integral_constant<int, 0>{}); one(std::integral_constant<int, 1>{}); one(std::integral_constant<int, 2>{}); one(std::integral_constant<int, 3>{});
+    one(std::integral_constant<int, 4>{}); one(std::integral_constant<int, 5>{}); one(std::integral_constant<int, 6>{}); one(std::integral_constant<int, 7>{});
+    return u32x4_t{v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16};
+}
+
 template <int BITS, int MODE, int T>
 __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
 {
-    constexpr int ND = Planes<BITS>::ND, GU = few_groups<BITS>();
+    static_assert(BITS <= 4 || MODE == 0, "");
+    constexpr int ND = Planes<BITS>::ND, GU = few_groups<BITS>(), NL = few_loads(BITS), kUnit = few_unit(BITS);
     extern __shared__ __align__(256) unsigned char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
     const DecodeArgs &a = fa.a;
@@ -139,7 +166,7 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
     const uint32_t J = fa.J;
     const int32_t rpv = a.rp[row0 + min(wave * J + min(lane, J), rows)];
     Planes<BITS> P;
-    uint32_t cbw[1 << (BITS - 1)];
+    uint32_t cbw[BITS > 4 ? 1 : 1 << (BITS - 1)];
     uint2 libw = make_uint2(0u, 0u);
     uint32_t idw = 0;
     uint16_t scw = 0, miw = 0;
@@ -162,11 +189,13 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
         }
         return v;
     };
-    if constexpr (MODE == 0) {
-        const uint32_t *cb = reinterpret_cast<const uint32_t *>(a.cb) + row0 * (1 << (BITS - 1));
-        const uint32_t o = min(rb * 16 + i, rows - 1) * (1 << (BITS - 1));
+    const uint32_t *cb = reinterpret_cast<const uint32_t *>(a.cb) + row0 * (1 << (BITS - 1));
+    const uint32_t co = min(rb * 16 + i, rows - 1) * (1 << (BITS - 1));
+    if constexpr (BITS > 4) {
+        cbw[0] = cb[co + min(kw, (1u << (BITS - 1)) - 1)];
+    } else if constexpr (MODE == 0) {
 #pragma unroll
-        for (int d = 0; d < (1 << (BITS - 1)); ++d) cbw[d] = cb[o + d];
+        for (int d = 0; d < (1 << (BITS - 1)); ++d) cbw[d] = cb[co + d];
     } else {
         const uint32_t j = min(tid, a.L * ND - 1);
         libw = *reinterpret_cast<const uint2 *>(lib + 4 * j);
@@ -189,11 +218,18 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
     const u32x4_t ri = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base),
                         (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(base >> 32) & 0xFFFFu)),
                         rb * 16 < rows ? min(16u, rows - rb * 16) * (wpr * 4) : 0u, 0x00020000u};
-    uint32_t voff;
-    if constexpr (BITS == 3) voff = lane < 48 ? lane / 3 * (wpr * 4) + lane % 3 * 16 : 0x7FFFFFF0u;
-    else voff = lane / 4 * (wpr * 4) + ((lane ^ (lane >> 4)) & 3) * 16;
+    uint32_t voff[NL];
+#pragma unroll
+    for (int d = 0; d < NL; ++d) {
+        const uint32_t id = d * 64 + lane;
+        if constexpr (BITS == 4 || BITS == 2) voff[d] = id / 4 * (wpr * 4) + ((id ^ (id >> 4)) & 3) * 16;
+        else voff[d] = id < 16 * BITS ? id / BITS * (wpr * 4) + id % BITS * 16 : 0x7FFFFFF0u;
+    }
     auto request = [&](uint32_t t) {                           // the wave's t-th unit
-        load_to_lds(__builtin_amdgcn_readfirstlane(ring + (t % kFewRing) * kFewUnit), voff + (g0 + (u0 + t) * GU) * (16 * BITS), ri, 0);
+#pragma unroll
+        for (int d = 0; d < NL; ++d)
+            if (d == 0 || lane < 16 * BITS - 64)               // (a lane that is off writes nothing to LDS)
+                load_to_lds(__builtin_amdgcn_readfirstlane(ring + (t % kFewRing) * kUnit + d * 1024), voff[d] + (g0 + (u0 + t) * GU) * (16 * BITS), ri, 0);
     };
 #pragma unroll
     for (uint32_t t = 0; t < (uint32_t)kFewRing; ++t)
@@ -231,6 +267,13 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
             if (j != tid) idw = load_id4(j);
             at_lds<lds_u32_t>(lds0 + fa.o_ids + 4 * j) = idw;
         }
+    } else if constexpr (BITS > 4) {
+        // a table per row, twice, in banks of its own (LDS serves 32 lanes at a time): entry e of lane l at e * 128 + l % 32 * 4;
+        // lanes 0 to 31 write the first entry of a dword, the others the second
+        for (uint32_t d = kw; d < (1u << (BITS - 1)); d += KW) {
+            const uint32_t v = d == kw ? cbw[0] : cb[co + d];
+            at_lds<lds_u32_t>(lds0 + fa.o_lib + rb * (128u << BITS) + d * 256 + (lane >> 5) * 128 + (lane & 31) * 4) = lane < 32 ? v & 0xFFFFu : v >> 16;
+        }
     } else {
         P.set(cbw);
     }
@@ -254,13 +297,14 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
     for (int t = 0; t < T; ++t) xb[t] = lds0 + min(16u * t + i, M - 1) * fa.xpitch + 64 * q;
     const uint32_t ids = lds0 + fa.o_ids + (rb * 16 + min(i, rows - 1 - min(rb * 16, rows - 1))) * gs;
     const uint32_t recs = lds0 + fa.o_rec + (rb * gs * 20 + 4 * q) * 4;
+    const uint32_t table = lds0 + fa.o_lib + rb * (128u << BITS) + (lane & 31) * 4;    // (5 and 6 bits)
     words_t<BITS> w[GU], wn[GU];
     auto take = [&](uint32_t t, words_t<BITS> (&v)[GU]) {      // a unit's words: lane (i, q): 32 weights of row i per group
-        const uint32_t s = ring + (t % kFewRing) * kFewUnit;
+        const uint32_t s = ring + (t % kFewRing) * kUnit;
         if constexpr (BITS == 4) v[0] = at_lds<lds_cu4_t>(s + i * 64 + ((q ^ (i >> 2)) & 3) * 16);
-        else if constexpr (BITS == 3) {
+        else if constexpr (BITS != 2) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d) v[0][d] = at_lds<lds_cu32_t>(s + i * 48 + q * 12 + d * 4);
+            for (int d = 0; d < BITS; ++d) v[0][d] = at_lds<lds_cu32_t>(s + i * (16 * BITS) + q * (4 * BITS) + d * 4);
         } else {
 #pragma unroll
             for (int g = 0; g < 2; ++g) v[g] = at_lds<lds_cu2_t>(s + i * 64 + (((2 * g + (q >> 1)) ^ (i >> 2)) & 3) * 16 + (q & 1) * 8);
@@ -268,8 +312,8 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
     };
     // unit t has landed; the min(kFewRing - 2, n - 1 - t) units behind it that have been requested may be under way
     auto wait = [&](uint32_t t) {
-        if (t + kFewRing - 2 < n) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kFewRing - 2) : "memory");
-        else if (t + 1 < n && kFewRing > 3) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+        if (t + kFewRing - 2 < n) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kFewRing - 2) * NL) : "memory");
+        else if (t + 1 < n && kFewRing > 3) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NL) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
     static_assert(kFewRing == 4, "the waits");
@@ -301,13 +345,15 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
                     P.lo[0] = l[0]; P.hi[0] = l[1];
                 }
             }
-            arrange<BITS>(w[s]);
+            if constexpr (BITS <= 4) arrange<BITS>(w[s]);
             // two chains of two steps: what a longer one loses shows in the results (512 columns: 8.9e-8 of them against 64 bits
             // with one chain of four, 7.5e-8 with two)
             float4_t acc[2][T], ones[2][MODE == 2 ? T : 1];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const half8_t af = __builtin_bit_cast(half8_t, chunk<BITS>(P, w[s], c));
+            auto step = [&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                half8_t af;
+                if constexpr (BITS > 4) af = __builtin_bit_cast(half8_t, look_up<BITS, c>(w[s], table));
+                else af = __builtin_bit_cast(half8_t, chunk<BITS>(P, w[s], c));
 #pragma unroll
                 for (int tt = 0; tt < T; ++tt) {
                     const half8_t bf = at_lds<lds_ch8_t>(xb[tt] + g * 256 + 16 * c);
@@ -317,7 +363,11 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
                         ones[c / 2][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(one, bf, c % 2 == 0 ? float4_t{} : ones[c / 2][tt], 0, 0, 0);
                     }
                 }
-            }
+            };
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
+            step(std::integral_constant<int, 3>{});
             if constexpr (MODE == 2) {
                 const u32x4_t rec = at_lds<lds_cu4_t>(recs + g * 80);
 #pragma unroll
@@ -453,11 +503,12 @@ inline uint32_t few_layout(int bits, int mode, uint32_t L, uint32_t M, uint32_t 
     uint32_t o = M * fa.xpitch;
     fa.o_lib = o;
     if (mode) o += L * (2u << bits);
+    if (bits > 4) o += RB * (128u << bits);
     fa.o_ids = o;
     if (mode) o = few_up16(o + RB * 16 * GS + 4);
     fa.o_rec = o;
     if (mode == 2) o += RB * GS * 80;
-    fa.ringw = (most < (uint32_t)kFewRing ? most : (uint32_t)kFewRing) * kFewUnit;
+    fa.ringw = (most < (uint32_t)kFewRing ? most : (uint32_t)kFewRing) * (uint32_t)few_unit(bits);
     if (fa.ringw < M * 80) fa.ringw = M * 80;                  // the wave's sums take its place
     fa.o_ring = o;
     o += nw * fa.ringw;
@@ -488,7 +539,8 @@ hipError_t launch_few_bits(int mode, const FewArgs &fa, dim3 grid, int lds, hipS
 #define XFP_FEW(MODE) \
     (T == 1 ? launch_few_t<BITS, MODE, 1>(fa, grid, lds, s) : T == 2 ? launch_few_t<BITS, MODE, 2>(fa, grid, lds, s) \
                                                                              : launch_few_t<BITS, MODE, 4>(fa, grid, lds, s))
-    return mode == 2 ? XFP_FEW(2) : mode == 1 ? XFP_FEW(1) : XFP_FEW(0);
+    if constexpr (BITS > 4) return mode == 0 ? XFP_FEW(0) : hipErrorInvalidValue;
+    else return mode == 2 ? XFP_FEW(2) : mode == 1 ? XFP_FEW(1) : XFP_FEW(0);
 #undef XFP_FEW
 }
 

@@ -108,7 +108,8 @@ __device__ __forceinline__ u32x4_t chunk(const Planes<BITS> &P, const words_t<BI
 template <int BITS>
 __device__ __forceinline__ uint32_t slot_of(uint32_t k)
 {
-    if constexpr (BITS == 4) return (k & 24u) + (k & 1u) * 4 + (k >> 1 & 3u);
+    if constexpr (BITS > 4) return k;                          // (looked up one by one, in natural order)
+    else if constexpr (BITS == 4) return (k & 24u) + (k & 1u) * 4 + (k >> 1 & 3u);
     else if constexpr (BITS == 3) return (k >> 1 & 3u) * 8 + (k & 1u) * 4 + (k >> 3);
     else return (k & 16u) + (k >> 1 & 1u) * 8 + (k & 1u) * 4 + (k >> 2 & 3u);
 }

@@ -55,6 +55,15 @@ def test_resident_kernel_matches_oracle(mode, bits, N, K, M):
     check(W, xi.activations(np.random.default_rng(M + N), M, K))
 
 
+# 5 and 6 bits (tables of one entry per index): rows that fill no block, one group, more outliers than pass through LDS at
+# once, several passes of fewer tokens because the activations do not fit; the last two stay in the general kernel
+@pytest.mark.parametrize("N,K,M,density", [(4097, 128, 2, 0.01), (4100, 256, 17, 0.01), (5003, 1408, 5, 0.05), (9000, 384, 64, 0.003),
+                                           (70, 14336, 43, 0.003), (4111, 8320, 21, 0.001), (333, 1152, 13, 0.01), (4097, 512, 1, 0.01)])
+@pytest.mark.parametrize("bits", [5, 6])
+def test_wide_indices_match_oracle(bits, N, K, M, density):
+    check(xi.random_weights(V2, bits, N, K, density=density, seed=N + M), xi.activations(np.random.default_rng(M), M, K))
+
+
 def test_large_libraries_and_one_token_of_long_library_rows():
     check(xi.random_weights(V2A, 4, 100, 1280, L=256, density=0.003, seed=1), xi.activations(np.random.default_rng(1), 5, 1280))
     check(xi.random_weights(V2A, 2, 4100, 16512, L=3, density=0.001, seed=2), xi.activations(np.random.default_rng(2), 1, 16512))
