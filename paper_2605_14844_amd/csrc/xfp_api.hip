@@ -288,7 +288,8 @@ int resident_tokens(const xfp_weights *W, bool expert_indexed, int left, const P
     if (left == 1 && g_kernel_choice.load(std::memory_order_relaxed) != XFP_KERNEL_AUTO) return 0;
     // a call that needs no scratch memory elsewhere gets none here: no slices
     const bool scratch = p.route == XFP_ROUTE_WIDE || p.route == XFP_ROUTE_BATCH || p.route == XFP_ROUTE_SPLIT_K;
-    return xfp::few_tokens((int)W->bits, (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : (int)W->mode, W->L, W->N, W->K, left, scratch ? xfp::kPlaneFloats : 0);
+    return xfp::few_tokens((int)W->bits, (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : (int)W->mode, W->L, W->N, W->K, left, scratch ? xfp::kPlaneFloats : 0,
+                           p.route == XFP_ROUTE_GENERAL);
 }
 
 // The tokens that the tiled product takes in place of planned passes of 64 or 16 (0: none).  The plan keeps the product for

@@ -45,7 +45,7 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 }  // namespace
 
 // How many of `left` tokens the next launch takes in this kernel, 0: none (another kernel is faster).  plane: floats of the
-// scratch plane for the sums of several slices.
+// scratch plane for the sums of several slices.  general: the other kernel is the general one.
 // One launch without a re-laid copy of the activations and without tables wins wherever the activations fit, and loses its
 // edge with the slices that they are cut into otherwise: every slice stages its activations and reads its rows' outliers
 // anew.  Measured, us in the other kernels / here (graph replay, cold weights):
@@ -64,7 +64,10 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 //    16 4.7 / 6.2.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
 //  - one token: library rows that neither fit the registers of the streaming kernel nor leave it time for slices:
 //    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 300 x 20480 6.7 / 12.
-int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane)
+//    Rows of a length with no equal slices for that kernel, which one wave each of the general kernel walks: V2 and V2a 2 bits
+//    300 x 21376 15.4 / 11.3, 3300 x 22784 35 / 14, 3 bits 1300 x 18688 16 / 12.6, 5000 x 17792 29 / 18; 4 bits 300 x 21376
+//    16.7 / 16.3, but V2a 3300 x 17024 27 / 18; a scale and a mid-point 3300 x 21376 29 / 18, 1300 x 17792 12.8 / 14.2.
+int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane, bool general)
 {
     if (bits < 2 || (bits > 4 && mode != 0) || K > 65536 || left < 1) return 0;   // (an outlier's column is kept in 16 bits)
     FewPlan p;
@@ -78,7 +81,11 @@ int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left,
         }
         return 0;
     }
-    if (left == 1) return mode != 0 && K > 16384 && N >= 4096 && fits(1) ? 1 : 0;
+    if (left == 1) {
+        if (K <= 16384) return 0;
+        const bool faster = general ? (bits <= 3 && mode != 2) || (N >= 2048 && mode != 0) : N >= 4096 && mode != 0;
+        return faster && fits(1) ? 1 : 0;
+    }
     const bool split = K > 8192 && N <= 8160;                  // three launches in the 16-token kernel
     const uint32_t m = left < 64 ? (uint32_t)left : 64u;
     if (m <= 16) {

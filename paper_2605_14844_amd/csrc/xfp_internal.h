@@ -151,7 +151,7 @@ hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bo
 // Resident kernel: up to 64 tokens of one matrix, the activations in LDS (2 to 4 bits; mode 2 = V2a with a scale and a
 // mid-point per group).  few_tokens: how many of `left` tokens it takes next, 0 where another kernel is faster; plane, part:
 // the scratch plane for the sums of several slices of K (few_is_sliced), in floats.
-int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane);
+int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane, bool general);
 bool few_is_sliced(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M);
 hipError_t launch_decode_few(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, float *part, hipStream_t s);
 // Prompt kernel: many tokens as one tiled product (V2 and V2a at 2..4 bits, any library), up to gemm_tokens per launch.

@@ -69,6 +69,13 @@ def test_large_libraries_and_one_token_of_long_library_rows():
     check(xi.random_weights(V2A, 2, 4100, 16512, L=3, density=0.001, seed=2), xi.activations(np.random.default_rng(2), 1, 16512))
 
 
+@pytest.mark.parametrize("mode,bits,N", [(V2, 2, 300), (V2A, 3, 33), (V2A, 4, 2050), (2, 2, 2049), (V2, 4, 100)])
+def test_one_token_of_rows_without_equal_slices(mode, bits, N):
+    """139 groups: no number of equal slices is short enough for the streaming kernel (the last stays in the general kernel)."""
+    W = xi.random_weights(V2A if mode == 2 else mode, bits, N, 139 * 128, density=0.003, seed=N)
+    check(with_records(W, 3) if mode == 2 else W, xi.activations(np.random.default_rng(N), 1, W.K))
+
+
 @pytest.mark.parametrize("M", [2, 16, 40])
 def test_rows_with_more_outliers_than_pass_through_lds_at_once(M):
     """One row holds 700 entries (three windows of 256), the next none, its neighbours a few: windows move within a row, and
