@@ -19,7 +19,7 @@
 namespace xfp {
 namespace {
 
-constexpr int kMaxSlots = 8;               // pair tables a wave keeps in LDS (plus the all-zero one)
+constexpr int kMaxSlots = 8;               // pair tables a wave keeps in LDS 
 
 struct CombineArgs {
     const uint32_t *idx;   // [E][N][K*bits/32]
@@ -40,7 +40,7 @@ struct CombineArgs {
 
 // NCH : 2048-wide chunks of the concatenated row, T * K <= NCH * 2048
 // TAIL: T * K is not a multiple of 2048: lanes past the end read a clamped
-//       address, zero activations, the all-zero table and weight 0
+//       address and add nothing
 // U   : output rows a wave decodes at once.  A wave needs the activations of ALL
 //       slots (T * K values, 16 KB at C4's shape) however few rows it owns, so
 //       with one row per wave the activation traffic through L2 is several times
@@ -56,10 +56,11 @@ __global__ __launch_bounds__(kWave, combine_waves_per_simd(NCH * U)) void decode
 {
     using Fmt = TableFmt<BITS>;
     constexpr int ENT = Fmt::kEntries, GPL = Fmt::kGroupsPerLaneLoad;
-    constexpr int kNumTables = U * kMaxSlots;              // table u * 8 + t: row u of the batch, slot t; then the all-zero one
-    constexpr int kTables = (kNumTables + 1) * Fmt::kRowBytes;
-    const uint32_t lds_base = static_lds<kTables + kNumTables * Fmt::kRawBytes + 16>();
-    const uint32_t raw_base = lds_base + kTables;
+    // LDS: table t * U + u: slot t, row u of the batch; behind the T * U tables the codebooks they are built from
+    extern __shared__ __align__(16) unsigned char lds_dyn[];   // at LDS address 0: no static segment here
+    if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_dyn != 0u) return;
+    constexpr uint32_t lds_base = 0u;
+    const uint32_t tables = a.T * U, raw_base = tables * Fmt::kRowBytes;
 
     const uint32_t lane = threadIdx.x;
     const uint32_t N = a.N, K = a.K, T = a.T;
@@ -138,19 +139,6 @@ __global__ __launch_bounds__(kWave, combine_waves_per_simd(NCH * U)) void decode
     const float ow = o_on ? weight_of(ot) : 0.f;
 
     const bool xbf = a.x_bf16 != 0;
-    if (xbf) {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) xr[c][i] = bf16x2_to_f16x2(xr[c][i]);
-    }
-
-    // the all-zero table that dead lanes look up
-    if constexpr (TAIL) {
-#pragma unroll
-        for (int i = lane; i < Fmt::kRowBytes / 4; i += kWave)
-            *(lds_u32_w_t *)(uintptr_t)(lds_base + kNumTables * Fmt::kRowBytes + i * 4) = 0u;
-    }
     for (uint32_t row0 = row_begin; row0 < row_end; row0 += U) {
         // ---- all loads of the batch up front: codebooks, row pointers, index words ----
         uint32_t cbv[U];
@@ -170,6 +158,13 @@ __global__ __launch_bounds__(kWave, combine_waves_per_simd(NCH * U)) void decode
             for (int c = 0; c < NCH; ++c) lw[u][c] = load_lane_words<BITS>(ip[c] + (size_t)row * wpr);
         }
         __builtin_amdgcn_sched_barrier(0);
+        // (behind the batch's requests: converting waits for the activations)
+        if (xbf && row0 == row_begin) {
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) xr[c][i] = bf16x2_to_f16x2(xr[c][i]);
+        }
         // Keep the activations as packed fp16 pairs (the compiler would otherwise hoist
         // their fp32 conversions out of the row loop and double the registers).
 #pragma unroll
@@ -177,27 +172,36 @@ __global__ __launch_bounds__(kWave, combine_waves_per_simd(NCH * U)) void decode
 #pragma unroll
             for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(xr[c][i]));
 
-        // ---- a2: eight pair tables per row (slots past T repeat the last one: no branches) ----
+        // ---- a2: T pair tables per row.  A lane builds four entries of a table that differ in their first index: an
+        // 8- and a 2-byte read, a 16-byte write, for 1, 4 or 16 tables at once at 4, 3 and 2 bits.  Four steps side by
+        // side (steps past the end build the last table again).  Eight tables per row for any T, an entry at a time, were
+        // most of this kernel's instructions, and their 17 KB of LDS left a CU nine waves at 4 bits (5120 rows of 2 x 512,
+        // 4 bits: 8.0 us, now 5.7; 4608 of 7 x 1024, 3 bits 11.9 -> 10.8).
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (kMaxSlots * (ENT / 2) == kWave || lane < kMaxSlots * (ENT / 2))
-                *(lds_u32_w_t *)(uintptr_t)(raw_base + u * kMaxSlots * Fmt::kRawBytes + lane * 4) = cbv[u];
+                *(lds_u32_w_t *)(uintptr_t)(raw_base + (ct * U + u) * Fmt::kRawBytes + lane % (ENT / 2) * 4) = cbv[u];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        constexpr int PE = 1 << (2 * BITS);                    // pair entries per table (16, 64 or 256)
-        constexpr int PR = PE >= kWave ? PE / kWave : 1;
-        if (PE >= kWave || lane < PE) {
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) const u2 lds_u2_t;
+        constexpr uint32_t LPT = (1u << (2 * BITS)) / 4, TPS = kWave / LPT;   // lanes of a table, tables of a step
+        const uint32_t tl = lane % LPT, lo = tl * 4 % ENT * 2, hi = tl * 4 / ENT * 2;
+        for (uint32_t t0 = lane / LPT; t0 - lane / LPT < tables; t0 += 4 * TPS) {
+            u2 w[4];
+            uint32_t h[4], r[4];
 #pragma unroll
-            for (int r = 0; r < kNumTables; ++r) {
-                const uint32_t lo = *(lds_u16_t *)(uintptr_t)(raw_base + r * Fmt::kRawBytes + (lane & (ENT - 1)) * 2);
-#pragma unroll
-                for (int p = 0; p < PR; ++p) {
-                    const uint32_t e = lane + p * kWave;
-                    const uint32_t hi = *(lds_u16_t *)(uintptr_t)(raw_base + r * Fmt::kRawBytes + (e >> BITS) * 2);
-                    *(lds_u32_w_t *)(uintptr_t)(lds_base + r * Fmt::kRowBytes + e * 4) = lo | (hi << 16);
-                }
+            for (uint32_t k = 0; k < 4; ++k) {
+                r[k] = min(t0 + k * TPS, tables - 1);
+                w[k] = *(lds_u2_t *)(uintptr_t)(raw_base + r[k] * Fmt::kRawBytes + lo);
+                h[k] = *(lds_u16_t *)(uintptr_t)(raw_base + r[k] * Fmt::kRawBytes + hi);
             }
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                *(__attribute__((address_space(3))) u4 *)(uintptr_t)(lds_base + r[k] * Fmt::kRowBytes + tl * 16) =
+                    u4{(w[k].x & 0xFFFFu) | h[k] << 16, w[k].x >> 16 | h[k] << 16, (w[k].y & 0xFFFFu) | h[k] << 16, w[k].y >> 16 | h[k] << 16};
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -230,8 +234,7 @@ __global__ __launch_bounds__(kWave, combine_waves_per_simd(NCH * U)) void decode
             for (int u = 0; u < U; ++u) sum[u] = 0.f;
             auto issue = [&](int t, uint32_t (&v)[8]) {
                 const int u = t / TPR, c = (t % TPR) / GPL, g = t % GPL;
-                issue_group<BITS, true, true>(lw[u][c], g, lds_base,
-                                              live[c] ? u * kMaxSlots + slot[c] : (uint32_t)kNumTables, v, k2);
+                issue_group<BITS, true, true>(lw[u][c], g, lds_base + u * Fmt::kRowBytes, slot[c] * U, v, k2);
             };
             issue(0, val[0]);
 #pragma unroll
@@ -245,7 +248,8 @@ __global__ __launch_bounds__(kWave, combine_waves_per_simd(NCH * U)) void decode
                 __builtin_amdgcn_sched_barrier(0);
                 consume_group<BITS>(g, val[t & 1], xr[c], acc);
                 if (g == GPL - 1) {                            // unit finished: scale by its slot's router weight
-                    sum[u] = fmaf(wt[c], (acc[0] + acc[1]) + (acc[2] + acc[3]), sum[u]);
+                    const float s = fmaf(wt[c], (acc[0] + acc[1]) + (acc[2] + acc[3]), sum[u]);
+                    sum[u] = live[c] ? s : sum[u];             // (a lane past the end looked up the first slot's entries)
                     acc[0] = acc[1] = acc[2] = acc[3] = 0.f;
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -274,23 +278,21 @@ hipError_t launch_combine_u(CombineArgs a, hipStream_t s)
     uint32_t rpw = U;                                      // one batch per wave unless that makes too many waves
     while ((a.N + rpw - 1) / rpw > 8192 && rpw < 64 * U) rpw += U;
     a.rows_per_wave = rpw;
-    hipLaunchKernelGGL((decode_combine_kernel<BITS, NCH, TAIL, U>), dim3((a.N + rpw - 1) / rpw), dim3(kWave), 0, s, a);
+    hipLaunchKernelGGL((decode_combine_kernel<BITS, NCH, TAIL, U>), dim3((a.N + rpw - 1) / rpw), dim3(kWave),
+                       U * a.T * (TableFmt<BITS>::kRowBytes + TableFmt<BITS>::kRawBytes), s, a);
     return hipGetLastError();
 }
 
-// Rows per batch: as many as keep the tables of a wave within 20 KB of LDS (4 for 2 and 3 bits, 2 for
-// 4 bits) and the index words of a batch within 64 registers, fewer when the matrix is too small to
-// give every CU a few waves that way, or when the concatenated row is long (registers).
+// Rows per batch: two, one where the matrix is too small to give every SIMD a few waves that way or the concatenated row is
+// long (registers).  Four leave a SIMD a wave or less, which issues an instruction every five clocks; us for 1 / 2 / 4 rows:
+// 4096 rows of 8 x 1024, 3 bits 9.7 / 7.8 / 8.3; 5888 of 8 x 640, 4 bits 10.7 / 10.5 / 14.5; 5632 of 6 x 768, 4 bits 10.8 / 9.0 /
+// 10.5; 2176 of 5 x 512, 4 bits 4.7 / 5.1 / 6.2; 2560 and more 2 at least as good as 1 but for two of 17 shapes.
 template <int BITS, int NCH, bool TAIL>
 hipError_t launch_combine_t(const CombineArgs &a, hipStream_t s)
 {
-    constexpr int kUmax = (BITS == 4 ? 2 : 4);
-    constexpr bool f4 = kUmax >= 4 && NCH <= 4, f2 = NCH <= 6;       // beyond that the registers spill
-    if constexpr (f4) {
-        if (a.N >= 4 * 1024) return launch_combine_u<BITS, NCH, TAIL, 4>(a, s);
-    }
+    constexpr bool f2 = NCH <= 6;                              // beyond that the registers spill
     if constexpr (f2) {
-        if (a.N >= 2 * 1024) return launch_combine_u<BITS, NCH, TAIL, 2>(a, s);
+        if (a.N > 2304) return launch_combine_u<BITS, NCH, TAIL, 2>(a, s);
     }
     return launch_combine_u<BITS, NCH, TAIL, 1>(a, s);
 }

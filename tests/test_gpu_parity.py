@@ -582,6 +582,25 @@ def test_down_projection_with_combine(mode, bits, N, K, E, T):
     assert gated_rel_err(y32, ref) <= TOL_F32 and gated_rel_err(y16, ref) <= TOL_F16
 
 
+@pytest.mark.parametrize("bits,N,K,T", [(4, 2310, 384, 8), (4, 2305, 128, 1), (3, 2307, 640, 5), (3, 2304, 256, 3), (2, 2306, 128, 7)])
+def test_down_projection_with_combine_tables_of_every_step(bits, N, K, T):
+    """One and two rows per batch, 1 to 16 tables (of which a wave builds 1, 4 or 16 at a time), lanes past the end of the
+    concatenated row; an infinite entry that every row of the first slot uses gives an infinity, not a NaN, where x is not zero."""
+    W = xi.random_weights(V2, bits, N, K, E=T + 1, density=0.003, seed=N)
+    rng = np.random.default_rng(K)
+    ids = rng.permutation(T + 1)[:T].astype(np.int32)
+    w = rng.random(T).astype(np.float32) + 0.1
+    xb = xi.activations(rng, T, K)
+    args = [torch.from_numpy(ids).cuda(), dev_x(xb), torch.from_numpy(w).cuda()]
+    ref = oracle.moe_combine(oracle.gemv_moe(W, ids, xb, shared_x=False), w)
+    assert gated_rel_err(host(xfp.xfp_gemv_moe_combine(xfp.upload(W), *args, y_dtype=torch.float32)), ref) <= TOL_F32
+    W.out_row_ptr, W.out_col, W.out_val = np.zeros_like(W.out_row_ptr), W.out_col[:0], W.out_val[:0]
+    W.codebooks.reshape(T + 1, N, -1)[ids[0]] = 0x7C00
+    xb[0] = 0x3C00
+    args[1] = dev_x(xb)
+    assert (host(xfp.xfp_gemv_moe_combine(xfp.upload(W), *args, y_dtype=torch.float32)) == np.inf).all()
+
+
 def test_down_projection_with_combine_shared_input_and_bf16():
     W = xi.random_weights(V2, 4, 72, 1024, E=4, density=0.004, seed=64)
     ids = np.array([3, 1, 3, 0, 2], dtype=np.int32)
