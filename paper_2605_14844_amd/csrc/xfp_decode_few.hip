@@ -57,11 +57,11 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 //  - 33 to 64, where the other kernel's tables serve more tokens: 300 x 4096 15 / 13, 600 x 14336 52 / 21, 1200 x 14336
 //    53 / 22, but 1200 x 4096 23 / 28 and 1200 x 640 10.6 / 13.7;
 //  - a scale and a mid-point per group, which run token by token or 16 at a time elsewhere: 8 tokens 16384 x 3072 17.8 / 12.7,
-//    24 4096 x 4096 30 / 14, 64 2000 x 2048 36 / 16, 64 12000 x 5504 94 / 82 (16 at a time), but 2 to 4 tokens of
+//    24 4096 x 4096 30 / 14, 64 2000 x 2048 37 / 30 and 64 12000 x 5504 97 / 95 (16 at a time), but 2 to 4 tokens of
 //    1200 x 4096 6.6 / 7.3 and 40 of 8192 x 8192 66 / 88;
-//  - 5 and 6 bits, which run token by token elsewhere: 8192 x 4096 2 tokens 17.6 / 12.8, 16 92 / 18; 12933 x 1152 2 14.8 / 13.0;
-//    1838 x 10240 3 14.8 / 13.1; 617 x 14208 9 26 / 13, but 2 12.6 / 16.2; 500 x 8192 9 11.8 / 12.3; 300 x 1024
-//    16 4.7 / 6.2.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
+//  - 5 and 6 bits, which run token by token elsewhere: 8192 x 4096 2 tokens 16.5 / 12.8, 16 95 / 26 (8 at a time); 12933 x 1152 2 14.8 / 13.0;
+//    16257 x 6400 9 227 / 56; 8192 x 8192 4 51 / 21; 1838 x 10240 3 14.8 / 13.1; but 617 x 14208 2 12.6 / 16.2; 500 x 8192 9
+//    11.8 / 12.3; 300 x 1024 16 4.7 / 6.2.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
 //  - one token: library rows that neither fit the registers of the streaming kernel nor leave it time for slices:
 //    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 300 x 20480 6.7 / 12.
 //    Rows of a length with no equal slices for that kernel, which one wave each of the general kernel walks: V2 and V2a 2 bits

@@ -20,8 +20,8 @@
 // What bounds it: small matrices the launch (1.5 us), one round trip to memory and the instructions around the main loop
 // (3000 x 2048, 3 bits, 8 tokens: 5.9 us, of which the main loop takes 0.8); large ones the VALU (28672 x 8192, 4 bits, one
 // token: 36 us, HBM 22).  7001 x 5504 as above 9.9 us; 16384 x 3072, a scale and a mid-point per group, 24 tokens 36 -> 20.
-// 5 and 6 bits the lookups (8192 x 4096, 5 bits, 16 tokens 92 us token by token in the general kernel, 18 here; 16257 x 6400,
-// 9 tokens 226 / 36).
+// 5 and 6 bits the lookups (8192 x 4096, 5 bits, 16 tokens 95 us token by token in the general kernel, 26 here; 16257 x 6400,
+// 9 tokens 227 / 56).
 #pragma once
 #include "xfp_dequant.h"
 
