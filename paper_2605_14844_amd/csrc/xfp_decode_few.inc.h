@@ -424,13 +424,13 @@ __global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
                     const uint32_t en = at_lds<lds_u32_t>(ring + (uint32_t)(at - from) * 4), k = (en & 0xFFFFu) - g0 * kGroup;
                     if (k >= gs * kGroup) continue;            // another slice's column
                     const float v = half_bits_to_float((uint16_t)(en >> 16));
-                    const uint32_t xo = lds0 + t0 * fa.xpitch + (k >> 5) * 64 + slot_of<BITS>(k & 31u) * 2;
+                    const uint32_t xo = lds0 + (k >> 5) * 64 + slot_of<BITS>(k & 31u) * 2;
 #pragma unroll
                     for (int m4 = 0; m4 < 16; m4 += 4) {
                         if (t0 + m4 >= M) break;
                         uint16_t xw[4];
 #pragma unroll
-                        for (int m = 0; m < 4; ++m) xw[m] = at_lds<lds_u16_t>(xo + (m4 + m) * fa.xpitch);       // (tokens that are not there: anything)
+                        for (int m = 0; m < 4; ++m) xw[m] = at_lds<lds_u16_t>(xo + min(t0 + m4 + m, M - 1) * fa.xpitch);        // (past the last token: again the last)
 #pragma unroll
                         for (int m = 0; m < 4; ++m) s[m4 + m] = fmaf(v, half_bits_to_float(xw[m]), s[m4 + m]);
                     }

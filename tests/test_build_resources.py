@@ -83,6 +83,15 @@ def test_no_load_in_inline_asm_has_a_result_register():
     assert found == 1                                                 # the prompt kernel's loads of the activations
 
 
+def test_the_resident_kernel_reads_no_token_behind_the_last():
+    """Its activations are the first thing in a workgroup's LDS, a row per token: a row that is not there may lie behind all
+    of it (three rows of 28672 columns behind the only one are 172 KB).  Every row that it addresses is one of the call's."""
+    with open(os.path.join(os.path.dirname(xfp.library_path()), "csrc", "xfp_decode_few.inc.h")) as f:
+        rows = re.findall(r"((?:min\([^()]*\)|\([^()]*\)|[\w\[\]]+)) \* fa\.xpitch", f.read())
+    # M: the size of them all; xm[b]: staged only below M
+    assert sorted(rows) == ["M", "min(16u * t + i, M - 1)", "min(t0 + m4 + m, M - 1)", "xm[b]"]
+
+
 def test_kernels_that_address_lds_from_zero_have_no_static_lds():
     """The matrix-core kernels, the tile kernel and the V2a streaming kernels form lookup addresses that assume
     their tables at LDS offset 0 (one v_perm_b32 writes the whole address).  That holds because they declare

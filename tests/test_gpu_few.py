@@ -90,6 +90,17 @@ def test_rows_with_more_outliers_than_pass_through_lds_at_once(M):
     check(W, xi.activations(np.random.default_rng(3), M, W.K))
 
 
+@pytest.mark.parametrize("mode,N,K,M", [(V2A, 4100, 28672, 1), (V2A, 33, 28672, 2), (V2, 50, 16640, 3), (V2, 20, 9088, 5), (V2, 20, 128, 2)])
+def test_outliers_of_token_counts_that_are_no_multiple_of_four(mode, N, K, M):
+    """An entry's activations are read four tokens at a time; rows as long as a workgroup's LDS, infinities in the last token."""
+    W = xi.random_weights(mode, 3, N, K, density=0.01, seed=N + M)
+    x = xi.activations(np.random.default_rng(K), M, K)
+    y = check(W, x)
+    x[M - 1, ::7] = 0x7C00                                            # (V2A entries and outliers of both signs: no finite result)
+    special = xfp.xfp_gemv(xfp.upload(W), dev_x(x), y_dtype=torch.float32)
+    assert torch.equal(special[:M - 1], y[:M - 1]) and not torch.isfinite(special[M - 1]).any()
+
+
 @pytest.mark.parametrize("K", [1152, 10880])
 def test_infinities_and_nan_stay_with_their_tokens(K):
     W = xi.random_weights(V2A, 2, 50, K, density=0.01, seed=4)
