@@ -26,7 +26,7 @@ struct FewPlan {
 
 bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M, FewPlan &p)
 {
-    const uint32_t G = K / kGroup, GU = bits == 2 ? 2 : 1, blocks = (N + 15) / 16, most = M <= 32 && bits <= 4 ? 16 : 8;
+    const uint32_t G = K / kGroup, GU = bits == 2 ? 2 : 1, blocks = (N + 15) / 16, most = (uint32_t)few_waves(bits, (int)M);
     const uint32_t x_most = kLds - most * 1024 - (mode ? L * (2u << bits) : 0u) - (bits > 4 ? 128u << bits : 0u);
     for (uint32_t S = (uint32_t)(((uint64_t)M * G * 256 + x_most - 1) / x_most); S <= G; ++S) {
         uint32_t GS = (G + S - 1) / S;

@@ -114,8 +114,12 @@ __device__ __forceinline__ u32x4_t look_up(const words_t<BITS> &w, uint32_t tabl
     return u32x4_t{v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16};
 }
 
+// Waves of a workgroup at most (few_plan).  With more than 32 tokens the sums alone ask for more than the 128 registers that 16
+// waves leave (2 bits, a scale and a mid-point per group: 146, spilled within 128).
+constexpr int few_waves(int bits, int tokens) { return tokens <= 32 && bits <= 4 ? 16 : 8; }
+
 template <int BITS, int MODE, int T>
-__global__ __launch_bounds__(1024) void decode_few_kernel(FewArgs fa)
+__global__ __launch_bounds__(kWave * few_waves(BITS, 16 * T)) void decode_few_kernel(FewArgs fa)
 {
     static_assert(BITS <= 4 || MODE == 0, "");
     constexpr int ND = Planes<BITS>::ND, GU = few_groups<BITS>(), NL = few_loads(BITS), kUnit = few_unit(BITS);

@@ -68,6 +68,14 @@ def test_the_prompt_kernels_stay_in_registers():
         assert v["vgpr_spills"] == 0 and v["agprs"] == 0 and v["scratch_bytes_per_lane"] == 0, (k, v)
 
 
+def test_the_resident_kernels_stay_in_registers():
+    """Scratch memory is read through the counter that the kernel's waits for its index words count on."""
+    few = {k: v for k, v in resources().items() if "decode_few_kernel" in k}
+    assert len(few) == 33                                             # 16, 32, 64 tokens: three formats at 2 to 4 bits, V2 at 5 and 6
+    for k, v in few.items():
+        assert v["vgpr_spills"] == 0 and v["agprs"] == 0 and v["scratch_bytes_per_lane"] == 0, (k, v)
+
+
 def test_no_load_in_inline_asm_has_a_result_register():
     """The compiler takes an asm statement's results as there when it ends: it may move, reuse or overwrite their
     registers while the load is under way.  A load into registers is a builtin's; asm loads go to LDS."""
