@@ -159,7 +159,7 @@ typedef struct xfp_weights {
  * 4-bit V2 (whose rows of any length the tile kernel takes), with no split into
  * equal slices of at most 8192 (or partial sums beyond the scratch plane) AND
  * too long for the general kernel to stage on chip (2 K bytes plus its tables
- * within 160 KB).  xfp_route tells on the host which kernel a call takes.
+ * within 160 KB).  xfp_launch_route tells on the host which kernel a call takes.
  */
 int xfp_gemv(const xfp_weights *W, const void *x, int M, int64_t ldx,
              void *y, int y_dtype, int64_t ldy, void *hip_stream);
@@ -351,16 +351,18 @@ typedef enum { XFP_KERNEL_AUTO = 0, XFP_KERNEL_STREAM = 1, XFP_KERNEL_TILE = 2 }
 int xfp_select_kernel(int which);
 
 /*
- * The dispatch rule, queryable on the host (no paper counterpart; touches no device): which kernel family the
- * FIRST launch of xfp_gemv(W, x, M, ...) (expert_indexed == 0) or of xfp_gemv_moe(bank, ids, T = M, ...)
- * (expert_indexed != 0) would be, and in *tokens (may be NULL) how many of the M tokens / slots that launch
- * covers; a call with tokens left over continues with the rule applied to the rest.  The descriptor is validated
- * as by the decode calls (its pointers are not dereferenced).  Returns an xfp_route_id, or a negative xfp_status
- * (XFP_ERR_UNSUPPORTED for a row no kernel takes).  xfp_select_kernel changes what it reports, as it changes
- * what runs.  The families are those of the format's and the sizes' limits: where a launch of STREAM, SPLIT_K,
- * BATCH, WIDE or GENERAL with up to 64 tokens is faster in the kernel that keeps the activations in LDS, that
- * kernel runs in its place, and where one of BATCH or WIDE with more than 64 tokens left is faster as a tiled
- * product, that does, for these tokens or more of the call's.
+ * The dispatch rule, queryable on the host (no paper counterpart; touches no device): of the FIRST launch of
+ * xfp_gemv(W, x, M, ...) (expert_indexed == 0) or of xfp_gemv_moe(bank, ids, T = M, ...) (expert_indexed != 0) the
+ * kernel family, and in *tokens (may be NULL) how many of the M tokens / slots it covers; a call with tokens left over
+ * continues with the rule applied to the rest.  The descriptor is validated as by the decode calls (its pointers are
+ * not dereferenced).  Both return an xfp_route_id, or a negative xfp_status (XFP_ERR_UNSUPPORTED for a row no kernel
+ * takes).  xfp_select_kernel changes what they report, as it changes what runs.
+ *
+ * xfp_launch_route  what runs.
+ * xfp_route         the family by the limits of the format and of the sizes alone, never XFP_ROUTE_RESIDENT: where a launch of
+ *                   STREAM, SPLIT_K, BATCH, WIDE or GENERAL with up to 64 tokens is faster in the kernel that keeps the
+ *                   activations in LDS, that one runs in its place, and where one of BATCH or WIDE with more than 64
+ *                   tokens left is faster as a tiled product, that does, for these tokens or more of the call's.
  */
 typedef enum {
     XFP_ROUTE_GENERAL = 0,   /* one wave per row, x and tables in LDS: widths 5 and 6, scale + mid-point, odd shapes */
@@ -369,9 +371,11 @@ typedef enum {
     XFP_ROUTE_TILE = 3,      /* M = 1 per slot, 32 rows across the lanes                                             */
     XFP_ROUTE_BATCH = 4,     /* 2 .. 16 tokens on the matrix cores, activations in registers                         */
     XFP_ROUTE_WIDE = 5,      /* 17 .. 64 tokens on the matrix cores in one pass over the weights                     */
-    XFP_ROUTE_GEMM = 6       /* prompts: many tokens as a tiled product on the matrix cores                          */
+    XFP_ROUTE_GEMM = 6,      /* prompts: many tokens as a tiled product on the matrix cores                          */
+    XFP_ROUTE_RESIDENT = 7   /* up to 64 tokens on the matrix cores, activations in LDS (xfp_launch_route only)      */
 } xfp_route_id;
 int xfp_route(const xfp_weights *W, int M, int expert_indexed, int *tokens);
+int xfp_launch_route(const xfp_weights *W, int M, int expert_indexed, int *tokens);
 
 /*
  * Test hook for the ring's slot arithmetic (host only, touches no device): the

@@ -75,11 +75,11 @@ def load_library():
     lib.xfp_probe_read.argtypes = [vp, u64, vp, vp]
     lib.xfp_probe_copy.argtypes = [vp, vp, u64, vp]
     lib.xfp_select_kernel.argtypes = [i32]
-    lib.xfp_route.argtypes = [wp, i32, i32, ctypes.POINTER(ctypes.c_int)]
+    lib.xfp_route.argtypes = lib.xfp_launch_route.argtypes = [wp, i32, i32, ctypes.POINTER(ctypes.c_int)]
     lib.xfp_strerror.argtypes = [i32]
     lib.xfp_strerror.restype = ctypes.c_char_p
     for name in ("xfp_gemv", "xfp_gemv_noalloc", "xfp_gemv_moe", "xfp_gemv_moe_silu_mul", "xfp_gemv_moe_combine", "xfp_check_contents", "xfp_convert_bf16_to_f16", "xfp_repack_word10", "xfp_repack_words", "xfp_unpack_indices", "xfp_dequant_bulk",
-                 "xfp_probe_read", "xfp_probe_copy", "xfp_version", "xfp_init", "xfp_select_kernel", "xfp_route"):
+                 "xfp_probe_read", "xfp_probe_copy", "xfp_version", "xfp_init", "xfp_select_kernel", "xfp_route", "xfp_launch_route"):
         getattr(lib, name).restype = i32
     _lib = lib
     return lib
@@ -119,18 +119,28 @@ def xfp_select_kernel(which: int) -> None:
     _check(load_library().xfp_select_kernel(int(which)))
 
 
-XFP_ROUTE_GENERAL, XFP_ROUTE_STREAM, XFP_ROUTE_SPLIT_K, XFP_ROUTE_TILE, XFP_ROUTE_BATCH, XFP_ROUTE_WIDE, XFP_ROUTE_GEMM = range(7)
+XFP_ROUTE_GENERAL, XFP_ROUTE_STREAM, XFP_ROUTE_SPLIT_K, XFP_ROUTE_TILE, XFP_ROUTE_BATCH, XFP_ROUTE_WIDE, XFP_ROUTE_GEMM, XFP_ROUTE_RESIDENT = range(8)
 
 
-def xfp_route(W, M: int, expert_indexed: bool = False):
-    """(route id, tokens) of the first launch xfp_gemv / xfp_gemv_moe would make for M tokens / slots (host only).
-    W: a DeviceWeights or an xfp_weights descriptor."""
+def _ask(query, W, M, expert_indexed):
     desc = W.desc if hasattr(W, "desc") else W
     n = ctypes.c_int(0)
-    r = load_library().xfp_route(ctypes.byref(desc), int(M), int(bool(expert_indexed)), ctypes.byref(n))
+    r = query(ctypes.byref(desc), int(M), int(bool(expert_indexed)), ctypes.byref(n))
     if r < 0:
         _check(r)
     return r, n.value
+
+
+def xfp_route(W, M: int, expert_indexed: bool = False):
+    """(route id, tokens): the kernel family, by the limits of format and sizes alone, of the first launch of xfp_gemv /
+    xfp_gemv_moe for M tokens / slots (host only).  W: a DeviceWeights or an xfp_weights descriptor."""
+    return _ask(load_library().xfp_route, W, M, expert_indexed)
+
+
+def xfp_launch_route(W, M: int, expert_indexed: bool = False):
+    """(route id, tokens) of the first launch that xfp_gemv / xfp_gemv_moe make for M tokens / slots (host only), including
+    the kernels that stand in for a family where they are faster."""
+    return _ask(load_library().xfp_launch_route, W, M, expert_indexed)
 
 
 def xfp_init() -> None:

@@ -188,8 +188,9 @@ bool prefer_tile(const xfp_weights *W, int slots)
     return W->K > 16384 || (uint64_t)W->N * W->K * (uint64_t)slots >= kTileFromWeights;
 }
 
-// What the next launch of a plain decode call is: the kernel family and how many of the remaining slots it
-// takes.  The one place the dispatch rule lives: decode() executes it, xfp_route() reports it.
+// A launch of a plain decode call: the kernel family and how many of the remaining slots it takes.  plan() is the families by
+// what formats and sizes allow (xfp_route reports it); next_launch() below puts the two kernels in front that are faster for some
+// of them, and is what decode() executes and xfp_launch_route reports.
 struct Plan {
     int route;      // an xfp_route_id, or a negative status
     int take;       // slots (tokens) the launch covers
@@ -311,6 +312,16 @@ int product_tokens(const xfp_weights *W, bool expert_indexed, int left, const Pl
     return xfp::gemm_tokens(K, left);
 }
 
+// The one place that decides what runs: decode() executes it launch by launch, xfp_launch_route() reports it.
+Plan next_launch(const xfp_weights *W, bool expert_indexed, int left)
+{
+    const Plan p = plan(W, expert_indexed, left);
+    if (p.route < 0) return p;
+    if (const int take = product_tokens(W, expert_indexed, left, p)) return Plan{XFP_ROUTE_GEMM, take, 0};
+    if (const int take = resident_tokens(W, expert_indexed, left, p)) return Plan{XFP_ROUTE_RESIDENT, take, 0};
+    return p;
+}
+
 // y_dtype: an xfp_dtype, optionally OR-ed with XFP_X_BF16
 int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, int64_t x_stride,
            void *y, int y_dtype, int64_t ldy, Scratch &sc, hipStream_t s)
@@ -330,34 +341,23 @@ int decode(const xfp_weights *W, const int32_t *eids, int slots, const void *x, 
     const size_t ysz = y_f32 ? 4 : 2;
     // the launches of a call run in stream order, so they share the call's workspace
     for (int m0 = 0; m0 < slots;) {
-        Plan p = plan(W, eids != nullptr, slots - m0);
+        const Plan p = next_launch(W, eids != nullptr, slots - m0);
         if (p.route < 0) return p.route;
-        if (const int take = product_tokens(W, eids != nullptr, slots - m0, p)) p = Plan{XFP_ROUTE_GEMM, take, 0};
         xfp::DecodeArgs c = a;
         c.x = a.x + (int64_t)m0 * x_stride;
         c.y = static_cast<char *>(y) + (size_t)m0 * (size_t)ldy * ysz;
         if (eids) c.eids = eids + m0;
+        const int fmode = (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : mode;
         const xfp::Workspace *ws = nullptr;
-        if (const int few = resident_tokens(W, eids != nullptr, slots - m0, p)) {
-            const int fmode = (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : mode;
-            if (xfp::few_is_sliced(bits, fmode, W->L, W->N, W->K, few)) {
-                hipError_t werr = sc.get(&ws);
-                if (werr != hipSuccess) return finish(werr);
-            }
-            hipError_t err = xfp::launch_decode_few(bits, fmode, c, few, y_f32, ws ? ws->part : nullptr, s);
-            if (err != hipSuccess) return finish(err);
-            m0 += few;
-            continue;
-        }
-        if (p.route == XFP_ROUTE_GEMM || p.route == XFP_ROUTE_WIDE || p.route == XFP_ROUTE_BATCH || p.route == XFP_ROUTE_SPLIT_K) {
+        if (p.route == XFP_ROUTE_GEMM || p.route == XFP_ROUTE_WIDE || p.route == XFP_ROUTE_BATCH || p.route == XFP_ROUTE_SPLIT_K ||
+            (p.route == XFP_ROUTE_RESIDENT && xfp::few_is_sliced(bits, fmode, W->L, W->N, W->K, p.take))) {
             hipError_t werr = sc.get(&ws);
             if (werr != hipSuccess) return finish(werr);
         }
         hipError_t err = hipSuccess;
         switch (p.route) {
-        case XFP_ROUTE_WIDE:
-            err = xfp::launch_decode_wide(bits, (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : mode, c, p.take, y_f32, ws->xc, ws->part, s);
-            break;
+        case XFP_ROUTE_WIDE: err = xfp::launch_decode_wide(bits, fmode, c, p.take, y_f32, ws->xc, ws->part, s); break;
+        case XFP_ROUTE_RESIDENT: err = xfp::launch_decode_few(bits, fmode, c, p.take, y_f32, ws ? ws->part : nullptr, s); break;
         case XFP_ROUTE_GEMM: {
             xfp::PromptCopies *copies = nullptr;
             err = xfp::prompt_copies(*ws, &copies);
@@ -637,15 +637,25 @@ int xfp_select_kernel(int which)
     return XFP_OK;
 }
 
-int xfp_route(const xfp_weights *W, int M, int expert_indexed, int *tokens)
+static int report_route(Plan (*rule)(const xfp_weights *, bool, int), const xfp_weights *W, int M, int expert_indexed, int *tokens)
 {
     int rc = check_weights(W);
     if (rc) return rc;
     if (M < 1 || M > 65535) return XFP_ERR_SHAPE;
     if (!expert_indexed && W->E != 1) return XFP_ERR_SHAPE;
-    const Plan p = plan(W, expert_indexed != 0, M);
+    const Plan p = rule(W, expert_indexed != 0, M);
     if (tokens) *tokens = p.take;
     return p.route;
+}
+
+int xfp_route(const xfp_weights *W, int M, int expert_indexed, int *tokens)
+{
+    return report_route(plan, W, M, expert_indexed, tokens);
+}
+
+int xfp_launch_route(const xfp_weights *W, int M, int expert_indexed, int *tokens)
+{
+    return report_route(next_launch, W, M, expert_indexed, tokens);
 }
 
 int xfp_ring_slot(unsigned ticket, int capturing) { return xfp::ring_slot_index(ticket, capturing != 0); }

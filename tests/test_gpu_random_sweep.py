@@ -1,7 +1,7 @@
 """Seeded random walk over what the dispatcher can be asked: format (V2 / V2a, 2 to 6 bits, with or without a scale
 and a mid-point per group), shape (ragged row counts, group counts around every kernel's limits), token count,
 outlier density, activation and output types, strides.  Every case goes through xfp_gemv and is compared with the
-fp64 oracle on the same inputs; the route the call takes is printed so that a failure names its kernel."""
+fp64 oracle on the same inputs; the route of the call's first launch is printed so that a failure names its kernel."""
 import numpy as np
 import pytest
 import torch
@@ -51,7 +51,7 @@ def test_random_calls_match_the_oracle(chunk):
         W = xi.random_weights(c["mode"], c["bits"], c["N"], c["K"], L=c["L"], density=c["dens"], seed=7000 + idx,
                               affine=c["affine"])
         dW = xfp.upload(W)
-        route = ROUTES[xfp.xfp_route(dW, c["M"])[0]]
+        route = ROUTES[xfp.xfp_launch_route(dW, c["M"])[0]]
         print(f"case {idx}: {c} -> {route}", flush=True)
         ldx = c["K"] + (64 if c["strided"] else 0)
         if c["x_bf16"]:

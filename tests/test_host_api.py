@@ -205,9 +205,9 @@ def route(d, M, moe=False):
 
 
 def test_dispatch_rule_on_the_host():
-    """xfp_route reports the rule the decode calls execute (one function in the library serves both): the five
-    workloads and the configurations bench.py times land on the kernels the design notes name, and the size
-    limits sit where the header says."""
+    """xfp_route reports the families by format and size, which is what the decode calls run but where another kernel stands in
+    (test_the_launches_of_a_call_are_reported_as_they_run): the five workloads and the configurations bench.py times land on the
+    families the design notes name, and the size limits sit where the header says."""
     R = xfp
     v2a = dict(mode=1, L=32, group_ids=FAKE)
     # the five workloads
@@ -406,3 +406,66 @@ def test_the_output_type_may_be_left_to_torch():
         assert e.value.status == status
     with pytest.raises(TypeError):
         xfp.xfp_gemv_noalloc(W, torch.zeros((1, 128), dtype=torch.float16), None, stream=0)
+
+
+def launches(kw, M, moe=False):
+    """[(route, tokens)] of every launch of a call, as xfp_launch_route reports them."""
+    out = []
+    while M:
+        out.append(xfp.xfp_launch_route(desc(**kw), M, moe))
+        M -= out[-1][1]
+    return out
+
+
+def test_the_launches_of_a_call_are_reported_as_they_run():
+    """decode() executes the function that xfp_launch_route reports: the resident kernel and the tiled product where they stand in
+    for a family of xfp_route, at the limits of either, and for nothing else."""
+    R, lib = xfp, dict(mode=1, L=32, group_ids=FAKE)
+    record = dict(flags=1, group_scale=FAKE, group_mid=FAKE, **lib)
+    Res, G, Wd, B = R.XFP_ROUTE_RESIDENT, R.XFP_ROUTE_GEMM, R.XFP_ROUTE_WIDE, R.XFP_ROUTE_BATCH
+    for kw, M, want in [
+            # a few tokens: the resident kernel, the others where it would take too many slices of the activations
+            (dict(N=7001, K=5504, bits=2), 5, [(Res, 5)]), (dict(N=28672, K=8192), 16, [(B, 16)]), (dict(N=4096, K=4096, **record), 24, [(Res, 24)]),
+            (dict(N=28672, K=8192, bits=3, **record), 16, [(Wd, 16)]),
+            # 5 and 6 bits: as many as fit in one slice
+            (dict(N=8192, K=4096, bits=5), 16, [(Res, 8), (Res, 8)]), (dict(N=617, K=14208, bits=5), 2, [(R.XFP_ROUTE_GENERAL, 2)]),
+            # a token of long rows
+            (dict(N=8192, K=28672, bits=3, **lib), 1, [(Res, 1)]), (dict(N=8192, K=28672, bits=3), 1, [(R.XFP_ROUTE_SPLIT_K, 1)]),
+            # the tiled product: from 80 tokens on, 65 for long rows, 128 for few long rows, not for two passes more than a round
+            (dict(N=4096, K=4096), 79, [(Wd, 64), (Res, 15)]), (dict(N=4096, K=4096), 80, [(G, 80)]), (dict(N=4096, K=4096), 96, [(G, 96)]),
+            (dict(N=8192, K=8192), 65, [(Wd, 64), (R.XFP_ROUTE_TILE, 1)]), (dict(N=4096, K=14336), 64, [(Wd, 32), (Wd, 32)]),
+            (dict(N=4096, K=14336), 65, [(G, 65)]), (dict(N=512, K=8192), 127, [(Res, 64), (Res, 63)]), (dict(N=512, K=8192), 128, [(G, 128)]),
+            (dict(N=8192, K=8192), 320, [(Wd, 64), (G, 256)]), (dict(N=40, K=4096), 130, [(Res, 64), (Res, 64), (Res, 2)])]:
+        assert launches(kw, M) == want, (kw, M)
+    assert launches(dict(N=2048, K=4096, bits=3, E=16), 8, moe=True) == [(R.XFP_ROUTE_STREAM, 8)]
+
+
+def test_what_stands_in_for_a_planned_launch():
+    """Over random descriptors: the resident kernel takes up to 64 tokens of the call, of a row it can hold; the product more
+    than 64; every other launch is the planned one; expert-indexed calls are as planned."""
+    import random
+    rnd = random.Random(14844)
+    R, seen = xfp, set()
+    for _ in range(3000):
+        kw = dict(N=rnd.choice([1, 33, 640, 1100, 4096, 8160, 8161, 28672, 70000]), K=128 * rnd.choice([1, 9, 32, 64, 65, 85, 128, 129, 167, 224, 512, 520]),
+                  bits=rnd.choice([2, 3, 4]))
+        kw.update(rnd.choice([{}, dict(mode=1, L=32, group_ids=FAKE), dict(mode=1, L=32, group_ids=FAKE, flags=1, group_scale=FAKE, group_mid=FAKE),
+                              dict(bits=5), dict(bits=6)]))
+        M = rnd.choice([1, 2, 5, 16, 17, 40, 64, 65, 79, 80, 128, 192, 321])
+        try:
+            planned = xfp.xfp_route(desc(**kw), M)
+        except xfp.XfpError as e:
+            with pytest.raises(xfp.XfpError) as ei:
+                xfp.xfp_launch_route(desc(**kw), M)
+            assert ei.value.status == e.status == -3
+            continue
+        r, n = xfp.xfp_launch_route(desc(**kw), M)
+        seen.add(r)
+        assert 1 <= n <= M, (kw, M, r, n)
+        if r == R.XFP_ROUTE_RESIDENT:
+            assert n <= 64 and kw["K"] <= 65536 and planned[0] in (R.XFP_ROUTE_STREAM, R.XFP_ROUTE_SPLIT_K, R.XFP_ROUTE_BATCH, R.XFP_ROUTE_WIDE,
+                                                                   R.XFP_ROUTE_GENERAL), (kw, M, n)
+        elif (r, n) != planned:
+            assert r == R.XFP_ROUTE_GEMM and n > 64 and planned[0] in (R.XFP_ROUTE_BATCH, R.XFP_ROUTE_WIDE), (kw, M, n)
+        assert xfp.xfp_launch_route(desc(**kw), M, True) == xfp.xfp_route(desc(**kw), M, True)
+    assert seen == set(range(8))
