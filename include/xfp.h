@@ -385,6 +385,13 @@ int xfp_launch_route(const xfp_weights *W, int M, int expert_indexed, int *token
  */
 int xfp_ring_slot(unsigned ticket, int capturing);
 
+/*
+ * Test hook for the sizes of a launch of the resident kernel with 1 .. 64 tokens (host only, touches no device, whether or not
+ * the dispatch rule takes it): shares[0] slices of K, [1] blocks of 16 rows of a workgroup, [2] waves per block, [3] workgroups.
+ * XFP_ERR_UNSUPPORTED where none fits.
+ */
+int xfp_resident_shares(const xfp_weights *W, int M, unsigned *shares);
+
 /* Text for a status code; never NULL.  For XFP_ERR_HIP the text of the last
  * HIP error seen by the calling thread is appended. */
 const char *xfp_strerror(int status);

@@ -76,10 +76,11 @@ def load_library():
     lib.xfp_probe_copy.argtypes = [vp, vp, u64, vp]
     lib.xfp_select_kernel.argtypes = [i32]
     lib.xfp_route.argtypes = lib.xfp_launch_route.argtypes = [wp, i32, i32, ctypes.POINTER(ctypes.c_int)]
+    lib.xfp_resident_shares.argtypes = [wp, i32, ctypes.POINTER(ctypes.c_uint)]
     lib.xfp_strerror.argtypes = [i32]
     lib.xfp_strerror.restype = ctypes.c_char_p
     for name in ("xfp_gemv", "xfp_gemv_noalloc", "xfp_gemv_moe", "xfp_gemv_moe_silu_mul", "xfp_gemv_moe_combine", "xfp_check_contents", "xfp_convert_bf16_to_f16", "xfp_repack_word10", "xfp_repack_words", "xfp_unpack_indices", "xfp_dequant_bulk",
-                 "xfp_probe_read", "xfp_probe_copy", "xfp_version", "xfp_init", "xfp_select_kernel", "xfp_route", "xfp_launch_route"):
+                 "xfp_probe_read", "xfp_probe_copy", "xfp_version", "xfp_init", "xfp_select_kernel", "xfp_route", "xfp_launch_route", "xfp_resident_shares"):
         getattr(lib, name).restype = i32
     _lib = lib
     return lib

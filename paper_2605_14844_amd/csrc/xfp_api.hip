@@ -658,6 +658,19 @@ int xfp_launch_route(const xfp_weights *W, int M, int expert_indexed, int *token
     return report_route(next_launch, W, M, expert_indexed, tokens);
 }
 
+int xfp_resident_shares(const xfp_weights *W, int M, unsigned *shares)
+{
+    int rc = check_weights(W);
+    if (rc) return rc;
+    if (!shares) return XFP_ERR_NULL;
+    const bool record = (W->flags & XFP_FLAG_GROUP_AFFINE) != 0;
+    if (M < 1 || M > 64 || W->K > 65536) return XFP_ERR_SHAPE;
+    if ((W->bits > 4 && (record || W->mode != XFP_MODE_V2)) ||
+        !xfp::few_shares((int)W->bits, record ? 2 : (int)W->mode, W->L, W->N, W->K, M, shares))
+        return XFP_ERR_UNSUPPORTED;
+    return XFP_OK;
+}
+
 int xfp_ring_slot(unsigned ticket, int capturing) { return xfp::ring_slot_index(ticket, capturing != 0); }
 
 int xfp_version(void) { return (0 << 16) | (2 << 8) | 0; }

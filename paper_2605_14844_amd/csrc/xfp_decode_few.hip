@@ -16,9 +16,10 @@ constexpr uint32_t kLds = 160 * 1024;
 constexpr uint32_t kCUs = 256;
 
 // Blocks of 16 rows, waves per block, groups per slice of K: as few slices as the activations' place in LDS allows (a second
-// launch adds the slices' sums), the blocks of a slice spread over the 256 CUs, and the 16 waves that a CU holds at this
-// kernel's registers (8 from 33 tokens on, whose sums take 5 KB of LDS per wave) sharing the blocks' columns.
-// 7001 x 5504, 2 bits, 5 tokens, us for blocks x waves: 2 x 8 9.9, 2 x 4 11.3, 1 x 8 10.6, 1 x 16 13.8, 4 x 4 14.1.
+// launch adds the slices' sums), the blocks of all slices in one round of the 256 CUs (a slice's share of them rounded down:
+// 86 x 3 workgroups of 3 blocks are two rounds, 4096 x 14336, 4 bits, 8 tokens 27.6 us, 64 x 3 of 4 blocks one, 20.1), and the
+// 16 waves that a CU holds at this kernel's registers (8 from 33 tokens on, whose sums take 5 KB of LDS per wave) sharing the
+// blocks' columns.  7001 x 5504, 2 bits, 5 tokens, us for blocks x waves: 2 x 8 9.9, 2 x 4 11.3, 1 x 8 10.6, 1 x 16 13.8, 4 x 4 14.1.
 struct FewPlan {
     uint32_t slices, lds;
     FewArgs fa;
@@ -32,10 +33,12 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
         uint32_t GS = (G + S - 1) / S;
         if (bits == 2) GS = (GS + 1) & ~1u;
         p.slices = (G + GS - 1) / GS;
-        uint32_t RB = (uint32_t)(((uint64_t)blocks * p.slices + kCUs - 1) / kCUs), KW;
+        const uint32_t share = p.slices < kCUs ? kCUs / p.slices : 1;       // workgroups of a slice in one round
+        uint32_t RB = (blocks + share - 1) / share, KW;
         if (RB > most) RB = most;
         KW = most / RB;
-        if (KW > (GS + GU - 1) / GU) KW = (GS + GU - 1) / GU;
+        const uint32_t units = (GS + GU - 1) / GU;
+        if (KW > units) KW = units;
         p.lds = few_layout(bits, mode, L, M, RB, KW, GS, p.fa);
         if (p.lds <= kLds) return true;
     }
@@ -51,7 +54,10 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 // anew.  Measured, us in the other kernels / here (graph replay, cold weights):
 //  - 2 to 8 tokens: 4096 x 2048 8.3 / 5.0, 7001 x 5504 16 / 9.9, 8192 x 8192 (2 slices) 24 / 18, 28672 x 4096 57 / 27, but
 //    8192 x 14336 (3 slices) 38 / 51; rows beyond 8192 columns in matrices of up to 8160 rows, which are three launches
-//    elsewhere: 3000 x 22016 32 / 16, 300 x 20480 35 / 13;
+//    elsewhere, in any number of slices while a workgroup has no more than eight blocks (of 1353 such calls one lost more than
+//    0.04; of 327 with nine and more, which leave its CU half of its waves, every fourth: 3000 x 28672 16 tokens 28 / 39): 4 bits
+//    4096 x 14336 8 tokens 21.8 / 20.1, 16 22.3 / 23.2; 4096 x 20480 16 30 / 28; 4096 x 28672 6 33 / 28; 300 x 20480 2 to 16
+//    16.4 .. 17.8 / 15.8 .. 12.1; 2 bits 8160 x 14336 8 29 / 21;
 //  - 9 to 16: 4096 x 2048 9.8 / 7.4, 28672 x 1024 22 / 12, 12000 x 5504 (2 slices) 43 / 21, but 4096 x 8192 (3) 19.5 / 22;
 //  - 17 to 32: 600 x 1536 11.2 / 7.7, 28672 x 1024 20.5 / 13.9, 600 x 14336 27 / 16, but 8192 x 4096 17 / 36;
 //  - 33 to 64, where the other kernel's tables serve more tokens: 300 x 4096 15 / 13, 600 x 14336 52 / 21, 1200 x 14336
@@ -60,7 +66,7 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 //    24 4096 x 4096 30 / 14, 64 2000 x 2048 37 / 30 and 64 12000 x 5504 97 / 95 (16 at a time), but 2 to 4 tokens of
 //    1200 x 4096 6.6 / 7.3 and 40 of 8192 x 8192 66 / 88;
 //  - 5 and 6 bits, which run token by token elsewhere: 8192 x 4096 2 tokens 16.5 / 12.8, 16 95 / 26 (8 at a time); 12933 x 1152 2 14.8 / 13.0;
-//    16257 x 6400 9 227 / 56; 8192 x 8192 4 51 / 21; 1838 x 10240 3 14.8 / 13.1; but 617 x 14208 2 12.6 / 16.2; 500 x 8192 9
+//    16257 x 6400 9 227 / 56; 8192 x 8192 4 51 / 21; 2213 x 11392 28 159 / 117; but 617 x 14208 2 12.6 / 16.2; 500 x 8192 9
 //    11.8 / 12.3; 300 x 1024 16 4.7 / 6.2.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
 //  - one token: library rows that neither fit the registers of the streaming kernel nor leave it time for slices:
 //    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 300 x 20480 6.7 / 12.
@@ -90,7 +96,7 @@ int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left,
     const uint32_t m = left < 64 ? (uint32_t)left : 64u;
     if (m <= 16) {
         if (mode == 2 && m <= 4 && K >= 4096 && (uint64_t)N * m <= 8192) return 0;
-        return fits(m) && (p.slices <= 2 || split) ? (int)m : 0;
+        return fits(m) && (p.slices <= 2 || (split && p.fa.RB <= 8)) ? (int)m : 0;
     }
     if (m <= 32) {
         if (fits(m) && (p.slices == 1 || N <= 1008 || (mode == 2 && p.slices <= 2))) return (int)m;
@@ -124,6 +130,17 @@ bool few_is_sliced(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
 {
     FewPlan p;
     return few_plan(bits, mode, L, N, K, (uint32_t)M, p) && p.slices > 1;
+}
+
+bool few_shares(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M, unsigned *out)
+{
+    FewPlan p;
+    if (!few_plan(bits, mode, L, N, K, (uint32_t)M, p)) return false;
+    out[0] = p.slices;
+    out[1] = p.fa.RB;
+    out[2] = p.fa.KW;
+    out[3] = (N + p.fa.RB * 16 - 1) / (p.fa.RB * 16) * p.slices;
+    return true;
 }
 
 }  // namespace xfp

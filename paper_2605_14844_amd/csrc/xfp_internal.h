@@ -153,6 +153,8 @@ hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bo
 // the scratch plane for the sums of several slices of K (few_is_sliced), in floats.
 int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane, bool general);
 bool few_is_sliced(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M);
+// How a launch is shared out (for a host-only test): slices of K, blocks of 16 rows of a workgroup, waves per block, workgroups.
+bool few_shares(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M, unsigned *out);
 hipError_t launch_decode_few(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, float *part, hipStream_t s);
 // Prompt kernel: many tokens as one tiled product (V2 and V2a at 2..4 bits, any library), up to gemm_tokens per launch.
 bool gemm_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M);

@@ -469,3 +469,48 @@ def test_what_stands_in_for_a_planned_launch():
             assert r == R.XFP_ROUTE_GEMM and n > 64 and planned[0] in (R.XFP_ROUTE_BATCH, R.XFP_ROUTE_WIDE), (kw, M, n)
         assert xfp.xfp_launch_route(desc(**kw), M, True) == xfp.xfp_route(desc(**kw), M, True)
     assert seen == set(range(8))
+
+
+def shares(M, **kw):
+    """(slices, blocks of 16 rows of a workgroup, waves per block, workgroups) of a launch of the resident kernel"""
+    out = (ctypes.c_uint * 4)()
+    status = xfp.load_library().xfp_resident_shares(ctypes.byref(desc(**kw)), M, out)
+    assert status in (0, -3), (kw, M, status)
+    return tuple(out) if status == 0 else None
+
+
+def resident_formats():
+    lib = dict(mode=1, L=32, group_ids=FAKE)
+    return [dict(bits=b, **f) for b in (2, 3, 4) for f in ({}, lib, dict(lib, flags=1, group_scale=FAKE, group_mid=FAKE))] + [dict(bits=5), dict(bits=6)]
+
+
+def test_the_resident_kernel_fills_one_round_of_the_cus():
+    """One workgroup runs on a CU: one more than the 256 is a second round for nothing, unless workgroups of as many blocks as they
+    have waves are still more than 256."""
+    for kw in resident_formats():
+        for N in (16, 300, 1100, 2048, 4096, 5200, 6000, 8160, 28672):
+            for K in (128, 4096, 8192, 8320, 14336, 20480, 28672):
+                for M in (1, 2, 6, 8, 12, 16, 30, 40, 64):
+                    s = shares(M, N=N, K=K, **kw)
+                    if s is None:
+                        continue
+                    most = 16 if M <= 32 and kw["bits"] <= 4 else 8
+                    assert s[1] * s[2] <= most and 16 * s[1] * (s[3] // s[0]) >= N, (kw, N, K, M, s)
+                    assert s[3] <= 256 or s[1] == most, (kw, N, K, M, s)
+    assert shares(8, N=4096, K=14336) == (3, 4, 4, 192)
+
+
+def test_slices_are_taken_where_a_workgroup_fills_its_cu():
+    """More than two slices only for the rows that take three launches elsewhere, in workgroups of up to eight blocks."""
+    R, kw = xfp, dict(N=4096, K=28672)
+    assert shares(12, **kw)[:2] == (8, 8) and launches(kw, 12) == [(R.XFP_ROUTE_RESIDENT, 12)]
+    assert shares(16, **kw)[:2] == (9, 10) and launches(kw, 16) == [(R.XFP_ROUTE_BATCH, 16)]
+    assert launches(dict(N=3000, K=28672), 16) == [(R.XFP_ROUTE_BATCH, 16)]
+    assert launches(dict(N=300, K=28672), 16) == [(R.XFP_ROUTE_RESIDENT, 16)] and launches(dict(N=4096, K=8192), 16) == [(R.XFP_ROUTE_BATCH, 16)]
+    for kw in resident_formats()[:9]:
+        for N in (100, 2048, 4096, 6000, 8160, 8161):
+            for K in (4096, 5120, 8192, 8320, 14336, 28672):
+                for M in (2, 5, 9, 16):
+                    if launches(dict(kw, N=N, K=K), M)[0][0] == R.XFP_ROUTE_RESIDENT:
+                        s = shares(M, N=N, K=K, **kw)
+                        assert s[0] <= 2 or (s[1] <= 8 and K > 8192 and N <= 8160), (kw, N, K, M, s)
