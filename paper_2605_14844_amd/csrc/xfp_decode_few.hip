@@ -20,6 +20,10 @@ constexpr uint32_t kCUs = 256;
 // 86 x 3 workgroups of 3 blocks are two rounds, 4096 x 14336, 4 bits, 8 tokens 27.6 us, 64 x 3 of 4 blocks one, 20.1), and the
 // 16 waves that a CU holds at this kernel's registers (8 from 33 tokens on, whose sums take 5 KB of LDS per wave) sharing the
 // blocks' columns.  7001 x 5504, 2 bits, 5 tokens, us for blocks x waves: 2 x 8 9.9, 2 x 4 11.3, 1 x 8 10.6, 1 x 16 13.8, 4 x 4 14.1.
+// A slice of one to three units has no work in the main loop for more waves than that, but activations to stage, outliers and
+// sums to share out: eight waves all the same, us with a wave per unit / eight: 335 x 256, 2 bits, 30 tokens 15.1 / 6.3; 1627 x
+// 128, 4 bits, 26 tokens 11.5 / 5.9; 4297 x 128, 3 bits, 40 17.6 / 9.1; not in matrices of more blocks than CUs with few tokens
+// (4096 rows and more of one unit, 2 to 4 tokens, 1.14 of the time with eight; 5 to 16 of two units 1.0).
 struct FewPlan {
     uint32_t slices, lds;
     FewArgs fa;
@@ -38,7 +42,7 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
         if (RB > most) RB = most;
         KW = most / RB;
         const uint32_t units = (GS + GU - 1) / GU;
-        if (KW > units) KW = units;
+        if (KW > units) KW = units >= 4 || (blocks > kCUs && M <= 16) ? units : KW < 8 ? KW : 8;
         p.lds = few_layout(bits, mode, L, M, RB, KW, GS, p.fa);
         if (p.lds <= kLds) return true;
     }

@@ -514,3 +514,20 @@ def test_slices_are_taken_where_a_workgroup_fills_its_cu():
                     if launches(dict(kw, N=N, K=K), M)[0][0] == R.XFP_ROUTE_RESIDENT:
                         s = shares(M, N=N, K=K, **kw)
                         assert s[0] <= 2 or (s[1] <= 8 and K > 8192 and N <= 8160), (kw, N, K, M, s)
+
+
+def test_short_rows_are_staged_by_more_waves_than_they_have_units():
+    """A unit is 128 columns (256 at 2 bits): with one to three of them a wave per unit left the staging of up to 64 tokens, the
+    outliers and the sums to one to three waves."""
+    for kw in resident_formats():
+        unit = 256 if kw["bits"] == 2 else 128
+        for N in (16, 1000, 4096, 4112, 8000):
+            for units in (1, 2, 3, 4, 6):
+                for M in (2, 16, 17, 32, 33, 64):
+                    s = shares(M, N=N, K=unit * units, **kw)
+                    most = 16 if M <= 32 and kw["bits"] <= 4 else 8
+                    if s[0] > 1:
+                        continue
+                    want = units if units >= 4 or (N > 4096 and M <= 16) else max(units, 8)
+                    assert s[2] == min(most // s[1], want), (kw, N, units, M, s)
+    assert shares(30, N=335, K=256, bits=2) == (1, 1, 8, 21)
