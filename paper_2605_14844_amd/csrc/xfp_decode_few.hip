@@ -68,7 +68,9 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 //    53 / 22, but 1200 x 4096 23 / 28 and 1200 x 640 10.6 / 13.7;
 //  - a scale and a mid-point per group, which run token by token or 16 at a time elsewhere: 8 tokens 16384 x 3072 17.8 / 12.7,
 //    24 4096 x 4096 30 / 14, 64 2000 x 2048 37 / 30 and 64 12000 x 5504 97 / 95 (16 at a time), but 2 to 4 tokens of
-//    1200 x 4096 6.6 / 7.3 and 40 of 8192 x 8192 66 / 88;
+//    1200 x 4096 6.6 / 7.3 and 40 of 8192 x 8192 66 / 88; and few rows, which leave the token-by-token kernel room for all tokens
+//    at once: 73 x 256 45 tokens 3.6 / 9, 387 x 2176 2 3.3 / 5.2, 1752 x 1664 2 4.4 / 5.6 but 16 14.6 / 7.5, 319 x 4480 8 5.3 / 8.1,
+//    851 x 1024 16 8.6 / 6.3, 125 x 2560 16 4.1 / 8.6, 835 x 2048 48 15.7 / 23.5;
 //  - 5 and 6 bits, which run token by token elsewhere: 8192 x 4096 2 tokens 16.5 / 12.8, 16 95 / 26 (8 at a time); 12933 x 1152 2 14.8 / 13.0;
 //    16257 x 6400 9 227 / 56; 8192 x 8192 4 51 / 21; 2213 x 11392 28 159 / 117; but 617 x 14208 2 12.6 / 16.2; 500 x 8192 9
 //    11.8 / 12.3; 300 x 1024 16 4.7 / 6.2.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
@@ -98,6 +100,7 @@ int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left,
     }
     const bool split = K > 8192 && N <= 8160;                  // three launches in the 16-token kernel
     const uint32_t m = left < 64 ? (uint32_t)left : 64u;
+    if (mode == 2 && plane == 0 && !general && (N <= (m <= 8 || (m > 32 && K >= 1280) ? 1008u : 640u) || (m <= 5 && (uint64_t)N * m <= (bits == 4 ? 4096u : 6144u)))) return 0;
     if (m <= 16) {
         if (mode == 2 && m <= 4 && K >= 4096 && (uint64_t)N * m <= 8192) return 0;
         return fits(m) && (p.slices <= 2 || (split && p.fa.RB <= 8)) ? (int)m : 0;

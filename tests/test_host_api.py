@@ -531,3 +531,16 @@ def test_short_rows_are_staged_by_more_waves_than_they_have_units():
                     want = units if units >= 4 or (N > 4096 and M <= 16) else max(units, 8)
                     assert s[2] == min(most // s[1], want), (kw, N, units, M, s)
     assert shares(30, N=335, K=256, bits=2) == (1, 1, 8, 21)
+
+
+def test_few_rows_with_records_stay_token_by_token():
+    """A scale and a mid-point per group: with up to 640 rows (1008 for 2 to 8 tokens and for more than 32 of rows that are not
+    short, more for 2 to 5) the streaming kernel runs all tokens side by side in less time than the resident kernel stages them."""
+    R, record = xfp, dict(mode=1, L=32, group_ids=FAKE, flags=1, group_scale=FAKE, group_mid=FAKE)
+    stream, res = R.XFP_ROUTE_STREAM, R.XFP_ROUTE_RESIDENT
+    for bits, N, K, M, want in [(2, 73, 256, 45, stream), (3, 640, 2048, 20, stream), (3, 641, 2048, 20, res), (3, 641, 2048, 40, stream), (3, 641, 1152, 40, res),
+                                (3, 1008, 2048, 8, stream), (3, 1009, 2048, 8, res), (3, 1024, 1024, 5, stream), (3, 3072, 1024, 2, stream),
+                                (3, 3073, 1024, 2, res), (4, 2048, 1024, 2, stream), (4, 2049, 1024, 2, res), (4, 1008, 128, 2, stream)]:
+        assert launches(dict(record, bits=bits, N=N, K=K), M)[0][0] == want, (bits, N, K, M)
+    # rows that the streaming kernel does not hold: sixteen tokens at a time or one wave per row and token elsewhere
+    assert launches(dict(record, bits=3, N=600, K=20480), 16) == [(res, 16)]
