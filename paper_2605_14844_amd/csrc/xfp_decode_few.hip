@@ -73,7 +73,8 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 //    851 x 1024 16 8.6 / 6.3, 125 x 2560 16 4.1 / 8.6, 835 x 2048 48 15.7 / 23.5;
 //  - 5 and 6 bits, which run token by token elsewhere: 8192 x 4096 2 tokens 16.5 / 12.8, 16 95 / 26 (8 at a time); 12933 x 1152 2 14.8 / 13.0;
 //    16257 x 6400 9 227 / 56; 8192 x 8192 4 51 / 21; 2213 x 11392 28 159 / 117; but 617 x 14208 2 12.6 / 16.2; 500 x 8192 9
-//    11.8 / 12.3; 300 x 1024 16 4.7 / 6.2.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
+//    11.8 / 12.3; 300 x 1024 16 4.7 / 6.2; and of few long rows, in several launches that leave CUs idle, 1024 x 23424 42 251 / 468,
+//    1526 x 14592 6 37 / 41, 32 152 / 213, 1201 x 7936 22 46 / 52, 827 x 3840 27 18 / 23.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
 //  - one token: library rows that neither fit the registers of the streaming kernel nor leave it time for slices:
 //    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 300 x 20480 6.7 / 12.
 //    Rows of a length with no equal slices for that kernel, which one wave each of the general kernel walks: V2 and V2a 2 bits
@@ -86,6 +87,7 @@ int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left,
     auto fits = [&](uint32_t m) { return few_plan(bits, mode, L, N, K, m, p) && (p.slices == 1 || (uint64_t)p.slices * m * N <= plane); };
     if (bits > 4) {
         const uint32_t all = left < 64 ? (uint32_t)left : 64u;
+        if (N <= (K > 8192 ? 2048u : K >= 5632 ? 1280u : K >= 3072 ? 896u : 0u)) return 0;
         for (uint32_t c = 1; c < all; ++c) {
             const uint32_t m = (all + c - 1) / c;
             if (N < 4096 && (uint64_t)m * N * K < 40u << 20) return 0;

@@ -544,3 +544,14 @@ def test_few_rows_with_records_stay_token_by_token():
         assert launches(dict(record, bits=bits, N=N, K=K), M)[0][0] == want, (bits, N, K, M)
     # rows that the streaming kernel does not hold: sixteen tokens at a time or one wave per row and token elsewhere
     assert launches(dict(record, bits=3, N=600, K=20480), 16) == [(res, 16)]
+
+
+def test_few_long_rows_at_5_and_6_bits_stay_token_by_token():
+    """In one slice the resident kernel takes a few tokens of long rows per launch, on as many CUs as there are blocks of 16 rows:
+    few rows are faster in the general kernel, which runs all tokens side by side."""
+    R = xfp
+    for bits in (5, 6):
+        for N, K, M, want in [(1024, 23424, 42, R.XFP_ROUTE_GENERAL), (2048, 8320, 64, R.XFP_ROUTE_GENERAL), (2049, 8320, 64, R.XFP_ROUTE_RESIDENT),
+                              (1280, 5632, 20, R.XFP_ROUTE_GENERAL), (1281, 5632, 20, R.XFP_ROUTE_RESIDENT), (1280, 5504, 20, R.XFP_ROUTE_RESIDENT),
+                              (896, 3072, 64, R.XFP_ROUTE_GENERAL), (897, 3072, 64, R.XFP_ROUTE_RESIDENT), (896, 2944, 64, R.XFP_ROUTE_RESIDENT)]:
+            assert launches(dict(bits=bits, N=N, K=K), M)[0][0] == want, (bits, N, K, M)
