@@ -298,9 +298,13 @@ int resident_tokens(const xfp_weights *W, bool expert_indexed, int left, const P
 // tokens on, us in passes / as a product (graph replay, cold weights): 4096 x 4096 80 tokens 25 / 22, 96 31 / 25, 192 50 / 25;
 // 512 x 1024 96 20 / 14; 28672 x 8192 96 124 / 103, 192 192 / 137, 320 325 / 277; 28672 x 1024 224 94 / 37; from 65 on for rows
 // beyond 8192 columns, whose passes are of 16 to 48 tokens: 4096 x 14336 101 / 71, 8192 x 28672 158 / 95 (65 tokens of
-// 8192 x 8192 34 / 36, 80 51 / 43).  Two exceptions: few long rows, where the resident kernel takes the passes (512 x 8192,
-// 96 tokens 31 / 32, 128 43 / 34), and what is at most two passes more than one round of 128 x 64 tiles (8192 x 8192, 320 tokens:
-// a pass and a round 86, two rounds 105).
+// 8192 x 8192 34 / 36, 80 51 / 43).  Three exceptions: few long rows, where the resident kernel takes the passes (512 x 8192,
+// 96 tokens 31 / 32, 128 43 / 34); what is at most two passes more than one round of 128 x 64 tiles (8192 x 8192, 320 tokens:
+// a pass and a round 86, two rounds 105); and up to 192 tokens in a round and up to half another, at 3 and 4 bits for rows of 3072
+// to 8192 columns (17482 x 6400 105 tokens 96 / 122, 11589 x 6656 142 91 / 114, 22706 x 4224 91 66 / 80; with more of the
+// second round 27288 x 3712 107 80 / 74, 25208 x 6656 124 115 / 99; at 2 bits 11232 x 4480 190 74 / 64), otherwise where no more
+// than 32 tokens are left behind passes of 64 (19878 x 2944 80 56 / 73, 21071 x 9344 65 119 / 180, 11970 x 2816 129 54 / 68; 2 bits
+// 19633 x 2048 89 45 / 55) and the rows are not short (16962 x 768 88 39.5 / 37; 640 columns and more with two tiles, 1536 with three).
 int product_tokens(const xfp_weights *W, bool expert_indexed, int left, const Plan &p)
 {
     if (expert_indexed || left <= 64 || (p.route != XFP_ROUTE_WIDE && p.route != XFP_ROUTE_BATCH) || general_only(W)) return 0;
@@ -308,6 +312,10 @@ int product_tokens(const xfp_weights *W, bool expert_indexed, int left, const Pl
     if (!xfp::gemm_supports((int)W->bits, (int)W->mode, W->L, N, K, left)) return 0;
     if (left < (K > 8192 && N >= 2048 ? 65 : K >= 8192 && N < 1024 ? 128 : 80)) return 0;
     const uint32_t tiles = (N + 127) / 128, chunks = ((uint32_t)left + 63) / 64, round = tiles <= 256 ? 256 / tiles : 0;
+    if (left <= 192 && tiles * chunks > 256 && tiles * chunks <= 384) {
+        if (W->bits >= 3 && K >= 3072 && K <= 8192) return 0;
+        if ((left - 1) % 64 < 32 && K >= (chunks == 2 ? 640 : 1536) && (W->bits >= 3 || K <= 8192)) return 0;
+    }
     if (left > 192 && round >= 3 && chunks > round && chunks <= round + 2) return 0;
     return xfp::gemm_tokens(K, left);
 }

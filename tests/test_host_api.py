@@ -555,3 +555,23 @@ def test_few_long_rows_at_5_and_6_bits_stay_token_by_token():
                               (1280, 5632, 20, R.XFP_ROUTE_GENERAL), (1281, 5632, 20, R.XFP_ROUTE_RESIDENT), (1280, 5504, 20, R.XFP_ROUTE_RESIDENT),
                               (896, 3072, 64, R.XFP_ROUTE_GENERAL), (897, 3072, 64, R.XFP_ROUTE_RESIDENT), (896, 2944, 64, R.XFP_ROUTE_RESIDENT)]:
             assert launches(dict(bits=bits, N=N, K=K), M)[0][0] == want, (bits, N, K, M)
+
+
+def test_a_little_more_than_a_round_of_tiles_is_passes_first():
+    """Up to 192 tokens in 257 to 384 tiles of 128 x 64: a second round that is mostly empty costs more than a pass of 64 tokens."""
+    R, lib = xfp, dict(mode=1, L=32, group_ids=FAKE)
+    G, Wd = R.XFP_ROUTE_GEMM, R.XFP_ROUTE_WIDE
+    first = lambda M, **kw: launches(kw, M)[0]
+    # 3 and 4 bits, 3072 to 8192 columns: whatever is left behind the passes
+    for kw in (dict(bits=4), dict(bits=3), dict(bits=3, **lib)):
+        assert first(128, N=128 * 128, K=4096, **kw) == (G, 128) and first(128, N=128 * 128 + 1, K=4096, **kw) == (Wd, 64)
+        assert first(128, N=192 * 128, K=4096, **kw) == (Wd, 64) and first(128, N=192 * 128 + 1, K=4096, **kw) == (G, 128)
+        assert first(128, N=20000, K=2944, **kw) == (G, 128) and first(128, N=20000, K=8320, **kw) == (G, 128)
+    # all widths: where no more than 32 tokens are left, rows that are not short
+    for bits in (2, 3, 4):
+        assert first(96, N=20000, K=640, bits=bits) == (Wd, 64) and first(96, N=20000, K=512, bits=bits) == (G, 96)
+        assert first(97, N=20000, K=640, bits=bits) == (G, 97)
+        assert first(160, N=12000, K=1536, bits=bits) == (Wd, 64) and first(160, N=12000, K=1408, bits=bits) == (G, 160)
+        assert (first(65, N=21000, K=9344, bits=bits)[0] == G) == (bits == 2)
+    # more than 192 tokens: as before
+    assert first(193, N=11000, K=4096) == (G, 193)
