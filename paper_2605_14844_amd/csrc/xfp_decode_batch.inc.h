@@ -610,7 +610,9 @@ hipError_t launch_batch_n(const DecodeArgs &a, int M, bool y_f32, const void *xt
 // One launch of up to 16 tokens for one bit width.  Eight waves share a tile of
 // 16 rows: with 16 waves (128 registers each) the compiler spills the in-flight
 // index words and the kernel runs at half the speed.  part: an fp32 scratch plane
-// for the partial sums of a row cut into slices (K > 8192), unused otherwise.
+// for the partial sums of a row cut into slices (K > 8192), unused otherwise.  Rows
+// of up to 2048 columns and of 8320 to 10240 are the resident kernel's (few_tokens)
+// for any number of rows and tokens: there is no kernel for them here.
 template <int BITS, int MODE = 0>
 hipError_t launch_batch_bits(const DecodeArgs &a, int M, bool y_f32, float *part, const void *xt, const void *xb,
                              hipStream_t s)
@@ -618,8 +620,6 @@ hipError_t launch_batch_bits(const DecodeArgs &a, int M, bool y_f32, float *part
     const int nl = batch_split_nl(a.K);
     if (nl == 0) {
         switch ((a.K / kGroup + 7) / 8) {
-        case 1: return launch_batch_n<BITS, MODE, 1>(a, M, y_f32, xt, xb, s);
-        case 2: return launch_batch_n<BITS, MODE, 2>(a, M, y_f32, xt, xb, s);
         case 3: return launch_batch_n<BITS, MODE, 3>(a, M, y_f32, xt, xb, s);
         case 4: return launch_batch_n<BITS, MODE, 4>(a, M, y_f32, xt, xb, s);
         case 5: return launch_batch_n<BITS, MODE, 5>(a, M, y_f32, xt, xb, s);
@@ -634,7 +634,6 @@ hipError_t launch_batch_bits(const DecodeArgs &a, int M, bool y_f32, float *part
     DecodeArgs c = a;
     c.y = part;
     switch (nl) {
-    case 5: err = launch_batch_t<BITS, MODE, 8, 5, true, true>(c, M, true, xt, xb, s); break;
     case 6: err = launch_batch_t<BITS, MODE, 8, 6, true, true>(c, M, true, xt, xb, s); break;
     case 7: err = launch_batch_t<BITS, MODE, 8, 7, true, true>(c, M, true, xt, xb, s); break;
     case 8: err = launch_batch_t<BITS, MODE, 8, 8, true, true>(c, M, true, xt, xb, s); break;

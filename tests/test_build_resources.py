@@ -88,7 +88,7 @@ def test_no_load_in_inline_asm_has_a_result_register():
             if re.search(r"(global|buffer|flat|scratch)_load|ds_read|s_load", m.group(1)):
                 found += 1
                 assert operands and re.search(r"\blds\b", code), (path, m.group(0))
-    assert found == 1                                                 # the prompt kernel's loads of the activations
+    assert found == 1                                                 # load_to_lds (index words, activations)
 
 
 def test_the_resident_kernel_reads_no_token_behind_the_last():
@@ -101,12 +101,13 @@ def test_the_resident_kernel_reads_no_token_behind_the_last():
 
 
 def test_kernels_that_address_lds_from_zero_have_no_static_lds():
-    """The matrix-core kernels, the tile kernel and the V2a streaming kernels form lookup addresses that assume
-    their tables at LDS offset 0 (one v_perm_b32 writes the whole address).  That holds because they declare
+    """The matrix-core kernels, the tile kernel, the V2a streaming kernels and the down projection with the router's sum
+    form lookup addresses that assume their tables at LDS offset 0 (one v_perm_b32 writes the whole address).  That holds because they declare
     dynamic LDS only; a static __shared__ array added to one of them would move the tables and the kernel would
     return without writing (its guard).  This pins the guarantee at build time."""
     res = resources()
-    names = [k for k in res if any(p in k for p in ("decode_batch_kernel", "decode_tile_kernel", "decode_wide_kernel"))]
+    names = [k for k in res if any(p in k for p in ("decode_batch_kernel", "decode_tile_kernel", "decode_wide_kernel", "decode_combine_kernel"))]
+    assert sum("decode_combine_kernel" in k for k in names) >= 30
     # the streaming kernel's V2a instantiations: template argument 5 (MODE) is 1, or 2 with a scale and a mid-point per group
     names += [k for k in res if "decode_stream_kernelILi" in k and k.split("decode_stream_kernelI")[1].split("E")[4] in ("Li1", "Li2")]
     assert len(names) >= 100

@@ -575,3 +575,17 @@ def test_a_little_more_than_a_round_of_tiles_is_passes_first():
         assert (first(65, N=21000, K=9344, bits=bits)[0] == G) == (bits == 2)
     # more than 192 tokens: as before
     assert first(193, N=11000, K=4096) == (G, 193)
+
+
+def test_the_16_token_kernel_has_every_row_length_that_reaches_it():
+    """It is built for rows of more than 2048 columns and, in slices, of more than 10240: shorter ones are the resident kernel's at
+    any number of rows and tokens, whatever room the library takes."""
+    rows = [1, 16, 500, 1009, 2049, 4096, 4097, 6000, 8160, 8161, 12288, 16384, 20480, 24576, 28672, 32768, 32769, 45056, 61440, 65536, 128256, 1000000]
+    for bits in (2, 3, 4):
+        for L in (0, 1, 32, 64, 128, 256):
+            fmt = dict(mode=1, L=L, group_ids=FAKE) if L else {}
+            for G in list(range(1, 17)) + list(range(65, 81)):
+                for N in rows:
+                    for M in (2, 5, 8, 12, 15, 16, 17, 33, 64, 70):
+                        r, _ = xfp.xfp_launch_route(desc(bits=bits, N=N, K=128 * G, **fmt), M)
+                        assert r != xfp.XFP_ROUTE_BATCH, (bits, L, G, N, M)
