@@ -168,8 +168,9 @@ def used():
     return (total - free) >> 20
 
 W = xfp.upload(xi.random_weights(xi.MODE_V2, 4, 256, 512, density=0.003, seed=3))
-x = torch.from_numpy(xi.activations(np.random.default_rng(4), 600, 512).view(np.int16)).cuda().view(torch.float16)
-y, y4 = torch.empty((600, 256), dtype=torch.float16, device="cuda"), torch.empty((4, 256), dtype=torch.float16, device="cuda")
+M = int(sys.argv[1])
+x = torch.from_numpy(xi.activations(np.random.default_rng(4), M, 512).view(np.int16)).cuda().view(torch.float16)
+y, y4 = torch.empty((M, 256), dtype=torch.float16, device="cuda"), torch.empty((4, 256), dtype=torch.float16, device="cuda")
 xfp.xfp_gemv(W, x[:1], y=y4[:1])
 before = used()
 xfp.xfp_init()
@@ -195,10 +196,11 @@ print("MB", few, prompt, used() - before)
 """
 
 
-def test_only_prompts_load_the_memory_of_prompts():
-    """Eight workspaces and the static array are 90 MB; the first prompt loads 512 more (and 64 for xfp_gemv_noalloc), also
-    where it is a call that is being captured."""
-    r = subprocess.run([sys.executable, "-c", FIRST_PROMPT], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+@pytest.mark.parametrize("M", [600, 100])
+def test_only_prompts_load_the_memory_of_prompts(M):
+    """Eight workspaces and the static array are 90 MB; the first tiled product, of a prompt or of a batch of more than 64 tokens,
+    loads 512 more (and 64 for xfp_gemv_noalloc), also where it is a call that is being captured."""
+    r = subprocess.run([sys.executable, "-c", FIRST_PROMPT, str(M)], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                        capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stderr[-2000:]
     few, prompt, both = map(int, re.search(r"MB (\d+) (\d+) (\d+)", r.stdout).groups())

@@ -217,6 +217,8 @@ def test_strided_x_and_y():
 
 
 # ------------------------------------------------------------------ batched
+# (which kernel runs is the dispatch's business: most of these shapes are the resident kernel's, those that reach the 16-token
+# kernel are in test_gpu_routes.py)
 @pytest.mark.parametrize("mode,bits,N,K,M", [(V2, 4, 200, 8192, 16), (V2, 4, 77, 1024, 5),
                                              (V2, 3, 64, 4096, 16), (V2A, 3, 48, 2048, 8),
                                              (V2, 4, 33, 4096, 2), (V2, 4, 40, 2048, 33),
@@ -232,9 +234,7 @@ def test_batched_matches_oracle_and_single_calls(mode, bits, N, K, M):
         assert gated_rel_err(yb[m], y1[0]) <= TOL_F32
 
 
-# batched tokens on rows above 8192 columns: the matrix-core kernel in slices of K (equal, or the
-# last one short: 8320 = 40 + 25 groups, 11008 = 48 + 38, 27648 = 4 x 56 - 8), M = 17 and 33 leave
-# one token for the M = 1 kernels
+# batched tokens on rows above 8192 columns, in slices of K in either matrix-core kernel; M = 17 and 33 leave one token over
 @pytest.mark.parametrize("N,K,M,dens", [(200, 16384, 16, 0.003), (90, 8320, 5, 0.003), (70, 11008, 16, 0.003),
                                         (64, 28672, 16, 0.003), (50, 27648, 9, 0.0), (33, 32768, 2, 0.01),
                                         (40, 20480, 17, 0.003), (24, 12288, 33, 0.003), (600, 14336, 16, 0.003)])
@@ -251,7 +251,7 @@ def test_batched_long_rows_in_slices(N, K, M, dens):
     assert gated_rel_err(host(yb16), refb) <= TOL_BF16
 
 
-# 3-bit and 2-bit rows through the matrix-core kernel: every count of groups per wave (1..8), ragged, long rows in slices
+# 3-bit and 2-bit rows: group counts from 1 to 224, ragged, long rows in slices
 @pytest.mark.parametrize("N,K,M,dens", [(200, 8192, 16, 0.003), (77, 1024, 5, 0.003), (64, 4096, 16, 0.003),
                                         (33, 128, 2, 0.01), (90, 1408, 16, 0.003), (50, 5120, 7, 0.0),
                                         (35, 7296, 3, 0.003), (41, 3072, 16, 0.003), (40, 6144, 9, 0.003),
@@ -268,7 +268,7 @@ def test_batched_3bit_2bit_matches_oracle_and_single_calls(bits, N, K, M, dens):
         assert gated_rel_err(yb[m], y1[0]) <= TOL_F32
 
 
-# V2a (library tables, ids per group) through the matrix-core kernel
+# V2a (library tables, ids per group)
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("N,K,M,dens", [(200, 8192, 16, 0.003), (77, 1024, 5, 0.003), (64, 4096, 16, 0.003),
                                         (33, 128, 2, 0.01), (90, 1408, 16, 0.003), (50, 5120, 7, 0.0),
@@ -286,15 +286,14 @@ def test_batched_library_mode_matches_oracle_and_single_calls(bits, N, K, M, den
 
 @pytest.mark.parametrize("bits,L", [(4, 64), (4, 65), (3, 200), (3, 1), (4, 7), (2, 256), (2, 3)])
 def test_batched_library_sizes(bits, L):
-    """Libraries up to the 64 KB of pair tables the kernel holds (64 entries at 4 bits), and one past it, which
-    takes the per-token kernels."""
+    """Libraries up to the 64 KB of pair tables the 16-token kernel holds (64 entries at 4 bits), and one past it."""
     W = xi.random_weights(V2A, bits, 70, 2048, L=L, density=0.003, seed=L + bits)
     check_gemv(W, xi.activations(np.random.default_rng(L), 16, 2048))
 
 
 def test_batched_with_more_outliers_than_a_tile_keeps_on_chip():
-    """5 % outliers: a 16-row tile of K = 4096 holds about 3300 entries, far past the on-chip product
-    buffer, and one row alone holds every entry of its tile."""
+    """5 % outliers: 16 rows of K = 4096 hold about 3300 entries, far past what either kernel keeps on chip, and one row
+    alone holds every entry of its matrix."""
     W = xi.random_weights(V2, 4, 80, 4096, density=0.05, seed=77)
     check_gemv(W, xi.activations(np.random.default_rng(70), 16, 4096))
     K = 2048

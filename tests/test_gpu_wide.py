@@ -1,6 +1,7 @@
 """The wide matrix-core kernel (V2 and V2a, 2 to 4 bits, 17 .. 64 tokens in one pass over the weights): parity with the oracle,
 bit-exact depack + gather through one-hot activations, agreement with the single-token calls, the token counts and
-row lengths at which the call falls back to chunks of 16."""
+row lengths at which the call falls back to chunks of 16.  Shapes that the resident kernel takes instead (17 to 32 tokens, few long
+rows) are kept as they were; what reaches each form of this kernel is in test_gpu_routes.py."""
 import numpy as np
 import pytest
 import torch
@@ -192,8 +193,8 @@ def test_every_token_count_up_to_130(mode, bits):
 @pytest.mark.parametrize("bits,N,K,M,L", [(3, 4096, 4096, 16, 32), (4, 2100, 8192, 9, 32), (2, 1030, 16384, 16, 7), (4, 33000, 512, 16, 63),
                                           (3, 600, 28672, 8, 200), (4, 8200, 4096, 35, 1)])
 def test_scale_and_mid_point_per_group_with_several_tokens(bits, N, K, M, L):
-    """Flagged V2a tensors with 2 .. 16 tokens per launch on the wide kernel (from 2^27 weights x tokens on): ragged
-    last tile, rows of 4 and of 224 groups, more than 16 tokens in chunks; against the oracle, and every token's row
+    """Flagged V2a tensors with several tokens, of the wide kernel's family (from 2^27 weights x tokens on; these sizes run the
+    resident kernel): ragged last tile, rows of 4 and of 224 groups, more than 16 tokens in chunks; against the oracle, and every token's row
     against the single-token call (the streaming kernel's mode for the same tensors)."""
     W = xi.random_weights(V2A, bits, N, K, L=L, density=0.002, seed=N + K + bits, affine=True)
     x = xi.activations(np.random.default_rng(N + M), M, K)
@@ -212,8 +213,8 @@ def test_scale_and_mid_point_per_group_with_several_tokens(bits, N, K, M, L):
 
 
 def test_scale_and_mid_point_one_hot_is_the_affine_value():
-    """One-hot tokens through the wide kernel's mode: y[m][n] = entry * scale + mid of one weight, one fp32 rounding
-    of an exact product plus the mid-point (the block of the group holds the entry alone, the token's sum is 1)."""
+    """One-hot tokens: y[m][n] = entry * scale + mid of one weight, one fp32 rounding of an exact product plus the
+    mid-point (the block of the group holds the entry alone, the token's sum is 1)."""
     W = xi.random_weights(V2A, 4, 8200, 1024, L=9, density=0.0, seed=10, affine=True)
     dW = xfp.upload(W)
     q = oracle.unpack(W.indices[0], W.K, 4).astype(np.int64)

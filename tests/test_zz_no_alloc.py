@@ -70,8 +70,8 @@ def test_sizes_beyond_the_static_array_are_refused():
 
 
 def test_flagged_tensor_with_several_tokens_matches_xfp_gemv():
-    """A scale and a mid-point per group, 16 then 5 tokens: the wide kernel's mode for them keeps its activation sums
-    in a scratch plane of the same static array."""
+    """A scale and a mid-point per group, 16 then 5 tokens, of the wide kernel's family (these run the resident kernel; the wide
+    kernel's mode, which keeps activation sums in a scratch plane of the same static array, is in test_gpu_routes.py)."""
     for (N, M, seed) in ((2100, 16, 9400), (8300, 5, 9500)):
         W = xi.random_weights(V2A, 3, N, 4096, density=0.002, seed=seed, affine=True)
         xb = xi.activations(np.random.default_rng(seed + 1), M, W.K)
