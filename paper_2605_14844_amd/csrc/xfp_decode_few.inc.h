@@ -429,12 +429,14 @@ __global__ __launch_bounds__(kWave * few_waves(BITS, 16 * T)) void decode_few_ke
                     if (k >= gs * kGroup) continue;            // another slice's column
                     const float v = half_bits_to_float((uint16_t)(en >> 16));
                     const uint32_t xo = lds0 + (k >> 5) * 64 + slot_of<BITS>(k & 31u) * 2;
+                    // (one chunk: the tokens' rows do not change with t0 and are worked out once)
+                    const uint32_t chunk0 = T == 1 ? 0u : t0;
 #pragma unroll
                     for (int m4 = 0; m4 < 16; m4 += 4) {
                         if (t0 + m4 >= M) break;
                         uint16_t xw[4];
 #pragma unroll
-                        for (int m = 0; m < 4; ++m) xw[m] = at_lds<lds_u16_t>(xo + min(t0 + m4 + m, M - 1) * fa.xpitch);        // (past the last token: again the last)
+                        for (int m = 0; m < 4; ++m) xw[m] = at_lds<lds_u16_t>(xo + min(chunk0 + m4 + m, M - 1) * fa.xpitch);        // (past the last token: again the last)
 #pragma unroll
                         for (int m = 0; m < 4; ++m) s[m4 + m] = fmaf(v, half_bits_to_float(xw[m]), s[m4 + m]);
                     }

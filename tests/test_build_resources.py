@@ -97,7 +97,7 @@ def test_the_resident_kernel_reads_no_token_behind_the_last():
     with open(os.path.join(os.path.dirname(xfp.library_path()), "csrc", "xfp_decode_few.inc.h")) as f:
         rows = re.findall(r"((?:min\([^()]*\)|\([^()]*\)|[\w\[\]]+)) \* fa\.xpitch", f.read())
     # M: the size of them all; xm[b]: staged only below M
-    assert sorted(rows) == ["M", "min(16u * t + i, M - 1)", "min(t0 + m4 + m, M - 1)", "xm[b]"]
+    assert sorted(rows) == ["M", "min(16u * t + i, M - 1)", "min(chunk0 + m4 + m, M - 1)", "xm[b]"]
 
 
 def test_kernels_that_address_lds_from_zero_have_no_static_lds():
