@@ -632,7 +632,10 @@ hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
     using Large = GemmTile<1, 4, 8, 1, 4, 3, 2>;
     using Small = GemmTile<1, 2, 4, 2, 4, 3, BITS == 4 ? 2 : 3>;
     using Small16 = GemmTile<1, 2, 4, 4, 2, 3, 2>;
-    using Tiny = GemmTile<1, 2, 2, 4, 2, 4, 2>;
+    // (parts of a whole turn where the index words leave LDS for three, 2 and 3 bits: with parts of half a turn the waves met twice
+    // as often, us without outliers 287 x 10880, 3 bits, 458 tokens 49.4 / 45.8, 1908 x 7168, 2 bits, 310 31.9 / 30.7, with 0.05 %
+    // 326 x 16896, 3 bits, 475 78.5 / 72.8)
+    using Tiny = std::conditional_t<BITS == 4, GemmTile<1, 2, 2, 4, 2, 4, 2>, GemmTile<1, 2, 2, 4, 4, 3, 2>>;
     const uint64_t m = (ga.M + 63) / 64, small = (uint64_t)((ga.a.N + 127) / 128) * m;
     if ((uint64_t)((ga.a.N + 63) / 64) * m <= 256) return launch_gemm_t<BITS, MODE, Tiny>(ga, s);
     // (rows that ask for a third set of sums, in matrices that the 16-token kernel would cut into slices: see kDeepK)
