@@ -19,7 +19,7 @@
 namespace xfp {
 namespace {
 
-constexpr int kMaxSlots = 8;               // pair tables a wave keeps in LDS 
+constexpr int kMaxSlots = 8;               // pair tables a wave keeps in LDS for a row, at most
 
 struct CombineArgs {
     const uint32_t *idx;   // [E][N][K*bits/32]
@@ -286,13 +286,14 @@ hipError_t launch_combine_u(CombineArgs a, hipStream_t s)
 // Rows per batch: two, one where the matrix is too small to give every SIMD a few waves that way or the concatenated row is
 // long (registers).  Four leave a SIMD a wave or less, which issues an instruction every five clocks; us for 1 / 2 / 4 rows:
 // 4096 rows of 8 x 1024, 3 bits 9.7 / 7.8 / 8.3; 5888 of 8 x 640, 4 bits 10.7 / 10.5 / 14.5; 5632 of 6 x 768, 4 bits 10.8 / 9.0 /
-// 10.5; 2176 of 5 x 512, 4 bits 4.7 / 5.1 / 6.2; 2560 and more 2 at least as good as 1 but for two of 17 shapes.
+// 10.5; 2176 of 5 x 512, 4 bits 4.7 / 5.1 / 6.2; 2560 and more 2 at least as good as 1 but for two of 17 shapes;
+// with the longest rows from 2049 on: 2304 of 6 x 1792, 4 bits 11.2 / 9.7, 2 bits 9.7 / 8.7, 2176, 3 bits 9.7 / 9.1.
 template <int BITS, int NCH, bool TAIL>
 hipError_t launch_combine_t(const CombineArgs &a, hipStream_t s)
 {
     constexpr bool f2 = NCH <= 6;                              // beyond that the registers spill
     if constexpr (f2) {
-        if (a.N > 2304) return launch_combine_u<BITS, NCH, TAIL, 2>(a, s);
+        if (a.N > (NCH < 6 ? 2304u : 2048u)) return launch_combine_u<BITS, NCH, TAIL, 2>(a, s);
     }
     return launch_combine_u<BITS, NCH, TAIL, 1>(a, s);
 }

@@ -581,7 +581,8 @@ def test_down_projection_with_combine(mode, bits, N, K, E, T):
     assert gated_rel_err(y32, ref) <= TOL_F32 and gated_rel_err(y16, ref) <= TOL_F16
 
 
-@pytest.mark.parametrize("bits,N,K,T", [(4, 2310, 384, 8), (4, 2305, 128, 1), (3, 2307, 640, 5), (3, 2304, 256, 3), (2, 2306, 128, 7)])
+@pytest.mark.parametrize("bits,N,K,T", [(4, 2310, 384, 8), (4, 2305, 128, 1), (3, 2307, 640, 5), (3, 2304, 256, 3), (2, 2306, 128, 7),
+                                           (3, 2049, 1792, 6), (4, 2050, 1536, 7)])
 def test_down_projection_with_combine_tables_of_every_step(bits, N, K, T):
     """One and two rows per batch, 1 to 16 tables (of which a wave builds 1, 4 or 16 at a time), lanes past the end of the
     concatenated row; an infinite entry that every row of the first slot uses gives an infinity, not a NaN, where x is not zero."""
