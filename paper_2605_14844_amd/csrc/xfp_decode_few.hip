@@ -76,7 +76,8 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 //    11.8 / 12.3; 300 x 1024 16 4.7 / 6.2; and of few long rows, in several launches that leave CUs idle, 1024 x 23424 42 251 / 468,
 //    1526 x 14592 6 37 / 41, 32 152 / 213, 1201 x 7936 22 46 / 52, 827 x 3840 27 18 / 23.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
 //  - one token: library rows that neither fit the registers of the streaming kernel nor leave it time for slices:
-//    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 300 x 20480 6.7 / 12.
+//    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 4 bits 6411 x 19712 31 / 29,
+//    but 5524 x 28672 35 / 39, 4577 x 21888 24 / 29; 3 bits 5310 x 23680 31 / 25, 4611 x 17280 18.7 / 20.1; 300 x 20480 6.7 / 12.
 //    Rows of a length with no equal slices for that kernel, which one wave each of the general kernel walks: V2 and V2a 2 bits
 //    300 x 21376 15.4 / 11.3, 3300 x 22784 35 / 14, 3 bits 1300 x 18688 16 / 12.6, 5000 x 17792 29 / 18; 4 bits 300 x 21376
 //    16.7 / 16.3, but V2a 3300 x 17024 27 / 18; a scale and a mid-point 3300 x 21376 29 / 18, 1300 x 17792 12.8 / 14.2.
@@ -97,7 +98,8 @@ int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left,
     }
     if (left == 1) {
         if (K <= 16384) return 0;
-        const bool faster = general ? (bits <= 3 && mode != 2) || (N >= 2048 && mode != 0) : N >= 4096 && mode != 0;
+        const bool faster = general ? (bits <= 3 && mode != 2) || (N >= 2048 && mode != 0)
+                                    : mode != 0 && N >= (mode == 2 || bits == 2 ? 4096u : bits == 3 ? 4864u : 5632u);
         return faster && fits(1) ? 1 : 0;
     }
     const bool split = K > 8192 && N <= 8160;                  // three launches in the 16-token kernel

@@ -589,3 +589,15 @@ def test_the_16_token_kernel_has_every_row_length_that_reaches_it():
                     for M in (2, 5, 8, 12, 15, 16, 17, 33, 64, 70):
                         r, _ = xfp.xfp_launch_route(desc(bits=bits, N=N, K=128 * G, **fmt), M)
                         assert r != xfp.XFP_ROUTE_BATCH, (bits, L, G, N, M)
+
+
+def test_one_token_of_long_library_rows():
+    """Rows that the streaming kernel takes in slices are the resident kernel's where the matrix keeps all CUs busy in one round of blocks
+    or nearly: fewer rows the fewer bits an index has."""
+    R, lib = xfp, dict(mode=1, L=32, group_ids=FAKE)
+    record = dict(lib, flags=1, group_scale=FAKE, group_mid=FAKE)
+    for kw, N in [(dict(lib, bits=4), 5632), (dict(lib, bits=3), 4864), (dict(lib, bits=2), 4096)]:
+        assert launches(dict(kw, N=N, K=21504), 1) == [(R.XFP_ROUTE_RESIDENT, 1)] and launches(dict(kw, N=N - 1, K=21504), 1) == [(R.XFP_ROUTE_SPLIT_K, 1)], kw
+    # with records, and rows without equal slices: one wave per row of the general kernel otherwise
+    for kw in (dict(record, bits=4), dict(lib, bits=4, K=21376)):
+        assert launches(dict(dict(K=21504), N=2048, **kw), 1) == [(R.XFP_ROUTE_RESIDENT, 1)] and launches(dict(dict(K=21504), N=2047, **kw), 1) == [(R.XFP_ROUTE_GENERAL, 1)], kw
