@@ -142,19 +142,21 @@ typedef struct xfp_weights {
  * W      one matrix (W->E must be 1).
  * x      fp16 [M][ldx], ldx >= K, ldx % 8 == 0, 16-byte aligned.
  * y      [M][ldy] of y_dtype, ldy >= N, 16-byte aligned base.
- * M      1 .. 65535.  M = 1 is the decode case.  M >= 2 takes a matrix-core
- *        (MFMA) path that reads the weights once per 16 tokens, for V2 and
- *        V2a at 2 to 4 bits (a V2a library with L * 4^bits * 4 bytes <= 64 KB),
- *        K <= 32768; rows above 8192 columns in one launch when the matrix
- *        has 8161 rows or more, else in slices of K whose partial sums go
- *        through a static scratch plane.  The same formats with more than 16
- *        tokens read the weights once per up to 64 tokens (as many chunks
- *        of 16 as 16 * ceil(m / 16) * K <= 2^19 allows: 64 tokens up to
- *        K = 8192, 32 up to 16384); prompts (more than about 200 tokens,
- *        more where the matrix is large, 128 rows and more, K <= 65536) run
- *        as one tiled product per 2^24 / K tokens, tokens left over as above;
- *        any other shape or width runs the M = 1 path once per token.  Same
- *        results either way, to rounding.
+ * M      1 .. 65535.  M = 1 is the decode case.  M >= 2 runs on the
+ *        matrix cores (MFMA) and reads the weights once per launch: up to
+ *        64 tokens whose activations fit on chip, whole or in slices of K,
+ *        in one launch (any format but V2a at 5 and 6 bits; K <= 65536);
+ *        where they would take too many slices, V2 and V2a at 2 to 4 bits
+ *        (a library with L * 4^bits * 4 bytes <= 64 KB) 16 tokens at a
+ *        time (K <= 32768; rows above 8192 columns in one launch when the
+ *        matrix has 8161 rows or more, else in slices of K whose partial
+ *        sums go through a static scratch plane) or, with more than 16, up
+ *        to 64 (as many chunks of 16 as 16 * ceil(m / 16) * K <= 2^19
+ *        allows: 64 tokens up to K = 8192, 32 up to 16384); from 65 to 128
+ *        tokens on (128 rows and more, K <= 65536, the tokens by the
+ *        matrix) as one tiled product per 2^24 / K tokens, tokens left over
+ *        as above; what none of them takes runs the M = 1 path once per
+ *        token.  Same results either way, to rounding.
  * XFP_ERR_UNSUPPORTED for a row no kernel takes: longer than 16384 columns, not
  * 4-bit V2 (whose rows of any length the tile kernel takes), with no split into
  * equal slices of at most 8192 (or partial sums beyond the scratch plane) AND
@@ -170,7 +172,7 @@ int xfp_gemv(const xfp_weights *W, const void *x, int M, int64_t ldx,
  * harnesses that forbid hipMalloc.  (No paper counterpart.)  Same arguments and
  * same results, bit for bit, as xfp_gemv.  Whatever scratch the call needs
  * (re-laid activations for M >= 2, partial sums of rows cut into slices of K)
- * lives in ONE static device array of 10 MB (and one of 64 MB for prompts, from
+ * lives in ONE static device array of 10 MB (and one of 64 MB for tiled products, from
  * the first one on), not in the ring the other entry points cycle through; each
  * GPU the process uses holds its own copy until the process ends.  The call allocates nothing, frees nothing and calls no
  * allocating routine.
@@ -332,7 +334,8 @@ int xfp_probe_copy(const void *src, void *dst, uint64_t bytes, void *hip_stream)
 /*
  * Resolves, for the current device, the addresses of the library's static
  * device memory (the ring of workspaces and xfp_gemv_noalloc's array; not the
- * memory of prompts, which the first prompt loads, also under capture).
+ * memory of tiled products, which the first of them loads, also under capture:
+ * a program that records calls of more than 64 tokens makes one before).
  * Optional: the first call that needs them does the same; call it once per
  * device before recording calls into a HIP graph, so that nothing but launches
  * happens under capture.

@@ -215,18 +215,16 @@ bool wide_affine(const xfp_weights *W, bool expert_indexed, int tokens)
            xfp::wide_supports((int)W->bits, 2, W->L, W->N, W->K, tokens);
 }
 
-// Prompts: the tiled product against passes of the wide kernel (64 tokens up to 8192 columns, 32 to 16 beyond).  A round
-// of tiles takes the same time for any number of them up to the 256 CUs, a pass grows with the rows only from 256 tiles
-// of 32 on.  Measured, us as this rule has it / in passes alone / as one product (fp16 results; fp32 within a tenth):
-//  - one round of 128 x 64 tiles or less, from 193 tokens on: 4096 x 4096 193 tokens 36 / 59 / 36, 384 50 / 105 / 50;
-//    8192 x 8192 193 81 / 89 / 81; 65 tokens: 25 / 25 / 32 and 37 / 37 / 49;
+// Prompts by size alone (what xfp_route reports): the tiled product against passes of the wide kernel (64 tokens up to 8192 columns,
+// 32 to 16 beyond).  A round of tiles takes the same time for any number of them up to the 256 CUs, a pass grows with the rows only
+// from 256 tiles of 32 on.  product_tokens takes more calls, at the limits that the product's present speed gives.  Measured,
+// us as it runs / in passes alone / as one product (fp16 results, 4 bits, 0.3 % outliers):
+//  - one round of 128 x 64 tiles or less, from 193 tokens on: 4096 x 4096 193 tokens 29 / 58 / 30, 384 41 / 103 / 41;
+//    8192 x 8192 193 74 / 86 / 73; 65 tokens: 23 / 23 / 26 and 37 / 37 / 48;
 //  - a little more than that: passes until one round is left (each launch's leftover is planned anew): 8192 x 8192 257 tokens
-//    106 / 114 / 146, 384 130 / 154 / 145, 448 155 / 179 / 146; 6144 x 4096 333 66 / 105 / 84;
-//  - 28672 x 8192: 320 tokens 332 / 325 / 353, 384 353 / 431 / 353;
-//  - rows beyond 16384 columns, which are passed over once per 16 tokens: 4096 x 28672 128 tokens 123 / 280 / 122.
-// It is nowhere slower than passes (128 .. 28672 rows, 512 .. 28672 columns, 65 .. 511 tokens).  It asks for more tokens than it
-// would have to: the product would win from 100 to 160 tokens on in many shapes (4096 x 4096, 160 tokens 50 / 50 / 34),
-// from 193 on in tall ones (16384 x 2048, 300 tokens 88 / 87 / 61) and from 65 on in long rows (2048 x 16384 91 / 90 / 72).
+//    99 / 112 / 130, 320 100 / 133 / 130, 384 125 / 159 / 131, 448 135 / 184 / 137; 6144 x 4096 333 64 / 102 / 74;
+//  - 28672 x 8192: 384 tokens 309 / 425 / 299, 512 338 / 559 / 325 (the first and the third are one launch each);
+//  - rows beyond 16384 columns, which are passed over once per 16 tokens: 4096 x 28672 128 tokens 133 / 288 / 128.
 // Formats that no matrix-core kernel takes otherwise (libraries beyond LDS, rows beyond 32768 columns) run token by token.
 bool gemm_only(const xfp_weights *W)
 {
@@ -295,11 +293,11 @@ int resident_tokens(const xfp_weights *W, bool expert_indexed, int left, const P
 
 // The tokens that the tiled product takes in place of planned passes of 64 or 16 (0: none).  The plan keeps the product for
 // more than 192 tokens and single rounds of its tiles; in launches that cost what they do now it is the faster one from 80
-// tokens on, us in passes / as a product (graph replay, cold weights): 4096 x 4096 80 tokens 25 / 22, 96 31 / 25, 192 50 / 25;
-// 512 x 1024 96 20 / 14; 28672 x 8192 96 124 / 103, 192 192 / 137, 320 325 / 277; 28672 x 1024 224 94 / 37; from 65 on for rows
-// beyond 8192 columns, whose passes are of 16 to 48 tokens: 4096 x 14336 101 / 71, 8192 x 28672 158 / 95 (65 tokens of
-// 8192 x 8192 34 / 36, 80 51 / 43).  Three exceptions: few long rows, where the resident kernel takes the passes (512 x 8192,
-// 96 tokens 31 / 32, 128 43 / 34); what is at most two passes more than one round of 128 x 64 tiles (8192 x 8192, 320 tokens:
+// tokens on, us in passes / as a product (graph replay, cold weights): 4096 x 4096 80 tokens 27 / 25, 96 31 / 25, 160 48 / 27;
+// 512 x 1024 96 20 / 13; 28672 x 8192 96 138 / 142, 192 223 / 164, 320 356 / 295; 28672 x 1024 224 99 / 38; 16384 x 2048 300 95 / 51;
+// from 65 on for rows beyond 8192 columns, whose passes are of 16 to 48 tokens: 2048 x 16384 65 86 / 70, 4096 x 14336 80 87 / 65,
+// 8192 x 28672 80 224 / 132 (8192 x 8192 65 37 / 48, 80 52 / 45).  Three exceptions: few long rows, where the resident kernel takes
+// the passes (512 x 8192, 96 tokens 33 / 39, 128 41 / 39); what is at most two passes more than one round of 128 x 64 tiles (8192 x 8192, 320 tokens:
 // a pass and a round 86, two rounds 105); and up to 192 tokens in a round and up to half another, at 3 and 4 bits for rows of 3072
 // to 8192 columns (17482 x 6400 105 tokens 96 / 122, 11589 x 6656 142 91 / 114, 22706 x 4224 91 66 / 80; with more of the
 // second round 27288 x 3712 107 80 / 74, 25208 x 6656 124 115 / 99; at 2 bits 11232 x 4480 190 74 / 64), otherwise where no more

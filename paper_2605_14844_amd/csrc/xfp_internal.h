@@ -37,7 +37,7 @@ struct DecodeArgs {
     uint32_t fuse_half;
     uint32_t y_bf16;       // the 16-bit output type is bf16 instead of fp16
     uint32_t x_bf16;       // x holds bf16 values; every kernel converts them to fp16 as it loads them
-    const uint16_t *gscale;   // V2a with a scale and a mid-point per group (general kernel only): fp16 [E][N][K/128]
+    const uint16_t *gscale;   // V2a with a scale and a mid-point per group: fp16 [E][N][K/128]
     const uint16_t *gmid;
 };
 
@@ -61,9 +61,9 @@ struct XCopies {
 };
 // The prompt kernel's copies, [k][tokens] and [token][k], of as many tokens as fit.  They are 64 MB and apart from the
 // workspaces, in code objects of their own (xfp_workspace_prompt.hip, xfp_workspace_prompt_static.hip): the runtime loads
-// a code object, and with it its static arrays, when something in it is first asked for, so a process that sends no
-// prompts does not hold them.  (Half of it would do at 1024 tokens of 8192 columns a launch: 28672 x 8192, 2048 tokens
-// 1.31 ms, twice 1024 1.50: three and a half rounds of tiles, which take the time of four.)
+// a code object, and with it its static arrays, when something in it is first asked for, so a process that sends neither
+// prompts nor batches of more than 64 tokens does not hold them.  (Half of it would do at 1024 tokens of 8192 columns a launch:
+// 28672 x 8192, 2048 tokens 1.16 ms, twice 1024 1.42: three and a half rounds of tiles, which take the time of four.)
 constexpr uint64_t kGemmHalves = 1ull << 24;       // 2048 tokens of 8192 columns
 struct PromptCopies {
     uint16_t xt[kGemmHalves];
@@ -148,8 +148,8 @@ bool wide_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
                    uint64_t copy_cap = (uint64_t)kXtMaxK * kXtTokens);
 hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, float *sx,
                               hipStream_t s);
-// Resident kernel: up to 64 tokens of one matrix, the activations in LDS (2 to 4 bits; mode 2 = V2a with a scale and a
-// mid-point per group).  few_tokens: how many of `left` tokens it takes next, 0 where another kernel is faster; plane, part:
+// Resident kernel: up to 64 tokens of one matrix, the activations in LDS (2 to 4 bits, mode 2 = V2a with a scale and a
+// mid-point per group; V2 at 5 and 6 bits).  few_tokens: how many of `left` tokens it takes next, 0 where another kernel is faster; plane, part:
 // the scratch plane for the sums of several slices of K (few_is_sliced), in floats.
 int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane, bool general);
 bool few_is_sliced(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M);
