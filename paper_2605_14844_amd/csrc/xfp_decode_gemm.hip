@@ -72,6 +72,12 @@ struct GemmTile {
     template <int BITS> static constexpr int kLoop = kTiles + NW * IBUF * kWordBlock<BITS>;
     template <int BITS> static constexpr int kBase = kPlane > kSums ? (kLoop<BITS> > kPlane ? kLoop<BITS> : kPlane) : (kLoop<BITS> > kSums ? kLoop<BITS> : kSums);
     static constexpr int kIds = BN * 64;                       // ids of 64 groups
+    static constexpr bool ROOM = NW <= 8;                      // registers for more than the loop needs
+    // A step's VALU work is dealt out between its matrix instructions, which 64 columns of tokens need (4096 x 4096, 333 tokens, 3
+    // bits 37 us in the compiler's order, 34); with 128 the chip's power sets the pace and the compiler's order is the better one
+    // (11008 x 4096, 2 bits, 700 tokens 139 us, 144 dealt out; 28672 x 8192, 4 bits, 2048 tokens 971 / 990 without outliers).
+    static constexpr bool DEAL = TB <= 2;
+    static constexpr bool EARLY = NW <= 8 && DEAL;             // there are registers for what is asked for ahead of its use
     static constexpr bool FINE = NW <= 8;                      // takes short rows (half blocks as chains)
     static constexpr bool DEEP = WK > 1 && NW <= 8;            // a third set of sums for long rows
     static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && BN % NW == 0, "");
@@ -117,6 +123,7 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     static_assert(MODE == 0 || MODE == 1, "V2, V2a");
     constexpr int BN = C::BN, BM = C::BM, RB = C::RB, TB = C::TB, WK = C::WK, NW = C::NW;
     constexpr int CB = C::KB / 8;                              // 16-byte chunks of a row of a part
+    constexpr bool DEAL = C::DEAL, EARLY = C::EARLY;
     extern __shared__ __align__(256) unsigned char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
     const DecodeArgs &a = ga.a;
@@ -238,45 +245,107 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             load_to_lds(dst + e * 1024, boff[e], rx, so);
         if (e1 == C::ND) bload = bload + 1 == C::NBUF ? 0 : bload + 1;
     };
-    words_t<BITS> cw[RB];                                      // the words of the turn whose A operands are being made
-    uint32_t wcur = 0;                                         // slot of the block they are of
-    auto planes = [&](uint32_t t) {                            // the lane's codebooks for the wave's t-th block
-        const bool dead = 2 * (t * WK + wk) + h >= G;          // second half of the last block of a row with an odd number of groups
+    words_t<BITS> cw[RB], cn[RB];                              // the words of the turn whose A operands are being made; of the next
+    uint32_t wcur = 0;                                         // slot of the block that cn is of
+    uint32_t at_book[RB];                                      // V2a: where the codebooks of the wave's next block lie
+    auto find_books = [&](uint32_t t) {                        // of the wave's t-th block
+        if constexpr (MODE == 1) {
+            const bool dead = 2 * (t * WK + wk) + h >= G;      // second half of the last block of a row with an odd number of groups
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            if constexpr (MODE == 1) {
+            for (int rb = 0; rb < RB; ++rb) {
                 const uint32_t id = *(lds_cu8_t *)(uintptr_t)(ids + (row[rb] - n0) * 64 + ((2 * (t * WK + wk) + h) & 63u));
-                const uint32_t o = lds0 + C::template kBase<BITS> + (dead ? a.L : id) * (2u << BITS);
-#pragma unroll
-                for (int d = 0; d < Planes<BITS>::ND; ++d) {
-                    P[rb].lo[d] = *(lds_cu32_t *)(uintptr_t)(o + d * 4);
-                    P[rb].hi[d] = *(lds_cu32_t *)(uintptr_t)(o + (Planes<BITS>::ND + d) * 4);
-                }
-            } else if (dead) {                                 // (such a block is the wave's last)
-#pragma unroll
-                for (int d = 0; d < Planes<BITS>::ND; ++d) P[rb].lo[d] = P[rb].hi[d] = 0u;
+                at_book[rb] = lds0 + C::template kBase<BITS> + (dead ? a.L : id) * (2u << BITS);
             }
         }
     };
-    auto take = [&](int p) {                                   // turn p's words
+    Planes<BITS> Pn[MODE == 1 ? RB : 1];
+    auto read_books = [&] {
+        if constexpr (MODE == 1) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                if constexpr (BITS == 2) {
+                    const u32x2_t v = *(lds_cu2_t *)(uintptr_t)at_book[rb];
+                    Pn[rb].lo[0] = v[0]; Pn[rb].hi[0] = v[1];
+                } else {
+                    uint32_t v[2 * Planes<BITS>::ND];
+#pragma unroll
+                    for (int d = 0; d < Planes<BITS>::ND / 2; ++d) {
+                        const u32x4_t q = *(lds_cu4_t *)(uintptr_t)(at_book[rb] + d * 16);
+                        v[4 * d] = q[0]; v[4 * d + 1] = q[1]; v[4 * d + 2] = q[2]; v[4 * d + 3] = q[3];
+                    }
+#pragma unroll
+                    for (int d = 0; d < Planes<BITS>::ND; ++d) { Pn[rb].lo[d] = v[d]; Pn[rb].hi[d] = v[Planes<BITS>::ND + d]; }
+                }
+            }
+        }
+    };
+    auto next_books = [&](uint32_t t) {                        // from here on the A operands are the t-th block's
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            if constexpr (MODE == 1) P[rb] = Pn[rb];
+            else if (2 * (t * WK + wk) + h >= G)               // (such a block is the wave's last)
+#pragma unroll
+                for (int d = 0; d < Planes<BITS>::ND; ++d) P[rb].lo[d] = P[rb].hi[d] = 0u;
+        }
+    };
+    auto read_words = [&](int p) {                             // turn p's words, as they are
         const uint32_t o = ring + wcur * C::template kWordBlock<BITS> + i * (32 * BITS);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const uint32_t w = o + rb * (1024 * BITS);
-            if constexpr (BITS == 4) cw[rb] = *(lds_cu4_t *)(uintptr_t)(w + turned(4 * h + p, i) * 16);
+            if constexpr (BITS == 4) cn[rb] = *(lds_cu4_t *)(uintptr_t)(w + turned(4 * h + p, i) * 16);
             else if constexpr (BITS == 3) {
 #pragma unroll
-                for (int d = 0; d < 3; ++d) cw[rb][d] = *(lds_cu32_t *)(uintptr_t)(w + h * 48 + p * 12 + d * 4);
-            } else cw[rb] = *(lds_cu2_t *)(uintptr_t)(w + turned(2 * h + p / 2, i) * 16 + p % 2 * 8);
+                for (int d = 0; d < 3; ++d) cn[rb][d] = *(lds_cu32_t *)(uintptr_t)(w + h * 48 + p * 12 + d * 4);
+            } else cn[rb] = *(lds_cu2_t *)(uintptr_t)(w + turned(2 * h + p / 2, i) * 16 + p % 2 * 8);
+        }
+    };
+    auto next_words = [&] {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            cw[rb] = cn[rb];
             arrange<BITS>(cw[rb]);
         }
     };
 
+    // The outliers of the tile's rows (the term itself comes last): the rows' first entries and the first batch's entries are asked
+    // for in front of the main loop.
+    constexpr int GL = BM / 8, RP = 64 / GL, RW = BN / NW;     // lanes of a row; rows of a wave at a time, in all
+    static_assert((GL == 4 || GL == 8 || GL == 16) && RW % RP == 0 && RW < 64, "");
+    const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
+    const int32_t ofirst = rp[min(n0, N)], olast = rp[min(n0 + BN, N)];
+    const bool outliers = a.col && ofirst < olast;
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + ofirst), 0, outliers ? (olast - ofirst) * 4 : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + ofirst), 0, outliers ? (olast - ofirst) * 2 : 0, 0x00020000);
+    const uint32_t oo = lane % GL, orow = lane / GL;
+    int32_t rpv = 0;                                           // lane r: first entry of row r
+    auto first_of = [&](uint32_t r) { return __builtin_amdgcn_ds_bpermute((int)(min(r, (uint32_t)RW) * 4), rpv); };
+    int32_t oe = 0, oend = 0;                                  // this lane's row: first entry of the batch, end of the row
+    uint32_t oc = 0, ov = 0;
+    auto entries = [&] {                                       // (past the tile's entries: zeros)
+        oc = __builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(oe + (int32_t)oo - ofirst) * 4, 0, 0);
+        ov = __builtin_amdgcn_raw_buffer_load_b16(rv, (uint32_t)(oe + (int32_t)oo - ofirst) * 2, 0, 0);
+    };
+
+    auto first_entries = [&] {
+        if (!EARLY) rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];
+        oe = first_of(orow);
+        oend = first_of(orow + 1);
+        entries();
+    };
+
     // ---------------------------------------------------------------- prologue: as if the turns before the first had run
-    half8_t af[4][RB], bf[2][TB];
-    auto dequantise = [&](int s) {
+    u32x4_t af[4][RB];
+    half8_t bf[2][TB];
+    auto dequantise = [&](int s, int part) {                   // half of a step's A operand
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) af[s][rb] = __builtin_bit_cast(half8_t, chunk<BITS>(P[rb], cw[rb], s));
+        for (int rb = 0; rb < RB; ++rb) {
+            uint32_t d0, d1;
+            chunk_half<BITS>(P[rb], cw[rb], s, part, d0, d1);
+            if constexpr (EARLY) asm volatile("" : "+v"(d0), "+v"(d1));     // (here and not in front of its use)
+            af[s][rb][2 * part] = d0;
+            af[s][rb][2 * part + 1] = d1;
+        }
     };
     const uint32_t br = lds0 + i * C::RSB + (((wk * (2 * C::SP) + h) ^ swz<CB>(i)) * 16);
     auto operands = [&](int set, uint32_t buf, int s) {
@@ -284,25 +353,38 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) bf[set][tb] = *(lds_ch8_t *)(uintptr_t)(ba + tb * (32 * C::RSB));
     };
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if constexpr (MODE == 1) load_ids(0);
+    if constexpr (EARLY) rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];
 #pragma unroll
     for (int b = 0; b < C::IBUF - 1; ++b) load_words(b);
 #pragma unroll
     for (int q = 0; q < C::AHEAD; ++q) load_b(q, 0, C::ND);
+    if constexpr (MODE == 1) load_ids(0);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    planes(0);
-    take(0);
+    if constexpr (EARLY) first_entries();                   // (older than every load that is waited for below)
+    find_books(0);
+    read_books();
+    next_books(0);
+    read_words(0);
+    next_words();
 #pragma unroll
-    for (int s = 0; s < 3; ++s) dequantise(s);
+    for (int s = 0; s < 3; ++s) {
+        dequantise(s, 0);
+        dequantise(s, 1);
+    }
     operands(0, 0, 0);
 
     // ---------------------------------------------------------------- main loop
     // A block is four turns of four steps.  In step s the B operands of step s + 1 are read, the A operands of the next
-    // turn's step s - 1 are made (their registers were read by the step before) and the matrix instructions run.  The
-    // barrier that opens the next part stands in front of a part's last step, whose matrix instructions then cover the
-    // first reads behind it; the loads that refill a ring slot follow the barrier behind its last reads.
+    // turn's step s - 1 are made (their registers were read by the step before) and the matrix instructions run, with the
+    // other work of the step dealt out between them: an instruction of 32 x 32 x 16 keeps the matrix core for 32 clocks, in
+    // which a wave's VALU instructions run, but one that follows it at once only waits, and so does the other wave of the SIMD,
+    // which the barriers keep in step (figures: GemmTile::DEAL).  The barrier that opens the next part stands behind the first matrix instruction of a
+    // part's last step; the loads that refill a ring slot follow the barrier behind its last reads.
     uint32_t bcur = 0;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) acc[rb][tb] = float16_t{};
     auto add = [&] {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
@@ -318,16 +400,24 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
                 sum[rb][tb] = float16_t{};
             }
     };
-    auto block = [&](uint32_t t) {
-        const bool on = WK == 1 || t * WK + wk < NB;           // (the last round of a row may have no block for this wave)
+    auto wait_part = [&](auto part) {
+        // The part behind part x of a block, requested AHEAD parts ago.  Younger: the parts requested since, and a block's words if
+        // they have been since its last load (they come in the second step of a block).
+        constexpr int x = decltype(part)::value, from = x + 1 - C::AHEAD + (C::SP == 4 ? 1 : 0);           // first part whose words are younger
+        constexpr bool words = from <= 0 || (from > x ? false : from % (4 * C::U) == 0);
+        constexpr int kYounger = (C::AHEAD - 1) * C::ND + (words && from <= x ? kWords : 0);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kYounger) : "memory");
+    };
+    // In the compiler's order (one wave per row and column: it has every block).
+    auto compiled_block = [&](uint32_t t) {
         for_each<16>([&](auto step) {
-            constexpr int p = decltype(step)::value / 4, s = decltype(step)::value % 4;        // turn, step in it
-            constexpr int x = p * C::U + s / C::SP;            // part of the block
-            constexpr bool last = s % C::SP == C::SP - 1;      // of the part
+            constexpr int p = decltype(step)::value / 4, s = decltype(step)::value % 4;
+            constexpr int x = p * C::U + s / C::SP;
+            constexpr bool last = s % C::SP == C::SP - 1;
             const uint32_t bnext = bcur + 1 == C::NBUF ? 0 : bcur + 1;
-            constexpr int set = s & 1;                         // where the step's operands are
+            constexpr int set = s & 1;
             if constexpr (C::FINE && p == 2 && s == 0)
-                if (ga.fine && on) {
+                if (ga.fine) {
                     add();
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb)
@@ -336,47 +426,107 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
                 }
             load_b(t * (4 * C::U) + x + C::AHEAD, s % C::SP * C::ND / C::SP, (s % C::SP + 1) * C::ND / C::SP);
             if constexpr (!last) operands(set ^ 1, bcur, s + 1);
-            if constexpr (s == 0) dequantise(3);
+            if constexpr (s == 0) {
+                dequantise(3, 0);
+                dequantise(3, 1);
+            }
             if constexpr (s == 1) {
                 if constexpr (p == 0) load_words(t + C::IBUF - 1);
-                if constexpr (p == 3) {                        // the next block's words, older than the part that the last wait was for
+                if constexpr (p == 3) {
                     wcur = wcur + 1 == C::IBUF ? 0 : wcur + 1;
-                    planes(t + 1);
-                    take(0);
-                } else {
-                    take(p + 1);
+                    find_books(t + 1);
+                    read_books();
+                    next_books(t + 1);
                 }
+                read_words((p + 1) % 4);
+                next_words();
             }
-            // the ids of the next 64 groups, behind the barrier that every wave passes after its last use of the old ones; two
-            // more barriers follow before their first use
             if constexpr (MODE == 1 && p == 1 && s == 0)
                 if ((t + 1) * (2 * WK) % 64 == 0 && t + 1 < NS) load_ids((t + 1) * (2 * WK));
             if constexpr (last) {
-                // The next part, requested AHEAD parts ago.  Younger: the parts requested since, and a block's words if
-                // they have been since its last load (they come in the second step of a block).
-                constexpr int from = x + 1 - C::AHEAD + (C::SP == 4 ? 1 : 0);                  // first part whose words are younger
-                constexpr bool words = from <= 0 || (from > x ? false : from % (4 * C::U) == 0);
-                constexpr int kYounger = (C::AHEAD - 1) * C::ND + (words && from <= x ? kWords : 0);
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kYounger) : "memory");
+                wait_part(std::integral_constant<int, x>{});
                 operands(set ^ 1, bnext, (s + 1) % 4);
             }
-            if constexpr (s > 0) dequantise(s - 1);
-            if (on)
+            if constexpr (s > 0) {
+                dequantise(s - 1, 0);
+                dequantise(s - 1, 1);
+            }
 #pragma unroll
-                for (int tb = 0; tb < TB; ++tb)
+            for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-                    for (int rb = 0; rb < RB; ++rb)
-                        acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[s][rb], bf[set][tb], p + s == 0 ? float16_t{} : acc[rb][tb], 0, 0, 0);
+                for (int rb = 0; rb < RB; ++rb)
+                    acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, af[s][rb]), bf[set][tb], p + s == 0 ? float16_t{} : acc[rb][tb], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (last) bcur = bnext;
         });
-        if (on) add();
-        if constexpr (C::DEEP)
-            if (ga.deep && t % 8 == 7) fold();
+        add();
+    };
+    // MAYBE: the wave may have no such block (the last round of a row)
+    auto block = [&](auto maybe, uint32_t t) {
+        const bool on = !decltype(maybe)::value || t * WK + wk < NB;
+        for_each<16>([&](auto step) {
+            constexpr int p = decltype(step)::value / 4, s = decltype(step)::value % 4;        // turn, step in it
+            constexpr int x = p * C::U + s / C::SP;            // part of the block
+            constexpr bool last = s % C::SP == C::SP - 1;      // of the part
+            const uint32_t bnext = bcur + 1 == C::NBUF ? 0 : bcur + 1;
+            constexpr int set = s & 1;                         // where the step's operands are
+            constexpr bool fresh = p + s == 0 || (C::FINE && p == 2 && s == 0);            // half blocks are chains of their own
+            load_b(t * (4 * C::U) + x + C::AHEAD, s % C::SP * C::ND / C::SP, (s % C::SP + 1) * C::ND / C::SP);
+            if constexpr (!last) operands(set ^ 1, bcur, s + 1);
+            // the next turn's words and its books (older than the part that the last wait was for)
+            if constexpr (p == 2 && s == 2 && EARLY) find_books(t + 1);
+            if constexpr (s == (EARLY ? 0 : 1)) {
+                if constexpr (p == 3) {
+                    wcur = wcur + 1 == C::IBUF ? 0 : wcur + 1;
+                    if constexpr (!EARLY) find_books(t + 1);
+                    read_books();
+                }
+                read_words((p + 1) % 4);
+            }
+            if constexpr (p == 0 && s == 1) load_words(t + C::IBUF - 1);
+            // the ids of the next 64 groups, behind the barrier that every wave passes after its last use of the old ones; another
+            // barrier follows before their first use
+            if constexpr (MODE == 1 && p == 1 && s == 0)
+                if ((t + 1) * (2 * WK) % 64 == 0 && t + 1 < NS) load_ids((t + 1) * (2 * WK));
+            for_each<TB>([&](auto token_block) {
+                constexpr int tb = decltype(token_block)::value;
+                if constexpr (fresh)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) {
+                        asm volatile("" : "+v"(acc[rb][tb]));          // (the additions stay here)
+                        sum[rb][tb] += acc[rb][tb];
+                        acc[rb][tb] = float16_t{};
+                        asm volatile("" : "+v"(sum[rb][tb]));
+                    }
+                if (on)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+                        acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, af[s][rb]), bf[set][tb], acc[rb][tb], 0, 0, 0);
+                if constexpr (s == 1 && tb == 0) {
+                    if constexpr (p == 3) next_books(t + 1);
+                    next_words();
+                }
+                dequantise((s + 3) % 4, tb);
+                if constexpr (TB == 1) dequantise((s + 3) % 4, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (last && tb == 0) {
+                    wait_part(std::integral_constant<int, x>{});
+                    operands(set ^ 1, bnext, (s + 1) % 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+            if constexpr (C::DEEP && p + s == 0)
+                if (ga.deep && t && t % 8 == 0) fold();
+            if constexpr (last) bcur = bnext;
+        });
     };
 #pragma unroll 1
-    for (uint32_t t = 0; t < NS; ++t) block(t);
+    for (uint32_t t = 0; t + (WK > 1) < NS; ++t)
+        if constexpr (DEAL) block(std::false_type{}, t);
+        else compiled_block(t);
+    if constexpr (WK > 1) block(std::true_type{}, NS - 1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // (loads to LDS that nobody waits for)
+    if constexpr (DEAL) add();
     if constexpr (C::DEEP)
         if (ga.deep) {
             fold();
@@ -421,63 +571,64 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     // from row to row: 28672 x 8192, 2048 tokens 309 us of 1366 at 0.3 % outliers, 165 at 0.05 %; 4096 x 1024, 256 tokens 6.)
     // A row's entries are fetched GL at a time, one per lane, and handed to its lanes one by one (row_newbcast); a sum is
     // taken per GL entries and those are added up.
-    const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
-    const int32_t ob = rp[min(n0, N)], oe = rp[min(n0 + BN, N)];
-    if (a.col && ob < oe) {
+    if (outliers) {
+        if constexpr (!EARLY) first_entries();
         lds_barrier();                                         // every wave is past its tiles (and sums)
-        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + ob), 0, (oe - ob) * 4, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + ob), 0, (oe - ob) * 2, 0x00020000);
-        constexpr int GL = BM / 8, RP = 64 / GL, RW = BN / NW;
-        static_assert((GL == 8 || GL == 16) && RW % RP == 0 && RW < 64, "");
         const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc((void *)ga.xt, 0, K * ga.MP * 2, 0x00020000);
-        const uint32_t o = lane % GL, rr = lane / GL, octet = min(m0 + 8 * o, ga.MP - 8) * 2, plane = lds0 + wave * (RW * BM * 4) + rr * (BM * 4) + o * 32;
-        const int32_t rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];         // lane r: first entry of row r
-        auto first_of = [&](uint32_t r) { return __builtin_amdgcn_ds_bpermute((int)(min(r, (uint32_t)RW) * 4), rpv); };
+        const uint32_t octet = min(m0 + 8 * oo, ga.MP - 8) * 2, plane = lds0 + wave * (RW * BM * 4) + orow * (BM * 4) + oo * 32;
         // lane k of every row's lanes to all of them
         auto deal = [&](auto k, uint32_t v) -> uint32_t {
             constexpr int kk = decltype(k)::value;
-            if constexpr (GL == 16) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + kk, 0xf, 0xf, true);
+            if constexpr (GL == 4) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kk * 0x55, 0xf, 0xf, true);
+            else if constexpr (GL == 16) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + kk, 0xf, 0xf, true);
             else
-                return (uint32_t)__builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + kk, 0xf, 0x3, false),
+                return (uint32_t)__builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + kk, 0xf, 0xf, true),
                                                              (int)v, 0x158 + kk, 0xf, 0xc, false);
         };
+        // A batch: GL entries of each of RP rows.  begin() asks for the next batch's entries, then for this one's activations;
+        // finish() adds them.
+        struct Batch {
+            int32_t at, to;                                    // its first entry, the end of the row
+            bool more;                                         // of any of the rows
+            uint32_t row, val;
+        };
         uint32_t r0 = 0;
-        int32_t e = first_of(rr), e1 = first_of(rr + 1);
-        // (past the tile's entries: zeros)
-        uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(e + (int32_t)o - ob) * 4, 0, 0),
-                 v = __builtin_amdgcn_raw_buffer_load_b16(rv, (uint32_t)(e + (int32_t)o - ob) * 2, 0, 0);
-        float total[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (;;) {
+        auto begin = [&](Batch &b, u32x4_t (&x)[GL]) {
+            asm volatile("" : "+v"(oc), "+v"(ov));             // (waited for here, whatever the lane has)
             // an entry that is not there: a place past the copy, which reads as zeros, times zero
-            const bool have = e + (int32_t)o < e1;
-            const uint32_t off = have ? __umul24(c, ga.MP * 2) : 0x80000000u, val = __builtin_bit_cast(uint32_t, half_bits_to_float((uint16_t)(have ? v : 0u)));
-            const int32_t at = e, to = e1;
-            const bool more = __builtin_amdgcn_ballot_w64(e + GL < e1) != 0;
-            const uint32_t row = r0;
-            if (more) e += GL;
+            const bool have = oe + (int32_t)oo < oend;
+            const uint32_t off = have ? __umul24(oc, ga.MP * 2) : 0x80000000u;
+            b.val = __builtin_bit_cast(uint32_t, half_bits_to_float((uint16_t)(have ? ov : 0u)));
+            b.at = oe;
+            b.to = oend;
+            b.more = __builtin_amdgcn_ballot_w64(oe + GL < oend) != 0;
+            b.row = r0;
+            if (b.more) oe += GL;
             else {
                 r0 += RP;
-                e = first_of(r0 + rr);
-                e1 = first_of(r0 + rr + 1);
+                oe = first_of(r0 + orow);
+                oend = first_of(r0 + orow + 1);
             }
-            c = __builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(e + (int32_t)o - ob) * 4, 0, 0);
-            v = __builtin_amdgcn_raw_buffer_load_b16(rv, (uint32_t)(e + (int32_t)o - ob) * 2, 0, 0);
-            u32x4_t x[GL];
+            entries();
+            // (two batches under way: always all of them, so that the wait for the entries knows how many loads are younger)
             for_each<GL / 4>([&](auto q) {
                 constexpr int k0 = 4 * decltype(q)::value;
-                if (__builtin_amdgcn_ballot_w64(at + k0 < to))
+                if (GL <= 8 || __builtin_amdgcn_ballot_w64(b.at + k0 < b.to))
                     for_each<4>([&](auto k) {
                         constexpr int kk = k0 + decltype(k)::value;
                         x[kk] = __builtin_amdgcn_raw_buffer_load_b128(rt, deal(std::integral_constant<int, kk>{}, off) + octet, 0, 0);
                     });
             });
+        };
+        float total[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        auto finish = [&](const Batch &b, const u32x4_t (&x)[GL]) {
             float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             for_each<GL / 4>([&](auto q) {
                 constexpr int k0 = 4 * decltype(q)::value;
-                if (__builtin_amdgcn_ballot_w64(at + k0 < to))
+                if (__builtin_amdgcn_ballot_w64(b.at + k0 < b.to))
                     for_each<4>([&](auto k) {
                         constexpr int kk = k0 + decltype(k)::value;
-                        const float w = __builtin_bit_cast(float, deal(std::integral_constant<int, kk>{}, val));
+                        const float w = __builtin_bit_cast(float, deal(std::integral_constant<int, kk>{}, b.val));
 #pragma unroll
                         for (int t = 0; t < 8; ++t)
                             s[t] = fmaf(w, half_bits_to_float((uint16_t)(t & 1 ? x[kk][t / 2] >> 16 : x[kk][t / 2])), s[t]);
@@ -485,12 +636,34 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
             });
 #pragma unroll
             for (int t = 0; t < 8; ++t) total[t] += s[t];
-            if (more) continue;
-            *(lds_f4_t *)(uintptr_t)(plane + row * (BM * 4)) = float4_t{total[0], total[1], total[2], total[3]};
-            *(lds_f4_t *)(uintptr_t)(plane + row * (BM * 4) + 16) = float4_t{total[4], total[5], total[6], total[7]};
-            if (r0 >= (uint32_t)RW) break;
+            if (b.more) return;
+            *(lds_f4_t *)(uintptr_t)(plane + b.row * (BM * 4)) = float4_t{total[0], total[1], total[2], total[3]};
+            *(lds_f4_t *)(uintptr_t)(plane + b.row * (BM * 4) + 16) = float4_t{total[4], total[5], total[6], total[7]};
 #pragma unroll
             for (int t = 0; t < 8; ++t) total[t] = 0.f;
+        };
+        auto last = [&](const Batch &b) { return !b.more && r0 >= (uint32_t)RW; };
+        if constexpr (GL <= 8 && EARLY) {
+            // two batches' activations under way (registers)
+            Batch b0, b1;
+            u32x4_t x0[GL], x1[GL];
+            begin(b0, x0);
+            for (;;) {
+                if (last(b0)) { finish(b0, x0); break; }
+                begin(b1, x1);
+                finish(b0, x0);
+                if (last(b1)) { finish(b1, x1); break; }
+                begin(b0, x0);
+                finish(b1, x1);
+            }
+        } else {
+            for (;;) {
+                Batch b;
+                u32x4_t x[GL];
+                begin(b, x);
+                finish(b, x);
+                if (last(b)) break;
+            }
         }
         lds_barrier();
         if (wk == 0)
@@ -629,8 +802,9 @@ hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
     //   2048: 212 / 181 (1024) / 119 (256)
     //   8192 x 8192, 256 tokens: 95 (512) / 84 (256) / 155 (64); 512: 177 / 151 (512) / 157 (128); 700: 256 / 216 (704) / 169 (192)
     //   2048 x 28672, 512 tokens: 143 (256) / 237 (128) / 463 (32); 28672 x 8192, 512 tokens: 610 / 511 (1792) / 346 (448)
+    // (Four parts in the ring of Small, three of them requested ahead: 4096 x 4096, 333 tokens, 3 bits 34 us with three, 32.7 with four.)
     using Large = GemmTile<1, 4, 8, 1, 4, 3, 2>;
-    using Small = GemmTile<1, 2, 4, 2, 4, 3, BITS == 4 ? 2 : 3>;
+    using Small = GemmTile<1, 2, 4, 2, 4, 4, BITS == 4 ? 2 : 3>;
     using Small16 = GemmTile<1, 2, 4, 4, 2, 3, 2>;
     // (parts of a whole turn where the index words leave LDS for three, 2 and 3 bits: with parts of half a turn the waves met twice
     // as often, us without outliers 287 x 10880, 3 bits, 458 tokens 49.4 / 45.8, 1908 x 7168, 2 bits, 310 31.9 / 30.7, with 0.05 %

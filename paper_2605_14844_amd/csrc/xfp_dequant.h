@@ -71,15 +71,14 @@ __device__ __forceinline__ void arrange(words_t<BITS> &w)
     }
 }
 
-// Chunk c (0..3) of a run of 32: slots 8 c .. 8 c + 7 as fp16 pairs.
+// Half of chunk c (0..3) of a run of 32: slots 8 c + 4 half .. 8 c + 4 half + 3 as fp16 pairs.
 template <int BITS>
-__device__ __forceinline__ u32x4_t chunk(const Planes<BITS> &P, const words_t<BITS> &w, int c)
+__device__ __forceinline__ void chunk_half(const Planes<BITS> &P, const words_t<BITS> &w, int c, int half, uint32_t &d0, uint32_t &d1)
 {
-    uint32_t d0, d1, d2, d3;
     if constexpr (BITS == 4) {
         const uint32_t v = w[c], kTop = 0x03020100u;
-        four<4>(P, v & 0x07070707u, ((v >> 1) & 0x04040404u) | kTop, d0, d1);
-        four<4>(P, (v >> 4) & 0x07070707u, ((v >> 5) & 0x04040404u) | kTop, d2, d3);
+        if (half == 0) four<4>(P, v & 0x07070707u, ((v >> 1) & 0x04040404u) | kTop, d0, d1);
+        else four<4>(P, (v >> 4) & 0x07070707u, ((v >> 5) & 0x04040404u) | kTop, d0, d1);
     } else if constexpr (BITS == 3) {
         auto sel = [&](int k0) -> uint32_t {
             switch (k0) {
@@ -93,14 +92,19 @@ __device__ __forceinline__ u32x4_t chunk(const Planes<BITS> &P, const words_t<BI
             default: return (w[2] >> 5) & 0x07070707u;
             }
         };
-        four<3>(P, sel(2 * c), 0u, d0, d1);
-        four<3>(P, sel(2 * c + 1), 0u, d2, d3);
+        four<3>(P, sel(2 * c + half), 0u, d0, d1);
     } else {
-        const uint32_t v = w[c >> 1];
-        const int s = 4 * (c & 1);
-        four<2>(P, (v >> s) & 0x03030303u, 0u, d0, d1);
-        four<2>(P, (v >> (s + 2)) & 0x03030303u, 0u, d2, d3);
+        four<2>(P, (w[c >> 1] >> (4 * (c & 1) + 2 * half)) & 0x03030303u, 0u, d0, d1);
     }
+}
+
+// The whole chunk.
+template <int BITS>
+__device__ __forceinline__ u32x4_t chunk(const Planes<BITS> &P, const words_t<BITS> &w, int c)
+{
+    uint32_t d0, d1, d2, d3;
+    chunk_half<BITS>(P, w, c, 0, d0, d1);
+    chunk_half<BITS>(P, w, c, 1, d2, d3);
     return u32x4_t{d0, d1, d2, d3};
 }
 
