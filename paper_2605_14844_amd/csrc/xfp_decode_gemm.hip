@@ -100,6 +100,8 @@ __device__ __forceinline__ uint32_t swz(uint32_t r)
     else return (r / (16 / C)) & (uint32_t)(C - 1);
 }
 
+constexpr uint64_t kCopyHalves = (uint64_t)kXtMaxK * kXtTokens;        // of a workspace's copies
+
 struct GemmArgs {
     DecodeArgs a;
     const uint16_t *xp;    // [M][K rounded up to 256] fp16, every block of 256 columns in the order of the kernel's steps
@@ -118,7 +120,7 @@ template <int n, class F>
 __device__ __forceinline__ void for_each(F &&f) { for_each_of(f, std::make_integer_sequence<int, n>{}); }
 
 template <int BITS, int MODE, class C>
-__global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(GemmArgs ga)
+__device__ __forceinline__ void tile_product(const GemmArgs &ga)
 {
     static_assert(MODE == 0 || MODE == 1, "V2, V2a");
     constexpr int BN = C::BN, BM = C::BM, RB = C::RB, TB = C::TB, WK = C::WK, NW = C::NW;
@@ -708,6 +710,19 @@ __global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(Gem
     }
 }
 
+template <int BITS, int MODE, class C>
+__global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_gemm_kernel(GemmArgs ga)
+{
+    tile_product<BITS, MODE, C>(ga);
+}
+
+// Up to 32 tokens of many rows: the same product in tiles of 32 tokens (launch_wide_tiles).
+template <int BITS, int MODE, class C>
+__global__ __launch_bounds__(C::T, C::kWavesPerSimd) void decode_wide_tiles_kernel(GemmArgs ga)
+{
+    tile_product<BITS, MODE, C>(ga);
+}
+
 // The two copies of the activations.  Blocks [0, nb): xp, one thread per (token, run of 32 columns).  The rest: xt, a
 // block per tile of 64 columns x 64 tokens, through LDS.  bf16 activations are converted to fp16 on the way.
 template <int BITS>
@@ -772,7 +787,9 @@ __global__ __launch_bounds__(256) void relayout_x_gemm_kernel(const uint16_t *x,
 template <int BITS, int MODE, class C>
 hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
 {
-    auto kern = decode_gemm_kernel<BITS, MODE, C>;
+    void (*kern)(GemmArgs);
+    if constexpr (C::BM == 32) kern = decode_wide_tiles_kernel<BITS, MODE, C>;
+    else kern = decode_gemm_kernel<BITS, MODE, C>;
     const int lds = C::template kBase<BITS> + (MODE == 1 ? ((int)((ga.a.L + 1) * (2u << BITS)) + 15) / 16 * 16 + C::kIds : 0);
     static_assert(C::template kBase<BITS> + (MODE == 1 ? (257 * (2 << BITS) + 15) / 16 * 16 + C::kIds : 0) <= 160 * 1024, "");
     ga.fine = ga.a.K <= kFineK || C::WK > 1;
@@ -793,6 +810,16 @@ hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
     return hipGetLastError();
 }
 
+// 128 rows x 64 tokens (four parts in the ring, three of them requested ahead: 4096 x 4096, 333 tokens, 3 bits 34 us with three, 32.7
+// with four), x 32; 64 x 64, in parts of a whole turn where the index words leave LDS for three, 2 and 3 bits (with parts of half a
+// turn the waves met twice as often, us without outliers 287 x 10880, 3 bits, 458 tokens 49.4 / 45.8, 1908 x 7168, 2 bits, 310
+// 31.9 / 30.7, with 0.05 % 326 x 16896, 3 bits, 475 78.5 / 72.8).
+template <int BITS>
+using SmallTile = GemmTile<1, 2, 4, 2, 4, 4, BITS == 4 ? 2 : 3>;
+using LowTile = GemmTile<1, 1, 4, 2, 4, 5, 3>;
+template <int BITS>
+using TinyTile = std::conditional_t<BITS == 4, GemmTile<1, 2, 2, 4, 2, 4, 2>, GemmTile<1, 2, 2, 4, 4, 3, 2>>;
+
 template <int BITS, int MODE>
 hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
 {
@@ -802,14 +829,10 @@ hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
     //   2048: 212 / 181 (1024) / 119 (256)
     //   8192 x 8192, 256 tokens: 95 (512) / 84 (256) / 155 (64); 512: 177 / 151 (512) / 157 (128); 700: 256 / 216 (704) / 169 (192)
     //   2048 x 28672, 512 tokens: 143 (256) / 237 (128) / 463 (32); 28672 x 8192, 512 tokens: 610 / 511 (1792) / 346 (448)
-    // (Four parts in the ring of Small, three of them requested ahead: 4096 x 4096, 333 tokens, 3 bits 34 us with three, 32.7 with four.)
     using Large = GemmTile<1, 4, 8, 1, 4, 3, 2>;
-    using Small = GemmTile<1, 2, 4, 2, 4, 4, BITS == 4 ? 2 : 3>;
+    using Small = SmallTile<BITS>;
     using Small16 = GemmTile<1, 2, 4, 4, 2, 3, 2>;
-    // (parts of a whole turn where the index words leave LDS for three, 2 and 3 bits: with parts of half a turn the waves met twice
-    // as often, us without outliers 287 x 10880, 3 bits, 458 tokens 49.4 / 45.8, 1908 x 7168, 2 bits, 310 31.9 / 30.7, with 0.05 %
-    // 326 x 16896, 3 bits, 475 78.5 / 72.8)
-    using Tiny = std::conditional_t<BITS == 4, GemmTile<1, 2, 2, 4, 2, 4, 2>, GemmTile<1, 2, 2, 4, 4, 3, 2>>;
+    using Tiny = TinyTile<BITS>;
     const uint64_t m = (ga.M + 63) / 64, small = (uint64_t)((ga.a.N + 127) / 128) * m;
     if ((uint64_t)((ga.a.N + 63) / 64) * m <= 256) return launch_gemm_t<BITS, MODE, Tiny>(ga, s);
     // (rows that ask for a third set of sums, in matrices that the 16-token kernel would cut into slices: see kDeepK)
@@ -821,27 +844,80 @@ hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
     return launch_gemm_t<BITS, MODE, Small>(ga, s);
 }
 
+// What both kinds of launch begin with: the arguments and the copies of the activations, of cap halves each.
 template <int BITS>
-hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, PromptCopies *xc, hipStream_t s)
+hipError_t prepare_gemm(GemmArgs &ga, const DecodeArgs &a, int M, bool y_f32, uint16_t *xp, uint16_t *xt, uint64_t cap, hipStream_t s)
 {
     const uint32_t runs = (a.K + 255) / 256 * 8;
-    GemmArgs ga;
     ga.a = a;
     ga.M = (uint32_t)M;
     ga.MP = (ga.M + 7) / 8 * 8;
-    if ((uint64_t)a.K * ga.MP > kGemmHalves || (uint64_t)ga.M * runs * 32 > kGemmHalves) return hipErrorInvalidValue;
-    ga.xp = xc->xb;
-    ga.xt = xc->xt;
+    if ((uint64_t)a.K * ga.MP > cap || (uint64_t)ga.M * runs * 32 > cap) return hipErrorInvalidValue;
+    ga.xp = xp;
+    ga.xt = xt;
     ga.y_f32 = (int)y_f32;
     const uint32_t nb = (uint32_t)(((uint64_t)ga.M * runs + 255) / 256), nt = a.col ? a.K / 64 * ((ga.M + 63) / 64) : 0u;
     hipLaunchKernelGGL(relayout_x_gemm_kernel<BITS>, dim3(nb + nt), dim3(256), 0, s, a.x, a.x_stride, ga.M, a.K, (int)a.x_bf16,
-                       xc->xb, xc->xt, ga.MP, nb);
-    hipError_t err = hipGetLastError();
+                       xp, xt, ga.MP, nb);
+    return hipGetLastError();
+}
+
+template <int BITS>
+hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, PromptCopies *xc, hipStream_t s)
+{
+    GemmArgs ga;
+    hipError_t err = prepare_gemm<BITS>(ga, a, M, y_f32, xc->xb, xc->xt, kGemmHalves, s);
     if (err != hipSuccess) return err;
     return mode == 1 ? launch_gemm_m<BITS, 1>(ga, s) : launch_gemm_m<BITS, 0>(ga, s);
 }
 
+template <int BITS, int MODE>
+hipError_t launch_wide_tiles_m(GemmArgs &ga, hipStream_t s)
+{
+    if (ga.M <= 32) return launch_gemm_t<BITS, MODE, LowTile>(ga, s);
+    return launch_gemm_t<BITS, MODE, SmallTile<BITS>>(ga, s);
+}
+
+template <int BITS>
+hipError_t launch_wide_tiles_b(int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
+{
+    GemmArgs ga;
+    hipError_t err = prepare_gemm<BITS>(ga, a, M, y_f32, xc->xb, xc->xt, kCopyHalves, s);
+    if (err != hipSuccess) return err;
+    return mode == 1 ? launch_wide_tiles_m<BITS, 1>(ga, s) : launch_wide_tiles_m<BITS, 0>(ga, s);
+}
+
 }  // namespace
+
+// 17 to 64 tokens of many rows, the 64-token kernel's, as one column of 128-row tiles: that kernel reads its activations from L2
+// once per 32 rows and a lookup per pair of weights from LDS, which is most of its time once the matrix is large.  A round of tiles
+// takes the same time for any number of them, so they have to fill most of the last one.  us in the 64-token kernel / in tiles (cold
+// weights, 0.3 % outliers; 1941 drawn shapes):
+//  - 28672 x 8192: 64 tokens, 3 bits, library 85 / 65, 4 bits 83 / 64; 32 tokens (tiles of 32), 3 bits 57 / 47, 4 bits 59 / 54;
+//    17 tokens, 2 bits 46 / 38; 32768 x 2048, 64 tokens 33 / 25; 26793 x 2048, 29 25 / 21;
+//  - less than three quarters of a round: 21764 x 2176, 45 tokens 25.4 / 24.2, 22800 x 6272, 20 up to 11 % slower; 14336 x 8192, 64
+//    42 / 54, 8192 x 4096 18 / 31;
+//  - more than 48 tokens pay from five eighths on (20500 to 22500 rows 2 to 37 % faster, 18500 to 20500 4 % slower to 30 % faster),
+//    rows of up to 1024 columns from half a round on (17000 x 768, 62 tokens 24 % faster);
+//  - behind whole rounds (1400 shapes of 33000 to 131072 rows): less than seven eighths of all rounds 7 % slower to 34 % faster for up
+//    to 48 tokens (50793 x 2176, 37: 4 % slower), 40933 x 5632, 54 tokens at 0.62 of two rounds 15 % slower; above these lines 5 %
+//    slower at most, 8 to 30 % faster at the median.
+bool prefer_wide_tiles(int mode, uint32_t N, uint32_t K, int M)
+{
+    const uint64_t m = (uint64_t)(M + 7) / 8 * 8, k = (uint64_t)(K + 255) / 256 * 256;
+    if (mode > 1 || M < 17 || m * k > kCopyHalves) return false;
+    const uint64_t tiles = ((uint64_t)N + 127) / 128, rounds = (tiles + 255) / 256;
+    const uint64_t least = rounds == 1 ? (M > 32 && K <= 1024 ? 8 : M > 48 ? 10 : 12) : (M > 32 && K <= 1024 ? 11 : M > 48 ? 13 : 14);
+    return tiles >= least * 16 * rounds;                       // sixteenths of all rounds
+}
+
+hipError_t launch_wide_tiles(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)
+{
+    if (!xc || mode < 0 || mode > 1) return hipErrorInvalidValue;
+    if (bits == 4) return launch_wide_tiles_b<4>(mode, a, M, y_f32, xc, s);
+    if (bits == 3) return launch_wide_tiles_b<3>(mode, a, M, y_f32, xc, s);
+    return launch_wide_tiles_b<2>(mode, a, M, y_f32, xc, s);
+}
 
 // What the kernel takes: V2 and V2a at 2 to 4 bits, more than 64 tokens (which calls prefer it: prefer_gemm).  Rows up to 65536 columns (an outlier's column is kept in 16 bits;
 // the copies of 256 tokens fit the workspace) and 128 rows and more: smaller matrices leave the chip to a few workgroups

@@ -631,6 +631,7 @@ hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bo
 {
     if (!xc || bits < 2 || bits > 4 || M < 1 || M > 64 || mode < 0 || mode > 2) return hipErrorInvalidValue;
     if (mode == 2 && (!sx || M > 16 || !a.gscale || !a.gmid)) return hipErrorInvalidValue;
+    if (prefer_wide_tiles(mode, a.N, a.K, M)) return launch_wide_tiles(bits, mode, a, M, y_f32, xc, s);
     const int T = (M + 15) / 16;
     const uint32_t nb = (a.K * 2 * (uint32_t)T + 255) / 256 + (a.K / 8 * 16 * (uint32_t)T + 255) / 256 +
                         (mode == 2 ? (a.K / kGroup * 16 + 255) / 256 : 0u);

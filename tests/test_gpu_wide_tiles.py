@@ -1,0 +1,58 @@
+"""17 to 64 tokens of matrices tall enough for one column of the prompt kernel's tiles (tiles of 32 tokens for up to 32): both sides
+of the rule's limits, ragged last tiles, rows of an odd number of groups and of fewer blocks than waves that share them."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_14844_amd as xfp
+import xfp_inputs as xi
+from helpers import gated_rel_err
+
+pytestmark = pytest.mark.gpu
+V2, V2A = xi.MODE_V2, xi.MODE_V2A
+
+
+@pytest.mark.parametrize("mode,bits,N,K,M", [
+    (V2, 4, 24449, 3200, 17), (V2, 4, 24448, 3200, 17), (V2A, 3, 24500, 1664, 32), (V2, 2, 24577, 128, 33), (V2A, 4, 24450, 384, 48),
+    (V2, 3, 20353, 1152, 49), (V2, 3, 20352, 1152, 49), (V2A, 2, 20400, 256, 64), (V2, 3, 16257, 640, 33), (V2A, 2, 16300, 768, 61), (V2, 4, 16300, 1024, 64),
+    (V2, 2, 57217, 1664, 25), (V2A, 3, 45057, 640, 40)])
+def test_wide_calls_in_tiles(mode, bits, N, K, M):
+    W = xi.random_weights(mode, bits, N, K, density=0.004, seed=N + K)
+    x = xi.activations(np.random.default_rng(N + M), M, K)
+    dW, xd = xfp.upload(W), torch.from_numpy(x.view(np.int16)).cuda().view(torch.float16)
+    assert xfp.xfp_launch_route(dW, M) == (xfp.XFP_ROUTE_WIDE, M)
+    y = xfp.xfp_gemv(dW, xd, y_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert gated_rel_err(y.cpu().numpy().astype(np.float64), oracle.gemv_weights(W, x)) <= 1e-4      # fp32 results, as in the other kernels' tests
+    for t in (torch.float16, torch.bfloat16):
+        assert torch.equal(xfp.xfp_gemv(dW, xd, y_dtype=t), y.to(t))
+    fixed = torch.full((M, N), 7.0, device="cuda")
+    xfp.xfp_gemv_noalloc(dW, xd, fixed)
+    assert torch.equal(fixed, y)
+
+
+@pytest.mark.parametrize("M", [29, 64])
+def test_infinities_and_nan_stay_with_their_tokens(M):
+    W = xi.random_weights(V2, 3, 24600, 1920, density=0.01, seed=M)
+    x, dW = torch.randn(M, W.K, device="cuda").half(), xfp.upload(W)
+    clean = xfp.xfp_gemv(dW, x, y_dtype=torch.float32)
+    x[3, 7], x[M - 1, W.K - 1] = float("inf"), float("nan")
+    y = xfp.xfp_gemv(dW, x, y_dtype=torch.float32)
+    rest = [m for m in range(M) if m not in (3, M - 1)]
+    assert torch.equal(y[rest], clean[rest]) and torch.isnan(y[M - 1]).all() and not torch.isfinite(y[3]).any()
+
+
+def test_they_replay_from_a_graph():
+    W = xi.random_weights(V2A, 4, 24600, 1664, density=0.003, seed=7)
+    dW, x = xfp.upload(W), torch.randn(30, W.K, device="cuda").half()
+    xfp.xfp_gemv(dW, x, y_dtype=torch.float32)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        y = xfp.xfp_gemv(dW, x, y_dtype=torch.float32)
+    for i in range(4):
+        x.copy_(torch.randn(30, W.K, device="cuda").half())
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, xfp.xfp_gemv(dW, x, y_dtype=torch.float32))
