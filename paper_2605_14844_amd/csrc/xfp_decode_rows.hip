@@ -14,101 +14,187 @@ namespace xfp {
 constexpr int kRowsThreads = 256;
 constexpr int kRowsWaves = kRowsThreads / kWave;
 
+typedef __attribute__((address_space(3))) const uint16_t lds_entry_t;
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
+}
+
+// Entry of field F: the table (2^BITS entries, aligned to its size) is OR-ed into the field's address, an instruction less than added.
+template <int BITS, int F>
+__device__ __forceinline__ uint32_t entry(const LaneWords<BITS> &lw, uint32_t table)
+{
+    constexpr int bit = F * BITS, word = bit / 32, sh = bit % 32;
+    uint32_t t;                                                           // the field at bit 1
+    if constexpr (sh + BITS > 32) t = __builtin_amdgcn_alignbit(lw.w[word + 1], lw.w[word], sh - 1);
+    else if constexpr (sh >= 1) t = lw.w[word] >> (sh - 1);
+    else t = lw.w[word] << 1;
+    return *(lds_entry_t *)(uintptr_t)((t & (2u * ((1u << BITS) - 1u))) | table);
+}
+
 template <int BITS, int I>
-__device__ __forceinline__ void accumulate_pairs(const LaneWords<BITS> &lw, const _Float16 *tbl,
-                                                 const uint32_t *xw, float &acc)
+__device__ __forceinline__ void accumulate_pairs(const LaneWords<BITS> &lw, uint32_t table, const uint32_t *xw, float &acc)
 {
     if constexpr (I < 16) {
-        half2_t c;
-        c.x = tbl[field<BITS, 2 * I>(lw)];
-        c.y = tbl[field<BITS, 2 * I + 1>(lw)];
-        acc = dot2(c, as_half2(xw[I]), acc);
-        accumulate_pairs<BITS, I + 1>(lw, tbl, xw, acc);
+        const uint32_t c = entry<BITS, 2 * I>(lw, table) | (entry<BITS, 2 * I + 1>(lw, table) << 16);
+        acc = dot2(as_half2(c), as_half2(xw[I]), acc);
+        accumulate_pairs<BITS, I + 1>(lw, table, xw, acc);
     }
 }
+
+// 16-byte chunk c of the 32 activations of unit u, in LDS: turned by the unit, so that the 16 lanes that LDS serves together, which
+// read one chunk of 16 neighbouring units, find it in 16 different places of the 64 banks (in plain order in four).
+__device__ __forceinline__ uint32_t x_chunk(uint32_t u, uint32_t c) { return u * 4 + ((c + (u >> 2)) & 3u); }
 
 // AFF (V2a only): every group carries a scale and a mid-point (paper section 3.4; no formula given, reading
 // taken: entry * scale + mid).  By linearity a unit of 32 weights inside one group contributes
 // scale * sum(x * entry) + mid * sum(x), both sums in fp32, one fused multiply-add on top.
+//
+// What bounds it at 5 and 6 bits is the chain of round trips of a wave that owns a row or two, so everything that does not depend on
+// something else is asked for at once and ahead: codebook and row pointers of the next row, the index words two steps ahead, across
+// rows, a row's outliers in front of its products (each behind the other: 8192 x 4096, 5 bits 9.4 us, now 9.0; 1000 x 20480 15.4, 9.1; 2048 x 3072 5.4, 4.5; 30000 x 640 14.9, 12.8).
 template <int BITS, int MODE, bool YF32, bool AFF>
-__global__ __launch_bounds__(kRowsThreads) void decode_rows_kernel(DecodeArgs a)
+__global__ __launch_bounds__(kRowsThreads, AFF ? 4 : 8) void decode_rows_kernel(DecodeArgs a)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
+    extern __shared__ __align__(256) unsigned char smem[];                // (2 K bytes are a multiple of 256: the tables are aligned to their size)
     constexpr int ENT = 1 << BITS;
-    uint32_t *xs = reinterpret_cast<uint32_t *>(smem);                    // K halves
+    _Float16 *xs = reinterpret_cast<_Float16 *>(smem);                    // K halves, in the order of x_chunk
+    uint4 *xs4 = reinterpret_cast<uint4 *>(smem);
     _Float16 *tables = reinterpret_cast<_Float16 *>(smem + (size_t)a.K * 2);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t slot = blockIdx.y;
     const uint32_t e = a.eids ? (uint32_t)a.eids[slot] : 0u;
-    const uint32_t N = a.N, K = a.K;
+    const uint32_t N = a.N, K = a.K, G = K / kGroup;
     const uint32_t wpr = K / 32 * BITS;                                  // words per row
     const uint32_t *idx = a.idx + (size_t)e * N * wpr;
     const int32_t *rp = a.rp + (size_t)e * N;
     const uint16_t *x = a.x + (int64_t)slot * a.x_stride;
+    const uint32_t row1 = min(N, (blockIdx.x + 1) * a.rows_per_block);
+    uint32_t row = blockIdx.x * a.rows_per_block + wave;
+    const uint32_t units = K / kLaneWeights, steps = (units + kWave - 1) / kWave;
+
+    // Requests.  Units that are not there: the row's last one, results dropped; rows behind the wave's: none.
+    auto codebook = [&](uint32_t r) -> uint32_t {
+        if constexpr (MODE != 0) return 0u;
+        return reinterpret_cast<const uint32_t *>(a.cb + ((size_t)e * N + r) * ENT)[min(lane, (uint32_t)ENT / 2 - 1)];
+    };
+    int32_t j0 = rp[min(row, row1 - 1)], j1 = rp[min(row, row1 - 1) + 1];
+    uint32_t cbn = codebook(min(row, row1 - 1));
+    constexpr int XB = 3;
+    uint4 xv[XB];
+#pragma unroll
+    for (int b = 0; b < XB; ++b) xv[b] = reinterpret_cast<const uint4 *>(x)[min(tid + b * kRowsThreads, K / 8 - 1)];
+    constexpr int P = 2;                                                  // steps ahead
+    LaneWords<BITS> lw[P];
+    uint32_t gid[P], gsc[P], gmd[P];
+    uint32_t prow = row, pstep = 0;                                       // of the next request
+    auto request = [&](int j) {
+        if (prow >= row1) return;
+        const uint32_t r = prow, u = min(pstep * kWave + lane, units - 1);
+        lw[j] = load_lane_words<BITS>(idx + (size_t)r * wpr + (size_t)u * BITS);
+        if constexpr (MODE == 1) gid[j] = a.gid[((size_t)e * N + r) * G + u / (kGroup / kLaneWeights)];
+        if constexpr (AFF) {
+            gsc[j] = a.gscale[((size_t)e * N + r) * G + u / (kGroup / kLaneWeights)];
+            gmd[j] = a.gmid[((size_t)e * N + r) * G + u / (kGroup / kLaneWeights)];
+        }
+        if (++pstep == steps) {
+            pstep = 0;
+            prow += kRowsWaves;
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < P; ++j) request(j);
 
     // a1: stage the activation row.
-    for (uint32_t i = tid; i < K / 8; i += kRowsThreads) {
-        uint4 v = reinterpret_cast<const uint4 *>(x)[i];
+    auto stage = [&](uint32_t i, uint4 v) {
         if (a.x_bf16) v = make_uint4(bf16x2_to_f16x2(v.x), bf16x2_to_f16x2(v.y), bf16x2_to_f16x2(v.z), bf16x2_to_f16x2(v.w));
-        reinterpret_cast<uint4 *>(xs)[i] = v;
-    }
+        xs4[x_chunk(i >> 2, i & 3u)] = v;
+    };
+#pragma unroll
+    for (int b = 0; b < XB; ++b)
+        if (tid + b * kRowsThreads < K / 8) stage(tid + b * kRowsThreads, xv[b]);
+    for (uint32_t i = tid + XB * kRowsThreads; i < K / 8; i += kRowsThreads) stage(i, reinterpret_cast<const uint4 *>(x)[i]);
     // a2: V2a library -> LDS once per workgroup.
     if constexpr (MODE == 1) {
         const uint16_t *lib = a.cb + (size_t)e * a.L * ENT;
         for (uint32_t i = tid; i < a.L * ENT; i += kRowsThreads)
             tables[i] = __builtin_bit_cast(_Float16, lib[i]);
     }
-    __syncthreads();
+    lds_barrier();
 
-    const uint32_t row0 = blockIdx.x * a.rows_per_block;
-    const uint32_t row1 = min(N, row0 + a.rows_per_block);
     _Float16 *mytbl = tables + wave * ENT;                                // V2: per-wave table
-
-    for (uint32_t row = row0 + wave; row < row1; row += kRowsWaves) {
+    const uint32_t table0 = lds_address(tables);
+    for (; row < row1; row += kRowsWaves) {
         if constexpr (MODE == 0) {
-            const uint32_t *cbw = reinterpret_cast<const uint32_t *>(a.cb + ((size_t)e * N + row) * ENT);
             __builtin_amdgcn_wave_barrier();
-            if (lane < ENT / 2) reinterpret_cast<uint32_t *>(mytbl)[lane] = cbw[lane];
+            if (lane < ENT / 2) reinterpret_cast<uint32_t *>(mytbl)[lane] = cbn;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
-        const uint32_t *rw = idx + (size_t)row * wpr;
+        // a7, requests: the row's first 64 outliers; the next row's codebook and row pointers
+        const int32_t jl = j0 + (int32_t)lane, jend = j1;
+        uint32_t oc = 0, ov = 0;
+        if (jl < jend) {
+            oc = (uint32_t)a.col[jl];
+            ov = a.val[jl];
+        }
+        const uint32_t nrow = min(row + kRowsWaves, row1 - 1);
+        cbn = codebook(nrow);
+        j0 = rp[nrow];
+        j1 = rp[nrow + 1];
         float acc = 0.f;
-        for (uint32_t u = lane; u < K / kLaneWeights; u += kWave) {
-            // a3/a4: stream and depack; a5: gather; a6: multiply-accumulate.
-            LaneWords<BITS> lw = load_lane_words<BITS>(rw + (size_t)u * BITS);
-            const _Float16 *tbl = mytbl;
-            if constexpr (MODE == 1) {
-                uint32_t g = a.gid[((size_t)e * N + row) * (K / kGroup) + u / (kGroup / kLaneWeights)];
-                tbl = tables + g * ENT;
-            }
-            uint32_t xw[16];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                uint4 v = reinterpret_cast<const uint4 *>(xs)[u * 4 + i];
-                xw[4 * i] = v.x; xw[4 * i + 1] = v.y; xw[4 * i + 2] = v.z; xw[4 * i + 3] = v.w;
-            }
+        // a3/a4: stream and depack; a5: gather; a6: multiply-accumulate.  One step, whose words are request j's.
+        auto step = [&](uint32_t s, int j) {
+                                            const uint32_t u = s * kWave + lane;
+                            const LaneWords<BITS> w = lw[j];
+                            const uint32_t id = MODE == 1 ? gid[j] : 0u;
+                            const float sc = AFF ? half_bits_to_float((uint16_t)gsc[j]) : 0.f, md = AFF ? half_bits_to_float((uint16_t)gmd[j]) : 0.f;
+                            request(j);
+                            if (u < units) {
+                                const uint32_t tbl = MODE == 1 ? table0 + id * (ENT * 2) : table0 + wave * (ENT * 2);
+                                uint32_t xw[16];
+            #pragma unroll
+                                for (int i = 0; i < 4; ++i) {
+                                    const uint4 v = xs4[x_chunk(u, i)];
+                                    xw[4 * i] = v.x; xw[4 * i + 1] = v.y; xw[4 * i + 2] = v.z; xw[4 * i + 3] = v.w;
+                                }
+                                if constexpr (AFF) {
+                                    float au = 0.f, sum = 0.f;
+                                    accumulate_pairs<BITS, 0>(w, tbl, xw, au);
+                                    const half2_t ones = {(_Float16)1.0f, (_Float16)1.0f};
+            #pragma unroll
+                                    for (int i = 0; i < 16; ++i) sum = dot2(ones, as_half2(xw[i]), sum);
+                                    acc += fmaf(sc, au, md * sum);
+                                } else {
+                                    accumulate_pairs<BITS, 0>(w, tbl, xw, acc);
+                                }
+                            }
+        };
+        static_assert(P == 2, "the steps below");
+        uint32_t s = 0;
+        for (; s + 1 < steps; s += 2) {
+            step(s, 0);
+            step(s + 1, 1);
+        }
+        if (s < steps) {                                                  // an odd number of them: the requests change places
+            step(s, 0);
+            const LaneWords<BITS> t = lw[0];
+            lw[0] = lw[1];
+            lw[1] = t;
+            if constexpr (MODE == 1) { const uint32_t v = gid[0]; gid[0] = gid[1]; gid[1] = v; }
             if constexpr (AFF) {
-                const size_t g = ((size_t)e * N + row) * (K / kGroup) + u / (kGroup / kLaneWeights);
-                const float sc = half_bits_to_float(a.gscale[g]), md = half_bits_to_float(a.gmid[g]);
-                float au = 0.f, xs = 0.f;
-                accumulate_pairs<BITS, 0>(lw, tbl, xw, au);
-                const half2_t ones = {(_Float16)1.0f, (_Float16)1.0f};
-#pragma unroll
-                for (int i = 0; i < 16; ++i) xs = dot2(ones, as_half2(xw[i]), xs);
-                acc += fmaf(sc, au, md * xs);
-            } else {
-                accumulate_pairs<BITS, 0>(lw, tbl, xw, acc);
+                const uint32_t v = gsc[0], w = gmd[0];
+                gsc[0] = gsc[1]; gsc[1] = v;
+                gmd[0] = gmd[1]; gmd[1] = w;
             }
         }
         // a7: outlier fold, CSR row owned by this wave.
-        const int32_t j1 = rp[row + 1];
-        for (int32_t j = rp[row] + lane; j < j1; j += kWave) {
-            float v = half_bits_to_float(a.val[j]);
-            float xv = (float)reinterpret_cast<const _Float16 *>(xs)[a.col[j]];
-            acc = fmaf(v, xv, acc);
-        }
+        auto fold = [&](uint32_t k, uint32_t v) {
+            acc = fmaf(half_bits_to_float((uint16_t)v), (float)xs[x_chunk(k >> 5, k >> 3 & 3u) * 8 + (k & 7u)], acc);
+        };
+        if (jl < jend) fold(oc, ov);
+        for (int32_t j = jl + kWave; j < jend; j += kWave) fold((uint32_t)a.col[j], a.val[j]);
         // a8: reduce and store.
         acc = wave_sum(acc);
         if (lane == 0) store_y<YF32>(a.y, (int64_t)slot * a.y_stride + row, acc, a.y_bf16 != 0);
