@@ -315,16 +315,21 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
     constexpr int GL = BM / 8, RP = 64 / GL, RW = BN / NW;     // lanes of a row; rows of a wave at a time, in all
     static_assert((GL == 4 || GL == 8 || GL == 16) && RW % RP == 0 && RW < 64, "");
     const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
-    const int32_t ofirst = rp[min(n0, N)], olast = rp[min(n0 + BN, N)];
-    const bool outliers = a.col && ofirst < olast;
-    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + ofirst), 0, outliers ? (olast - ofirst) * 4 : 0, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + ofirst), 0, outliers ? (olast - ofirst) * 2 : 0, 0x00020000);
+    int32_t ofirst = 0, olast = 0;
+    auto tile_entries = [&] {
+        ofirst = rp[min(n0, N)];
+        olast = rp[min(n0 + BN, N)];
+    };
+    if constexpr (EARLY) tile_entries();
     const uint32_t oo = lane % GL, orow = lane / GL;
     int32_t rpv = 0;                                           // lane r: first entry of row r
     auto first_of = [&](uint32_t r) { return __builtin_amdgcn_ds_bpermute((int)(min(r, (uint32_t)RW) * 4), rpv); };
     int32_t oe = 0, oend = 0;                                  // this lane's row: first entry of the batch, end of the row
     uint32_t oc = 0, ov = 0;
     auto entries = [&] {                                       // (past the tile's entries: zeros)
+        const int32_t n = a.col ? olast - ofirst : 0;
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + ofirst), 0, n * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + ofirst), 0, n * 2, 0x00020000);
         oc = __builtin_amdgcn_raw_buffer_load_b32(rc, (uint32_t)(oe + (int32_t)oo - ofirst) * 4, 0, 0);
         ov = __builtin_amdgcn_raw_buffer_load_b16(rv, (uint32_t)(oe + (int32_t)oo - ofirst) * 2, 0, 0);
     };
@@ -573,7 +578,8 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
     // from row to row: 28672 x 8192, 2048 tokens 309 us of 1366 at 0.3 % outliers, 165 at 0.05 %; 4096 x 1024, 256 tokens 6.)
     // A row's entries are fetched GL at a time, one per lane, and handed to its lanes one by one (row_newbcast); a sum is
     // taken per GL entries and those are added up.
-    if (outliers) {
+    if constexpr (!EARLY) tile_entries();
+    if (a.col && ofirst < olast) {
         if constexpr (!EARLY) first_entries();
         lds_barrier();                                         // every wave is past its tiles (and sums)
         const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc((void *)ga.xt, 0, K * ga.MP * 2, 0x00020000);
