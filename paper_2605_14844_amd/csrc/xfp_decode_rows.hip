@@ -9,6 +9,9 @@
 // the row's CSR outliers are folded in before the wave reduction.
 #include "xfp_device.h"
 
+#include <type_traits>
+#include <utility>
+
 namespace xfp {
 
 constexpr int kRowsThreads = 256;
@@ -32,14 +35,38 @@ __device__ __forceinline__ uint32_t entry(const LaneWords<BITS> &lw, uint32_t ta
     return *(lds_entry_t *)(uintptr_t)((t & (2u * ((1u << BITS) - 1u))) | table);
 }
 
-template <int BITS, int I>
-__device__ __forceinline__ void accumulate_pairs(const LaneWords<BITS> &lw, uint32_t table, const uint32_t *xw, float &acc)
+// Eight of them: fields 8 C .. 8 C + 7.
+template <int BITS, int C, int... Is>
+__device__ __forceinline__ void eight_entries(const LaneWords<BITS> &lw, uint32_t table, uint32_t (&c)[8], std::integer_sequence<int, Is...>)
 {
-    if constexpr (I < 16) {
-        const uint32_t c = entry<BITS, 2 * I>(lw, table) | (entry<BITS, 2 * I + 1>(lw, table) << 16);
-        acc = dot2(as_half2(c), as_half2(xw[I]), acc);
-        accumulate_pairs<BITS, I + 1>(lw, table, xw, acc);
+    ((c[Is] = entry<BITS, 8 * C + Is>(lw, table)), ...);
+}
+
+// A lane's words through bounds-checked buffer loads: past the end zeros, with no traffic.
+template <int BITS>
+__device__ __forceinline__ LaneWords<BITS> buffer_lane_words(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int kOnce = 2;                                              // non-temporal
+    LaneWords<BITS> w;
+    if constexpr (BITS == 2) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kOnce);
+        w.w[0] = v.x; w.w[1] = v.y;
+    } else if constexpr (BITS == 3) {
+        const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(r, off, 0, kOnce);
+        w.w[0] = v.x; w.w[1] = v.y; w.w[2] = v.z;
+    } else {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kOnce);
+        w.w[0] = v.x; w.w[1] = v.y; w.w[2] = v.z; w.w[3] = v.w;
+        if constexpr (BITS == 5) w.w[4] = __builtin_amdgcn_raw_buffer_load_b32(r, off + 16, 0, kOnce);
+        if constexpr (BITS == 6) {
+            const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(r, off + 16, 0, kOnce);
+            w.w[4] = q.x; w.w[5] = q.y;
+        }
     }
+    return w;
 }
 
 // 16-byte chunk c of the 32 activations of unit u, in LDS: turned by the unit, so that the 16 lanes that LDS serves together, which
@@ -52,7 +79,12 @@ __device__ __forceinline__ uint32_t x_chunk(uint32_t u, uint32_t c) { return u *
 //
 // What bounds it at 5 and 6 bits is the chain of round trips of a wave that owns a row or two, so everything that does not depend on
 // something else is asked for at once and ahead: codebook and row pointers of the next row, the index words two steps ahead, across
-// rows, a row's outliers in front of its products (each behind the other: 8192 x 4096, 5 bits 9.4 us, now 9.0; 1000 x 20480 15.4, 9.1; 2048 x 3072 5.4, 4.5; 30000 x 640 14.9, 12.8).
+// rows, a row's outliers in front of its products.  Words and outliers come through buffer loads, which need no branch, so that every
+// wait knows how many loads are younger than what it is for.  A step's 32 lookups are four runs of eight beside the run before: at
+// 6 bits, in 64 registers, the compiler had made sixteen round trips to LDS of them, one behind the other.
+// us with each behind the other / asked for ahead / as it is: 5 bits 8192 x 4096 9.2 / 9.0 / 8.4, 1000 x 20480 15.3 / 9.1 / 8.7,
+// 2048 x 3072 5.6 / 4.7 / 4.3, 30000 x 640 15.1 / 13.3 / 12.0; 6 bits 7457 x 1152 5.8 / 6.5 / 5.4, 4974 x 7040 11.0 / 11.8 / 10.9,
+// 1828 x 640, 4 tokens 5.5 / 6.2 / 5.3, 11008 x 8192 22.1 / 20.5 / 19.3.
 template <int BITS, int MODE, bool YF32, bool AFF>
 __global__ __launch_bounds__(kRowsThreads, AFF ? 4 : 8) void decode_rows_kernel(DecodeArgs a)
 {
@@ -70,11 +102,11 @@ __global__ __launch_bounds__(kRowsThreads, AFF ? 4 : 8) void decode_rows_kernel(
     const uint32_t *idx = a.idx + (size_t)e * N * wpr;
     const int32_t *rp = a.rp + (size_t)e * N;
     const uint16_t *x = a.x + (int64_t)slot * a.x_stride;
-    const uint32_t row1 = min(N, (blockIdx.x + 1) * a.rows_per_block);
-    uint32_t row = blockIdx.x * a.rows_per_block + wave;
+    const uint32_t row0 = blockIdx.x * a.rows_per_block, row1 = min(N, row0 + a.rows_per_block);
+    uint32_t row = row0 + wave;
     const uint32_t units = K / kLaneWeights, steps = (units + kWave - 1) / kWave;
 
-    // Requests.  Units that are not there: the row's last one, results dropped; rows behind the wave's: none.
+    // Requests.  Units that are not there: no words, the row's last id, results dropped; rows behind the wave's: none.
     auto codebook = [&](uint32_t r) -> uint32_t {
         if constexpr (MODE != 0) return 0u;
         return reinterpret_cast<const uint32_t *>(a.cb + ((size_t)e * N + r) * ENT)[min(lane, (uint32_t)ENT / 2 - 1)];
@@ -84,27 +116,29 @@ __global__ __launch_bounds__(kRowsThreads, AFF ? 4 : 8) void decode_rows_kernel(
     constexpr int XB = 3;
     uint4 xv[XB];
 #pragma unroll
-    for (int b = 0; b < XB; ++b) xv[b] = reinterpret_cast<const uint4 *>(x)[min(tid + b * kRowsThreads, K / 8 - 1)];
+    for (int b = 0; b < XB; ++b)
+        if (b == 0 || (uint32_t)(b * kRowsThreads) < K / 8) xv[b] = reinterpret_cast<const uint4 *>(x)[min(tid + b * kRowsThreads, K / 8 - 1)];
     constexpr int P = 2;                                                  // steps ahead
     LaneWords<BITS> lw[P];
     uint32_t gid[P], gsc[P], gmd[P];
     uint32_t prow = row, pstep = 0;                                       // of the next request
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void *)(idx + (size_t)row0 * wpr), 0, (row1 - row0) * wpr * 4, 0x00020000);
     auto request = [&](int j) {
-        if (prow >= row1) return;
-        const uint32_t r = prow, u = min(pstep * kWave + lane, units - 1);
-        lw[j] = load_lane_words<BITS>(idx + (size_t)r * wpr + (size_t)u * BITS);
-        if constexpr (MODE == 1) gid[j] = a.gid[((size_t)e * N + r) * G + u / (kGroup / kLaneWeights)];
+        const uint32_t u = pstep * kWave + lane;
+        lw[j] = buffer_lane_words<BITS>(rw, u < units ? (prow - row0) * (wpr * 4) + u * (BITS * 4) : 0x80000000u);
+        const size_t g = ((size_t)e * N + min(prow, row1 - 1)) * G + min(u, units - 1) / (kGroup / kLaneWeights);
+        if constexpr (MODE == 1) gid[j] = a.gid[g];
         if constexpr (AFF) {
-            gsc[j] = a.gscale[((size_t)e * N + r) * G + u / (kGroup / kLaneWeights)];
-            gmd[j] = a.gmid[((size_t)e * N + r) * G + u / (kGroup / kLaneWeights)];
+            gsc[j] = a.gscale[g];
+            gmd[j] = a.gmid[g];
         }
         if (++pstep == steps) {
             pstep = 0;
             prow += kRowsWaves;
         }
     };
-#pragma unroll
-    for (int j = 0; j < P; ++j) request(j);
+    request(0);
+    if (prow < row1) request(1);
 
     // a1: stage the activation row.
     auto stage = [&](uint32_t i, uint4 v) {
@@ -134,42 +168,59 @@ __global__ __launch_bounds__(kRowsThreads, AFF ? 4 : 8) void decode_rows_kernel(
         }
         // a7, requests: the row's first 64 outliers; the next row's codebook and row pointers
         const int32_t jl = j0 + (int32_t)lane, jend = j1;
-        uint32_t oc = 0, ov = 0;
-        if (jl < jend) {
-            oc = (uint32_t)a.col[jl];
-            ov = a.val[jl];
+        const int32_t jfirst = __builtin_amdgcn_readfirstlane(j0), entries = max(__builtin_amdgcn_readfirstlane(j1) - jfirst, 0);
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.col + jfirst), 0, entries * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)(a.val + jfirst), 0, entries * 2, 0x00020000);
+        const uint32_t oc = __builtin_amdgcn_raw_buffer_load_b32(rc, lane * 4, 0, 0), ov = __builtin_amdgcn_raw_buffer_load_b16(rv, lane * 2, 0, 0);
+        if (const uint32_t nrow = row + kRowsWaves; nrow < row1) {
+            cbn = codebook(nrow);
+            j0 = rp[nrow];
+            j1 = rp[nrow + 1];
         }
-        const uint32_t nrow = min(row + kRowsWaves, row1 - 1);
-        cbn = codebook(nrow);
-        j0 = rp[nrow];
-        j1 = rp[nrow + 1];
         float acc = 0.f;
         // a3/a4: stream and depack; a5: gather; a6: multiply-accumulate.  One step, whose words are request j's.
         auto step = [&](uint32_t s, int j) {
-                                            const uint32_t u = s * kWave + lane;
-                            const LaneWords<BITS> w = lw[j];
-                            const uint32_t id = MODE == 1 ? gid[j] : 0u;
-                            const float sc = AFF ? half_bits_to_float((uint16_t)gsc[j]) : 0.f, md = AFF ? half_bits_to_float((uint16_t)gmd[j]) : 0.f;
-                            request(j);
-                            if (u < units) {
-                                const uint32_t tbl = MODE == 1 ? table0 + id * (ENT * 2) : table0 + wave * (ENT * 2);
-                                uint32_t xw[16];
-            #pragma unroll
-                                for (int i = 0; i < 4; ++i) {
-                                    const uint4 v = xs4[x_chunk(u, i)];
-                                    xw[4 * i] = v.x; xw[4 * i + 1] = v.y; xw[4 * i + 2] = v.z; xw[4 * i + 3] = v.w;
-                                }
-                                if constexpr (AFF) {
-                                    float au = 0.f, sum = 0.f;
-                                    accumulate_pairs<BITS, 0>(w, tbl, xw, au);
-                                    const half2_t ones = {(_Float16)1.0f, (_Float16)1.0f};
-            #pragma unroll
-                                    for (int i = 0; i < 16; ++i) sum = dot2(ones, as_half2(xw[i]), sum);
-                                    acc += fmaf(sc, au, md * sum);
-                                } else {
-                                    accumulate_pairs<BITS, 0>(w, tbl, xw, acc);
-                                }
-                            }
+            const uint32_t u = s * kWave + lane;
+            const LaneWords<BITS> w = lw[j];
+            const uint32_t id = MODE == 1 ? gid[j] : 0u;
+            const float sc = AFF ? half_bits_to_float((uint16_t)gsc[j]) : 0.f, md = AFF ? half_bits_to_float((uint16_t)gmd[j]) : 0.f;
+            if (prow < row1) request(j);
+            if (u >= units) return;
+            const uint32_t tbl = MODE == 1 ? table0 + id * (ENT * 2) : table0 + wave * (ENT * 2);
+            const half2_t ones = {(_Float16)1.0f, (_Float16)1.0f};
+            float au = 0.f, sum = 0.f;
+            uint4 xq[2];
+            uint32_t c[2][8];
+            auto read = [&](auto quarter) {                               // eight activations and their entries
+                constexpr int q = decltype(quarter)::value;
+                xq[q & 1] = xs4[x_chunk(u, q)];
+                eight_entries<BITS, q>(w, tbl, c[q & 1], std::make_integer_sequence<int, 8>{});
+            };
+            auto add = [&](auto quarter) {
+                constexpr int q = decltype(quarter)::value;
+                const uint32_t xw[4] = {xq[q & 1].x, xq[q & 1].y, xq[q & 1].z, xq[q & 1].w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const half2_t pair = as_half2(c[q & 1][2 * i] | (c[q & 1][2 * i + 1] << 16));
+                    if constexpr (AFF) {
+                        au = dot2(pair, as_half2(xw[i]), au);
+                        sum = dot2(ones, as_half2(xw[i]), sum);
+                    } else {
+                        acc = dot2(pair, as_half2(xw[i]), acc);
+                    }
+                }
+            };
+            const std::integral_constant<int, 0> q0; const std::integral_constant<int, 1> q1;
+            const std::integral_constant<int, 2> q2; const std::integral_constant<int, 3> q3;
+            read(q0);
+            read(q1);
+            add(q0);
+            read(q2);
+            add(q1);
+            read(q3);
+            add(q2);
+            add(q3);
+            if constexpr (AFF) acc += fmaf(sc, au, md * sum);
         };
         static_assert(P == 2, "the steps below");
         uint32_t s = 0;

@@ -68,6 +68,14 @@ def test_the_prompt_kernels_stay_in_registers():
         assert v["vgpr_spills"] == 0 and v["agprs"] == 0 and v["scratch_bytes_per_lane"] == 0, (k, v)
 
 
+def test_the_general_kernel_keeps_its_waves_at_5_and_6_bits():
+    """A wave there owns a row or two: eight of them per SIMD are what hides a round trip, in 64 registers."""
+    rows = {k: v for k, v in resources().items() if re.search(r"decode_rows_kernelILi[56]ELi0E", k)}
+    assert len(rows) == 4
+    for k, v in rows.items():
+        assert v["waves_per_simd"] == 8 and v["vgpr_spills"] == 0 and v["sgpr_spills"] == 0 and v["scratch_bytes_per_lane"] == 0, (k, v)
+
+
 def test_the_resident_kernels_stay_in_registers():
     """Scratch memory is read through the counter that the kernel's waits for its index words count on."""
     few = {k: v for k, v in resources().items() if "decode_few_kernel" in k}

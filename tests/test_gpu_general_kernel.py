@@ -16,7 +16,9 @@ V2, V2A = xi.MODE_V2, xi.MODE_V2A
 @pytest.mark.parametrize("mode,bits,N,K,L,affine,density", [
     (V2, 5, 1, 128, 0, False, 0.1), (V2, 6, 20011, 128, 0, False, 0.02), (V2, 5, 33001, 256, 0, False, 0.02), (V2, 6, 7, 2048, 0, False, 0.2), (V2, 5, 4099, 2176, 0, False, 0.005),
     (V2, 6, 301, 4224, 0, False, 0.03), (V2, 5, 130, 6144, 0, False, 0.01), (V2, 5, 66, 20480, 0, False, 0.01), (V2A, 5, 75, 4224, 16, False, 0.01),
-    (V2A, 6, 41, 2176, 9, True, 0.01), (V2A, 3, 50, 18432, 32, True, 0.004), (V2A, 4, 37, 4224, 256, True, 0.01)])
+    (V2A, 6, 41, 2176, 9, True, 0.01), (V2A, 3, 50, 18432, 32, True, 0.004), (V2A, 4, 37, 4224, 256, True, 0.01),
+    # two and four rows of a wave, of two, three and four steps: the requests go on in the next row
+    (V2, 5, 16399, 2176, 0, False, 0.004), (V2, 6, 16390, 4224, 0, False, 0.002), (V2, 5, 33001, 4352, 0, False, 0.0), (V2, 6, 16387, 6272, 0, False, 0.03)])
 def test_general_kernel(mode, bits, N, K, L, affine, density):
     W = xi.random_weights(mode, bits, N, K, density=density, seed=N + K, **(dict(L=L, affine=affine) if mode == V2A else {}))
     x = xi.activations(np.random.default_rng(N + K), 1, K)
