@@ -56,7 +56,7 @@ typedef __attribute__((address_space(4))) const int32_t const_i32_t;   // unifor
 // of a row's products of 16 loses grows with the root of its length (4096 columns: 3.1e-7 of the result, 1.2e-7 in two
 // steps).  The second set halves the tokens that a dequantised weight meets in a wave (28672 x 8192, 2048 tokens, fp16:
 // 256 x 256 tiles in one chain were 13 % faster than 256 x 128 in two steps).
-template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_, int IBUF_>
+template <int RB_, int TB_, int WN_, int WK_, int SP_, int NBUF_, int IBUF_, bool PLAIN_ = false>
 struct GemmTile {
     static constexpr int RB = RB_, TB = TB_, WN = WN_, WK = WK_, SP = SP_, NBUF = NBUF_, IBUF = IBUF_;
     static constexpr int BN = 32 * RB * WN, BM = 32 * TB, NW = WN * WK, T = NW * kWave;
@@ -72,17 +72,17 @@ struct GemmTile {
     template <int BITS> static constexpr int kLoop = kTiles + NW * IBUF * kWordBlock<BITS>;
     template <int BITS> static constexpr int kBase = kPlane > kSums ? (kLoop<BITS> > kPlane ? kLoop<BITS> : kPlane) : (kLoop<BITS> > kSums ? kLoop<BITS> : kSums);
     static constexpr int kIds = BN * 64;                       // ids of 64 groups
-    static constexpr bool ROOM = NW <= 8;                      // registers for more than the loop needs
     // A step's VALU work is dealt out between its matrix instructions, which 64 columns of tokens need (4096 x 4096, 333 tokens, 3
     // bits 37 us in the compiler's order, 34); with 128 the chip's power sets the pace and the compiler's order is the better one
     // (11008 x 4096, 2 bits, 700 tokens 139 us, 144 dealt out; 28672 x 8192, 4 bits, 2048 tokens 971 / 990 without outliers).
-    static constexpr bool DEAL = TB <= 2;
+    // PLAIN: in the compiler's order all the same, with nothing asked for ahead (rows of a block or two: see kPlainTinyK).
+    static constexpr bool DEAL = TB <= 2 && !PLAIN_;
     static constexpr bool EARLY = NW <= 8 && DEAL;             // there are registers for what is asked for ahead of its use
     static constexpr bool FINE = NW <= 8;                      // takes short rows (half blocks as chains)
-    static constexpr bool DEEP = WK > 1 && NW <= 8;            // a third set of sums for long rows
+    static constexpr bool DEEP = WK > 1 && NW <= 8 && !PLAIN_; // a third set of sums for long rows
     static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && BN % NW == 0, "");
     // registers: accumulators and sums, operands (B twice), index words, planes; then waves per SIMD
-    static constexpr int kRegs = (DEEP ? 48 : 32) * RB * TB + 16 * RB + 8 * TB + 4 * RB + 8 * RB + 56;
+    static constexpr int kRegs = (WK > 1 && NW <= 8 ? 48 : 32) * RB * TB + 16 * RB + 8 * TB + 4 * RB + 8 * RB + 56;
     static constexpr int kWavesPerSimd = kRegs <= 128 ? 4 : kRegs <= 168 ? 3 : kRegs <= 256 ? 2 : 1;
 };
 
@@ -91,6 +91,14 @@ struct GemmTile {
 // result's norm, this kernel / passes of 64 tokens: 1024 rows, 512 columns 8.5 / 8.6; 1536 9.5 / 11.3; 4096 10.4 / 15.6; 8192
 // 11.6 / 21.1; 28672 12.2 / 14.2; 8320 rows, 8192 columns 14.9 / 21.1.
 constexpr uint32_t kFineK = 2048, kDeepK = 16384;
+
+// Rows of a block or two for each of the waves that share them: a step dealt out between its matrix instructions stands behind each
+// barrier with one instruction less to cover its reads, and asking ahead is only more to wait for.  us in the order above / plain:
+// 64 x 64 tiles, 3 bits, 143 x 256, 150 tokens 12.2 / 11.7, 212 x 512, 92 12.2 / 11.7, but 300 x 1024, 200 12.7 / 13.1, 4096 columns
+// 21.3 / 22.8; 4 bits, 300 x 512, 200 12.4 / 12.4; of 862 drawn calls of up to 2048 columns two are more than 2 % slower than with
+// plain tiles alone (201 before; 2.8 % at most, 640 and 768 columns), the median 2 % faster.  128 x 64: 21235 x 128, 98 tokens 26.7 / 26.2,
+// at 384 columns the same.
+constexpr uint32_t kPlainTinyK = 512, kPlainSmallK = 256;
 
 // 16-byte chunk c of row r of a tile with C chunks per row sits at position c ^ swz<C>(r)
 template <int C>
@@ -311,18 +319,18 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
     };
 
     // The outliers of the tile's rows (the term itself comes last): the rows' first entries and the first batch's entries are asked
-    // for in front of the main loop.
+    // for in front of the main loop, in vector loads: a scalar one is waited for with the next of any kind, a round trip to memory in front of
+    // all other loads (4263 x 384, 145 tokens without outliers 13.1 / 12.6 us).
     constexpr int GL = BM / 8, RP = 64 / GL, RW = BN / NW;     // lanes of a row; rows of a wave at a time, in all
-    static_assert((GL == 4 || GL == 8 || GL == 16) && RW % RP == 0 && RW < 64, "");
+    static_assert((GL == 4 || GL == 8 || GL == 16) && RW % RP == 0 && RW < 62, "");
     const_i32_t *rp = (const_i32_t *)(uintptr_t)a.rp;
     int32_t ofirst = 0, olast = 0;
     auto tile_entries = [&] {
         ofirst = rp[min(n0, N)];
         olast = rp[min(n0 + BN, N)];
     };
-    if constexpr (EARLY) tile_entries();
     const uint32_t oo = lane % GL, orow = lane / GL;
-    int32_t rpv = 0;                                           // lane r: first entry of row r
+    int32_t rpv = 0;                                           // lane r: first entry of row r; early: lanes 62 and 63: of the tile, of the next
     auto first_of = [&](uint32_t r) { return __builtin_amdgcn_ds_bpermute((int)(min(r, (uint32_t)RW) * 4), rpv); };
     int32_t oe = 0, oend = 0;                                  // this lane's row: first entry of the batch, end of the row
     uint32_t oc = 0, ov = 0;
@@ -335,7 +343,10 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
     };
 
     auto first_entries = [&] {
-        if (!EARLY) rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];
+        if constexpr (EARLY) {
+            ofirst = __builtin_amdgcn_readlane(rpv, 62);
+            olast = __builtin_amdgcn_readlane(rpv, 63);
+        } else rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];
         oe = first_of(orow);
         oend = first_of(orow + 1);
         entries();
@@ -360,7 +371,7 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) bf[set][tb] = *(lds_ch8_t *)(uintptr_t)(ba + tb * (32 * C::RSB));
     };
-    if constexpr (EARLY) rpv = a.rp[min(n0 + wave * RW + min(lane, (uint32_t)RW), N)];
+    if constexpr (EARLY) rpv = a.rp[min(lane < 62 ? n0 + wave * RW + min(lane, (uint32_t)RW) : n0 + (lane - 62) * BN, N)];
 #pragma unroll
     for (int b = 0; b < C::IBUF - 1; ++b) load_words(b);
 #pragma unroll
@@ -415,8 +426,9 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
         constexpr int kYounger = (C::AHEAD - 1) * C::ND + (words && from <= x ? kWords : 0);
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kYounger) : "memory");
     };
-    // In the compiler's order (one wave per row and column: it has every block).
+    // In the compiler's order.
     auto compiled_block = [&](uint32_t t) {
+        const bool on = WK == 1 || t * WK + wk < NB;           // (the last round of a row may have no block for this wave)
         for_each<16>([&](auto step) {
             constexpr int p = decltype(step)::value / 4, s = decltype(step)::value % 4;
             constexpr int x = p * C::U + s / C::SP;
@@ -424,7 +436,7 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
             const uint32_t bnext = bcur + 1 == C::NBUF ? 0 : bcur + 1;
             constexpr int set = s & 1;
             if constexpr (C::FINE && p == 2 && s == 0)
-                if (ga.fine) {
+                if (ga.fine && on) {
                     add();
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb)
@@ -458,15 +470,16 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
                 dequantise(s - 1, 0);
                 dequantise(s - 1, 1);
             }
+            if (on)
 #pragma unroll
-            for (int tb = 0; tb < TB; ++tb)
+                for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
-                    acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, af[s][rb]), bf[set][tb], p + s == 0 ? float16_t{} : acc[rb][tb], 0, 0, 0);
+                    for (int rb = 0; rb < RB; ++rb)
+                        acc[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, af[s][rb]), bf[set][tb], p + s == 0 ? float16_t{} : acc[rb][tb], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (last) bcur = bnext;
         });
-        add();
+        if (on) add();
     };
     // MAYBE: the wave may have no such block (the last round of a row)
     auto block = [&](auto maybe, uint32_t t) {
@@ -528,10 +541,10 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
         });
     };
 #pragma unroll 1
-    for (uint32_t t = 0; t + (WK > 1) < NS; ++t)
+    for (uint32_t t = 0; t + (WK > 1 && DEAL) < NS; ++t)
         if constexpr (DEAL) block(std::false_type{}, t);
         else compiled_block(t);
-    if constexpr (WK > 1) block(std::true_type{}, NS - 1);
+    if constexpr (WK > 1 && DEAL) block(std::true_type{}, NS - 1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // (loads to LDS that nobody waits for)
     if constexpr (DEAL) add();
     if constexpr (C::DEEP)
@@ -618,10 +631,11 @@ __device__ __forceinline__ void tile_product(const GemmArgs &ga)
                 oend = first_of(r0 + orow + 1);
             }
             entries();
-            // (two batches under way: always all of them, so that the wait for the entries knows how many loads are younger)
+            // (only the fours that some row has: all of them in any case, for the sake of the waits, is slower where rows have few
+            // entries, 30636 x 128, 123 tokens 22.8 / 22.1 us, and no faster elsewhere, 4096 x 4096, 4 bits, 333 tokens 34.7 / 34.3)
             for_each<GL / 4>([&](auto q) {
                 constexpr int k0 = 4 * decltype(q)::value;
-                if (GL <= 8 || __builtin_amdgcn_ballot_w64(b.at + k0 < b.to))
+                if (__builtin_amdgcn_ballot_w64(b.at + k0 < b.to))
                     for_each<4>([&](auto k) {
                         constexpr int kk = k0 + decltype(k)::value;
                         x[kk] = __builtin_amdgcn_raw_buffer_load_b128(rt, deal(std::integral_constant<int, kk>{}, off) + octet, 0, 0);
@@ -820,11 +834,11 @@ hipError_t launch_gemm_t(GemmArgs &ga, hipStream_t s)
 // with four), x 32; 64 x 64, in parts of a whole turn where the index words leave LDS for three, 2 and 3 bits (with parts of half a
 // turn the waves met twice as often, us without outliers 287 x 10880, 3 bits, 458 tokens 49.4 / 45.8, 1908 x 7168, 2 bits, 310
 // 31.9 / 30.7, with 0.05 % 326 x 16896, 3 bits, 475 78.5 / 72.8).
-template <int BITS>
-using SmallTile = GemmTile<1, 2, 4, 2, 4, 4, BITS == 4 ? 2 : 3>;
+template <int BITS, bool PLAIN = false>
+using SmallTile = GemmTile<1, 2, 4, 2, 4, PLAIN ? 3 : 4, BITS == 4 ? 2 : 3, PLAIN>;
 using LowTile = GemmTile<1, 1, 4, 2, 4, 5, 3>;
-template <int BITS>
-using TinyTile = std::conditional_t<BITS == 4, GemmTile<1, 2, 2, 4, 2, 4, 2>, GemmTile<1, 2, 2, 4, 4, 3, 2>>;
+template <int BITS, bool PLAIN = false>
+using TinyTile = std::conditional_t<BITS == 4, GemmTile<1, 2, 2, 4, 2, 4, 2, PLAIN>, GemmTile<1, 2, 2, 4, 4, 3, 2, PLAIN>>;
 
 template <int BITS, int MODE>
 hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
@@ -838,15 +852,18 @@ hipError_t launch_gemm_m(GemmArgs &ga, hipStream_t s)
     using Large = GemmTile<1, 4, 8, 1, 4, 3, 2>;
     using Small = SmallTile<BITS>;
     using Small16 = GemmTile<1, 2, 4, 4, 2, 3, 2>;
-    using Tiny = TinyTile<BITS>;
     const uint64_t m = (ga.M + 63) / 64, small = (uint64_t)((ga.a.N + 127) / 128) * m;
-    if ((uint64_t)((ga.a.N + 63) / 64) * m <= 256) return launch_gemm_t<BITS, MODE, Tiny>(ga, s);
+    if ((uint64_t)((ga.a.N + 63) / 64) * m <= 256) {
+        if (ga.a.K <= kPlainTinyK) return launch_gemm_t<BITS, MODE, TinyTile<BITS, true>>(ga, s);
+        return launch_gemm_t<BITS, MODE, TinyTile<BITS>>(ga, s);
+    }
     // (rows that ask for a third set of sums, in matrices that the 16-token kernel would cut into slices: see kDeepK)
     if (small > 512 && (ga.a.K <= kDeepK || ga.a.N >= 8192)) return launch_gemm_t<BITS, MODE, Large>(ga, s);
     // 2-bit weights leave registers for four waves to a SIMD, of which four share their rows and a quarter of K each
     // (4096 x 4096, 333 tokens: 42 us against 46 with two waves to a SIMD)
     if constexpr (BITS == 2)
         if (ga.a.K > kFineK) return launch_gemm_t<BITS, MODE, Small16>(ga, s);
+    if (ga.a.K <= kPlainSmallK) return launch_gemm_t<BITS, MODE, SmallTile<BITS, true>>(ga, s);
     return launch_gemm_t<BITS, MODE, Small>(ga, s);
 }
 

@@ -63,7 +63,7 @@ def test_the_workloads_kernels_keep_their_registers(parts, min_waves):
 
 def test_the_prompt_kernels_stay_in_registers():
     prompt = {k: v for k, v in resources().items() if "decode_gemm_kernel" in k}
-    assert len(prompt) == 20                                          # 2 to 4 bits, V2 and V2a, three tiles; one of 16 waves at 2 bits
+    assert len(prompt) == 32                                          # 2 to 4 bits, V2 and V2a, three tiles, two of them for short rows too; one of 16 waves at 2 bits
     for k, v in prompt.items():
         assert v["vgpr_spills"] == 0 and v["agprs"] == 0 and v["scratch_bytes_per_lane"] == 0, (k, v)
 

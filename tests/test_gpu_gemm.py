@@ -43,6 +43,24 @@ def test_prompt_parity(mode, bits, N, K, M, dens):
     assert torch.equal(y32, again)
 
 
+# rows of a block or two, which have tiles of their own (up to 512 columns of 64 x 64 tiles, 256 of 128 x 64): both sides of either
+# limit, ragged last tiles, waves with no block, an infinity and a NaN that stay with their tokens
+@pytest.mark.parametrize("N,K,M", [(130, 128, 95), (143, 256, 150), (700, 384, 97), (212, 512, 92), (213, 640, 92), (8193, 128, 130), (6145, 256, 200), (8300, 384, 131)])
+@pytest.mark.parametrize("mode,bits", [(V2, 4), (V2A, 3), (V2, 2), (V2A, 4), (V2, 3), (V2A, 2)])
+def test_short_rows(mode, bits, N, K, M):
+    W = xi.random_weights(mode, bits, N, K, L=33, density=0.01, seed=N + K + M + bits)
+    xb = xi.activations(np.random.default_rng(M), M, K)
+    dW, xd = xfp.upload(W), dev_x(xb)
+    assert xfp.xfp_launch_route(dW, M) == (xfp.XFP_ROUTE_GEMM, M)
+    y = xfp.xfp_gemv(dW, xd, y_dtype=torch.float32)
+    assert gated_rel_err(y.cpu().numpy(), oracle.gemv_weights(W, xb)) <= 1e-4
+    assert torch.equal(xfp.xfp_gemv(dW, xd), y.half())
+    xd[3, 7], xd[M - 1, K - 1] = float("inf"), float("nan")
+    z = xfp.xfp_gemv(dW, xd, y_dtype=torch.float32)
+    rest = [m for m in range(M) if m not in (3, M - 1)]
+    assert torch.equal(z[rest], y[rest]) and torch.isnan(z[M - 1]).all() and not torch.isfinite(z[3]).any()
+
+
 @pytest.mark.parametrize("mode,bits,K", [(V2, 4, 640), (V2, 3, 640), (V2, 2, 384), (V2A, 4, 384), (V2A, 3, 640), (V2A, 2, 384)])
 def test_one_hot_tokens_read_single_weights(mode, bits, K):
     """Token m is one at column (7 m) mod K: y[m][n] is that column of the matrix, one rounding of the sum of its codebook
