@@ -152,7 +152,8 @@ typedef struct xfp_weights {
  *        matrix has 8161 rows or more, else in slices of K whose partial
  *        sums go through a static scratch plane) or, with more than 16, up
  *        to 64 (as many chunks of 16 as 16 * ceil(m / 16) * K <= 2^19
- *        allows: 64 tokens up to K = 8192, 32 up to 16384); from 65 to 128
+ *        allows: 64 tokens up to K = 8192, 32 up to 16384), which tall
+ *        matrices run as one column of the tiled product; from 65 to 128
  *        tokens on (128 rows and more, K <= 65536, the tokens by the
  *        matrix) as one tiled product per 2^24 / K tokens, tokens left over
  *        as above; what none of them takes runs the M = 1 path once per
@@ -161,7 +162,8 @@ typedef struct xfp_weights {
  * 4-bit V2 (whose rows of any length the tile kernel takes), with no split into
  * equal slices of at most 8192 (or partial sums beyond the scratch plane) AND
  * too long for the general kernel to stage on chip (2 K bytes plus its tables
- * within 160 KB).  xfp_launch_route tells on the host which kernel a call takes.
+ * within 160 KB).  xfp_launch_route tells on the host which kernel a call takes
+ * (and xfp_wide_tile which of the two of XFP_ROUTE_WIDE).
  */
 int xfp_gemv(const xfp_weights *W, const void *x, int M, int64_t ldx,
              void *y, int y_dtype, int64_t ldy, void *hip_stream);
@@ -373,7 +375,8 @@ typedef enum {
     XFP_ROUTE_SPLIT_K = 2,   /* the streaming kernel over slices of K plus the fixed-order sum                      */
     XFP_ROUTE_TILE = 3,      /* M = 1 per slot, 32 rows across the lanes                                             */
     XFP_ROUTE_BATCH = 4,     /* 2 .. 16 tokens on the matrix cores, activations in registers                         */
-    XFP_ROUTE_WIDE = 5,      /* 17 .. 64 tokens on the matrix cores in one pass over the weights                     */
+    XFP_ROUTE_WIDE = 5,      /* up to 64 tokens on the matrix cores in one pass over the weights: tiles of 32 rows, or
+                                from 17 tokens on of tall matrices one column of GEMM's tiles (xfp_wide_tile)        */
     XFP_ROUTE_GEMM = 6,      /* prompts: many tokens as a tiled product on the matrix cores                          */
     XFP_ROUTE_RESIDENT = 7   /* up to 64 tokens on the matrix cores, activations in LDS (xfp_launch_route only)      */
 } xfp_route_id;
@@ -394,6 +397,13 @@ int xfp_ring_slot(unsigned ticket, int capturing);
  * XFP_ERR_UNSUPPORTED where none fits.
  */
 int xfp_resident_shares(const xfp_weights *W, int M, unsigned *shares);
+
+/*
+ * Which kernel an XFP_ROUTE_WIDE launch of M tokens runs in, by its tile (host only, touches no device, whether or not the
+ * dispatch rule asks for such a launch): tile[0] rows, tile[1] tokens.  32 rows: the kernel of that route; 128 rows: one column
+ * of the prompt kernel's tiles.  XFP_ERR_UNSUPPORTED where the route does not take the matrix with as many tokens.
+ */
+int xfp_wide_tile(const xfp_weights *W, int M, unsigned *tile);
 
 /* Text for a status code; never NULL.  For XFP_ERR_HIP the text of the last
  * HIP error seen by the calling thread is appended. */

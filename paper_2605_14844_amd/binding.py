@@ -76,11 +76,11 @@ def load_library():
     lib.xfp_probe_copy.argtypes = [vp, vp, u64, vp]
     lib.xfp_select_kernel.argtypes = [i32]
     lib.xfp_route.argtypes = lib.xfp_launch_route.argtypes = [wp, i32, i32, ctypes.POINTER(ctypes.c_int)]
-    lib.xfp_resident_shares.argtypes = [wp, i32, ctypes.POINTER(ctypes.c_uint)]
+    lib.xfp_resident_shares.argtypes = lib.xfp_wide_tile.argtypes = [wp, i32, ctypes.POINTER(ctypes.c_uint)]
     lib.xfp_strerror.argtypes = [i32]
     lib.xfp_strerror.restype = ctypes.c_char_p
     for name in ("xfp_gemv", "xfp_gemv_noalloc", "xfp_gemv_moe", "xfp_gemv_moe_silu_mul", "xfp_gemv_moe_combine", "xfp_check_contents", "xfp_convert_bf16_to_f16", "xfp_repack_word10", "xfp_repack_words", "xfp_unpack_indices", "xfp_dequant_bulk",
-                 "xfp_probe_read", "xfp_probe_copy", "xfp_version", "xfp_init", "xfp_select_kernel", "xfp_route", "xfp_launch_route", "xfp_resident_shares"):
+                 "xfp_probe_read", "xfp_probe_copy", "xfp_version", "xfp_init", "xfp_select_kernel", "xfp_route", "xfp_launch_route", "xfp_resident_shares", "xfp_wide_tile"):
         getattr(lib, name).restype = i32
     _lib = lib
     return lib
@@ -142,6 +142,14 @@ def xfp_launch_route(W, M: int, expert_indexed: bool = False):
     """(route id, tokens) of the first launch that xfp_gemv / xfp_gemv_moe make for M tokens / slots (host only), including
     the kernels that stand in for a family where they are faster."""
     return _ask(load_library().xfp_launch_route, W, M, expert_indexed)
+
+
+def xfp_wide_tile(W, M: int):
+    """(rows, tokens) of the tile that an XFP_ROUTE_WIDE launch of M tokens runs in (host only): 32 rows are that route's kernel,
+    128 one column of the prompt kernel's tiles."""
+    tile = (ctypes.c_uint * 2)()
+    _check(load_library().xfp_wide_tile(ctypes.byref(W.desc if hasattr(W, "desc") else W), int(M), tile))
+    return tile[0], tile[1]
 
 
 def xfp_init() -> None:

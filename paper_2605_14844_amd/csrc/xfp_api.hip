@@ -677,6 +677,18 @@ int xfp_resident_shares(const xfp_weights *W, int M, unsigned *shares)
     return XFP_OK;
 }
 
+int xfp_wide_tile(const xfp_weights *W, int M, unsigned *tile)
+{
+    int rc = check_weights(W);
+    if (rc) return rc;
+    if (!tile) return XFP_ERR_NULL;
+    if (M < 1 || M > 64 || W->E != 1) return XFP_ERR_SHAPE;
+    const int mode = (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : (int)W->mode;
+    if (!xfp::wide_supports((int)W->bits, mode, W->L, W->N, W->K, M)) return XFP_ERR_UNSUPPORTED;
+    xfp::wide_tile(mode, W->N, W->K, M, tile);
+    return XFP_OK;
+}
+
 int xfp_ring_slot(unsigned ticket, int capturing) { return xfp::ring_slot_index(ticket, capturing != 0); }
 
 int xfp_version(void) { return (0 << 16) | (2 << 8) | 0; }

@@ -624,6 +624,13 @@ bool wide_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
     return (uint64_t)K * 16u * (uint64_t)((M + 15) / 16) <= copy_cap && (uint64_t)K * 32u * 4u <= 0xFFFFFFFFull;
 }
 
+void wide_tile(int mode, uint32_t N, uint32_t K, int M, unsigned *out)
+{
+    const bool tiles = prefer_wide_tiles(mode, N, K, M);
+    out[0] = tiles ? 128u : (unsigned)kWideRows;
+    out[1] = !tiles ? (unsigned)(M + 15) / 16 * 16 : M <= 32 ? 32u : 64u;
+}
+
 // M <= 64 tokens in one pass over the weights.  xc: the workspace's re-laid activation copies, written by a
 // small kernel in front of the decode kernel (launches on one stream may share them).
 // sx: MODE 2 only, room for 16 K / 128 floats (a scratch plane of the workspace).

@@ -148,6 +148,8 @@ bool wide_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
                    uint64_t copy_cap = (uint64_t)kXtMaxK * kXtTokens);
 hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, float *sx,
                               hipStream_t s);
+// Rows and tokens of the tile that launch_decode_wide runs in (for a host-only query).
+void wide_tile(int mode, uint32_t N, uint32_t K, int M, unsigned *out);
 // The tokens of the wide kernel as one column of the prompt kernel's tiles, with the same copies in the same workspace; where that
 // is the faster one launch_decode_wide hands the call on.
 bool prefer_wide_tiles(int mode, uint32_t N, uint32_t K, int M);

@@ -13,15 +13,19 @@ pytestmark = pytest.mark.gpu
 V2, V2A = xi.MODE_V2, xi.MODE_V2A
 
 
-@pytest.mark.parametrize("mode,bits,N,K,M", [
-    (V2, 4, 24449, 3200, 17), (V2, 4, 24448, 3200, 17), (V2A, 3, 24500, 1664, 32), (V2, 2, 24577, 128, 33), (V2A, 4, 24450, 384, 48),
-    (V2, 3, 20353, 1152, 49), (V2, 3, 20352, 1152, 49), (V2A, 2, 20400, 256, 64), (V2, 3, 16257, 640, 33), (V2A, 2, 16300, 768, 61), (V2, 4, 16300, 1024, 64),
-    (V2, 2, 57217, 1664, 25), (V2A, 3, 45057, 640, 40)])
-def test_wide_calls_in_tiles(mode, bits, N, K, M):
+TILE = lambda M: (128, 32 if M <= 32 else 64)                         # of the prompt kernel; the 64-token kernel's has 32 rows
+
+
+@pytest.mark.parametrize("mode,bits,N,K,M,tiles", [
+    (V2, 4, 24449, 3200, 17, True), (V2, 4, 24448, 3200, 17, False), (V2A, 3, 24500, 1664, 32, True), (V2, 2, 24577, 128, 33, True), (V2A, 4, 24450, 384, 48, True),
+    (V2, 3, 20353, 1152, 49, True), (V2, 3, 20352, 1152, 49, False), (V2A, 2, 20400, 256, 64, True), (V2, 3, 16257, 640, 33, True), (V2A, 2, 16300, 768, 61, True),
+    (V2, 4, 16300, 1024, 64, True), (V2, 2, 57217, 1664, 25, True), (V2A, 3, 45057, 640, 40, True)])
+def test_wide_calls_in_tiles(mode, bits, N, K, M, tiles):
     W = xi.random_weights(mode, bits, N, K, density=0.004, seed=N + K)
     x = xi.activations(np.random.default_rng(N + M), M, K)
     dW, xd = xfp.upload(W), torch.from_numpy(x.view(np.int16)).cuda().view(torch.float16)
     assert xfp.xfp_launch_route(dW, M) == (xfp.XFP_ROUTE_WIDE, M)
+    assert xfp.xfp_wide_tile(dW, M) == (TILE(M) if tiles else (32, (M + 15) // 16 * 16))
     y = xfp.xfp_gemv(dW, xd, y_dtype=torch.float32)
     torch.cuda.synchronize()
     assert gated_rel_err(y.cpu().numpy().astype(np.float64), oracle.gemv_weights(W, x)) <= 1e-4      # fp32 results, as in the other kernels' tests
@@ -36,6 +40,7 @@ def test_wide_calls_in_tiles(mode, bits, N, K, M):
 def test_infinities_and_nan_stay_with_their_tokens(M):
     W = xi.random_weights(V2, 3, 24600, 1920, density=0.01, seed=M)
     x, dW = torch.randn(M, W.K, device="cuda").half(), xfp.upload(W)
+    assert xfp.xfp_launch_route(dW, M) == (xfp.XFP_ROUTE_WIDE, M) and xfp.xfp_wide_tile(dW, M) == TILE(M)
     clean = xfp.xfp_gemv(dW, x, y_dtype=torch.float32)
     x[3, 7], x[M - 1, W.K - 1] = float("inf"), float("nan")
     y = xfp.xfp_gemv(dW, x, y_dtype=torch.float32)
@@ -46,6 +51,7 @@ def test_infinities_and_nan_stay_with_their_tokens(M):
 def test_they_replay_from_a_graph():
     W = xi.random_weights(V2A, 4, 24600, 1664, density=0.003, seed=7)
     dW, x = xfp.upload(W), torch.randn(30, W.K, device="cuda").half()
+    assert xfp.xfp_launch_route(dW, 30) == (xfp.XFP_ROUTE_WIDE, 30) and xfp.xfp_wide_tile(dW, 30) == TILE(30)
     xfp.xfp_gemv(dW, x, y_dtype=torch.float32)
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()

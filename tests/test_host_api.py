@@ -471,6 +471,26 @@ def test_what_stands_in_for_a_planned_launch():
     assert seen == set(range(8))
 
 
+def test_the_tile_of_a_wide_launch_is_reported():
+    """Two kernels run XFP_ROUTE_WIDE launches; the tile tells them apart: 32 rows and as many chunks of 16 tokens as there are, or
+    128 rows and 32 or 64 tokens."""
+    R, lib = xfp, dict(mode=1, L=32, group_ids=FAKE)
+    record = dict(flags=1, group_scale=FAKE, group_mid=FAKE, **lib)
+    tile = lambda M, **kw: R.xfp_wide_tile(desc(**kw), M)
+    for kw in (dict(), dict(bits=3), dict(bits=2, **lib)):
+        assert [tile(M, N=28672, K=8192, **kw) for M in (16, 17, 32, 33, 64)] == [(32, 16), (128, 32), (128, 32), (128, 64), (128, 64)]
+        assert [tile(M, N=14336, K=8192, **kw) for M in (2, 17, 33, 49, 64)] == [(32, 16), (32, 32), (32, 48), (32, 64), (32, 64)]
+    assert tile(16, N=28672, K=8192, **record) == (32, 16)
+    assert tile(2, N=8192, K=28672) == (32, 16)
+    for M, kw, status in [(33, dict(N=28672, K=16384), -3), (17, dict(N=28672, K=8192, **record), -3), (20, dict(N=28672, K=4096, bits=5), -3),
+                          (20, dict(N=28672, K=4096, mode=1, L=65, group_ids=FAKE), -3), (65, dict(N=28672, K=4096), -2), (0, dict(N=28672, K=4096), -2),
+                          (20, dict(N=28672, K=4096, E=2), -2), (20, dict(N=28672, K=100), -2)]:
+        with pytest.raises(R.XfpError) as e:
+            tile(M, **kw)
+        assert e.value.status == status, (M, kw)
+    assert R.load_library().xfp_wide_tile(ctypes.byref(desc(N=28672, K=4096)), 20, None) == -1
+
+
 def shares(M, **kw):
     """(slices, blocks of 16 rows of a workgroup, waves per block, workgroups) of a launch of the resident kernel"""
     out = (ctypes.c_uint * 4)()
