@@ -685,7 +685,7 @@ int xfp_wide_tile(const xfp_weights *W, int M, unsigned *tile)
     if (M < 1 || M > 64 || W->E != 1) return XFP_ERR_SHAPE;
     const int mode = (W->flags & XFP_FLAG_GROUP_AFFINE) ? 2 : (int)W->mode;
     if (!xfp::wide_supports((int)W->bits, mode, W->L, W->N, W->K, M)) return XFP_ERR_UNSUPPORTED;
-    xfp::wide_tile(mode, W->N, W->K, M, tile);
+    xfp::wide_tile((int)W->bits, mode, W->N, W->K, M, tile);
     return XFP_OK;
 }
 

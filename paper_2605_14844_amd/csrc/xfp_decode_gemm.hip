@@ -914,24 +914,35 @@ hipError_t launch_wide_tiles_b(int mode, const DecodeArgs &a, int M, bool y_f32,
 
 // 17 to 64 tokens of many rows, the 64-token kernel's, as one column of 128-row tiles: that kernel reads its activations from L2
 // once per 32 rows and a lookup per pair of weights from LDS, which is most of its time once the matrix is large.  A round of tiles
-// takes the same time for any number of them, so they have to fill most of the last one.  us in the 64-token kernel / in tiles (cold
-// weights, 0.3 % outliers; 1941 drawn shapes):
-//  - 28672 x 8192: 64 tokens, 3 bits, library 85 / 65, 4 bits 83 / 64; 32 tokens (tiles of 32), 3 bits 57 / 47, 4 bits 59 / 54;
-//    17 tokens, 2 bits 46 / 38; 32768 x 2048, 64 tokens 33 / 25; 26793 x 2048, 29 25 / 21;
-//  - less than three quarters of a round: 21764 x 2176, 45 tokens 25.4 / 24.2, 22800 x 6272, 20 up to 11 % slower; 14336 x 8192, 64
-//    42 / 54, 8192 x 4096 18 / 31;
-//  - more than 48 tokens pay from five eighths on (20500 to 22500 rows 2 to 37 % faster, 18500 to 20500 4 % slower to 30 % faster),
-//    rows of up to 1024 columns from half a round on (17000 x 768, 62 tokens 24 % faster);
-//  - behind whole rounds (1400 shapes of 33000 to 131072 rows): less than seven eighths of all rounds 7 % slower to 34 % faster for up
-//    to 48 tokens (50793 x 2176, 37: 4 % slower), 40933 x 5632, 54 tokens at 0.62 of two rounds 15 % slower; above these lines 5 %
-//    slower at most, 8 to 30 % faster at the median.
-bool prefer_wide_tiles(int mode, uint32_t N, uint32_t K, int M)
+// takes the same time for any number of them, so they have to fill most of the last one; more of it for a library, whose ids the tiles
+// fetch through LDS and whose tables the other kernel builds once, most of all at 3 bits.  Always more than the line: at the half and at
+// three quarters of a round the other kernel's own rounds, of 512 tiles of 32 rows, are full (16370 x 640, 36 tokens, 3 bits, library
+// 14.1 us there, 17.9 in tiles; 24458 x 9856, 24, 4 bits 63 / 70).  us in the 64-token kernel / in tiles (cold weights, 0.05 to 1 %
+// outliers), at 7664 shapes drawn near the lines and above, of which 6314 are above: 21 of these are more than 2.5 % slower in tiles, all but
+// three in three rounds and more or within 3.1 % (7 % at most: 148979 x 2176, 53 tokens 144 / 154), the median 16 % faster:
+//  - 28672 x 8192: 64 tokens, 3 bits, library 83 / 63, 4 bits 83 / 64; 32 tokens (tiles of 32), 3 bits 57 / 48, 17, 2 bits 46 / 39;
+//  - one round: 17 to 48 tokens above three quarters 3 % slower at most, the median 11 to 15 % faster; more than 48 above five eighths
+//    4 % slower at most, but libraries at 3 and 4 bits 10 % below three quarters (23810 x 2176, 49 30 / 33); rows of up to 1024 columns from
+//    half a round on, where no library at 3 bits has more than 512 (16367 x 512, 59 14.3 / 15.6 at the half);
+//  - several rounds: 4 bits, 17 to 32 tokens below fifteen sixteenths up to 8 % slower (146550 x 2176, 32 117 / 127), 33 to 48 tokens at 3
+//    bits up to 10 % (115953 x 2176, 44 105 / 115), of a library 13 % (144207 x 1792, 43 115 / 130) and 6 % above that line; more than 48
+//    tokens of a library below seven eighths 14 % (107614 x 1664, 56 95 / 109); rows of 640 to 1024 columns of a library below seven
+//    eighths 15 % (72223 x 1024, 44 51 / 59), up to 512 columns 10 to 20 % faster there.
+// What lies below the lines is given up for the sake of the slower ones: 4 % faster in tiles at the median.
+bool prefer_wide_tiles(int bits, int mode, uint32_t N, uint32_t K, int M)
 {
     const uint64_t m = (uint64_t)(M + 7) / 8 * 8, k = (uint64_t)(K + 255) / 256 * 256;
     if (mode > 1 || M < 17 || m * k > kCopyHalves) return false;
     const uint64_t tiles = ((uint64_t)N + 127) / 128, rounds = (tiles + 255) / 256;
-    const uint64_t least = rounds == 1 ? (M > 32 && K <= 1024 ? 8 : M > 48 ? 10 : 12) : (M > 32 && K <= 1024 ? 11 : M > 48 ? 13 : 14);
-    return tiles >= least * 16 * rounds;                       // sixteenths of all rounds
+    const bool lib = mode == 1, many = rounds > 1;
+    uint64_t line;                                             // sixteenths of all rounds
+    if (M > 32 && K <= 512) line = many ? 11 : 8;
+    else if (M > 32 && K <= 1024) line = many ? (lib ? 14 : 12) : lib && bits == 3 ? 12 : 8;
+    else if (M > 48) line = many ? (lib ? 14 : 13) : lib && bits >= 3 ? 12 : 10;
+    else if (!many) line = 12;
+    else if (M > 32) line = lib && bits == 3 ? 16 : bits == 3 || (lib && bits == 4) ? 15 : 14;
+    else line = bits == 4 ? 15 : 14;
+    return tiles > line * 16 * rounds;
 }
 
 hipError_t launch_wide_tiles(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s)

@@ -624,9 +624,9 @@ bool wide_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
     return (uint64_t)K * 16u * (uint64_t)((M + 15) / 16) <= copy_cap && (uint64_t)K * 32u * 4u <= 0xFFFFFFFFull;
 }
 
-void wide_tile(int mode, uint32_t N, uint32_t K, int M, unsigned *out)
+void wide_tile(int bits, int mode, uint32_t N, uint32_t K, int M, unsigned *out)
 {
-    const bool tiles = prefer_wide_tiles(mode, N, K, M);
+    const bool tiles = prefer_wide_tiles(bits, mode, N, K, M);
     out[0] = tiles ? 128u : (unsigned)kWideRows;
     out[1] = !tiles ? (unsigned)(M + 15) / 16 * 16 : M <= 32 ? 32u : 64u;
 }
@@ -638,7 +638,7 @@ hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bo
 {
     if (!xc || bits < 2 || bits > 4 || M < 1 || M > 64 || mode < 0 || mode > 2) return hipErrorInvalidValue;
     if (mode == 2 && (!sx || M > 16 || !a.gscale || !a.gmid)) return hipErrorInvalidValue;
-    if (prefer_wide_tiles(mode, a.N, a.K, M)) return launch_wide_tiles(bits, mode, a, M, y_f32, xc, s);
+    if (prefer_wide_tiles(bits, mode, a.N, a.K, M)) return launch_wide_tiles(bits, mode, a, M, y_f32, xc, s);
     const int T = (M + 15) / 16;
     const uint32_t nb = (a.K * 2 * (uint32_t)T + 255) / 256 + (a.K / 8 * 16 * (uint32_t)T + 255) / 256 +
                         (mode == 2 ? (a.K / kGroup * 16 + 255) / 256 : 0u);

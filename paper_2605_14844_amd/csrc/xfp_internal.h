@@ -149,10 +149,10 @@ bool wide_supports(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int M
 hipError_t launch_decode_wide(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, float *sx,
                               hipStream_t s);
 // Rows and tokens of the tile that launch_decode_wide runs in (for a host-only query).
-void wide_tile(int mode, uint32_t N, uint32_t K, int M, unsigned *out);
+void wide_tile(int bits, int mode, uint32_t N, uint32_t K, int M, unsigned *out);
 // The tokens of the wide kernel as one column of the prompt kernel's tiles, with the same copies in the same workspace; where that
 // is the faster one launch_decode_wide hands the call on.
-bool prefer_wide_tiles(int mode, uint32_t N, uint32_t K, int M);
+bool prefer_wide_tiles(int bits, int mode, uint32_t N, uint32_t K, int M);
 hipError_t launch_wide_tiles(int bits, int mode, const DecodeArgs &a, int M, bool y_f32, XCopies *xc, hipStream_t s);
 // Resident kernel: up to 64 tokens of one matrix, the activations in LDS (2 to 4 bits, mode 2 = V2a with a scale and a
 // mid-point per group; V2 at 5 and 6 bits).  few_tokens: how many of `left` tokens it takes next, 0 where another kernel is faster; plane, part:

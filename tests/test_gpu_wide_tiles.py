@@ -17,9 +17,9 @@ TILE = lambda M: (128, 32 if M <= 32 else 64)                         # of the p
 
 
 @pytest.mark.parametrize("mode,bits,N,K,M,tiles", [
-    (V2, 4, 24449, 3200, 17, True), (V2, 4, 24448, 3200, 17, False), (V2A, 3, 24500, 1664, 32, True), (V2, 2, 24577, 128, 33, True), (V2A, 4, 24450, 384, 48, True),
-    (V2, 3, 20353, 1152, 49, True), (V2, 3, 20352, 1152, 49, False), (V2A, 2, 20400, 256, 64, True), (V2, 3, 16257, 640, 33, True), (V2A, 2, 16300, 768, 61, True),
-    (V2, 4, 16300, 1024, 64, True), (V2, 2, 57217, 1664, 25, True), (V2A, 3, 45057, 640, 40, True)])
+    (V2, 4, 24577, 3200, 17, True), (V2, 4, 24576, 3200, 17, False), (V2A, 3, 24600, 1664, 32, True), (V2, 2, 24577, 128, 33, True), (V2A, 4, 24577, 384, 48, True),
+    (V2, 3, 20481, 1152, 49, True), (V2, 3, 20480, 1152, 49, False), (V2A, 2, 20500, 256, 64, True), (V2, 3, 16385, 640, 33, True), (V2A, 2, 16400, 768, 61, True),
+    (V2, 4, 16400, 1024, 64, True), (V2, 2, 57345, 1664, 25, True), (V2A, 3, 45057, 512, 40, True), (V2A, 3, 45057, 640, 40, False)])
 def test_wide_calls_in_tiles(mode, bits, N, K, M, tiles):
     W = xi.random_weights(mode, bits, N, K, density=0.004, seed=N + K)
     x = xi.activations(np.random.default_rng(N + M), M, K)

@@ -491,6 +491,28 @@ def test_the_tile_of_a_wide_launch_is_reported():
     assert R.load_library().xfp_wide_tile(ctypes.byref(desc(N=28672, K=4096)), 20, None) == -1
 
 
+@pytest.mark.parametrize("lib", [False, True])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_the_lines_of_the_tall_matrix_rule(bits, lib):
+    """Tiles of 128 rows where they fill more of the last round of 256 than the 64-token kernel is the faster one at: the first matrix above
+    a line, the last below it."""
+    fmt = dict(mode=1, L=32, group_ids=FAKE) if lib else {}
+    rows = lambda M, N, K: xfp.xfp_wide_tile(desc(N=N, K=K, bits=bits, **fmt), M)[0]
+    lib3 = lib and bits == 3
+    for M, K, one, many in [(17, 4096, 12, 15 if bits == 4 else 14), (32, 128, 12, 15 if bits == 4 else 14), (33, 512, 8, 11), (64, 128, 8, 11),
+                            (33, 640, 12 if lib3 else 8, 14 if lib else 12), (64, 1024, 12 if lib3 else 8, 14 if lib else 12),
+                            (33, 1152, 12, 16 if lib3 else 15 if bits == 3 or (lib and bits == 4) else 14),
+                            (48, 8192, 12, 16 if lib3 else 15 if bits == 3 or (lib and bits == 4) else 14),
+                            (49, 1152, 12 if lib and bits >= 3 else 10, 14 if lib else 13), (64, 8192, 12 if lib and bits >= 3 else 10, 14 if lib else 13)]:
+        for rounds, line in ((1, one), (2, many), (3, many)):
+            last = 128 * 16 * line * rounds                           # rows of the tiles at the line
+            assert rows(M, last, K) == 32, (M, K, rounds)
+            if line < 16:
+                assert rows(M, last + 1, K) == 128 and rows(M, 128 * 256 * rounds, K) == 128, (M, K, rounds)
+        assert rows(M, 128 * 256 + 1, K) == 32
+    assert rows(16, 28672, 4096) == 32
+
+
 def shares(M, **kw):
     """(slices, blocks of 16 rows of a workgroup, waves per block, workgroups) of a launch of the resident kernel"""
     out = (ctypes.c_uint * 4)()
