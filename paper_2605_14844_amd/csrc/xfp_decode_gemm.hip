@@ -79,7 +79,8 @@ struct GemmTile {
     static constexpr bool DEAL = TB <= 2 && !PLAIN_;
     static constexpr bool EARLY = NW <= 8 && DEAL;             // there are registers for what is asked for ahead of its use
     static constexpr bool FINE = NW <= 8;                      // takes short rows (half blocks as chains)
-    static constexpr bool DEEP = WK > 1 && NW <= 8 && !PLAIN_; // a third set of sums for long rows
+    // A third set of sums for long rows: tiles of 32 tokens are taken for 17 and more, whose copies hold rows of up to 16384 columns.
+    static constexpr bool DEEP = WK > 1 && NW <= 8 && TB > 1 && !PLAIN_;
     static_assert(kB % (NW * 1024) == 0 && AHEAD >= 1 && BN % NW == 0, "");
     // registers: accumulators and sums, operands (B twice), index words, planes; then waves per SIMD
     static constexpr int kRegs = (WK > 1 && NW <= 8 ? 48 : 32) * RB * TB + 16 * RB + 8 * TB + 4 * RB + 8 * RB + 56;
@@ -894,6 +895,7 @@ hipError_t launch_gemm_b(int mode, const DecodeArgs &a, int M, bool y_f32, Promp
     return mode == 1 ? launch_gemm_m<BITS, 1>(ga, s) : launch_gemm_m<BITS, 0>(ga, s);
 }
 
+static_assert(kCopyHalves / 32 <= kDeepK, "the longest row with more than 16 tokens (wide_supports)");
 template <int BITS, int MODE>
 hipError_t launch_wide_tiles_m(GemmArgs &ga, hipStream_t s)
 {
