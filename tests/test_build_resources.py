@@ -68,6 +68,14 @@ def test_the_prompt_kernels_stay_in_registers():
         assert v["vgpr_spills"] == 0 and v["agprs"] == 0 and v["scratch_bytes_per_lane"] == 0, (k, v)
 
 
+def test_the_tiles_of_tall_matrices_stay_in_registers():
+    """The same loop, with the same counted waits, under another name."""
+    tiles = {k: v for k, v in resources().items() if "decode_wide_tiles_kernel" in k}
+    assert len(tiles) == 6                                            # 2 to 4 bits, V2 and V2a
+    for k, v in tiles.items():
+        assert v["vgpr_spills"] == 0 and v["agprs"] == 0 and v["scratch_bytes_per_lane"] == 0 and v["waves_per_simd"] >= 3, (k, v)
+
+
 def test_the_general_kernel_keeps_its_waves_at_5_and_6_bits():
     """A wave there owns a row or two: eight of them per SIMD are what hides a round trip, in 64 registers."""
     rows = {k: v for k, v in resources().items() if re.search(r"decode_rows_kernelILi[56]ELi0E", k)}

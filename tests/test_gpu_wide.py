@@ -143,6 +143,16 @@ def test_strided_tokens_and_outputs():
     assert np.all(got[:, 100:] == 7.0)                                          # nothing written past N
 
 
+# more tiles than CUs, in two and three rounds of workgroups, with long rows: the full-size cases behind these run in the prompt kernel's tiles
+@pytest.mark.parametrize("mode,bits,N,K,M", [(V2, 4, 14336, 8192, 64), (V2A, 3, 14336, 8192, 64), (V2, 3, 20000, 4096, 33), (V2, 2, 24000, 2176, 48),
+                                             (V2A, 4, 19000, 10752, 48), (V2A, 2, 24000, 16384, 32), (V2, 4, 33000, 1152, 40)])
+def test_many_tiles_of_long_rows(mode, bits, N, K, M):
+    W = xi.random_weights(mode, bits, N, K, density=0.003, seed=N + K + M)
+    dW = xfp.upload(W)
+    assert xfp.xfp_launch_route(dW, M) == (xfp.XFP_ROUTE_WIDE, M) and xfp.xfp_wide_tile(dW, M)[0] == 32
+    check(W, xi.activations(np.random.default_rng(M + N), M, K))
+
+
 def test_workload_5_shape_at_3_bits_with_48_tokens_full_size():
     """28672 x 8192, 3 bits (the matrix of bench.py --config 9), 48 tokens in one pass."""
     W = xi.random_weights(V2, 3, 28672, 8192, density=0.003, seed=xi.BASE_SEED + 9)

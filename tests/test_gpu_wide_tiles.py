@@ -1,5 +1,7 @@
 """17 to 64 tokens of matrices tall enough for one column of the prompt kernel's tiles (tiles of 32 tokens for up to 32): both sides
 of the rule's limits, ragged last tiles, rows of an odd number of groups and of fewer blocks than waves that share them."""
+import copy
+
 import numpy as np
 import pytest
 import torch
@@ -34,6 +36,51 @@ def test_wide_calls_in_tiles(mode, bits, N, K, M, tiles):
     fixed = torch.full((M, N), 7.0, device="cuda")
     xfp.xfp_gemv_noalloc(dW, xd, fixed)
     assert torch.equal(fixed, y)
+
+
+# rows of more than 64 groups, whose library ids are fetched in the loop, up to the longest that each tile takes (the other kernel's
+# row beside it); no outliers, outliers in the last row alone
+@pytest.mark.parametrize("mode,bits,N,K,M,density", [(V2A, 2, 24577, 8320, 20, 0.003), (V2A, 3, 24600, 16384, 32, 0.001), (V2A, 4, 24577, 12416, 17, 0.0), (V2, 4, 24577, 16384, 24, 0.001),
+                                                     (V2A, 4, 24700, 10752, 48, 0.001), (V2A, 2, 24577, 8320, 40, 0.0), (V2, 3, 24577, 8320, 33, None)])
+def test_long_rows_and_matrices_without_outliers(mode, bits, N, K, M, density):
+    W = xi.random_weights(mode, bits, N, K, density=density or 0.0, seed=N + K)
+    if density is None:
+        W.out_row_ptr = np.concatenate([np.zeros(N, np.int32), np.array([9], np.int32)])
+        W.out_col, W.out_val = np.arange(0, K, K // 9, dtype=np.int32)[:9], xi.activations(np.random.default_rng(2), 1, 9).ravel()
+    x = xi.activations(np.random.default_rng(K + M), M, K)
+    dW, xd = xfp.upload(W), torch.from_numpy(x.view(np.int16)).cuda().view(torch.float16)
+    assert xfp.xfp_launch_route(dW, M) == (xfp.XFP_ROUTE_WIDE, M) and xfp.xfp_wide_tile(dW, M) == TILE(M)
+    y = xfp.xfp_gemv(dW, xd, y_dtype=torch.float32)
+    rows = np.unique(np.concatenate([np.arange(0, N, 997), np.arange(N - 140, N)]))                        # (the oracle's time)
+    assert gated_rel_err(y.cpu().numpy()[:, rows].astype(np.float64), oracle.gemv_weights(some_rows(W, rows), x)) <= 1e-4
+
+
+def some_rows(W, rows):
+    ptr = W.out_row_ptr
+    pick = np.concatenate([np.arange(ptr[r], ptr[r + 1]) for r in rows] + [np.zeros(0, np.int64)]).astype(np.int64)
+    V = copy.copy(W)
+    V.N, V.indices = len(rows), W.indices[:, rows]
+    if W.mode == V2:
+        V.codebooks = W.codebooks[:, rows]
+    else:
+        V.group_ids = W.group_ids[:, rows]
+    V.out_row_ptr = np.concatenate([[0], np.cumsum([ptr[r + 1] - ptr[r] for r in rows])]).astype(np.int32)
+    V.out_col, V.out_val = W.out_col[pick], W.out_val[pick]
+    return V
+
+
+@pytest.mark.parametrize("mode,bits,M", [(V2, 4, 30), (V2A, 3, 50)])
+def test_bf16_strides_and_untouched_padding(mode, bits, M):
+    N, K = 24700, 1664
+    W = xi.random_weights(mode, bits, N, K, density=0.003, seed=M)
+    x = torch.randn((M, K + 24), device="cuda").bfloat16()[:, :K]
+    dW = xfp.upload(W)
+    assert xfp.xfp_launch_route(dW, M) == (xfp.XFP_ROUTE_WIDE, M) and xfp.xfp_wide_tile(dW, M) == TILE(M)
+    want = xfp.xfp_gemv(dW, xfp.xfp_convert_bf16_to_f16(x), y_dtype=torch.float32)
+    for ldy in (N + 3, N + 4):                                                             # single and four-value stores
+        buf = torch.full((M, ldy), -3.0, dtype=torch.bfloat16, device="cuda")
+        xfp.xfp_gemv(dW, x, y=buf[:, :N])
+        assert torch.equal(buf[:, :N], want.bfloat16()) and bool((buf[:, N:] == -3.0).all())
 
 
 @pytest.mark.parametrize("M", [29, 64])
