@@ -219,12 +219,12 @@ bool wide_affine(const xfp_weights *W, bool expert_indexed, int tokens)
 // 32 to 16 beyond).  A round of tiles takes the same time for any number of them up to the 256 CUs, a pass grows with the rows only
 // from 256 tiles of 32 on.  product_tokens takes more calls, at the limits that the product's present speed gives.  Measured,
 // us as it runs / in passes alone / as one product (fp16 results, 4 bits, 0.3 % outliers):
-//  - one round of 128 x 64 tiles or less, from 193 tokens on: 4096 x 4096 193 tokens 29 / 58 / 30, 384 41 / 103 / 41;
-//    8192 x 8192 193 74 / 86 / 73; 65 tokens: 23 / 23 / 26 and 37 / 37 / 48;
+//  - one round of 128 x 64 tiles or less, from 193 tokens on: 4096 x 4096 193 tokens 27 / 57 / 27, 384 36 / 103 / 36;
+//    8192 x 8192 193 67 / 91 / 67; 65 tokens: 23 / 23 / 24 and 36 / 36 / 42;
 //  - a little more than that: passes until one round is left (each launch's leftover is planned anew): 8192 x 8192 257 tokens
-//    99 / 112 / 130, 320 100 / 133 / 130, 384 125 / 159 / 131, 448 135 / 184 / 137; 6144 x 4096 333 64 / 102 / 74;
-//  - 28672 x 8192: 384 tokens 309 / 425 / 299, 512 338 / 559 / 325 (the first and the third are one launch each);
-//  - rows beyond 16384 columns, which are passed over once per 16 tokens: 4096 x 28672 128 tokens 133 / 288 / 128.
+//    96 / 118 / 114, 320 95 / 140 / 113, 384 121 / 165 / 115, 448 121 / 192 / 120; 6144 x 4096 333 56 / 101 / 65;
+//  - 28672 x 8192: 384 tokens 308 / 377 / 307, 512 331 / 505 / 331 (the first and the third are one launch each);
+//  - rows beyond 16384 columns, which are passed over once per 16 tokens: 4096 x 28672 128 tokens 112 / 283 / 112.
 // Formats that no matrix-core kernel takes otherwise (libraries beyond LDS, rows beyond 32768 columns) run token by token.
 bool gemm_only(const xfp_weights *W)
 {
@@ -293,16 +293,17 @@ int resident_tokens(const xfp_weights *W, bool expert_indexed, int left, const P
 
 // The tokens that the tiled product takes in place of planned passes of 64 or 16 (0: none).  The plan keeps the product for
 // more than 192 tokens and single rounds of its tiles; in launches that cost what they do now it is the faster one from 80
-// tokens on, us in passes / as a product (graph replay, cold weights): 4096 x 4096 80 tokens 27 / 25, 96 31 / 25, 160 48 / 27;
-// 512 x 1024 96 20 / 13; 28672 x 8192 96 138 / 142, 192 223 / 164, 320 356 / 295; 28672 x 1024 224 99 / 38; 16384 x 2048 300 95 / 51;
-// from 65 on for rows beyond 8192 columns, whose passes are of 16 to 48 tokens: 2048 x 16384 65 86 / 70, 4096 x 14336 80 87 / 65,
-// 8192 x 28672 80 224 / 132 (8192 x 8192 65 37 / 48, 80 52 / 45).  Three exceptions: few long rows, where the resident kernel takes
-// the passes (512 x 8192, 96 tokens 33 / 39, 128 41 / 39); what is at most two passes more than one round of 128 x 64 tiles (8192 x 8192, 320 tokens:
-// a pass and a round 86, two rounds 105); and up to 192 tokens in a round and up to half another, at 3 and 4 bits for rows of 3072
-// to 8192 columns (17482 x 6400 105 tokens 96 / 122, 11589 x 6656 142 91 / 114, 22706 x 4224 91 66 / 80; with more of the
-// second round 27288 x 3712 107 80 / 74, 25208 x 6656 124 115 / 99; at 2 bits 11232 x 4480 190 74 / 64), otherwise where no more
-// than 32 tokens are left behind passes of 64 (19878 x 2944 80 56 / 73, 21071 x 9344 65 119 / 180, 11970 x 2816 129 54 / 68; 2 bits
-// 19633 x 2048 89 45 / 55) and the rows are not short (16962 x 768 88 39.5 / 37; 640 columns and more with two tiles, 1536 with three).
+// tokens on, us in passes / as a product (graph replay, cold weights): 4096 x 4096 80 tokens 29 / 24, 96 32 / 24, 160 50 / 25;
+// 512 x 1024 96 20 / 13; 28672 x 8192, whose passes are columns of the same tiles, 96 118.5 / 119.4, 192 191 / 166, 320 317 / 306; 28672 x 1024
+// 224 71 / 37; 16384 x 2048 300 93 / 50; from 65 on for rows beyond 8192 columns, whose passes are of 16 to 48 tokens: 2048 x 16384 65 86 / 62,
+// 4096 x 14336 80 86 / 58, 8192 x 28672 80 219 / 131 (8192 x 8192 65 36 / 42, 80 52 / 43).  Three exceptions: few long rows, where the resident
+// kernel takes the passes (512 x 8192, 96 tokens 33.3 / 33.8, 128 41 / 34); what is at most two passes more than one round of 128 x 64 tiles
+// (8192 x 8192, 320 tokens: a pass and a round 95, two rounds 113); and up to 192 tokens in a round and up to half another, at 3 and 4 bits for rows
+// of 3072 to 8192 columns (17482 x 6400 105 tokens 94 / 100, 11589 x 6656 142 93 / 99, 22706 x 4224 91 72 / 77; with more of the
+// second round 27288 x 3712 107 76 / 71, 25208 x 6656 124 107 / 101; at 2 bits 11232 x 4480 190 76 / 62), otherwise where no more
+// than 32 tokens are left behind passes of 64 (19878 x 2944 80 52 / 58, 21071 x 9344 65 108 / 136, 11970 x 2816 129 50 / 56, but at 2 bits
+// 19633 x 2048 89 42.5 / 39.9 by now) and the rows are not short (16962 x 768 88 30.7 / 32.6, 39.5 / 37 when the line was drawn; 640 columns and
+// more with two tiles, 1536 with three).
 int product_tokens(const xfp_weights *W, bool expert_indexed, int left, const Plan &p)
 {
     if (expert_indexed || left <= 64 || (p.route != XFP_ROUTE_WIDE && p.route != XFP_ROUTE_BATCH) || general_only(W)) return 0;

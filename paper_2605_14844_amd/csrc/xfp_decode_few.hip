@@ -71,16 +71,18 @@ bool few_plan(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, uint32_t M
 //    1200 x 4096 6.6 / 7.3 and 40 of 8192 x 8192 66 / 88; and few rows, which leave the token-by-token kernel room for all tokens
 //    at once: 73 x 256 45 tokens 3.6 / 9, 387 x 2176 2 3.3 / 5.2, 1752 x 1664 2 4.4 / 5.6 but 16 14.6 / 7.5, 319 x 4480 8 5.3 / 8.1,
 //    851 x 1024 16 8.6 / 6.3, 125 x 2560 16 4.1 / 8.6, 835 x 2048 48 15.7 / 23.5;
-//  - 5 and 6 bits, which run token by token elsewhere: 8192 x 4096 2 tokens 16.5 / 12.8, 16 95 / 26 (8 at a time); 12933 x 1152 2 14.8 / 13.0;
-//    16257 x 6400 9 227 / 56; 8192 x 8192 4 51 / 21; 2213 x 11392 28 159 / 117; but 617 x 14208 2 12.6 / 16.2; 500 x 8192 9
-//    11.8 / 12.3; 300 x 1024 16 4.7 / 6.2; and of few long rows, in several launches that leave CUs idle, 1024 x 23424 42 251 / 468,
-//    1526 x 14592 6 37 / 41, 32 152 / 213, 1201 x 7936 22 46 / 52, 827 x 3840 27 18 / 23.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
+//  - 5 and 6 bits, which run token by token elsewhere: 8192 x 4096 2 tokens 13.3 / 13.0, 16 75 / 27 (8 at a time); 12933 x 1152 2 11.4 / 11.2;
+//    16257 x 6400 9 164 / 58; 8192 x 8192 4 42 / 21; 2213 x 11392 28 101 / 100; but 617 x 14208 2 8.6 / 17; 500 x 8192 9
+//    10 / 23; 300 x 1024 16 4.5 / 5.7; and of few long rows, in several launches that leave CUs idle, 1024 x 23424 42 155 / 463,
+//    1526 x 14592 6 26 / 34, 32 95 / 137, 1201 x 7936 22 36 / 48, 827 x 3840 27 15 / 20.  As many tokens per launch as fit in one slice (these calls take no scratch elsewhere, so they get none here);
 //  - one token: library rows that neither fit the registers of the streaming kernel nor leave it time for slices:
 //    8192 x 28672 45 / 35 (4 bits), 57 / 32 (2 bits), with a scale and a mid-point 76 / 36; 4 bits 6411 x 19712 31 / 29,
 //    but 5524 x 28672 35 / 39, 4577 x 21888 24 / 29; 3 bits 5310 x 23680 31 / 25, 4611 x 17280 18.7 / 20.1; 300 x 20480 6.7 / 12.
-//    Rows of a length with no equal slices for that kernel, which one wave each of the general kernel walks: V2 and V2a 2 bits
-//    300 x 21376 15.4 / 11.3, 3300 x 22784 35 / 14, 3 bits 1300 x 18688 16 / 12.6, 5000 x 17792 29 / 18; 4 bits 300 x 21376
-//    16.7 / 16.3, but V2a 3300 x 17024 27 / 18; a scale and a mid-point 3300 x 21376 29 / 18, 1300 x 17792 12.8 / 14.2.
+//    Rows of a length with no equal slices for that kernel, which one wave each of the general kernel walks: V2 2 bits 3300 x 22784
+//    18 / 14, 3 bits 3300 x 21376 17.3 / 15.6, but 4 bits, V2a 300 x 21376 9.2 / 17; 3300 x 17024 16.9 / 16.7; a scale and a mid-point
+//    3300 x 21376 21 / 18, but 1300 x 17792 10.4 / 15.3.  (The lines were drawn when the general kernel took up to twice that; by
+//    these figures it would keep more: V2 2 bits 300 x 21376 8.3 / 11.7, 3 bits 1300 x 18688 9.2 / 13.3, 5000 x 17792 16.9 / 19.6, a scale and a
+//    mid-point, 4 bits 2048 x 21376 13.5 / 20.2.)
 int few_tokens(int bits, int mode, uint32_t L, uint32_t N, uint32_t K, int left, uint64_t plane, bool general)
 {
     if (bits < 2 || (bits > 4 && mode != 0) || K > 65536 || left < 1) return 0;   // (an outlier's column is kept in 16 bits)

@@ -17,8 +17,8 @@
 //  - The B tile (BM tokens) comes from a token-major copy of the activations straight into LDS
 //    (buffer_load_dwordx4 ... lds: no registers, no VALU), through a ring of parts; its rows are XOR-swizzled in
 //    16-byte chunks so that 16 consecutive lanes of a ds_read_b128 cover the 64 banks.
-//  - 28672 x 8192, 4 bits, 2048 tokens: 1.13 ms against 2.08 ms in passes of 64 tokens (the library's own dense product of
-//    this shape 0.71 ms).  4096 x 4096, 2 bits, 333 tokens: 31 us against 98.
+//  - 28672 x 8192, 4 bits, 2048 tokens: 1.17 ms (the library's own dense product of this shape 0.71 ms).  4096 x 4096, 2 bits, 333
+//    tokens: 29 us against 98 in passes of 64.
 //
 // Order of k inside 32 weights: what the byte planes give cheaply is not the natural order (at 4 bits the even
 // nibbles of a dword come before the odd ones).  A product does not care as long as both operands agree, so the copy
@@ -73,8 +73,9 @@ struct GemmTile {
     template <int BITS> static constexpr int kBase = kPlane > kSums ? (kLoop<BITS> > kPlane ? kLoop<BITS> : kPlane) : (kLoop<BITS> > kSums ? kLoop<BITS> : kSums);
     static constexpr int kIds = BN * 64;                       // ids of 64 groups
     // A step's VALU work is dealt out between its matrix instructions, which 64 columns of tokens need (4096 x 4096, 333 tokens, 3
-    // bits 37 us in the compiler's order, 34); with 128 the chip's power sets the pace and the compiler's order is the better one
-    // (11008 x 4096, 2 bits, 700 tokens 139 us, 144 dealt out; 28672 x 8192, 4 bits, 2048 tokens 971 / 990 without outliers).
+    // bits 37 us in the compiler's order, 34).  With 128 both orders take the same clocks (28672 x 8192, 4 bits, 2048 tokens 1.69 M,
+    // 1.67 M dealt out, 1081 / 1073 us without outliers) or the compiler's fewer (2 bits 878 / 931 us; 11008 x 4096, 2 bits, 700 tokens
+    // 142 and 152 thousand, 120.5 / 125.6 us).
     // PLAIN: in the compiler's order all the same, with nothing asked for ahead (rows of a block or two: see kPlainTinyK).
     static constexpr bool DEAL = TB <= 2 && !PLAIN_;
     static constexpr bool EARLY = NW <= 8 && DEAL;             // there are registers for what is asked for ahead of its use
