@@ -18,7 +18,7 @@
 //    (buffer_load_dwordx4 ... lds: no registers, no VALU), through a ring of parts; its rows are XOR-swizzled in
 //    16-byte chunks so that 16 consecutive lanes of a ds_read_b128 cover the 64 banks.
 //  - 28672 x 8192, 4 bits, 2048 tokens: 1.17 ms (the library's own dense product of this shape 0.71 ms).  4096 x 4096, 2 bits, 333
-//    tokens: 29 us against 98 in passes of 64.
+//    tokens: 30 us against 90 in passes of 64.
 //
 // Order of k inside 32 weights: what the byte planes give cheaply is not the natural order (at 4 bits the even
 // nibbles of a dword come before the odd ones).  A product does not care as long as both operands agree, so the copy
